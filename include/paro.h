@@ -299,12 +299,13 @@ int paro_blocklist_cols_device(int nh, int k, const uint8_t* bitmask, const int3
  * metric is chosen per head; block sums of the chosen order, thresholded at a requested density,
  * give the head's static mask.  The map itself is never stored.
  *
- * Typical sequence, all on one stream:
+ * Typical sequence, all on one stream (block statistics of the six orders behind one another in memory):
  *   for t in 0..5:  paro_permute_quantize(bits 16, PARO_ROWS, perm_ids = t for every head) on Q and K
- *                   paro_calib_block_stats -> paro_calib_metrics(m_sparse6 + t*nh, m_quant6 + t*nh)
- *   paro_calib_choose -> perm_ids (copy the nh bytes to the host: the other entry points take them there)
- *   paro_permute_quantize(bits 16, chosen perm_ids) -> paro_calib_block_stats -> paro_calib_mask
- *   -> bitmask, ready for paro_mask_to_blocklist(_device). */
+ *                   t == 0: paro_calib_row_stats (the rows' maxima and denominators do not depend on the order)
+ *                   paro_calib_block_stats_from_rows
+ *   paro_calib_metrics_orders(6) -> paro_calib_choose -> perm_ids (DEVICE; the other entry points take them on the host)
+ *   paro_calib_pick -> paro_calib_mask -> bitmask, ready for paro_mask_to_blocklist(_device).
+ * A single order can also be looked at by itself: paro_calib_block_stats -> paro_calib_metrics. */
 
 /* Per-block statistics of P for operands that are already reordered (Eq. (M_sparse), (M_quant)).
  * P is formed from the 16-bit operands with fp32 accumulation; entries of padded rows and
@@ -317,6 +318,18 @@ int paro_blocklist_cols_device(int nh, int k, const uint8_t* bitmask, const int3
 int paro_calib_block_stats(const paro_shape* s, const void* q16, const void* k16, float eps,
                            float* block_sum, float* block_max, int32_t* block_cnt, void* stream);
 
+/* paro_calib_block_stats in two steps, for a caller that looks at several orders of the same Q and K.
+ * paro_calib_row_stats: per row of P its largest logit and its denominator, of operands in the DEFAULT token order
+ *   (axis order 0).  row_stats: paro_calib_row_stats_bytes(s) bytes on the device, 16-byte aligned.
+ * paro_calib_block_stats_from_rows: the block statistics of operands reordered by h_perm_ids (host, [nh]) from them.
+ *   The outputs are those of paro_calib_block_stats on the same operands: row maxima are exact and denominators are
+ *   accumulated in binary64 before they are rounded to binary32, so neither depends on the order of the keys. */
+int64_t paro_calib_row_stats_bytes(const paro_shape* s);
+int paro_calib_row_stats(const paro_shape* s, const void* q16, const void* k16, void* row_stats, void* stream);
+int paro_calib_block_stats_from_rows(const paro_shape* s, const uint8_t* h_perm_ids, const void* q16, const void* k16,
+                                     const void* row_stats, float eps, float* block_sum, float* block_max, int32_t* block_cnt,
+                                     void* stream);
+
 /* The two metrics of one axis order per head (Eq. (M_sparse), Eq. (M_quant)), averaged over the B
  * samples:  m_sparse[h] = share of blocks with n_ij >= sigma * entries_ij (compared in binary32;
  * entries_ij = real entries of the block, b*b except in the ragged last row / column);
@@ -325,6 +338,10 @@ int paro_calib_block_stats(const paro_shape* s, const void* q16, const void* k16
 int paro_calib_metrics(const paro_shape* s, const float* block_sum, const float* block_max,
                        const int32_t* block_cnt, float sigma, float* m_sparse, float* m_quant,
                        void* stream);
+
+/* paro_calib_metrics of `orders` (1..6) axis orders in one launch: block_* [orders][B,nh,k,k], m_* float32 [orders][nh]. */
+int paro_calib_metrics_orders(const paro_shape* s, int orders, const float* block_sum, const float* block_max,
+                              const int32_t* block_cnt, float sigma, float* m_sparse, float* m_quant, void* stream);
 
 /* Combined metric (last equation of Sec. 4.1) and the chosen order per head.  The text defines
  * M_sparse as the share of sparse blocks and picks the LOWEST combined value, so the sparsity
@@ -335,6 +352,10 @@ int paro_calib_metrics(const paro_shape* s, const float* block_sum, const float*
  *   m_combined6          float32 [6][nh] (out);  perm_ids  uint8 [nh] (out, DEVICE) */
 int paro_calib_choose(int nh, const float* m_sparse6, const float* m_quant6, float alpha,
                       float* m_combined6, uint8_t* perm_ids, void* stream);
+
+/* The block sums of every head's chosen order: block_sum[b][h] = block_sum6[perm_ids[h]][b][h].
+ *   block_sum6 float32 [6][B,nh,k,k];  perm_ids uint8 [nh] (DEVICE, as paro_calib_choose writes it);  block_sum [B,nh,k,k] */
+int paro_calib_pick(const paro_shape* s, const float* block_sum6, const uint8_t* perm_ids, float* block_sum, void* stream);
 
 /* Static mask of every head by block-sum thresholding with density control (Sec. 4.2 (3)):
  * among the k_img x k_img image blocks (k_img = ceil(F*Hg*Wg / block)) the

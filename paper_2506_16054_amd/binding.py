@@ -31,6 +31,7 @@ EXPORTS = (
     "paro_mask_to_blocklist_device", "paro_calib_block_stats", "paro_calib_metrics", "paro_calib_choose", "paro_calib_mask",
     "paro_sparse_attn_unpermuted_rawq", "paro_blocklist_cols_device", "paro_permute_quantize_qkv",
     "paro_k_channel_mean", "paro_permute_quantize_smoothed",
+    "paro_calib_row_stats_bytes", "paro_calib_row_stats", "paro_calib_block_stats_from_rows", "paro_calib_metrics_orders", "paro_calib_pick",
 )
 
 
@@ -78,6 +79,12 @@ def lib() -> ctypes.CDLL:
         L.paro_mask_to_blocklist_device.argtypes = [i32, i32, vp, vp, vp, i64, vp, vp]
         f32 = ctypes.c_float
         L.paro_calib_block_stats.argtypes = [sp, vp, vp, f32, vp, vp, vp, vp]
+        L.paro_calib_row_stats_bytes.restype = i64
+        L.paro_calib_row_stats_bytes.argtypes = [sp]
+        L.paro_calib_row_stats.argtypes = [sp, vp, vp, vp, vp]
+        L.paro_calib_block_stats_from_rows.argtypes = [sp, vp, vp, vp, vp, f32, vp, vp, vp, vp]
+        L.paro_calib_metrics_orders.argtypes = [sp, i32, vp, vp, vp, f32, vp, vp, vp]
+        L.paro_calib_pick.argtypes = [sp, vp, vp, vp, vp]
         L.paro_calib_metrics.argtypes = [sp, vp, vp, vp, f32, vp, vp, vp]
         L.paro_calib_choose.argtypes = [i32, vp, vp, f32, vp, vp, vp]
         L.paro_calib_mask.argtypes = [sp, vp, f32, vp, vp]
@@ -156,6 +163,13 @@ def paro_nblocks(s: paro_shape) -> int:
 
 def paro_npad(s: paro_shape) -> int:
     n = lib().paro_npad(ctypes.byref(s))
+    if n < 0:
+        _check(int(n))
+    return int(n)
+
+
+def paro_calib_row_stats_bytes(s: paro_shape) -> int:
+    n = lib().paro_calib_row_stats_bytes(ctypes.byref(s))
     if n < 0:
         _check(int(n))
     return int(n)
@@ -347,6 +361,55 @@ def paro_calib_block_stats(s: paro_shape, q16, k16, eps: float, block_sum, block
     _require(block_cnt, "block_cnt", (s.B, s.nh, kb, kb), torch.int32)
     _check(lib().paro_calib_block_stats(ctypes.byref(s), _ptr(q16), _ptr(k16), float(eps), _ptr(block_sum), _ptr(block_max),
                                         _ptr(block_cnt), _stream()))
+
+
+def paro_calib_row_stats(s: paro_shape, q16, k16, row_stats) -> None:
+    """q16, k16: bf16 rows in the default token order; row_stats: uint8 [row_stats_bytes(s)]."""
+    import torch
+
+    _require(q16, "q16", codes_shape(s, 16, PARO_ROWS), torch.bfloat16)
+    _require(k16, "k16", codes_shape(s, 16, PARO_ROWS), torch.bfloat16)
+    _require(row_stats, "row_stats", (paro_calib_row_stats_bytes(s),), torch.uint8)
+    _check(lib().paro_calib_row_stats(ctypes.byref(s), _ptr(q16), _ptr(k16), _ptr(row_stats), _stream()))
+
+
+def paro_calib_block_stats_from_rows(s: paro_shape, perm_ids, q16, k16, row_stats, eps: float, block_sum, block_max, block_cnt) -> None:
+    import torch
+
+    kb = paro_nblocks(s)
+    _require(q16, "q16", codes_shape(s, 16, PARO_ROWS), torch.bfloat16)
+    _require(k16, "k16", codes_shape(s, 16, PARO_ROWS), torch.bfloat16)
+    _require(row_stats, "row_stats", (paro_calib_row_stats_bytes(s),), torch.uint8)
+    _require(block_sum, "block_sum", (s.B, s.nh, kb, kb), torch.float32)
+    _require(block_max, "block_max", (s.B, s.nh, kb, kb), torch.float32)
+    _require(block_cnt, "block_cnt", (s.B, s.nh, kb, kb), torch.int32)
+    p = _perm_bytes(s, perm_ids)
+    _check(lib().paro_calib_block_stats_from_rows(ctypes.byref(s), p.ctypes.data, _ptr(q16), _ptr(k16), _ptr(row_stats), float(eps),
+                                                  _ptr(block_sum), _ptr(block_max), _ptr(block_cnt), _stream()))
+
+
+def paro_calib_metrics_orders(s: paro_shape, block_sum, block_max, block_cnt, sigma: float, m_sparse, m_quant) -> None:
+    """The metrics of several axis orders at once: block_* [orders, B, nh, k, k], m_* [orders, nh]."""
+    import torch
+
+    kb, orders = paro_nblocks(s), int(m_sparse.shape[0])
+    for name, t, dt in (("block_sum", block_sum, torch.float32), ("block_max", block_max, torch.float32), ("block_cnt", block_cnt, torch.int32)):
+        _require(t, name, (orders, s.B, s.nh, kb, kb), dt)
+    _require(m_sparse, "m_sparse", (orders, s.nh), torch.float32)
+    _require(m_quant, "m_quant", (orders, s.nh), torch.float32)
+    _check(lib().paro_calib_metrics_orders(ctypes.byref(s), orders, _ptr(block_sum), _ptr(block_max), _ptr(block_cnt), float(sigma),
+                                           _ptr(m_sparse), _ptr(m_quant), _stream()))
+
+
+def paro_calib_pick(s: paro_shape, block_sum6, perm_ids, block_sum) -> None:
+    """perm_ids: uint8 [nh] on the device."""
+    import torch
+
+    kb = paro_nblocks(s)
+    _require(block_sum6, "block_sum6", (6, s.B, s.nh, kb, kb), torch.float32)
+    _require(perm_ids, "perm_ids", (s.nh,), torch.uint8)
+    _require(block_sum, "block_sum", (s.B, s.nh, kb, kb), torch.float32)
+    _check(lib().paro_calib_pick(ctypes.byref(s), _ptr(block_sum6), _ptr(perm_ids), _ptr(block_sum), _stream()))
 
 
 def paro_calib_metrics(s: paro_shape, block_sum, block_max, block_cnt, sigma: float, m_sparse, m_quant) -> None:

@@ -19,6 +19,7 @@
 // This is an offline step (the paper runs it once per model on one or two prompts); it is written
 // for exactness of the integer decisions first and is not on the measured hot path.
 #include <math.h>
+#include <string.h>
 
 #include <type_traits>
 
@@ -30,223 +31,333 @@ typedef int c_v4i __attribute__((ext_vector_type(4)));
 typedef __bf16 c_v8bf __attribute__((ext_vector_type(8)));
 typedef float c_v16f __attribute__((ext_vector_type(16)));
 
+// Row statistics of the map are kept in column chunks, so that a launch has several times more workgroups than
+// the chip has room for: [kRowChunks][B * nh][npad] row maxima (float, log2 units) and, behind them, as many
+// denominators (double).
+constexpr int kRowChunks = 4;
+
 struct CalibArgs {
     const uint8_t* q;  // bf16 [B, nh, Npad, d], reordered, padded rows zero
     const uint8_t* k;
     float* bsum;       // [B, nh, k, k]
     float* bmax;
     int* bcnt;
+    float* row_max;    // row statistics in the DEFAULT token order (unused by the kernel that makes its own)
+    double* row_den;
     int nh;
     int kblocks;
     int n_tokens;
-    int total_wg;  // B * nh * kblocks
+    int npad;
+    int bh_total;      // B * nh
+    int groups;        // groups of four row blocks per (batch, head)
+    int chunks;        // column chunks per group
+    int total_wg;
     int per_xcd;
     float qk_scale;  // log2(e) / sqrt(d)
     float eps;
+    float log2_eps;
+    ReorderTable table;  // order of the operands (kernels that read row statistics of the default order)
+};
+
+// max / sum over the wavefront in lane 63; x >= 0 (0 is the identity of both)
+template <typename F>
+__device__ inline float lane63_fold(float x, F op) {
+#define PARO_FOLD(ctrl, rows) \
+    x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, rows, 0xf, false)));
+    PARO_FOLD(0xB1, 0xf)   // quad_perm [1,0,3,2]
+    PARO_FOLD(0x4E, 0xf)   // quad_perm [2,3,0,1]
+    PARO_FOLD(0x141, 0xf)  // row_half_mirror
+    PARO_FOLD(0x140, 0xf)  // row_mirror
+    PARO_FOLD(0x142, 0xa)  // row_bcast 15 into rows 1 and 3
+    PARO_FOLD(0x143, 0xc)  // row_bcast 31 into rows 2 and 3
+#undef PARO_FOLD
+    return x;
+}
+__device__ inline int lane63_sum(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+enum CalibPhase { kRowMax = 0, kRowDen = 1, kBlockStats = 2 };
+
+// One workgroup = four row blocks of one (batch, head), one wavefront each, that sweep a range of column blocks
+// together: every K tile is fetched once for the four (global_load_lds into a ring of two slots, one barrier per
+// tile) and the 16-byte pieces of a 128-byte line sit at position piece ^ (row % 8), which spreads the fragment
+// reads over all banks.  A wavefront holds its queries as halves of 32 (one half at block 32) in the transposed
+// orientation: the lanes n and n + 32 share query n of the half.
+//
+// Phases.  kRowMax: the row's largest logit (exact in any order).  kRowDen: its denominator against that maximum,
+// accumulated in binary64, so that - rounded to binary32 - it does not depend on the order of the keys: the row
+// statistics of one axis order serve all six.  kBlockStats: the exponent is formed against eps,
+//     y = c S - (m + log2 l + log2 eps),   p = eps 2^y,
+// so that its sign bit IS the comparison p < eps: the 32 signs of a half are shifted into one register
+// (v_alignbit) and counted by one v_bcnt; the maximum is taken on y.  The offset is rounded to binary32; what that
+// changes is put back by the row's factor, computed from the rounded offset.
+template <int BLK, int D>
+struct CalibSweep {
+    static constexpr int QH = BLK / 32;
+    static constexpr int KT = BLK / 32;
+    static constexpr int KS = D / 16;
+    static constexpr int TILE = BLK * D * 2;
+    static constexpr int PIECES = TILE / 4096;  // 1 KB pieces of a tile per wavefront
+
+    const CalibArgs& a;
+    uint8_t* ring;  // LDS [2][TILE]
+    int bh, i, lane, n, g, w;
+    const uint8_t* kbase;
+    unsigned fill[PIECES];
+    unsigned kread[KS];
+    c_v8bf qf[QH][KS];
+    float m[QH];      // kRowMax: running maximum; afterwards the final one
+    double den[QH];
+    float off[QH], factor[QH];
+
+    __device__ CalibSweep(const CalibArgs& args, uint8_t* lds, int bh_, int group) : a(args), ring(lds), bh(bh_) {
+        lane = threadIdx.x & 63;
+        w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        n = lane & 31;
+        g = lane >> 5;
+        i = min(4 * group + w, a.kblocks - 1);  // a wavefront past the last row block repeats it and stores nothing
+        kbase = a.k + (size_t)bh * a.npad * D * 2;
+#pragma unroll
+        for (int u = 0; u < PIECES; ++u) {
+            const unsigned p = (w * PIECES + u) * 1024u + 16u * lane;
+            const unsigned row = p / (2 * D), pos = (p % (2 * D)) / 16;
+            fill[u] = row * 2 * D + 16 * ((pos & ~7u) | ((pos ^ row) & 7u));
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const unsigned piece = 2 * s + g;
+            kread[s] = 2u * D * n + 16u * ((piece & ~7u) | ((piece ^ n) & 7u));
+        }
+#pragma unroll
+        for (int H = 0; H < QH; ++H) {
+            const uint8_t* qrow = a.q + ((size_t)bh * a.npad + row_of(H)) * D * 2 + 16 * g;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) qf[H][s] = *(const c_v8bf*)(qrow + 32 * s);
+        }
+    }
+    __device__ int row_of(int H) const { return i * BLK + 32 * H + n; }
+    __device__ bool row_valid(int H) const { return row_of(H) < a.n_tokens; }
+
+    __device__ void request(int t) {
+        const uint8_t* kp = kbase + (size_t)t * TILE;
+#pragma unroll
+        for (int u = 0; u < PIECES; ++u)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kp + fill[u]),
+                                             (__attribute__((address_space(3))) void*)(ring + (t & 1) * TILE + (w * PIECES + u) * 1024), 16, 0, 0);
+    }
+
+    template <int PHASE>
+    __device__ void tile(int t, bool store) {
+        const uint8_t* ks = ring + (t & 1) * TILE;
+        const int nkeys = a.n_tokens - t * BLK;  // real keys of the tile
+        float ps = 0.0f, pm = 0.0f;
+        int pc = 0;
+#pragma unroll
+        for (int H = 0; H < QH; ++H) {
+            c_v16f S[KT];
+#pragma unroll
+            for (int T = 0; T < KT; ++T) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) S[T][r] = 0.0f;
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    S[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const c_v8bf*)(ks + 64 * D * T + kread[s]), qf[H][s], S[T], 0, 0, 0);
+            }
+            int pad = 0;  // this lane's keys past N: they do not exist
+            if (nkeys < BLK) {
+#pragma unroll
+                for (int T = 0; T < KT; ++T)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (32 * T + 8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) {
+                            S[T][r] = -INFINITY;
+                            ++pad;
+                        }
+            }
+            const float o = PHASE == kRowMax ? 0.0f : PHASE == kRowDen ? -m[H] : off[H];
+#pragma unroll
+            for (int T = 0; T < KT; ++T)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) S[T][r] = fmaf(S[T][r], a.qk_scale, o);
+            if constexpr (PHASE != kRowDen) {
+                float part[4];
+#pragma unroll
+                for (int T = 0; T < KT; ++T)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) part[r & 3] = (T == 0 && r < 4) ? S[T][r] : fmaxf(part[r & 3], S[T][r]);
+                const float top = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+                if constexpr (PHASE == kRowMax) m[H] = fmaxf(m[H], top);
+                else pm = fmaxf(pm, factor[H] * __builtin_amdgcn_exp2f(top));
+            }
+            if constexpr (PHASE == kBlockStats) {
+                unsigned signs = 0;
+#pragma unroll
+                for (int T = 0; T < KT; ++T)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) signs = __builtin_amdgcn_alignbit(signs, __float_as_uint(S[T][r]), 31);
+                pc += row_valid(H) ? __popc(signs) - pad : 0;
+            }
+            if constexpr (PHASE != kRowMax) {
+#pragma unroll
+                for (int T = 0; T < KT; ++T)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) S[T][r] = __builtin_amdgcn_exp2f(S[T][r]);
+            }
+            if constexpr (PHASE == kRowDen) {
+#pragma unroll
+                for (int T = 0; T < KT; ++T)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) den[H] += (double)S[T][r];
+            }
+            if constexpr (PHASE == kBlockStats) {
+                float part[4];
+#pragma unroll
+                for (int T = 0; T < KT; ++T)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) part[r & 3] = (T == 0 && r < 4) ? S[T][r] : part[r & 3] + S[T][r];
+                ps = fmaf(factor[H], (part[0] + part[1]) + (part[2] + part[3]), ps);
+            }
+        }
+        if constexpr (PHASE == kBlockStats) {
+            ps = lane63_fold(ps, [](float x, float y) { return x + y; });
+            pm = lane63_fold(pm, [](float x, float y) { return fmaxf(x, y); });
+            pc = lane63_sum(pc);
+            if (store && lane == 63) {
+                const size_t at = ((size_t)bh * a.kblocks + i) * a.kblocks + t;
+                a.bsum[at] = ps;
+                a.bmax[at] = pm;
+                a.bcnt[at] = pc;
+            }
+        }
+    }
+
+    template <int PHASE>
+    __device__ void sweep(int t0, int t1, bool store) {
+        if constexpr (PHASE == kRowMax)
+#pragma unroll
+            for (int H = 0; H < QH; ++H) m[H] = -INFINITY;
+        if constexpr (PHASE == kRowDen)
+#pragma unroll
+            for (int H = 0; H < QH; ++H) den[H] = 0.0;
+        __syncthreads();  // the previous sweep is done with the ring
+        if (t0 < t1) request(t0);
+        for (int t = t0; t < t1; ++t) {
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's share of tile t has landed
+            __syncthreads();                     // and everybody's; tile t - 1 has been read by all
+            if (t + 1 < t1) request(t + 1);
+            tile<PHASE>(t, store);
+        }
+#pragma unroll
+        for (int H = 0; H < QH; ++H) {  // the two lanes of a query hold half of its keys each
+            if constexpr (PHASE == kRowMax) m[H] = fmaxf(m[H], __shfl_xor(m[H], 32));
+            if constexpr (PHASE == kRowDen) den[H] += __shfl_xor(den[H], 32);
+        }
+    }
+
+    // offset and factor of a row from its maximum and its denominator in binary32:  p = factor 2^(c S + off)
+    __device__ void finish_row(int H, float l) {
+        off[H] = -m[H] - (__builtin_amdgcn_logf(l) + a.log2_eps);
+        factor[H] = row_valid(H) ? __builtin_amdgcn_exp2f(-m[H] - off[H]) / l : 0.0f;
+    }
 };
 
 template <int BLK, int D>
-__global__ __launch_bounds__(BLK * 2, 2) void calib_stats_kernel(CalibArgs a) {
-    constexpr int NW = BLK / 32;
-    constexpr int NT = 64 * NW;
-    constexpr int KSTR = 2 * D + 16;  // bytes per K row in LDS (bf16 + 16 B pad)
-    constexpr int KBYTES = BLK * KSTR;
-    constexpr int NKC = BLK * D * 2 / 16 / NT;  // 16-byte pieces of a K tile per thread
-    constexpr int KS = D / 16;                  // contraction steps of 16 channels
-    constexpr int KT = BLK / 32;                // 32-key tiles per block
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * KBYTES];
-    __shared__ float red_sum[2][NW], red_max[2][NW];
-    __shared__ int red_cnt[2][NW];
+constexpr int calib_waves() { return BLK == 64 && D == 128 ? 2 : 3; }
 
-    // each XCD takes a contiguous range of (head, row block): a head's K stays in its L2
-    const int wg = blockIdx.x;
-    const int item = (wg & 7) * a.per_xcd + (wg >> 3);
+// the three sweeps of a row block by its own workgroup (operands in any order, nothing kept)
+template <int BLK, int D>
+__global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_stats_kernel(CalibArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * CalibSweep<BLK, D>::TILE];
+    const int item = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);  // a head's K stays in one XCD's L2
     if (item >= a.total_wg) return;
-    const int bh = item / a.kblocks;
-    const int i = item - bh * a.kblocks;
-    const int kb = a.kblocks;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int w = tid >> 6;
-    const int n = lane & 31;
-    const int g = lane >> 5;
-    const size_t head_rows = (size_t)bh * kb * BLK;
-    const int row = i * BLK + 32 * w + n;
-    const bool row_valid = row < a.n_tokens;
-    const uint8_t* kbase = a.k + head_rows * D * 2;
-    const float c = a.qk_scale;
-    const bool ragged = (a.n_tokens % BLK) != 0;
-    const int nkeys_tail = a.n_tokens - (kb - 1) * BLK;
-
-    c_v8bf qf[KS];
-    {
-        const uint8_t* qrow = a.q + (head_rows + row) * D * 2 + 16 * g;
+    const int bh = item / a.groups, group = item - bh * a.groups;
+    CalibSweep<BLK, D> c(a, lds, bh, group);
+    c.template sweep<kRowMax>(0, a.kblocks, false);
+    c.template sweep<kRowDen>(0, a.kblocks, false);
 #pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s] = *(const c_v8bf*)(qrow + 32 * s);
+    for (int H = 0; H < c.QH; ++H) c.finish_row(H, (float)c.den[H]);
+    c.template sweep<kBlockStats>(0, a.kblocks, 4 * group + c.w < a.kblocks);
+}
+
+// the same sweeps as one launch each, a workgroup per (four row blocks, column chunk)
+template <int BLK, int D, int PHASE>
+__global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_phase_kernel(CalibArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * CalibSweep<BLK, D>::TILE];
+    const int item = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+    if (item >= a.total_wg) return;
+    const int bh = item / (a.groups * a.chunks);
+    const int rest = item - bh * (a.groups * a.chunks);
+    const int group = rest / a.chunks, chunk = rest - group * a.chunks;
+    const int t0 = (int)((long long)a.kblocks * chunk / a.chunks), t1 = (int)((long long)a.kblocks * (chunk + 1) / a.chunks);
+    CalibSweep<BLK, D> c(a, lds, bh, group);
+    const bool store = 4 * group + c.w < a.kblocks;
+    const size_t plane = (size_t)a.bh_total * a.npad;
+    if constexpr (PHASE != kRowMax) {
+#pragma unroll
+        for (int H = 0; H < c.QH; ++H) {
+            const int row = min(c.row_of(H), a.n_tokens - 1);
+            const size_t at = (size_t)bh * a.npad + (PHASE == kBlockStats ? reorder_source(a.table, bh % a.nh, row) : row);
+            float m = a.row_max[at];
+            for (int z = 1; z < kRowChunks; ++z) m = fmaxf(m, a.row_max[z * plane + at]);
+            c.m[H] = m;
+            if constexpr (PHASE == kBlockStats) {
+                double l = a.row_den[at];
+                for (int z = 1; z < kRowChunks; ++z) l += a.row_den[z * plane + at];
+                c.finish_row(H, (float)l);
+            }
+        }
     }
-
-    c_v4i kreg[NKC];
-    auto gload = [&](int t) {
-        const uint8_t* kp = kbase + (size_t)t * (BLK * D * 2);
+    c.template sweep<PHASE>(t0, t1, store);
+    if constexpr (PHASE != kBlockStats) {
 #pragma unroll
-        for (int cc = 0; cc < NKC; ++cc) kreg[cc] = *(const c_v4i*)(kp + 16 * (tid + NT * cc));
-    };
-    auto lstore = [&](int stage) {
-        uint8_t* ks = lds + stage * KBYTES;
-#pragma unroll
-        for (int cc = 0; cc < NKC; ++cc) {
-            const int o = 16 * (tid + NT * cc);
-            *(c_v4i*)(ks + (o / (2 * D)) * KSTR + (o % (2 * D))) = kreg[cc];
-        }
-    };
-
-    float m = -INFINITY;  // running row maximum (log2 units), then the final one
-    float l = 0.0f;       // this lane's share of the denominator, then 1 / denominator
-    float* out_sum = a.bsum + ((size_t)bh * kb + i) * kb;
-    float* out_max = a.bmax + ((size_t)bh * kb + i) * kb;
-    int* out_cnt = a.bcnt + ((size_t)bh * kb + i) * kb;
-
-    // One column block.  PASS 0 updates the running maximum and denominator; PASS 1 forms the
-    // probabilities with the final maximum and denominator and reduces them over the block.
-    // The LDS ring is the one of the attention kernels: tile t+1 is stored at the top of
-    // iteration t (every wavefront finished reading tile t-1 before the previous barrier), one
-    // barrier per column block, registers refilled (tile t+2) after it.
-    int stage = 0;
-    auto step = [&](auto pass_tag, auto tail_tag, int t) {
-        constexpr int PASS = decltype(pass_tag)::value;
-        constexpr bool TAIL = decltype(tail_tag)::value;
-        const int next = stage ^ 1;
-        if (t + 1 < kb) lstore(next);
-        const uint8_t* ks = lds + stage * KBYTES;
-
-        c_v16f sacc[KT];
-#pragma unroll
-        for (int T = 0; T < KT; ++T) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sacc[T][r] = 0.0f;
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const c_v8bf kf = *(const c_v8bf*)(ks + (32 * T + n) * KSTR + 32 * s + 16 * g);
-                sacc[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc[T], 0, 0, 0);
+        for (int H = 0; H < c.QH; ++H)
+            if (store && c.g == 0) {
+                const size_t at = chunk * plane + (size_t)bh * a.npad + c.row_of(H);
+                if constexpr (PHASE == kRowMax) a.row_max[at] = c.m[H];
+                else a.row_den[at] = c.den[H];
             }
-        }
-        if constexpr (TAIL) {  // keys past N do not exist
-#pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (32 * T + 8 * (r >> 2) + 4 * g + (r & 3) >= nkeys_tail) sacc[T][r] = -INFINITY;
-        }
-        if constexpr (PASS == 0) {
-            float mx = -INFINITY;
-#pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[T][r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m, c * mx);
-            float rs = 0.0f;
-#pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) rs += __builtin_amdgcn_exp2f(fmaf(sacc[T][r], c, -m_new));
-            l = fmaf(l, __builtin_amdgcn_exp2f(m - m_new), rs);
-            m = m_new;
-        } else {
-            float ps = 0.0f, pm = 0.0f;
-            int pc = 0;
-#pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float p = __builtin_amdgcn_exp2f(fmaf(sacc[T][r], c, -m)) * l;
-                    ps += p;
-                    pm = fmaxf(pm, p);
-                    const bool real = !TAIL || (32 * T + 8 * (r >> 2) + 4 * g + (r & 3) < nkeys_tail);
-                    pc += (real && p < a.eps) ? 1 : 0;
-                }
-            if (!row_valid) {  // rows past N do not exist
-                ps = 0.0f;
-                pm = 0.0f;
-                pc = 0;
-            }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                ps += __shfl_xor(ps, off);
-                pm = fmaxf(pm, __shfl_xor(pm, off));
-                pc += __shfl_xor(pc, off);
-            }
-            if (lane == 0) {
-                red_sum[t & 1][w] = ps;
-                red_max[t & 1][w] = pm;
-                red_cnt[t & 1][w] = pc;
-            }
-        }
-        __syncthreads();
-        if (t + 2 < kb) gload(t + 2);
-        if constexpr (PASS == 1) {
-            if (tid == 0) {
-                float ps = red_sum[t & 1][0], pm = red_max[t & 1][0];
-                int pc = red_cnt[t & 1][0];
-#pragma unroll
-                for (int ww = 1; ww < NW; ++ww) {
-                    ps += red_sum[t & 1][ww];
-                    pm = fmaxf(pm, red_max[t & 1][ww]);
-                    pc += red_cnt[t & 1][ww];
-                }
-                out_sum[t] = ps;
-                out_max[t] = pm;
-                out_cnt[t] = pc;
-            }
-        }
-        stage = next;
-    };
-    auto sweep = [&](auto pass_tag) {
-        gload(0);
-        lstore(0);
-        if (kb > 1) gload(1);
-        __syncthreads();
-        stage = 0;
-        const int main_blocks = ragged ? kb - 1 : kb;
-        for (int t = 0; t < main_blocks; ++t) step(pass_tag, std::false_type{}, t);
-        if (ragged) step(pass_tag, std::true_type{}, kb - 1);
-        __syncthreads();  // every wavefront is done with both stages before the next sweep refills them
-    };
-
-    sweep(std::integral_constant<int, 0>{});
-    l = 1.0f / (l + __shfl_xor(l, 32));
-    sweep(std::integral_constant<int, 1>{});
+    }
 }
 
 // -------------------------------------------------------------------------------------------
-// M_sparse and M_quant of one head: a reduction over its B * k * k blocks.
+// M_sparse and M_quant: one workgroup per (head, axis order) reduces the head's B * k * k blocks.  Bound by latency
+// and the binary64 division per block, hence 1024 threads per workgroup and all orders in one launch.
 // -------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void calib_metrics_kernel(int B, int nh, int kb, int n_tokens, int blk, const float* __restrict__ bsum,
-                                                            const float* __restrict__ bmax, const int* __restrict__ bcnt, float sigma,
-                                                            float* __restrict__ m_sparse, float* __restrict__ m_quant) {
-    __shared__ double s_psi[256];
-    __shared__ int s_sparse[256];
+constexpr int kMetricThreads = 1024;
+
+__global__ __launch_bounds__(kMetricThreads) void calib_metrics_kernel(int B, int nh, int kb, int n_tokens, int blk, const float* __restrict__ bsum,
+                                                                       const float* __restrict__ bmax, const int* __restrict__ bcnt, float sigma,
+                                                                       float* __restrict__ m_sparse, float* __restrict__ m_quant) {
+    __shared__ double s_psi[kMetricThreads];
+    __shared__ int s_sparse[kMetricThreads];
     const int h = blockIdx.x;
+    const int order = blockIdx.y;
     const int t = threadIdx.x;
     const int per_head = kb * kb;
     double psi = 0.0;
     int sparse = 0;
     for (int b = 0; b < B; ++b) {
-        const size_t base = ((size_t)b * nh + h) * per_head;
-        for (int e = t; e < per_head; e += 256) {
+        const size_t base = (((size_t)order * B + b) * nh + h) * per_head;
+        for (int e = t; e < per_head; e += kMetricThreads) {
             const int i = e / kb, j = e - i * kb;
             const int rows = min(blk, n_tokens - i * blk), cols = min(blk, n_tokens - j * blk);
             const float entries = (float)(rows * cols);
             sparse += ((float)bcnt[base + e] >= sigma * entries) ? 1 : 0;
             const float s = bsum[base + e];
-            if (s > 0.0f) psi += (double)bmax[base + e] / ((double)s / (double)entries);
+            if (s > 0.0f) psi += (double)bmax[base + e] * (double)entries / (double)s;
         }
     }
     s_psi[t] = psi;
     s_sparse[t] = sparse;
     __syncthreads();
-    for (int off = 128; off >= 1; off >>= 1) {
+    for (int off = kMetricThreads / 2; off >= 1; off >>= 1) {
         if (t < off) {
             s_psi[t] += s_psi[t + off];
             s_sparse[t] += s_sparse[t + off];
@@ -255,9 +366,17 @@ __global__ __launch_bounds__(256) void calib_metrics_kernel(int B, int nh, int k
     }
     if (t == 0) {
         const double total = (double)B * per_head;
-        m_sparse[h] = (float)((double)s_sparse[0] / total);
-        m_quant[h] = (float)(s_psi[0] / total);
+        m_sparse[order * nh + h] = (float)((double)s_sparse[0] / total);
+        m_quant[order * nh + h] = (float)(s_psi[0] / total);
     }
+}
+
+// block sums of every head's chosen order out of the six: out[b][h] = in[perm_ids[h]][b][h]
+__global__ __launch_bounds__(256) void calib_pick_kernel(int B, int nh, int per_head, const float* __restrict__ in,
+                                                         const uint8_t* __restrict__ perm_ids, float* __restrict__ out) {
+    const int bh = blockIdx.y;
+    const size_t from = ((size_t)min((int)perm_ids[bh % nh], 5) * B * nh + bh) * per_head;
+    for (int e = blockIdx.x * 256 + threadIdx.x; e < per_head; e += gridDim.x * 256) out[(size_t)bh * per_head + e] = in[from + e];
 }
 
 __global__ __launch_bounds__(256) void calib_choose_kernel(int nh, const float* __restrict__ ms, const float* __restrict__ mq, float alpha,
@@ -290,6 +409,129 @@ __global__ __launch_bounds__(256) void calib_choose_kernel(int nh, const float* 
 constexpr int kMaskThreads = 1024;
 constexpr int kMaskMaxWords = 12288;  // k*k <= 393216 mask bits held in LDS
 
+// Heads of up to kMaskRegBlocks blocks: the keys stay in registers (thread t holds the blocks u * 1024 + t), the
+// threshold is found by bisection on the key values - one compare per key and step, counted by ballots - and the
+// bits of 64 consecutive blocks are one ballot, stored as they are.
+constexpr int kMaskRegKeys = 80;
+constexpr int kMaskRegBlocks = kMaskRegKeys * kMaskThreads;
+
+template <int PER>
+__global__ __launch_bounds__(kMaskThreads) void calib_mask_reg_kernel(int B, int nh, int kb, int k_img, int n_live, const float* __restrict__ bsum,
+                                                                      uint8_t* __restrict__ bitmask) {
+    __shared__ unsigned words[PER * kMaskThreads / 32];
+    __shared__ int part[2][kMaskThreads / 64];
+    constexpr int WAVES = kMaskThreads / 64;
+    const int h = blockIdx.x;
+    const int t = threadIdx.x;
+    const int lane = t & 63, w = t >> 6;
+    const int per_head = kb * kb;
+    const int nbytes = (per_head + 7) / 8;
+    // the sum over the calibration samples, in sample order; non-negative, so its bit pattern orders it
+    float sums[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) sums[u] = 0.0f;
+    for (int b = 0; b < B; ++b) {
+        // a buffer of exactly the head's sums: what lies past them reads as 0, with no compare per key
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(bsum + ((size_t)b * nh + h) * per_head), 0, per_head * 4, 0x00020000);
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            sums[u] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, t * 4, u * kMaskThreads * 4, 0));
+    }
+    // key: bit pattern + 1; 0 for text blocks and what lies past the end, which no step below counts
+    unsigned keys[PER];
+    unsigned top = 0u;
+    const int step_i = kMaskThreads / kb, step_j = kMaskThreads % kb;
+    int i = t / kb, j = t % kb;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        keys[u] = i < k_img && j < k_img ? __float_as_uint(sums[u]) + 1u : 0u;
+        asm volatile("" : "+v"(keys[u]));  // `key != 0` stays a compare: kept as flags, 80 of them would fill the scalar registers
+        top = max(top, keys[u]);
+        i += step_i;
+        j += step_j;
+        if (j >= kb) {
+            j -= kb;
+            ++i;
+        }
+    }
+    auto block_total = [&](int n, int slot) {  // sum over the wavefronts of a value that is uniform in each
+        if (lane == 0) part[slot][w] = n;
+        __syncthreads();
+        n = 0;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) n += part[slot][v];
+        return n;
+    };
+    // count(key >= below) >= n_live > count(key >= above)
+    unsigned below = 1u, above = 2u;
+    int at_above = 0;
+    const bool select = n_live > 0 && n_live < k_img * k_img;
+    if (select) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, off));
+        if (lane == 0) part[1][w] = (int)top;
+        __syncthreads();
+        for (int v = 0; v < WAVES; ++v) top = max(top, (unsigned)part[1][v]);
+        above = top + 1u;
+        for (int step = 0; above - below > 1u; ++step) {  // at most 32 steps
+            const unsigned mid = below + (above - below) / 2u;
+            int n = 0;
+#pragma unroll
+            for (int u = 0; u < PER; ++u) n += __popcll(__builtin_amdgcn_ballot_w64(keys[u] >= mid));
+            n = block_total(n, step & 1);
+            if (n >= n_live) {
+                below = mid;
+                if (n == n_live) break;  // exactly the wanted blocks are >= below: all of them are live
+            } else {
+                above = mid;
+                at_above = n;
+            }
+        }
+        __syncthreads();
+    }
+    // blocks above the threshold `below` are live, and of those equal to it `remaining` in ascending position
+    const unsigned thr = below;
+    int equal = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        equal += __popcll(__builtin_amdgcn_ballot_w64(keys[u] == thr));
+    equal = block_total(equal, 0);
+    const int remaining = n_live - at_above;
+    const bool all_equal = equal <= remaining;
+    int seen = 0;  // equal blocks in front of this pass's (only needed when some of them are not live)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const bool in = keys[u] != 0u;
+        const bool eq = keys[u] == thr;
+        bool live = !in || (select ? keys[u] > thr || (eq && all_equal) : n_live > 0);
+        if (select && !all_equal) {
+            const unsigned long long eqs = __builtin_amdgcn_ballot_w64(eq);
+            __syncthreads();
+            if (lane == 0) part[1][w] = __popcll(eqs);
+            __syncthreads();
+            int rank = seen + __popcll(eqs & ((1ull << lane) - 1ull));
+            for (int v = 0; v < WAVES; ++v) {
+                rank += v < w ? part[1][v] : 0;
+                seen += part[1][v];
+            }
+            live = live || (eq && rank < remaining);
+        }
+        const unsigned long long bits = __builtin_amdgcn_ballot_w64(live);
+        if (lane < 2) words[u * (kMaskThreads / 32) + 2 * w + lane] = (unsigned)(bits >> (32 * lane));
+    }
+    __syncthreads();
+    // bits past the last block stay zero
+    const int last_bits = per_head & 31;
+    uint8_t* out = bitmask + (size_t)h * nbytes;
+    for (int b = t; b < nbytes; b += kMaskThreads) {
+        unsigned word = words[b >> 2];
+        if (last_bits && (b >> 2) == per_head >> 5) word &= (1u << last_bits) - 1u;
+        out[b] = (uint8_t)((word >> (8 * (b & 3))) & 255u);
+    }
+}
+
+// Heads with more blocks: radix selection, 8 bits a pass, that reads the sums again in every pass.  (Its LDS histogram
+// is slow where many keys share their leading byte: at 275 x 275 blocks 235 us against the kernel above.)
 __global__ __launch_bounds__(kMaskThreads) void calib_mask_kernel(int B, int nh, int kb, int k_img, int n_live, const float* __restrict__ bsum,
                                                                   uint8_t* __restrict__ bitmask) {
     __shared__ unsigned words[kMaskMaxWords];
@@ -386,47 +628,134 @@ static int calib_shape(const paro_shape* s, int64_t* n, int64_t* kb) {
 
 }  // namespace paro
 
+namespace paro {
+static int calib_args(const paro_shape* s, const void* q16, const void* k16, CalibArgs* a) {
+    int64_t n, kb;
+    if (int st = calib_shape(s, &n, &kb)) return st;
+    if (!q16 || !k16) return fail(PARO_EINVAL, "q16 and k16 must not be NULL");
+    if (((uintptr_t)q16 | (uintptr_t)k16) & 15) return fail(PARO_EINVAL, "q16 and k16 must be 16-byte aligned");
+    memset(a, 0, sizeof(*a));
+    a->q = (const uint8_t*)q16;
+    a->k = (const uint8_t*)k16;
+    a->nh = s->nh;
+    a->kblocks = (int)kb;
+    a->n_tokens = (int)n;
+    a->npad = (int)(kb * s->block);
+    a->bh_total = s->B * s->nh;
+    a->groups = (int)((kb + 3) / 4);
+    a->qk_scale = (float)(1.4426950408889634 / sqrt((double)s->d));
+    return PARO_OK;
+}
+static dim3 calib_grid(CalibArgs* a, int chunks) {
+    a->chunks = chunks;
+    a->total_wg = a->bh_total * a->groups * chunks;
+    a->per_xcd = (a->total_wg + 7) / 8;
+    return dim3((unsigned)(a->per_xcd * 8));
+}
+static int calib_outputs(CalibArgs* a, float eps, float* block_sum, float* block_max, int32_t* block_cnt) {
+    if (!block_sum || !block_max || !block_cnt) return fail(PARO_EINVAL, "block_sum, block_max and block_cnt must not be NULL");
+    if (!(eps > 0.0f)) return fail(PARO_EINVAL, "eps=%g must be positive", (double)eps);
+    a->bsum = block_sum;
+    a->bmax = block_max;
+    a->bcnt = block_cnt;
+    a->eps = eps;
+    a->log2_eps = (float)log2((double)eps);
+    return PARO_OK;
+}
+// the row statistics in a buffer of paro_calib_row_stats_bytes(): denominators first (8-byte aligned), then maxima
+static void calib_row_buffers(CalibArgs* a, void* row_stats) {
+    const size_t rows = (size_t)kRowChunks * a->bh_total * a->npad;
+    a->row_den = (double*)row_stats;
+    a->row_max = (float*)((double*)row_stats + rows);
+}
+template <int PHASE>
+static void launch_phase(const paro_shape* s, dim3 grid, hipStream_t st, const CalibArgs& a) {
+    if (s->block == 64 && s->d == 64) hipLaunchKernelGGL((calib_phase_kernel<64, 64, PHASE>), grid, dim3(256), 0, st, a);
+    else if (s->block == 64 && s->d == 128) hipLaunchKernelGGL((calib_phase_kernel<64, 128, PHASE>), grid, dim3(256), 0, st, a);
+    else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_phase_kernel<32, 64, PHASE>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((calib_phase_kernel<32, 128, PHASE>), grid, dim3(256), 0, st, a);
+}
+}  // namespace paro
+
 extern "C" int paro_calib_block_stats(const paro_shape* s, const void* q16, const void* k16, float eps, float* block_sum,
                                       float* block_max, int32_t* block_cnt, void* stream) {
     using namespace paro;
+    CalibArgs a;
+    if (int st = calib_args(s, q16, k16, &a)) return st;
+    if (int st = calib_outputs(&a, eps, block_sum, block_max, block_cnt)) return st;
+    const dim3 grid = calib_grid(&a, 1);
+    hipStream_t st = (hipStream_t)stream;
+    if (s->block == 64 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<64, 64>), grid, dim3(256), 0, st, a);
+    else if (s->block == 64 && s->d == 128) hipLaunchKernelGGL((calib_stats_kernel<64, 128>), grid, dim3(256), 0, st, a);
+    else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<32, 64>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((calib_stats_kernel<32, 128>), grid, dim3(256), 0, st, a);
+    return check_launch("paro_calib_block_stats");
+}
+
+extern "C" int64_t paro_calib_row_stats_bytes(const paro_shape* s) {
+    using namespace paro;
     int64_t n, kb;
     if (int st = calib_shape(s, &n, &kb)) return st;
-    if (!q16 || !k16 || !block_sum || !block_max || !block_cnt) return fail(PARO_EINVAL, "q16, k16, block_sum, block_max and block_cnt must not be NULL");
-    if (((uintptr_t)q16 | (uintptr_t)k16) & 15) return fail(PARO_EINVAL, "q16 and k16 must be 16-byte aligned");
-    if (!(eps > 0.0f)) return fail(PARO_EINVAL, "eps=%g must be positive", (double)eps);
+    return (int64_t)kRowChunks * s->B * s->nh * kb * s->block * (int64_t)(sizeof(double) + sizeof(float));
+}
+
+extern "C" int paro_calib_row_stats(const paro_shape* s, const void* q16, const void* k16, void* row_stats, void* stream) {
+    using namespace paro;
     CalibArgs a;
-    a.q = (const uint8_t*)q16;
-    a.k = (const uint8_t*)k16;
-    a.bsum = block_sum;
-    a.bmax = block_max;
-    a.bcnt = block_cnt;
-    a.nh = s->nh;
-    a.kblocks = (int)kb;
-    a.n_tokens = (int)n;
-    a.total_wg = (int)((int64_t)s->B * s->nh * kb);
-    a.per_xcd = (a.total_wg + 7) / 8;
-    a.qk_scale = (float)(1.4426950408889634 / sqrt((double)s->d));
-    a.eps = eps;
-    const dim3 grid((unsigned)(a.per_xcd * 8));
-    hipStream_t st = (hipStream_t)stream;
-    if (s->block == 64 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<64, 64>), grid, dim3(128), 0, st, a);
-    else if (s->block == 64 && s->d == 128) hipLaunchKernelGGL((calib_stats_kernel<64, 128>), grid, dim3(128), 0, st, a);
-    else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<32, 64>), grid, dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((calib_stats_kernel<32, 128>), grid, dim3(64), 0, st, a);
-    return check_launch("paro_calib_block_stats");
+    if (int st = calib_args(s, q16, k16, &a)) return st;
+    if (!row_stats || ((uintptr_t)row_stats & 15)) return fail(PARO_EINVAL, "row_stats must be a 16-byte aligned buffer");
+    calib_row_buffers(&a, row_stats);
+    const dim3 grid = calib_grid(&a, kRowChunks);
+    launch_phase<kRowMax>(s, grid, (hipStream_t)stream, a);
+    launch_phase<kRowDen>(s, grid, (hipStream_t)stream, a);
+    return check_launch("paro_calib_row_stats");
+}
+
+extern "C" int paro_calib_block_stats_from_rows(const paro_shape* s, const uint8_t* h_perm_ids, const void* q16, const void* k16,
+                                                const void* row_stats, float eps, float* block_sum, float* block_max,
+                                                int32_t* block_cnt, void* stream) {
+    using namespace paro;
+    CalibArgs a;
+    if (int st = calib_args(s, q16, k16, &a)) return st;
+    if (int st = calib_outputs(&a, eps, block_sum, block_max, block_cnt)) return st;
+    if (!h_perm_ids) return fail(PARO_EINVAL, "perm_ids is NULL");
+    if (!row_stats || ((uintptr_t)row_stats & 15)) return fail(PARO_EINVAL, "row_stats must be a 16-byte aligned buffer");
+    if (int st = make_reorder_table(s, h_perm_ids, &a.table)) return st;
+    calib_row_buffers(&a, (void*)row_stats);
+    // column chunks of about 16 blocks: a launch of many short workgroups ends evenly
+    const dim3 grid = calib_grid(&a, (a.kblocks + 15) / 16);
+    launch_phase<kBlockStats>(s, grid, (hipStream_t)stream, a);
+    return check_launch("paro_calib_block_stats_from_rows");
+}
+
+extern "C" int paro_calib_metrics_orders(const paro_shape* s, int orders, const float* block_sum, const float* block_max,
+                                         const int32_t* block_cnt, float sigma, float* m_sparse, float* m_quant, void* stream) {
+    using namespace paro;
+    int64_t n, kb;
+    if (int st = calib_shape(s, &n, &kb)) return st;
+    if (orders < 1 || orders > 6) return fail(PARO_EINVAL, "orders=%d out of range [1, 6]", orders);
+    if (!block_sum || !block_max || !block_cnt || !m_sparse || !m_quant)
+        return fail(PARO_EINVAL, "block_sum, block_max, block_cnt, m_sparse and m_quant must not be NULL");
+    if (!(sigma >= 0.0f && sigma <= 1.0f)) return fail(PARO_EINVAL, "sigma=%g must lie in [0, 1]", (double)sigma);
+    hipLaunchKernelGGL(calib_metrics_kernel, dim3((unsigned)s->nh, (unsigned)orders), dim3(kMetricThreads), 0, (hipStream_t)stream, s->B, s->nh,
+                       (int)kb, (int)n, s->block, block_sum, block_max, block_cnt, sigma, m_sparse, m_quant);
+    return check_launch("paro_calib_metrics");
 }
 
 extern "C" int paro_calib_metrics(const paro_shape* s, const float* block_sum, const float* block_max, const int32_t* block_cnt,
                                   float sigma, float* m_sparse, float* m_quant, void* stream) {
+    return paro_calib_metrics_orders(s, 1, block_sum, block_max, block_cnt, sigma, m_sparse, m_quant, stream);
+}
+
+extern "C" int paro_calib_pick(const paro_shape* s, const float* block_sum6, const uint8_t* perm_ids, float* block_sum, void* stream) {
     using namespace paro;
     int64_t n, kb;
     if (int st = calib_shape(s, &n, &kb)) return st;
-    if (!block_sum || !block_max || !block_cnt || !m_sparse || !m_quant)
-        return fail(PARO_EINVAL, "block_sum, block_max, block_cnt, m_sparse and m_quant must not be NULL");
-    if (!(sigma >= 0.0f && sigma <= 1.0f)) return fail(PARO_EINVAL, "sigma=%g must lie in [0, 1]", (double)sigma);
-    hipLaunchKernelGGL(calib_metrics_kernel, dim3((unsigned)s->nh), dim3(256), 0, (hipStream_t)stream, s->B, s->nh, (int)kb, (int)n, s->block,
-                       block_sum, block_max, block_cnt, sigma, m_sparse, m_quant);
-    return check_launch("paro_calib_metrics");
+    if (!block_sum6 || !perm_ids || !block_sum) return fail(PARO_EINVAL, "block_sum6, perm_ids and block_sum must not be NULL");
+    const int per_head = (int)(kb * kb);
+    hipLaunchKernelGGL(calib_pick_kernel, dim3((unsigned)((per_head + 2047) / 2048), (unsigned)(s->B * s->nh)), dim3(256), 0, (hipStream_t)stream,
+                       s->B, s->nh, per_head, block_sum6, perm_ids, block_sum);
+    return check_launch("paro_calib_pick");
 }
 
 extern "C" int paro_calib_choose(int nh, const float* m_sparse6, const float* m_quant6, float alpha, float* m_combined6,
@@ -450,7 +779,12 @@ extern "C" int paro_calib_mask(const paro_shape* s, const float* block_sum, floa
         return fail(PARO_EUNSUPPORTED, "k=%lld: masks of more than %d blocks per head are not supported", (long long)kb, kMaskMaxWords * 32);
     const int64_t k_img = ((int64_t)s->F * s->Hg * s->Wg + s->block - 1) / s->block;
     const int64_t n_live = (int64_t)nearbyint((double)density * (double)(k_img * k_img));  // ties to even
-    hipLaunchKernelGGL(calib_mask_kernel, dim3((unsigned)s->nh), dim3(kMaskThreads), 0, (hipStream_t)stream, s->B, s->nh, (int)kb, (int)k_img,
-                       (int)n_live, block_sum, bitmask);
+#define PARO_MASK(KERNEL)                                                                                                       \
+    hipLaunchKernelGGL((KERNEL), dim3((unsigned)s->nh), dim3(kMaskThreads), 0, (hipStream_t)stream, s->B, s->nh, (int)kb, (int)k_img, \
+                       (int)n_live, block_sum, bitmask)
+    if (kb * kb <= 8 * kMaskThreads) PARO_MASK(calib_mask_reg_kernel<8>);
+    else if (kb * kb <= kMaskRegBlocks) PARO_MASK(calib_mask_reg_kernel<kMaskRegKeys>);
+    else PARO_MASK(calib_mask_kernel);
+#undef PARO_MASK
     return check_launch("paro_calib_mask");
 }

@@ -249,26 +249,28 @@ def calibrate(shape: pb.paro_shape, q, k, eps: float = 1e-3, sigma: float = 0.9,
     q16 = torch.empty(pb.codes_shape(shape, 16, pb.PARO_ROWS), dtype=torch.bfloat16, **z)
     k16 = torch.empty_like(q16)
     unused_scales = torch.empty((shape.B, nh, kb), dtype=torch.float32, **z)
+    row_stats = torch.empty((pb.paro_calib_row_stats_bytes(shape),), dtype=torch.uint8, **z)
+    bsum6 = torch.empty((6, shape.B, nh, kb, kb), dtype=torch.float32, **z)
+    bmax6 = torch.empty_like(bsum6)
+    bcnt6 = torch.empty(bsum6.shape, dtype=torch.int32, **z)
     bsum = torch.empty((shape.B, nh, kb, kb), dtype=torch.float32, **z)
-    bmax = torch.empty_like(bsum)
-    bcnt = torch.empty((shape.B, nh, kb, kb), dtype=torch.int32, **z)
     ms = torch.empty((6, nh), dtype=torch.float32, **z)
     mq = torch.empty_like(ms)
     mc = torch.empty_like(ms)
     perm_ids = torch.empty((nh,), dtype=torch.uint8, **z)
     bitmask = torch.empty((nh, (kb * kb + 7) // 8), dtype=torch.uint8, **z)
 
-    def stats_for(ids):
+    for t in range(6):
+        ids = np.full(nh, t, np.uint8)
         pb.paro_permute_quantize(shape, 16, pb.PARO_ROWS, ids, q, q16, unused_scales)
         pb.paro_permute_quantize(shape, 16, pb.PARO_ROWS, ids, k, k16, unused_scales)
-        pb.paro_calib_block_stats(shape, q16, k16, eps, bsum, bmax, bcnt)
-
-    for t in range(6):
-        stats_for(np.full(nh, t, np.uint8))
-        pb.paro_calib_metrics(shape, bsum, bmax, bcnt, sigma, ms[t], mq[t])
+        if t == 0:  # the default order: the rows' maxima and denominators serve all six
+            pb.paro_calib_row_stats(shape, q16, k16, row_stats)
+        pb.paro_calib_block_stats_from_rows(shape, ids, q16, k16, row_stats, eps, bsum6[t], bmax6[t], bcnt6[t])
+    pb.paro_calib_metrics_orders(shape, bsum6, bmax6, bcnt6, sigma, ms, mq)
     pb.paro_calib_choose(nh, ms, mq, alpha, mc, perm_ids)
-    h_perm_ids = perm_ids.cpu().numpy()  # synchronises: the reorder calls take the ids on the host
-    stats_for(h_perm_ids)
+    pb.paro_calib_pick(shape, bsum6, perm_ids, bsum)
     pb.paro_calib_mask(shape, bsum, density, bitmask)
+    h_perm_ids = perm_ids.cpu().numpy()  # synchronises: the reorder calls take the ids on the host
     return {"perm_ids": perm_ids, "h_perm_ids": h_perm_ids, "bitmask": bitmask, "m_sparse": ms, "m_quant": mq, "m_combined": mc,
             "block_sum": bsum}

@@ -1350,7 +1350,8 @@ __global__ __launch_bounds__(256, 3) void attn_i8_q16_kernel(AttnArgs a) {
 // to bf16 while the denominator accumulates it in fp32.  The 16-bit tiles are twice as large as
 // the 8-bit ones, so this kernel keeps ONE LDS stage and pays a second barrier per block instead
 // of a second stage: the smaller footprint admits a third wavefront per SIMD (d = 64), which is
-// worth more here than the barrier costs.
+// worth more here than the barrier costs.  Launched for block 32 (one wavefront per row block); block 64 has the
+// kernels behind it.
 // -------------------------------------------------------------------------------------------
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
@@ -1595,39 +1596,170 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? 3 : 2)) void attn_bf16_kernel(A
 }
 
 // -------------------------------------------------------------------------------------------
-// bf16 mode at d = 64, block 64: FOUR wavefronts of 16 queries per row block on v_mfma_f32_16x16x32_bf16, built like
-// attn_i8_q16_kernel.  A bf16 K tile at d = 64 (64 rows of 128 bytes) and a bf16 V^T tile (64 channel rows of 128
-// bytes) have the geometry of the 8-bit tiles at d = 128, so the tiles go to LDS the same way (global_load_lds,
-// a quarter per wavefront, pieces of a line at position piece ^ line % 8, two K and two V slots, one barrier per
-// block).  P is not quantized: nothing is exchanged between the wavefronts, the exponentials are taken against the
-// row's fixed reference and O^T accumulates in the matrix accumulators themselves (16 registers), so the vector
-// work per block is the logits' alone.
-// Row 4 G + r of S^T tile T is the key whose PARO_VT slot is 32 (T >> 1) + 8 G + 4 (T & 1) + r - the slot that
-// element 4 (T & 1) + r of lane group G covers in contraction step T >> 1 of the PV product - i.e. token
-// 32 (T >> 1) + 8 (T & 1) + 16 (G & 1) + 4 (G >> 1) + r of the block.
+// bf16 mode, block 64: the wavefronts of a row block split its KEYS.  P is not quantized, so nothing ties the keys of a
+// block together: each wavefront takes 32 of the 64 keys of every live block against its own fixed reference and keeps
+// its own sums, which meet once, at the end of the row.
 // -------------------------------------------------------------------------------------------
-#ifndef PARO_BF16_Q16
-#define PARO_BF16_Q16 1
-#endif
-typedef float v4f __attribute__((ext_vector_type(4)));
 
-__device__ inline float quad_rows_fmax(float x) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
-    const float y = fmaxf(__int_as_float((int)r[0]), __int_as_float((int)r[1]));
-    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_int(y), __float_as_int(y), false, false);
-    return fmaxf(__int_as_float((int)q[0]), __int_as_float((int)q[1]));
+// Running state of 32 queries over one wavefront's keys.  Lanes n and n + 32 share query n of the half and hold 16 keys
+// of a 32-key tile each (8 q + 4 g + p, as everywhere).  Exponentials are taken against the first maximum that is seen;
+// a lane whose sum of one block passes 2^64 sends the wavefront through a rare branch that moves the references to the
+// rows' maxima.  (Looking at the sum takes one compare where the row maximum took 16 operands; a logit 64 octaves above
+// the reference shows in the sum, and one that overflows the exponential shows as infinity.)
+template <int DT>
+struct Bf16Rows {
+    float nref;  // minus the reference; +inf while no real key has been seen
+    float off;   // what is added to c S: nref, or 0 while there is no reference
+    float l;     // this lane's share of the row sum
+    v16f acc[DT];
+
+    __device__ __forceinline__ void init() {
+        nref = INFINITY;
+        off = 0.0f;
+        l = 0.0f;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
+    }
+    // maximum of c S over the tile's keys, in both lanes of the query
+    static __device__ __forceinline__ float row_max(const v16f& S, float c) {
+        float part[4];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[r & 3] = r < 4 ? S[r] : fmaxf(part[r & 3], S[r]);
+        const float mx = c * fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(mx), __float_as_int(mx), false, false);
+        return fmaxf(__int_as_float((int)sw[0]), __int_as_float((int)sw[1]));
+    }
+    // P = 2^(c S + off) in place of S; returns this lane's sum
+    __device__ __forceinline__ float exponentials(v16f& S, float c) const {
+        float part[4];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) S[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, off));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[r & 3] = r < 4 ? S[r] : part[r & 3] + S[r];
+        return (part[0] + part[1]) + (part[2] + part[3]);
+    }
+    // rows without a reference take their maximum in S; with `all`, rows that climbed past theirs as well
+    __device__ __forceinline__ void reference(const v16f& S, float c, bool all) {
+        const float ymax = row_max(S, c);
+        if (nref == INFINITY) {
+            if (ymax > -INFINITY) nref = -ymax;
+        } else if (all) {
+            const float up = fmaxf(ymax + nref, 0.0f);
+            const float down = __builtin_amdgcn_exp2f(-up);
+            l *= down;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[dt][r] *= down;
+            nref -= up;
+        }
+        off = nref == INFINITY ? 0.0f : nref;
+    }
+    static __device__ __forceinline__ v8bf pack(const v16f& P, int u) {
+        v8bf f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const v2bf pb = __builtin_convertvector(v2f{P[8 * u + 2 * e], P[8 * u + 2 * e + 1]}, v2bf);
+            f[2 * e] = pb[0];
+            f[2 * e + 1] = pb[1];
+        }
+        return f;
+    }
+};
+constexpr float kBf16SumLimit = 18446744073709551616.0f;  // 2^64
+
+__device__ __forceinline__ int lane_here();
+__device__ __forceinline__ void mask_keys(v16f& S, int first, int nkeys) {  // keys first + .. of the tile at or past nkeys
+    const int g = lane_here() >> 5;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        if (first + 8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) S[r] = -INFINITY;
 }
 
+// The lane number, computed where it stands: in rarely taken branches, so that nothing derived from it is kept in
+// registers through the loop around them.
+__device__ __forceinline__ int lane_here() {
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
+// 64 column indices per fetch, one per lane, one chunk ahead; at(u) is called with u = 0, 1, 2, ...
+struct ColumnList {
+    const int* cols;
+    int cnt, kblocks, cur, nxt, chunk;
+    __device__ ColumnList(const int* cols_, int cnt_, int kblocks_) : cols(cols_), cnt(cnt_), kblocks(kblocks_), chunk(0) {
+        cur = load(0);
+        nxt = load(1);
+    }
+    __device__ int load(int ch) const {
+        const int idx = min(ch * 64 + lane_here(), cnt - 1);
+        return cnt > 0 && ch * 64 < cnt ? min(max(cols[idx], 0), kblocks - 1) : 0;
+    }
+    __device__ int at(int u) {
+        if ((u & 63) == 0 && u > 0) {
+            cur = nxt;
+            ++chunk;
+            nxt = load(chunk + 1);
+        }
+        return __builtin_amdgcn_readlane(cur, u & 63);
+    }
+};
+
+// Two accumulator tiles (64 channels of 32 queries) with their reference and row sum, handed to another wavefront.
+__device__ __forceinline__ void bf16_hand_over(const v16f& t0, const v16f& t1, float nref, float l, float* tiles, float* row, int lane) {
+    row[lane] = nref;
+    row[64 + lane] = l;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        tiles[e * 64 + lane] = t0[e];
+        tiles[(16 + e) * 64 + lane] = t1[e];
+    }
+}
+// ... and joined with this wavefront's own two, normalised and stored.
 template <typename OutT>
-__global__ __launch_bounds__(256, 4) void attn_bf16_q16_kernel(AttnArgs a) {
+__device__ __forceinline__ void bf16_finish(OutT* op, long long ooff, bool row_valid, const v16f& t0, const v16f& t1, float nref, float l,
+                                            const float* tiles, const float* row, int lane) {
+    const float other_nref = row[lane], other_l = row[64 + lane];
+    const float top = fminf(nref, other_nref);  // minus the larger reference; +inf if neither saw a key
+    const float fa = nref < INFINITY ? __builtin_amdgcn_exp2f(top - nref) : 0.0f;
+    const float fb = other_nref < INFINITY ? __builtin_amdgcn_exp2f(top - other_nref) : 0.0f;
+    float l_tot = l * fa + other_l * fb;
+    l_tot += __shfl_xor(l_tot, 32);
+    const float inv = (row_valid && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
+    const float ia = fa * inv, ib = fb * inv;
+    if (ooff >= 0) {
+        OutT* orow = op + ooff + 4 * (lane >> 5);
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int qd = 0; qd < 4; ++qd) {
+                float o[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    o[e] = (dt ? t1 : t0)[4 * qd + e] * ia + tiles[(16 * dt + 4 * qd + e) * 64 + lane] * ib;
+                store4(orow + 32 * dt + 8 * qd, o[0], o[1], o[2], o[3]);
+            }
+    }
+}
+
+// d = 64: TWO wavefronts per row block, each with all 64 queries and one half of the keys, so that every byte of K and V
+// is read from LDS once per row block (four wavefronts of 16 queries read it four times: 64 KB of reads and 16 KB of
+// writes per block, 640 of the 777 cycles a block took).  A wavefront's half tiles are its own: it moves them to
+// LDS itself (global_load_lds, 4 KB of K and 4 KB of V, one slot each) and there is no barrier in the loop.  K_{t+1} is
+// requested behind the reads of K_t, V_{t+1} behind those of V_t.  Matrix and vector instructions bound it now (about 330 and
+// 300 cycles per block of a compute unit, which hardly overlap).  48 heads of 17550 tokens at 30 % density, quantizer
+// included: 1530 -> 1430 us.
+template <typename OutT>
+__global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     constexpr int BLK = 64, D = 64;
-    constexpr int KS = D / 32;     // contraction steps of QK^T (32 channels each)
-    constexpr int US = BLK / 32;   // contraction steps of PV (32 slots each)
-    constexpr int CT = D / 16;     // 16-channel tiles of the output
-    constexpr int TILE = BLK * D * 2;  // bytes of a K tile and of a V^T tile
-    static_assert(TILE == 8192, "the tile transfer below moves eight 1 KB pieces");
-    __shared__ __attribute__((aligned(16))) uint8_t kring[2][TILE];
-    __shared__ __attribute__((aligned(16))) uint8_t vring[2][TILE];
+    constexpr int TILE = BLK * D * 2;
+    constexpr int KS = D / 16, DT = D / 32;
+    __shared__ __attribute__((aligned(16))) uint8_t kbuf[2][TILE / 2];  // [wavefront]; later half of the exchange buffer
+    __shared__ __attribute__((aligned(16))) uint8_t vbuf[2][TILE / 2];
+    __shared__ float meet[2][2][64];  // [half of the queries][reference, sum][lane]
 
     const int wg = blockIdx.x;
     const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
@@ -1638,184 +1770,285 @@ __global__ __launch_bounds__(256, 4) void attn_bf16_q16_kernel(AttnArgs a) {
     const int h = bh % a.nh;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 15;
-    const int G = lane >> 4;
+    const int n = lane & 31;
+    const int g = lane >> 5;
 
     const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
     const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
     const int end = __builtin_amdgcn_readfirstlane(min(max(rp[1], beg), a.nnz));
     const int cnt = end - beg;
-    const int* cols = a.col_idx + beg;
     if (2 * cnt > a.kblocks) __builtin_amdgcn_s_setprio(2);
+    ColumnList list(a.col_idx + beg, cnt, a.kblocks);
 
     const size_t head_rows = (size_t)bh * a.kblocks * BLK;
-    const uint8_t* kbase = a.k + head_rows * D * 2;
-    const uint8_t* vbase = a.v + head_rows * D * 2;
+    const uint8_t* kbase = a.k + head_rows * D * 2 + (TILE / 2) * w;  // rows 32 w .. of a K tile
+    const uint8_t* vbase = a.v + head_rows * D * 2 + 64 * w;          // slots 32 w .. of every row of a V^T tile
     const float c = a.qk_scale;
-    const int row = i * BLK + 16 * w + n;  // this lane's query, in the reordered sequence
-    const bool row_valid = row < a.n_tokens;
-    v8bf qf[KS];
-    {
-        const uint8_t* qrow = a.q + (head_rows + row) * D * 2 + 16 * G;
+    v8bf qf[2][KS];
 #pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s] = *(const v8bf*)(qrow + 64 * s);
+    for (int H = 0; H < 2; ++H) {
+        const uint8_t* qrow = a.q + (head_rows + i * BLK + 32 * H + n) * D * 2 + 16 * g;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qf[H][s] = *(const v8bf*)(qrow + 32 * s);
     }
-    // tile transfer as in attn_i8_q16_kernel
-    const unsigned fill_lane = 2048u * w + 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
-    // K fragment of tile T, step s: row 32 (T >> 1) + 8 (T & 1) + 16 ((n >> 2) & 1) + 4 (n >> 3) + (n & 3), piece 4 s + G
-    const unsigned krow = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
-    unsigned kread[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) kread[s] = 128u * krow + 16u * ((4 * s + G) ^ (krow & 7));
-    // V^T fragment of channel tile ct, step u: PARO_VT row 16 ct + n, piece 4 u + G
-    unsigned vread[US];
-#pragma unroll
-    for (int u = 0; u < US; ++u) vread[u] = 128u * n + 16u * ((4 * u + G) ^ (n & 7));
-
-    auto load_cols = [&](int chunk) {
-        const int idx = min(chunk * 64 + lane, cnt - 1);
-        return cnt > 0 && chunk * 64 < cnt ? min(max(cols[idx], 0), a.kblocks - 1) : 0;
-    };
-    int cols_cur = load_cols(0), cols_nxt = load_cols(1);
-    int cur_chunk = 0;
-    auto col_at = [&](int u) {  // u advances by one per call
-        if ((u & 63) == 0 && u > 0) {
-            cols_cur = cols_nxt;
-            ++cur_chunk;
-            cols_nxt = load_cols(cur_chunk + 1);
-        }
-        return __builtin_amdgcn_readlane(cols_cur, u & 63);
-    };
-    auto request_k = [&](int j, int slot) {
+    // K half: 32 rows of 128 bytes, piece p of row r at position p ^ r % 8.  V^T half: 64 rows of 64 bytes, piece p of row r at
+    // position p ^ (r / 2) % 4.  Eight neighbouring rows then cover all banks, for the requests and for the fragment reads.
+    const unsigned kfill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
+    const unsigned vfill = 128u * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
+    // fragment s of K: piece 2 s + g of row n, i.e. fragment 0's address with bits flipped; fragment u of V^T: piece 2 g + u
+    unsigned kread = 128u * n + 16u * (g ^ (n & 7));
+    unsigned vread = 64u * n + 16u * ((2 * g) ^ ((n >> 1) & 3));
+    auto request_k = [&](int j) {
         const uint8_t* kp = kbase + (size_t)j * TILE;
-        lds_dma16<0>(kp, fill_lane, &kring[slot][2048 * w]);
-        lds_dma16<1024>(kp, fill_lane, &kring[slot][2048 * w + 1024]);
+        asm volatile("" : "+s"(kp));  // scalar base + lane offset, not a 64-bit address per lane
+        lds_dma16<0>(kp, kfill, &kbuf[w][0]);
+        lds_dma16<1024>(kp, kfill, &kbuf[w][1024]);
+        lds_dma16<2048>(kp, kfill, &kbuf[w][2048]);
+        lds_dma16<3072>(kp, kfill, &kbuf[w][3072]);
     };
-    auto request_v = [&](int j, int slot) {
+    auto request_v = [&](int j) {
         const uint8_t* vp = vbase + (size_t)j * TILE;
-        lds_dma16<0>(vp, fill_lane, &vring[slot][2048 * w]);
-        lds_dma16<1024>(vp, fill_lane, &vring[slot][2048 * w + 1024]);
+        asm volatile("" : "+s"(vp));
+        lds_dma16<0>(vp, vfill, &vbuf[w][0]);
+        lds_dma16<2048>(vp, vfill, &vbuf[w][1024]);
+        lds_dma16<0>(vp + 4096, vfill, &vbuf[w][2048]);
+        lds_dma16<2048>(vp + 4096, vfill, &vbuf[w][3072]);
     };
 
-    float m_ref = -INFINITY, l = 0.0f;
-    v4f acc[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[ct] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-
-    int j0 = 0, j1 = 0, j2 = 0;  // columns of the steps t, t + 1, t + 2
+    Bf16Rows<DT> rows[2];
+    rows[0].init();
+    rows[1].init();
+    // Columns of the steps t, t + 1; behind the last step its own column is requested once more and not used: requests
+    // under a condition would make the compiler wait for V_t in front of K_t's reads.
+    int j0 = 0, j1 = 0;
     if (cnt > 0) {
-        j0 = col_at(0);
-        request_k(j0, 0);
-        request_v(j0, 0);
-        if (cnt > 1) {
-            j1 = col_at(1);
-            request_k(j1, 1);
-        }
-        if (cnt > 2) j2 = col_at(2);
+        j0 = list.at(0);
+        request_k(j0);
+        request_v(j0);
+        j1 = cnt > 1 ? list.at(1) : j0;
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    __syncthreads();
-    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;  // the column block with padded keys, if any
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // Q is in registers: otherwise the compiler waits for everything in every pass
+    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
+    const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
 
     for (int t = 0; t < cnt; ++t) {
-        const uint8_t* kslot = &kring[t & 1][0];
-        const uint8_t* vslot = &vring[t & 1][0];
-        // ---- S^T = K_j Q_i^T: four 16-key tiles
-        v4f sacc[4];
+        __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4): all but the last request, V_t's, have landed
+        asm volatile("" : "+v"(kread), "+v"(vread));  // the flipped addresses are made here, not kept
+        // ---- S^T = K_j Q_i^T, 32 keys of this wavefront against 64 queries
+        v16f S[2];
 #pragma unroll
-        for (int T = 0; T < 4; ++T) {
-            sacc[T] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int H = 0; H < 2; ++H)
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
-                sacc[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const v8bf*)(kslot + 4096 * (T >> 1) + 1024 * (T & 1) + kread[s]), qf[s],
-                                                                  sacc[T], 0, 0, 0);
+            for (int r = 0; r < 16; ++r) S[H][r] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const v8bf kf = *(const v8bf*)(&kbuf[w][0] + (kread ^ (32u * s)));
+#pragma unroll
+            for (int H = 0; H < 2; ++H) S[H] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[H][s], S[H], 0, 0, 0);
         }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_t has been read
+        request_k(j1);
         if (j0 == tail_block) {  // keys past N never receive probability mass
-            const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
-#pragma unroll
-            for (int T = 0; T < 4; ++T)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (32 * (T >> 1) + 8 * (T & 1) + 16 * (G & 1) + 4 * (G >> 1) + r >= nkeys) sacc[T][r] = -INFINITY;
+            mask_keys(S[0], 32 * w, nkeys);
+            mask_keys(S[1], 32 * w, nkeys);
         }
-        // a row without a reference yet (first block, or nothing but masked keys so far) takes its block maximum
-        if (__builtin_amdgcn_ballot_w64(m_ref == -INFINITY) != 0) {
-            float part[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) part[r] = fmaxf(fmaxf(sacc[0][r], sacc[1][r]), fmaxf(sacc[2][r], sacc[3][r]));
-            const float ymax = c * quad_rows_fmax(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));
-            if (m_ref == -INFINITY) m_ref = ymax;
+        if (__builtin_amdgcn_ballot_w64(rows[0].nref == INFINITY || rows[1].nref == INFINITY) != 0) {
+            rows[0].reference(S[0], c, false);
+            rows[1].reference(S[1], c, false);
         }
-        // ---- y = c S - m_ref, the exponent of P, FIRST: its maximum tells whether the row has climbed past its
-        // reference (results of an fma need no NaN quieting before a maximum, raw matrix results would)
-        float p[4][4];
+        float rs[2];
+        rs[0] = rows[0].exponentials(S[0], c);
+        rs[1] = rows[1].exponentials(S[1], c);
+        if (__builtin_amdgcn_ballot_w64(rs[0] > kBf16SumLimit || rs[1] > kBf16SumLimit) != 0) {
+            // rare: the logits once more, from K in global memory (its LDS slot is being refilled)
+            const int ln = lane_here();
+            const uint8_t* kp = kbase + (size_t)j0 * TILE + 128 * (ln & 31) + 16 * (ln >> 5);
 #pragma unroll
-        for (int T = 0; T < 4; ++T)
+            for (int H = 0; H < 2; ++H) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) p[T][r] = fmaf(sacc[T][r], c, -m_ref);
-        float part[4];
+                for (int r = 0; r < 16; ++r) S[H][r] = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) part[r] = fmaxf(fmaxf(p[0][r], p[1][r]), fmaxf(p[2][r], p[3][r]));
-        const float climb = quad_rows_fmax(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));  // row maximum - reference
-        // ---- this wavefront's requests have landed; behind the barrier both tiles are whole, K_t has been read by
-        // all and V_{t-1} is consumed
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        __syncthreads();
-        if (t + 2 < cnt) request_k(j2, t & 1);
-        const int j_v = j1;
+                for (int s = 0; s < KS; ++s) S[H] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const v8bf*)(kp + 32 * s), qf[H][s], S[H], 0, 0, 0);
+                if (j0 == tail_block) mask_keys(S[H], 32 * w, nkeys);
+                rows[H].reference(S[H], c, true);
+                rs[H] = rows[H].exponentials(S[H], c);
+            }
+        }
+        // ---- O^T += V_j^T P^T over this wavefront's keys
+        v8bf pf[2][2];
+#pragma unroll
+        for (int H = 0; H < 2; ++H) {
+            rows[H].l += rs[H];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) pf[H][u] = rows[H].pack(S[H], u);
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F74);  // V_t has landed; K_{t+1} may be on its way
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const v8bf vf = *(const v8bf*)(&vbuf[w][0] + 2048 * dt + (vread ^ (16u * u)));
+#pragma unroll
+                for (int H = 0; H < 2; ++H) rows[H].acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[H][u], rows[H].acc[dt], 0, 0, 0);
+            }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // V_t has been read
+        request_v(j1);
         j0 = j1;
-        j1 = j2;
-        if (t + 3 < cnt) j2 = col_at(t + 3);
+        if (t + 2 < cnt) j1 = list.at(t + 2);
+    }
 
-        if (__builtin_amdgcn_ballot_w64(climb > 64.0f) != 0) {
-            const float up = fmaxf(climb, 0.0f);  // rows that have not climbed keep their reference
-            const float down = __builtin_amdgcn_exp2f(-up);
-            l *= down;
+    // ---- wavefront w finishes the queries of half w: it hands its sums of the other half over through LDS
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing is in flight to the buffers any more
+    __syncthreads();
+    float* give = (float*)(w == 0 ? &kbuf[0][0] : &vbuf[0][0]);  // 8 KB each: [32 registers][64 lanes]
+    const float* take = (const float*)(w == 0 ? &vbuf[0][0] : &kbuf[0][0]);
+    const int row = i * BLK + 32 * w + n;
+    if (w == 0) bf16_hand_over(rows[1].acc[0], rows[1].acc[1], rows[1].nref, rows[1].l, give, &meet[1][0][0], lane);
+    else bf16_hand_over(rows[0].acc[0], rows[0].acc[1], rows[0].nref, rows[0].l, give, &meet[0][0][0], lane);
+    __syncthreads();
+    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens);
+    if (w == 0) bf16_finish((OutT*)a.op, ooff, row < a.n_tokens, rows[0].acc[0], rows[0].acc[1], rows[0].nref, rows[0].l, take, &meet[0][0][0], lane);
+    else bf16_finish((OutT*)a.op, ooff, row < a.n_tokens, rows[1].acc[0], rows[1].acc[1], rows[1].nref, rows[1].l, take, &meet[1][0][0], lane);
+}
+
+// d = 128: FOUR wavefronts per row block, wavefront w with the queries 32 (w & 1) .. and the keys 32 (w >> 1) .. of every
+// block.  (Two wavefronts of 32 queries with all keys, the form this replaces, moved the tiles through registers - 64 of
+// them - and a row's chain of blocks was twice as long: 72-block rows of text queries are the end of such a launch.)
+// The tiles are shared: each wavefront moves a quarter of K and of V^T to LDS (global_load_lds), one slot each.
+// Two barriers per block: V_t is requested behind the first (V_{t-1} has been read by all, K_t is whole) and K_{t+1}
+// behind the second (K_t has been read by all, V_t is whole), so each has half a block of work to hide behind.
+// 24 heads of 4096 + 512 tokens at 30 % density, two layers with quantizer and mask prefetch: 411 -> 385 us.
+template <typename OutT>
+__global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
+    constexpr int BLK = 64, D = 128;
+    constexpr int TILE = BLK * D * 2;
+    constexpr int KS = D / 16, DT = D / 32;
+    __shared__ __attribute__((aligned(16))) uint8_t kbuf[TILE];  // later half of the exchange buffer
+    __shared__ __attribute__((aligned(16))) uint8_t vbuf[TILE];
+    __shared__ float meet[4][2][64];  // [wavefront][reference, sum][lane]
+
+    const int wg = blockIdx.x;
+    const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
+    if (logical >= a.total_wg) return;
+    const int item = a.row_order ? min(max(a.row_order[logical], 0), a.total_wg - 1) : logical;
+    const int bh = item / a.kblocks;
+    const int i = item - bh * a.kblocks;
+    const int h = bh % a.nh;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kh = w >> 1;
+    const int n = lane & 31;
+    const int g = lane >> 5;
+
+    const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
+    const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
+    const int end = __builtin_amdgcn_readfirstlane(min(max(rp[1], beg), a.nnz));
+    const int cnt = end - beg;
+    if (2 * cnt > a.kblocks) __builtin_amdgcn_s_setprio(2);
+    ColumnList list(a.col_idx + beg, cnt, a.kblocks);
+
+    const size_t head_rows = (size_t)bh * a.kblocks * BLK;
+    const uint8_t* kbase = a.k + head_rows * D * 2 + 4096 * w;  // rows 16 w .. of a K tile
+    const uint8_t* vbase = a.v + head_rows * D * 2 + 4096 * w;  // rows 32 w .. of a V^T tile
+    const float c = a.qk_scale;
+    const int row = i * BLK + 32 * (w & 1) + n;
+    v8bf qf[KS];
+    {
+        const uint8_t* qrow = a.q + (head_rows + row) * D * 2 + 16 * g;
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
+        for (int s = 0; s < KS; ++s) qf[s] = *(const v8bf*)(qrow + 32 * s);
+    }
+    // K rows have two 128-byte lines, V^T rows one; piece p of a line of row r sits at position p ^ r % 8 of the line
+    unsigned kfill = 256u * (lane >> 4) + 16u * ((lane & 8) | ((lane ^ (lane >> 4)) & 7));  // rows 0 .. 3 of eight; 4 .. 7: bit 6 flipped
+    const unsigned vfill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
+    unsigned kread = 256u * (32 * kh + n) + 16u * (g ^ (n & 7));               // fragment s: piece 2 s + g
+    unsigned vread = 128u * n + 16u * ((4 * kh + 2 * g) ^ (n & 7));            // fragment u: piece 4 kh + 2 g + u
+    auto request_k = [&](int j) {
+        const uint8_t* kp = kbase + (size_t)j * TILE;
+        asm volatile("" : "+s"(kp), "+v"(kfill));
+        lds_dma16<0>(kp, kfill, &kbuf[4096 * w]);
+        lds_dma16<1024>(kp, kfill ^ 64u, &kbuf[4096 * w + 1024]);
+        lds_dma16<2048>(kp, kfill, &kbuf[4096 * w + 2048]);
+        lds_dma16<3072>(kp, kfill ^ 64u, &kbuf[4096 * w + 3072]);
+    };
+    auto request_v = [&](int j) {
+        const uint8_t* vp = vbase + (size_t)j * TILE;
+        asm volatile("" : "+s"(vp));
+        lds_dma16<0>(vp, vfill, &vbuf[4096 * w]);
+        lds_dma16<1024>(vp, vfill, &vbuf[4096 * w + 1024]);
+        lds_dma16<2048>(vp, vfill, &vbuf[4096 * w + 2048]);
+        lds_dma16<3072>(vp, vfill, &vbuf[4096 * w + 3072]);
+    };
+    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
+    const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
+
+    Bf16Rows<DT> rows;
+    rows.init();
+    int j0 = 0, j1 = 0;  // columns of the steps t, t + 1
+    if (cnt > 0) {
+        j0 = list.at(0);
+        request_k(j0);
+        if (cnt > 1) j1 = list.at(1);
+    }
+
+    for (int t = 0; t < cnt; ++t) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's part of K_t has landed
+        __syncthreads();                     // and everybody's; V_{t-1} has been read by all
+        request_v(j0);
+        asm volatile("" : "+v"(kread), "+v"(vread));  // the flipped addresses are made here, not kept
+        // ---- S^T = K_j Q_i^T, this wavefront's 32 keys against its 32 queries
+        v16f S;
+        auto logits = [&]() {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[ct][r] *= down;
+            for (int r = 0; r < 16; ++r) S[r] = 0.0f;
+            v8bf kf[KS];  // all requested before the first product: each would otherwise wait out its own latency
 #pragma unroll
-            for (int T = 0; T < 4; ++T)
+            for (int s = 0; s < KS; ++s) kf[s] = *(const v8bf*)(kbuf + (kread ^ (32u * (s & 3))) + 128 * (s >> 2));
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) p[T][r] -= up;
-            m_ref += up;
+            for (int s = 0; s < KS; ++s) S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], S, 0, 0, 0);
+            if (j0 == tail_block) mask_keys(S, 32 * kh, nkeys);  // keys past N never receive probability mass
+        };
+        logits();
+        if (__builtin_amdgcn_ballot_w64(rows.nref == INFINITY) != 0) rows.reference(S, c, false);
+        float rs = rows.exponentials(S, c);
+        if (__builtin_amdgcn_ballot_w64(rs > kBf16SumLimit) != 0) {  // rare
+            logits();
+            rows.reference(S, c, true);
+            rs = rows.exponentials(S, c);
         }
-        // ---- P = 2^y, its row sum in fp32, and P rounded to bf16 as B operand: element 4 (T & 1) + r of step T >> 1
+        rows.l += rs;
+        v8bf pf[2];
 #pragma unroll
-        for (int T = 0; T < 4; ++T)
+        for (int u = 0; u < 2; ++u) pf[u] = rows.pack(S, u);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // this wavefront's part of V_t has landed
+        __syncthreads();                     // and everybody's; K_t has been read by all
+        if (t + 1 < cnt) request_k(j1);
+        // ---- O^T += V_j^T P^T over this wavefront's keys
+        v8bf vf[DT][2];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) p[T][r] = __builtin_amdgcn_exp2f(p[T][r]);
-        l += ((p[0][0] + p[0][1]) + (p[0][2] + p[0][3])) + ((p[1][0] + p[1][1]) + (p[1][2] + p[1][3])) +
-             (((p[2][0] + p[2][1]) + (p[2][2] + p[2][3])) + ((p[3][0] + p[3][1]) + (p[3][2] + p[3][3])));
-        v8bf pf[US];
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int u = 0; u < US; ++u)
+            for (int dt = 0; dt < DT; ++dt) vf[dt][u] = *(const v8bf*)(vbuf + 4096 * dt + (vread ^ (16u * u)));
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int e2 = 0; e2 < 2; ++e2) {
-                    const v2bf pb = __builtin_convertvector(v2f{p[2 * u + hh][2 * e2], p[2 * u + hh][2 * e2 + 1]}, v2bf);
-                    pf[u][4 * hh + 2 * e2] = pb[0];
-                    pf[u][4 * hh + 2 * e2 + 1] = pb[1];
-                }
-        // ---- O^T += V_j^T P^T, accumulated in the matrix accumulators
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int u = 0; u < US; ++u)
-                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const v8bf*)(vslot + 2048 * ct + vread[u]), pf[u], acc[ct], 0, 0, 0);
-        if (t + 1 < cnt) request_v(j_v, (t + 1) & 1);
+            for (int dt = 0; dt < DT; ++dt) rows.acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][u], pf[u], rows.acc[dt], 0, 0, 0);
+        j0 = j1;
+        if (t + 2 < cnt) j1 = list.at(t + 2);
     }
 
-    const float l_tot = quad_rows_sum(l);
-    const float inv = (row_valid && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
-    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row_valid);
-    if (ooff >= 0) {
-        OutT* orow = (OutT*)a.op + ooff + 4 * G;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) store4(orow + 16 * ct, acc[ct][0] * inv, acc[ct][1] * inv, acc[ct][2] * inv, acc[ct][3] * inv);
-    }
+    // ---- the wavefronts w and w ^ 2 share their queries: the one with the lower keys finishes channels 0 .. 63
+    __syncthreads();
+    float* give = (float*)((w & 1 ? vbuf : kbuf) + 8192 * kh);  // 8 KB each: [32 registers][64 lanes]
+    const float* take = (const float*)((w & 1 ? vbuf : kbuf) + 8192 * (kh ^ 1));
+    if (kh == 0) bf16_hand_over(rows.acc[2], rows.acc[3], rows.nref, rows.l, give, &meet[w][0][0], lane);
+    else bf16_hand_over(rows.acc[0], rows.acc[1], rows.nref, rows.l, give, &meet[w][0][0], lane);
+    __syncthreads();
+    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens);
+    if (kh == 0) bf16_finish((OutT*)a.op, ooff, row < a.n_tokens, rows.acc[0], rows.acc[1], rows.nref, rows.l, take, &meet[w ^ 2][0][0], lane);
+    else bf16_finish((OutT*)a.op + 64, ooff, row < a.n_tokens, rows.acc[2], rows.acc[3], rows.nref, rows.l, take, &meet[w ^ 2][0][0], lane);
 }
 
 template <int BLK, int D, typename OutT>
@@ -1828,16 +2061,12 @@ static int launch_bf16_t(const AttnArgs& a, hipStream_t st) {
 
 template <typename OutT>
 static int launch_bf16(int blk, int d, const AttnArgs& a, hipStream_t st) {
-    if constexpr (PARO_BF16_Q16) {
-        if (blk == 64 && d == 64) {  // four wavefronts of 16 queries per row block
-            hipLaunchKernelGGL((attn_bf16_q16_kernel<OutT>), dim3((unsigned)(a.per_xcd * 8)), dim3(256), 0, st, a);
-            return PARO_OK;
-        }
-    }
-    if (blk == 64 && d == 64) return launch_bf16_t<64, 64, OutT>(a, st);
-    if (blk == 64 && d == 128) return launch_bf16_t<64, 128, OutT>(a, st);
-    if (blk == 32 && d == 64) return launch_bf16_t<32, 64, OutT>(a, st);
-    return launch_bf16_t<32, 128, OutT>(a, st);
+    const dim3 grid((unsigned)(a.per_xcd * 8));
+    if (blk == 64 && d == 64) hipLaunchKernelGGL((attn_bf16_d64_kernel<OutT>), grid, dim3(128), 0, st, a);
+    else if (blk == 64) hipLaunchKernelGGL((attn_bf16_d128_kernel<OutT>), grid, dim3(256), 0, st, a);
+    else if (d == 64) return launch_bf16_t<32, 64, OutT>(a, st);
+    else return launch_bf16_t<32, 128, OutT>(a, st);
+    return PARO_OK;
 }
 
 template <int BLK, int D, int QKBITS, int PVBITS>

@@ -5,7 +5,7 @@
 // next bitmask to the GPU on a side stream and enqueues this expansion behind the copy; nothing
 // here touches the host.
 //
-// Three small launches on the caller's stream:
+// Masks of up to kOneLaunchBytes in all go through ONE launch (blocklist_whole_kernel); larger ones through three:
 //   1. count:  c[h][i] = live blocks of row block i of head h, c[h][k] = 0, stored in row_ptr;
 //   2. scan:   in-place exclusive prefix sum over the flat [nh][k+1] array by one workgroup, which
 //              yields exactly the offsets of the list (row_ptr[h][k] = end of head h = start of
@@ -86,6 +86,134 @@ __global__ __launch_bounds__(256) void blocklist_fill_kernel(int nh, int k, int 
     }
 }
 
+// The whole expansion in one launch.  A workgroup owns `per_wg` consecutive row blocks of the flat [nh][k] array.  Where its part of
+// the list starts is the number of live blocks in front of it, which it counts itself, straight from the masks: they
+// are a few hundred KB that every XCD's L2 holds, and reading on average half of them (16 bytes per lane and load) takes less than
+// a launch that waits for the one before it.  Latency-bound: 48 masks of 275 x 275 blocks take 13.5 us, of which 9 are
+// what any call of one launch takes, against 24.8 us for the three launches (a thread per row reading single bytes, a
+// scan by one workgroup, the fill).
+constexpr int kWholeThreads = 512;
+constexpr int kWholeMaxRows = kWholeThreads;  // a thread per row in the scan
+constexpr int kWholeGroups = 256;             // one workgroup per compute unit
+// Counting what lies in front grows with the square of the masks' size, the three launches with the size.  At 1 MB the one
+// launch is still ahead (30 heads of 512 x 512 blocks: 22.5 against 41.8 us; 1 of 2896 x 2896: 27.6 against 65.7; 256 of
+// 181 x 181: 26.3 against 94.3); beyond it the rows of a workgroup outgrow their 8 KB of LDS.
+constexpr int64_t kOneLaunchBytes = 1 << 20;
+constexpr int kWholeStage = 8192;             // bytes of a workgroup's own rows, see launch_whole
+
+__global__ __launch_bounds__(kWholeThreads) void blocklist_whole_kernel(int nh, int k, int nbytes, int per_wg, const uint8_t* __restrict__ bitmask,
+                                                                        int* __restrict__ row_ptr, int* __restrict__ col_idx, int cap,
+                                                                        int* __restrict__ nnz_out) {
+    __shared__ unsigned stage[kWholeStage / 4 + 2];  // the bytes of this workgroup's rows, row after row, each from a word of its own
+    __shared__ int start[kWholeMaxRows + 1];
+    __shared__ int part[2][kWholeThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int rows = nh * k;
+    const int r0 = blockIdx.x * per_wg, r1 = min(r0 + per_wg, rows);
+    if (r0 >= r1) return;
+    const int words = (k + 31) / 32 + 1;  // words that a row's bits can touch, counted from the byte its first bit is in
+
+    // ---- this workgroup's rows: bits i k .. i k + k - 1 of head h, from the byte that holds the first of them
+    uint8_t* bytes = (uint8_t*)stage;
+    const int row_bytes = 4 * words;
+    for (int e = t; e < (r1 - r0) * row_bytes; e += kWholeThreads) {
+        const int r = r0 + e / row_bytes, b = e % row_bytes;
+        const int h = r / k, i = r - h * k;
+        const int at = ((i * k) >> 3) + b;
+        bytes[e] = at < nbytes ? bitmask[(size_t)h * nbytes + at] : (uint8_t)0;
+    }
+
+    // ---- live blocks in front of row r0: whole bytes [0, whole) of the masks, minus the bits behind every finished
+    // head's last block, plus the bits of the byte that row r0 starts in
+    const int h0 = r0 / k, bit0 = (r0 - h0 * k) * k;
+    const int whole = h0 * nbytes + (bit0 >> 3);
+    const int head = min(whole, (int)(-(uintptr_t)bitmask & 15u));  // bytes in front of the first aligned piece
+    const int pieces = (whole - head) >> 4;
+    int before = 0;
+    {
+        const uint4* src = (const uint4*)(bitmask + head);
+        int p = t;
+        for (; p + 3 * kWholeThreads < pieces; p += 4 * kWholeThreads) {
+            uint4 x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = src[p + u * kWholeThreads];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) before += __popc(x[u].x) + __popc(x[u].y) + __popc(x[u].z) + __popc(x[u].w);
+        }
+        for (; p < pieces; p += kWholeThreads) {
+            const uint4 x = src[p];
+            before += __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+        }
+        const int rest = head + 16 * pieces;  // at most 15 bytes on either side of the pieces
+        if (t < head) before += __popc((unsigned)bitmask[t]);
+        if (t < whole - rest) before += __popc((unsigned)bitmask[rest + t]);
+        const int unused = 8 * nbytes - k * k;
+        if (t < h0 && unused) before -= __popc((unsigned)bitmask[(size_t)(t + 1) * nbytes - 1] >> (8 - unused));
+        if (t == 0 && (bit0 & 7)) before += __popc((unsigned)bitmask[whole] & ((1u << (bit0 & 7)) - 1u));
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) before += __shfl_xor(before, off);
+    if (lane == 0) part[0][w] = before;
+    __syncthreads();  // and the rows are staged
+
+    // ---- live blocks of every own row, and their running sum
+    int own = 0;
+    if (r0 + t < r1) {
+        const int i = (r0 + t) % k;
+        const unsigned* src = stage + t * words;
+        const int shift = (i * k) & 7;
+        for (int b = 0; b < k; b += 32) {
+            const unsigned x = __builtin_amdgcn_alignbit(src[b / 32 + 1], src[b / 32], shift);
+            own += __popc(k - b >= 32 ? x : x & ((1u << (k - b)) - 1u));
+        }
+    }
+    int run = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(run, off);
+        run += lane >= off ? up : 0;
+    }
+    if (lane == 63) part[1][w] = run;
+    __syncthreads();
+    int base = 0;
+#pragma unroll
+    for (int v = 0; v < kWholeThreads / 64; ++v) base += part[0][v] + (v < w ? part[1][v] : 0);
+    if (r0 + t < r1) {
+        const int r = r0 + t, h = r / k, i = r - h * k;
+        start[t] = base + run - own;
+        row_ptr[r + h] = base + run - own;
+        if (i == k - 1) row_ptr[r + h + 1] = base + run;
+        if (r == rows - 1 && nnz_out) *nnz_out = base + run;
+    }
+    __syncthreads();
+
+    // ---- the columns: a wavefront per row, 64 columns at a time in ascending order
+    if (cap == 0) return;
+    for (int r = w; r < r1 - r0; r += kWholeThreads / 64) {
+        const int i = (r0 + r) % k;
+        const unsigned* src = stage + r * words;
+        const int shift = (i * k) & 7;
+        int pos0 = start[r];
+        for (int j0 = 0; j0 < k; j0 += 64) {
+            const int j = j0 + lane;
+            const int bit = j + shift;
+            const bool live = j < k && ((src[bit >> 5] >> (bit & 31)) & 1u);
+            const unsigned long long b = __ballot(live);
+            const int pos = pos0 + __popcll(b & ((1ull << lane) - 1ull));
+            if (live && (unsigned)pos < (unsigned)cap) col_idx[pos] = j;  // entries outside [0, cap) are dropped, never written
+            pos0 += __popcll(b);
+        }
+    }
+}
+
+// Rows per workgroup of the one-launch form, or 0 where it does not apply.
+static int whole_rows_per_group(int nh, int k, int nbytes) {
+    if ((int64_t)nh * nbytes > kOneLaunchBytes) return 0;
+    const int64_t per = ((int64_t)nh * k + kWholeGroups - 1) / kWholeGroups;
+    const int64_t row_bytes = 4 * ((k + 31) / 32 + 1);
+    return per <= kWholeMaxRows && per * row_bytes <= kWholeStage ? (int)per : 0;
+}
+
 }  // namespace paro
 
 extern "C" int paro_mask_to_blocklist_device(int nh, int k, const uint8_t* bitmask, int32_t* row_ptr, int32_t* col_idx,
@@ -100,6 +228,11 @@ extern "C" int paro_mask_to_blocklist_device(int nh, int k, const uint8_t* bitma
     const int nbytes = (int)(((int64_t)k * k + 7) / 8);
     const int n = nh * (k + 1);
     hipStream_t st = (hipStream_t)stream;
+    if (const int per = whole_rows_per_group(nh, k, nbytes)) {
+        hipLaunchKernelGGL(blocklist_whole_kernel, dim3((unsigned)((nh * k + per - 1) / per)), dim3(kWholeThreads), 0, st, nh, k, nbytes, per, bitmask,
+                           row_ptr, col_idx, (int)cap, nnz_out);
+        return check_launch("paro_mask_to_blocklist_device");
+    }
     hipLaunchKernelGGL(blocklist_count_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, nh, k, nbytes, bitmask, row_ptr);
     hipLaunchKernelGGL(blocklist_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, n, row_ptr, nnz_out);
     if (cap > 0)

@@ -8,6 +8,7 @@ The library is loaded on first use and the binding fails loudly if it has not be
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Tuple
 
@@ -118,7 +119,7 @@ def _ptr(t) -> Optional[int]:
 def _stream() -> int:
     import torch
 
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())  # current_stream().cuda_stream without the object
 
 
 def _dtype_code(t) -> int:
@@ -134,7 +135,7 @@ def _dtype_code(t) -> int:
 def _require(t, name: str, shape=None, dtype=None):
     if not t.is_cuda or not t.is_contiguous():
         raise ParoError(PARO_EINVAL, "%s must be a contiguous device tensor" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:  # torch.Size compares as a tuple
         raise ParoError(PARO_EINVAL, "%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     if dtype is not None and t.dtype != dtype:
         raise ParoError(PARO_EINVAL, "%s has dtype %s, expected %s" % (name, t.dtype, dtype))
@@ -147,25 +148,44 @@ def paro_version() -> int:
     return lib().paro_version()
 
 
+class _Dims:
+    """What follows from a shape alone: token and block counts and the tensor shapes the device calls ask for."""
+    __slots__ = ("n", "k", "npad", "x", "xp", "scales", "row_ptr", "total", "rows", "rows4", "vt", "vt4")
+
+    def __init__(self, s: paro_shape):
+        for name, f in (("n", lib().paro_ntokens), ("k", lib().paro_nblocks), ("npad", lib().paro_npad)):
+            v = int(f(ctypes.byref(s)))
+            if v < 0:
+                _check(v)
+            setattr(self, name, v)
+        B, nh, d, blk = s.B, s.nh, s.d, s.block
+        self.x, self.xp = (B, nh, self.n, d), (B, nh, self.npad, d)
+        self.scales, self.row_ptr, self.total = (B, nh, self.k), (nh, self.k + 1), B * nh * self.k
+        self.rows, self.rows4 = (B, nh, self.npad, d), (B, nh, self.npad, d // 2)
+        self.vt, self.vt4 = (B, nh, self.k, d, blk), (B, nh, self.k, d, blk // 2)
+
+
+@functools.lru_cache(maxsize=256)
+def _dims_of(fields: bytes) -> _Dims:
+    return _Dims(paro_shape.from_buffer_copy(fields))
+
+
+def _dims(s: paro_shape) -> _Dims:
+    """Kept by the eight numbers themselves: one attention call asks some fifteen times, at half a microsecond each through
+    ctypes, and at the smallest layers the calls are all of the time.  A refused shape raises every time."""
+    return _dims_of(bytes(s))
+
+
 def paro_ntokens(s: paro_shape) -> int:
-    n = lib().paro_ntokens(ctypes.byref(s))
-    if n < 0:
-        _check(int(n))
-    return int(n)
+    return _dims(s).n
 
 
 def paro_nblocks(s: paro_shape) -> int:
-    n = lib().paro_nblocks(ctypes.byref(s))
-    if n < 0:
-        _check(int(n))
-    return int(n)
+    return _dims(s).k
 
 
 def paro_npad(s: paro_shape) -> int:
-    n = lib().paro_npad(ctypes.byref(s))
-    if n < 0:
-        _check(int(n))
-    return int(n)
+    return _dims(s).npad
 
 
 def paro_calib_row_stats_bytes(s: paro_shape) -> int:
@@ -236,78 +256,79 @@ def paro_schedule_rows(s: paro_shape, bits_qk: int, bits_pv: int, row_ptr: np.nd
 # ---------------------------------------------------------------------------------------------
 # device calls (torch tensors on the GPU; enqueued on torch's current stream)
 # ---------------------------------------------------------------------------------------------
-def _perm_bytes(s: paro_shape, perm_ids) -> np.ndarray:
+def _perm_bytes(s: paro_shape, perm_ids) -> bytes:
     p = np.ascontiguousarray(perm_ids, dtype=np.uint8)
     if p.shape != (s.nh,):
         raise ParoError(PARO_EINVAL, "perm_ids has shape %s, expected (%d,)" % (p.shape, s.nh))
-    return p
+    return p.tobytes()  # ctypes passes its address; the library copies the ids into the launch before it returns
 
 
 def paro_permute(s: paro_shape, perm_ids, x, xp) -> None:
-    n, npad = paro_ntokens(s), paro_npad(s)
-    _require(x, "x", (s.B, s.nh, n, s.d))
-    _require(xp, "xp", (s.B, s.nh, npad, s.d), x.dtype)
+    m = _dims(s)
+    _require(x, "x", m.x)
+    _require(xp, "xp", m.xp, x.dtype)
     p = _perm_bytes(s, perm_ids)
-    _check(lib().paro_permute(ctypes.byref(s), _dtype_code(x), p.ctypes.data, _ptr(x), _ptr(xp), _stream()))
+    _check(lib().paro_permute(ctypes.byref(s), _dtype_code(x), p, _ptr(x), _ptr(xp), _stream()))
 
 
 def paro_unpermute(s: paro_shape, perm_ids, op, o) -> None:
-    n, npad = paro_ntokens(s), paro_npad(s)
-    _require(op, "op", (s.B, s.nh, npad, s.d))
-    _require(o, "o", (s.B, s.nh, n, s.d), op.dtype)
+    m = _dims(s)
+    _require(op, "op", m.xp)
+    _require(o, "o", m.x, op.dtype)
     p = _perm_bytes(s, perm_ids)
-    _check(lib().paro_unpermute(ctypes.byref(s), _dtype_code(op), p.ctypes.data, _ptr(op), _ptr(o), _stream()))
+    _check(lib().paro_unpermute(ctypes.byref(s), _dtype_code(op), p, _ptr(op), _ptr(o), _stream()))
 
 
 def codes_shape(s: paro_shape, bits: int, layout: int) -> Tuple[int, ...]:
     """Shape of the `codes` tensor of paro_quantize (int8 bytes for bits 8/4, bf16 for bits 16)."""
-    k, npad = paro_nblocks(s), paro_npad(s)
-    pack = 2 if bits == 4 else 1
+    m = _dims(s)
     if layout == PARO_ROWS:
-        return (s.B, s.nh, npad, s.d // pack)
-    return (s.B, s.nh, k, s.d, s.block // pack)
+        return m.rows4 if bits == 4 else m.rows
+    return m.vt4 if bits == 4 else m.vt
 
 
 def paro_quantize(s: paro_shape, bits: int, layout: int, xp, codes, scales) -> None:
     import torch
 
-    _require(xp, "xp", (s.B, s.nh, paro_npad(s), s.d))
+    _require(xp, "xp", _dims(s).xp)
     _require(codes, "codes", codes_shape(s, bits, layout), torch.bfloat16 if bits == 16 else torch.int8)
-    _require(scales, "scales", (s.B, s.nh, paro_nblocks(s)), torch.float32)
+    _require(scales, "scales", _dims(s).scales, torch.float32)
     _check(lib().paro_quantize(ctypes.byref(s), _dtype_code(xp), int(bits), int(layout), _ptr(xp), _ptr(codes), _ptr(scales), _stream()))
 
 
 def paro_permute_quantize(s: paro_shape, bits: int, layout: int, perm_ids, x, codes, scales) -> None:
     import torch
 
-    _require(x, "x", (s.B, s.nh, paro_ntokens(s), s.d))
+    _require(x, "x", _dims(s).x)
     _require(codes, "codes", codes_shape(s, bits, layout), torch.bfloat16 if bits == 16 else torch.int8)
-    _require(scales, "scales", (s.B, s.nh, paro_nblocks(s)), torch.float32)
+    _require(scales, "scales", _dims(s).scales, torch.float32)
     p = _perm_bytes(s, perm_ids)
-    _check(lib().paro_permute_quantize(ctypes.byref(s), _dtype_code(x), int(bits), int(layout), p.ctypes.data, _ptr(x), _ptr(codes),
+    _check(lib().paro_permute_quantize(ctypes.byref(s), _dtype_code(x), int(bits), int(layout), p, _ptr(x), _ptr(codes),
                                        _ptr(scales), _stream()))
 
 
 def paro_permute_quantize_qkv(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv) -> None:
     import torch
 
+    m = _dims(s)
     for name, x in (("q", q), ("k", k), ("v", v)):
-        _require(x, name, (s.B, s.nh, paro_ntokens(s), s.d), q.dtype)
+        _require(x, name, m.x, q.dtype)
+    rows = m.rows4 if bits_qk == 4 else m.rows
     ct_qk = torch.bfloat16 if bits_qk == 16 else torch.int8
-    _require(q_codes, "q_codes", codes_shape(s, bits_qk, PARO_ROWS), ct_qk)
-    _require(k_codes, "k_codes", codes_shape(s, bits_qk, PARO_ROWS), ct_qk)
-    _require(v_codes, "v_codes", codes_shape(s, bits_pv, PARO_VT), torch.bfloat16 if bits_pv == 16 else torch.int8)
+    _require(q_codes, "q_codes", rows, ct_qk)
+    _require(k_codes, "k_codes", rows, ct_qk)
+    _require(v_codes, "v_codes", m.vt4 if bits_pv == 4 else m.vt, torch.bfloat16 if bits_pv == 16 else torch.int8)
     for name, x in (("sq", sq), ("sk", sk), ("sv", sv)):
-        _require(x, name, (s.B, s.nh, paro_nblocks(s)), torch.float32)
+        _require(x, name, m.scales, torch.float32)
     p = _perm_bytes(s, perm_ids)
-    _check(lib().paro_permute_quantize_qkv(ctypes.byref(s), _dtype_code(q), int(bits_qk), int(bits_pv), p.ctypes.data, _ptr(q), _ptr(k),
+    _check(lib().paro_permute_quantize_qkv(ctypes.byref(s), _dtype_code(q), int(bits_qk), int(bits_pv), p, _ptr(q), _ptr(k),
                                            _ptr(v), _ptr(q_codes), _ptr(sq), _ptr(k_codes), _ptr(sk), _ptr(v_codes), _ptr(sv), _stream()))
 
 
 def paro_k_channel_mean(s: paro_shape, k, k_mean) -> None:
     import torch
 
-    _require(k, "k", (s.B, s.nh, paro_ntokens(s), s.d))
+    _require(k, "k", _dims(s).x)
     _require(k_mean, "k_mean", (s.B, s.nh, s.d), torch.float32)
     _check(lib().paro_k_channel_mean(ctypes.byref(s), _dtype_code(k), _ptr(k), _ptr(k_mean), _stream()))
 
@@ -315,12 +336,12 @@ def paro_k_channel_mean(s: paro_shape, k, k_mean) -> None:
 def paro_permute_quantize_smoothed(s: paro_shape, bits: int, perm_ids, k, k_mean, codes, scales) -> None:
     import torch
 
-    _require(k, "k", (s.B, s.nh, paro_ntokens(s), s.d))
+    _require(k, "k", _dims(s).x)
     _require(k_mean, "k_mean", (s.B, s.nh, s.d), torch.float32)
     _require(codes, "codes", codes_shape(s, bits, PARO_ROWS), torch.int8)
-    _require(scales, "scales", (s.B, s.nh, paro_nblocks(s)), torch.float32)
+    _require(scales, "scales", _dims(s).scales, torch.float32)
     p = _perm_bytes(s, perm_ids)
-    _check(lib().paro_permute_quantize_smoothed(ctypes.byref(s), _dtype_code(k), int(bits), p.ctypes.data, _ptr(k), _ptr(k_mean),
+    _check(lib().paro_permute_quantize_smoothed(ctypes.byref(s), _dtype_code(k), int(bits), p, _ptr(k), _ptr(k_mean),
                                                 _ptr(codes), _ptr(scales), _stream()))
 
 
@@ -384,7 +405,7 @@ def paro_calib_block_stats_from_rows(s: paro_shape, perm_ids, q16, k16, row_stat
     _require(block_max, "block_max", (s.B, s.nh, kb, kb), torch.float32)
     _require(block_cnt, "block_cnt", (s.B, s.nh, kb, kb), torch.int32)
     p = _perm_bytes(s, perm_ids)
-    _check(lib().paro_calib_block_stats_from_rows(ctypes.byref(s), p.ctypes.data, _ptr(q16), _ptr(k16), _ptr(row_stats), float(eps),
+    _check(lib().paro_calib_block_stats_from_rows(ctypes.byref(s), p, _ptr(q16), _ptr(k16), _ptr(row_stats), float(eps),
                                                   _ptr(block_sum), _ptr(block_max), _ptr(block_cnt), _stream()))
 
 
@@ -446,14 +467,15 @@ def paro_calib_mask(s: paro_shape, block_sum, density: float, bitmask) -> None:
 def _attn_operands(s: paro_shape, bits_qk: int, bits_pv: int, q, sq, k, sk, v, sv, row_ptr, col_idx) -> None:
     import torch
 
-    kb = paro_nblocks(s)
-    _require(q, "q", codes_shape(s, bits_qk, PARO_ROWS))
-    _require(k, "k", codes_shape(s, bits_qk, PARO_ROWS))
-    _require(v, "v", codes_shape(s, bits_pv, PARO_VT))
+    m = _dims(s)
+    rows = m.rows4 if bits_qk == 4 else m.rows
+    _require(q, "q", rows)
+    _require(k, "k", rows)
+    _require(v, "v", m.vt4 if bits_pv == 4 else m.vt)
     for name, t in (("sq", sq), ("sk", sk), ("sv", sv)):
         if t is not None:
-            _require(t, name, (s.B, s.nh, kb), torch.float32)
-    _require(row_ptr, "row_ptr", (s.nh, kb + 1), torch.int32)
+            _require(t, name, m.scales, torch.float32)
+    _require(row_ptr, "row_ptr", m.row_ptr, torch.int32)
     _require(col_idx, "col_idx", None, torch.int32)
 
 
@@ -462,18 +484,18 @@ def _order_ptr(s: paro_shape, row_order):
 
     if row_order is None:
         return None
-    _require(row_order, "row_order", (s.B * s.nh * paro_nblocks(s),), torch.int32)
+    _require(row_order, "row_order", (_dims(s).total,), torch.int32)
     return _ptr(row_order)
 
 
 def paro_sparse_attn_unpermuted(s: paro_shape, bits_qk: int, bits_pv: int, q, sq, k, sk, v, sv, row_ptr, col_idx, perm_ids, o,
                                 row_order=None) -> None:
     _attn_operands(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx)
-    _require(o, "o", (s.B, s.nh, paro_ntokens(s), s.d))
+    _require(o, "o", _dims(s).x)
     p = _perm_bytes(s, perm_ids)
     _check(lib().paro_sparse_attn_unpermuted(ctypes.byref(s), int(bits_qk), int(bits_pv), _ptr(q), _ptr(sq), _ptr(k), _ptr(sk), _ptr(v),
                                              _ptr(sv), _ptr(row_ptr), _ptr(col_idx) if col_idx.numel() else None,
-                                             int(col_idx.numel()), _order_ptr(s, row_order), p.ctypes.data, _dtype_code(o), _ptr(o),
+                                             int(col_idx.numel()), _order_ptr(s, row_order), p, _dtype_code(o), _ptr(o),
                                              _stream()))
 
 
@@ -481,35 +503,36 @@ def paro_sparse_attn_unpermuted_rawq(s: paro_shape, bits_pv: int, q, k, sk, v, s
     """q: unquantized [B, nh, N, d] (fp32 or bf16, default order); k, v: 8-bit K codes (rows) and 8/4-bit V codes (transposed)."""
     import torch
 
-    kb, n = paro_nblocks(s), paro_ntokens(s)
-    _require(q, "q", (s.B, s.nh, n, s.d))
-    _require(k, "k", codes_shape(s, 8, PARO_ROWS), torch.int8)
-    _require(v, "v", codes_shape(s, bits_pv, PARO_VT), torch.int8)
+    m = _dims(s)
+    _require(q, "q", m.x)
+    _require(k, "k", m.rows, torch.int8)
+    _require(v, "v", m.vt4 if bits_pv == 4 else m.vt, torch.int8)
     for name, t in (("sk", sk), ("sv", sv)):
-        _require(t, name, (s.B, s.nh, kb), torch.float32)
-    _require(row_ptr, "row_ptr", (s.nh, kb + 1), torch.int32)
+        _require(t, name, m.scales, torch.float32)
+    _require(row_ptr, "row_ptr", m.row_ptr, torch.int32)
     _require(col_idx, "col_idx", None, torch.int32)
-    _require(o, "o", (s.B, s.nh, n, s.d))
+    _require(o, "o", m.x)
     p = _perm_bytes(s, perm_ids)
     _check(lib().paro_sparse_attn_unpermuted_rawq(ctypes.byref(s), _dtype_code(q), int(bits_pv), _ptr(q), _ptr(k), _ptr(sk), _ptr(v),
                                                   _ptr(sv), _ptr(row_ptr), _ptr(col_idx) if col_idx.numel() else None,
-                                                  int(col_idx.numel()), _order_ptr(s, row_order), p.ctypes.data, _dtype_code(o),
+                                                  int(col_idx.numel()), _order_ptr(s, row_order), p, _dtype_code(o),
                                                   _ptr(o), _stream()))
 
 
 def paro_sparse_attn(s: paro_shape, bits_qk: int, bits_pv: int, q, sq, k, sk, v, sv, row_ptr, col_idx, op, row_order=None) -> None:
     import torch
 
-    kb, npad = paro_nblocks(s), paro_npad(s)
-    _require(q, "q", codes_shape(s, bits_qk, PARO_ROWS))
-    _require(k, "k", codes_shape(s, bits_qk, PARO_ROWS))
-    _require(v, "v", codes_shape(s, bits_pv, PARO_VT))
+    m = _dims(s)
+    rows = m.rows4 if bits_qk == 4 else m.rows
+    _require(q, "q", rows)
+    _require(k, "k", rows)
+    _require(v, "v", m.vt4 if bits_pv == 4 else m.vt)
     for name, t in (("sq", sq), ("sk", sk), ("sv", sv)):
         if t is not None:
-            _require(t, name, (s.B, s.nh, kb), torch.float32)
-    _require(row_ptr, "row_ptr", (s.nh, kb + 1), torch.int32)
+            _require(t, name, m.scales, torch.float32)
+    _require(row_ptr, "row_ptr", m.row_ptr, torch.int32)
     _require(col_idx, "col_idx", None, torch.int32)
-    _require(op, "op", (s.B, s.nh, npad, s.d))
+    _require(op, "op", m.xp)
     _check(lib().paro_sparse_attn(ctypes.byref(s), int(bits_qk), int(bits_pv), _ptr(q), _ptr(sq), _ptr(k), _ptr(sk), _ptr(v),
                                   _ptr(sv), _ptr(row_ptr), _ptr(col_idx) if col_idx.numel() else None, int(col_idx.numel()),
                                   _order_ptr(s, row_order), _dtype_code(op), _ptr(op), _stream()))

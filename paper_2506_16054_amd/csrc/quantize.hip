@@ -209,22 +209,30 @@ __global__ __launch_bounds__(256) void quantize_smoothed_kernel(const InT* __res
 }
 
 // Mean over the N tokens of every channel of every (batch, head), accumulated in binary64 and rounded to
-// bfloat16 (returned as float).  One workgroup of 1024 threads per (batch, head): a thread owns 8 channels of
-// every (1024 / (D/8))-th token; partial sums meet across the row lanes of a wavefront by shuffles and across
-// the 16 wavefronts through LDS.  Any constant would do for the smoothing (the softmax does not see it); the
+// bfloat16 (returned as float).  A workgroup of 1024 threads owns CHUNKS groups of 8 channels of one (batch, head), a thread
+// one of the groups of every (1024 / CHUNKS)-th token; partial sums meet across the row lanes of a wavefront by shuffles
+// and across the 16 wavefronts through LDS.  Any constant would do for the smoothing (the softmax does not see it); the
 // coarse rounding makes this one independent of the order of the additions.
-template <typename InT, int D>
-__global__ __launch_bounds__(1024) void channel_mean_kernel(const InT* __restrict__ x, float* __restrict__ mean, int n_tokens) {
-    constexpr int CHUNKS = D / 8;          // 8-channel chunks per token
+//
+// Bound by the few compute units that a launch of one workgroup per head uses.  The channels of a head are split over several
+// workgroups (mean_chunks), which need no scratch memory and no second launch to meet, as a split over the tokens would.
+// They read parts of the same 128-byte lines, so they are numbered to run on one XCD, whose L2 then fetches a line
+// once: workgroup b runs on XCD b % 8, and the parts of a head are 8 apart.  Whole head -> split, 17550 tokens: 30 bf16
+// heads 47 -> 35 us, 48 bf16 heads 49 -> 37, 30 fp32 heads 87 -> 45; 24 bf16 heads of 4096 tokens, d = 128: 18 -> 9.
+template <typename InT, int CHUNKS>
+__global__ __launch_bounds__(1024) void channel_mean_kernel(const InT* __restrict__ x, float* __restrict__ mean, int n_tokens, int heads, int D) {
     constexpr int ROWS = 1024 / CHUNKS;    // tokens per pass of the workgroup
-    __shared__ double part[16][D];
+    __shared__ double part[16][CHUNKS * 8];
+    const int parts = D / (CHUNKS * 8);
+    const int octet = blockIdx.x / (8 * parts), in_octet = blockIdx.x - octet * 8 * parts;
+    const int head = octet * 8 + (in_octet & 7), c0 = (in_octet >> 3) * CHUNKS * 8;
+    if (head >= heads) return;
     const int tid = threadIdx.x;
     const int cc = tid % CHUNKS;
     const int rl = tid / CHUNKS;
-    const InT* base = x + (size_t)blockIdx.x * n_tokens * D + cc * 8;
+    const InT* base = x + (size_t)head * n_tokens * D + c0 + cc * 8;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    // With one workgroup per head, latency is what binds: a thread keeps 8 (bf16) or 4 (fp32) loads in flight, held as loaded
-    // (16 or 32 bytes each) and widened only when they are added.
+    // 8 (bf16) or 4 (fp32) loads in flight per thread, held as loaded (16 or 32 bytes each) and widened only when they are added
     constexpr int INFLIGHT = sizeof(InT) == 2 ? 8 : 4;
     constexpr int WORDS = sizeof(InT) * 8 / 4;  // 32-bit words per 8 channels
     for (int r0 = rl; r0 < n_tokens; r0 += INFLIGHT * ROWS) {
@@ -264,13 +272,40 @@ __global__ __launch_bounds__(1024) void channel_mean_kernel(const InT* __restric
         for (int e = 0; e < 8; ++e) part[tid >> 6][cc * 8 + e] = acc[e];
     }
     __syncthreads();
-    if (tid < D) {
+    if (tid < CHUNKS * 8) {
         double sum = 0.0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) sum += part[w][tid];
         const float m = (float)(sum / (double)n_tokens);
-        mean[(size_t)blockIdx.x * D + tid] = __uint_as_float(f32_to_bf16_bits(m) << 16);
+        mean[(size_t)head * D + c0 + tid] = __uint_as_float(f32_to_bf16_bits(m) << 16);
     }
+}
+
+// 8-channel groups per workgroup: halved from the whole head until the launch covers the 256 compute units, as long as a
+// workgroup has more tokens than it keeps in flight (4 heads of 128 tokens: 5.4 us whole, 6.2 split to the end) and its share
+// of a token stays 32 bytes or more (48 bf16 heads of 17550 tokens: 37 us at 32 bytes, 67 at 16).
+template <typename InT>
+static int mean_chunks(int n, int heads, int d) {
+    constexpr int least = sizeof(InT) == 2 ? 2 : 1, in_flight = sizeof(InT) == 2 ? 8 : 4;
+    int chunks = d / 8;
+    while (chunks > least && 2 * heads * (d / (8 * chunks)) <= 256 && n > in_flight * (1024 / chunks)) chunks /= 2;
+    return chunks;
+}
+
+template <typename InT>
+static void launch_channel_mean(const InT* k, float* k_mean, int n, int heads, int d, hipStream_t st) {
+    const int chunks = mean_chunks<InT>(n, heads, d);
+    const dim3 grid((unsigned)((heads + 7) / 8 * 8 * (d / (8 * chunks))));
+#define PARO_MEAN(C) \
+    case C: hipLaunchKernelGGL((channel_mean_kernel<InT, C>), grid, dim3(1024), 0, st, k, k_mean, n, heads, d); break
+    switch (chunks) {
+        PARO_MEAN(1);  // fp32 only
+        PARO_MEAN(2);
+        PARO_MEAN(4);
+        PARO_MEAN(8);
+        PARO_MEAN(16);
+    }
+#undef PARO_MEAN
 }
 
 // Q, K and V of one attention call in a single launch (blockIdx.z selects the tensor): Q and K as
@@ -461,15 +496,8 @@ extern "C" int paro_k_channel_mean(const paro_shape* s, paro_dtype dtype, const 
     if (dtype != PARO_F32 && dtype != PARO_BF16) return fail(PARO_EINVAL, "dtype=%d is not a paro_dtype", (int)dtype);
     if (!k || !k_mean) return fail(PARO_EINVAL, "k and k_mean must not be NULL");
     if (((uintptr_t)k | (uintptr_t)k_mean) & 15) return fail(PARO_EINVAL, "k and k_mean must be 16-byte aligned");
-    const dim3 grid((unsigned)(s->B * s->nh));
-    hipStream_t st = (hipStream_t)stream;
-    if (dtype == PARO_F32) {
-        if (s->d == 64) hipLaunchKernelGGL((channel_mean_kernel<float, 64>), grid, dim3(1024), 0, st, (const float*)k, k_mean, (int)n);
-        else hipLaunchKernelGGL((channel_mean_kernel<float, 128>), grid, dim3(1024), 0, st, (const float*)k, k_mean, (int)n);
-    } else {
-        if (s->d == 64) hipLaunchKernelGGL((channel_mean_kernel<uint16_t, 64>), grid, dim3(1024), 0, st, (const uint16_t*)k, k_mean, (int)n);
-        else hipLaunchKernelGGL((channel_mean_kernel<uint16_t, 128>), grid, dim3(1024), 0, st, (const uint16_t*)k, k_mean, (int)n);
-    }
+    if (dtype == PARO_F32) launch_channel_mean((const float*)k, k_mean, (int)n, s->B * s->nh, s->d, (hipStream_t)stream);
+    else launch_channel_mean((const uint16_t*)k, k_mean, (int)n, s->B * s->nh, s->d, (hipStream_t)stream);
     return check_launch("paro_k_channel_mean");
 }
 

@@ -77,3 +77,24 @@ def test_channel_mean_of_a_long_head_is_bit_exact():
         torch.cuda.synchronize()
         for h in range(2):
             assert np.array_equal(mean[0, h].cpu().numpy(), po.k_channel_mean(k[0, h]))
+
+
+@pytest.mark.parametrize("heads,grid,d,dtype", [(1, (1, 8, 16), 64, "bf16"), (1, (1, 32, 33), 64, "f32"), (9, (3, 37, 41), 64, "bf16"), (9, (3, 37, 41), 128, "f32"),
+                                                (31, (2, 33, 35), 128, "bf16"), (3, (1, 5, 7), 128, "bf16"), (65, (1, 61, 67), 64, "bf16"), (130, (1, 45, 46), 64, "f32")])
+def test_channel_mean_with_the_channels_of_a_head_split(heads, grid, d, dtype):
+    """Every number of 8-channel groups per workgroup (1 .. 16), head counts that leave the last eight of them unfilled."""
+    import torch
+
+    from paper_2506_16054_amd import binding as pb
+
+    n = grid[0] * grid[1] * grid[2]
+    s = pb.make_shape(1, heads, d, *grid, 0, 32)
+    rng = np.random.default_rng(n + d)
+    k = (rng.standard_normal((1, heads, n, d)) * 2.0 + rng.uniform(-5, 5, size=(1, heads, 1, d))).astype(np.float32)
+    if dtype == "bf16":
+        k = po.round_to_bf16(k).astype(np.float32)
+    mean = torch.full((1, heads, d), float("nan"), dtype=torch.float32, device="cuda:0")
+    pb.paro_k_channel_mean(s, to_dev(k, dtype), mean)
+    torch.cuda.synchronize()
+    for h in range(heads):
+        assert np.array_equal(mean[0, h].cpu().numpy(), po.k_channel_mean(k[0, h])), h

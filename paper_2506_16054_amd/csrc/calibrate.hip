@@ -9,11 +9,13 @@
 //                            statistics, both on v_mfma_f32_32x32x16_bf16 in the transposed
 //                            orientation (a lane holds 16 keys of ONE query, so the row statistics
 //                            are in-lane plus one cross-lane step).
+//   paro_calib_row_stats, paro_calib_block_stats_from_rows
+//                            the two sweeps apart: the first serves every axis order of the same Q and K.
 //   paro_calib_metrics       M_sparse and M_quant of Eq. (M_sparse) / (M_quant) per head.
 //   paro_calib_choose        the combined metric over the six orders and the order that minimises it.
 //   paro_calib_mask          block-sum thresholding with explicit density control: the n_live
-//                            largest block sums of a head stay live (exact radix selection on the
-//                            bit patterns, equal sums resolved by position), written as the bitmask
+//                            largest block sums of a head stay live (exact selection on the bit
+//                            patterns, equal sums resolved by position), written as the bitmask
 //                            the attention path consumes.
 //
 // This is an offline step (the paper runs it once per model on one or two prompts); it is written

@@ -139,12 +139,15 @@ struct CalibSweep {
         }
 #pragma unroll
         for (int H = 0; H < QH; ++H) {
-            const uint8_t* qrow = a.q + ((size_t)bh * a.npad + row_of(H)) * D * 2 + 16 * g;
+            // a lane past the last token repeats it, query and statistics, and enters the block with factor 0 (a query of
+            // zeros against that token's statistics could overflow, and 0 times infinity is not 0)
+            const uint8_t* qrow = a.q + ((size_t)bh * a.npad + real_row(H)) * D * 2 + 16 * g;
 #pragma unroll
             for (int s = 0; s < KS; ++s) qf[H][s] = *(const c_v8bf*)(qrow + 32 * s);
         }
     }
     __device__ int row_of(int H) const { return i * BLK + 32 * H + n; }
+    __device__ int real_row(int H) const { return min(row_of(H), a.n_tokens - 1); }
     __device__ bool row_valid(int H) const { return row_of(H) < a.n_tokens; }
 
     __device__ void request(int t) {
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_phase_kern
     if constexpr (PHASE != kRowMax) {
 #pragma unroll
         for (int H = 0; H < c.QH; ++H) {
-            const int row = min(c.row_of(H), a.n_tokens - 1);
+            const int row = c.real_row(H);
             const size_t at = (size_t)bh * a.npad + (PHASE == kBlockStats ? reorder_source(a.table, bh % a.nh, row) : row);
             float m = a.row_max[at];
             for (int z = 1; z < kRowChunks; ++z) m = fmaxf(m, a.row_max[z * plane + at]);

@@ -207,7 +207,7 @@ struct CalibSweep {
                 for (int T = 0; T < KT; ++T)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) signs = __builtin_amdgcn_alignbit(signs, __float_as_uint(S[T][r]), 31);
-                pc += row_valid(H) ? __popc(signs) - pad : 0;
+                pc += factor[H] > 0.0f ? __popc(signs) - pad : 0;  // not past N and not NaN, whose signs say nothing
             }
             if constexpr (PHASE != kRowMax) {
 #pragma unroll

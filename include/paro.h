@@ -311,7 +311,7 @@ int paro_blocklist_cols_device(int nh, int k, const uint8_t* bitmask, const int3
  * P is formed from the 16-bit operands with fp32 accumulation; entries of padded rows and
  * columns (beyond N) do not exist and enter no statistic.
  *   q16, k16   bf16 [B,nh,Npad,d] as produced by paro_(permute_)quantize(bits 16, PARO_ROWS)
- *   eps        threshold of Eq. (M_sparse) (paper: e.g. 1e-3), > 0
+ *   eps        threshold of Eq. (M_sparse) (paper: e.g. 1e-3), any value > 0, infinity included; only block_cnt depends on it
  *   block_sum  float32 [B,nh,k,k]  sum of |P| over the block (the block sum of Sec. 4.2 (3))
  *   block_max  float32 [B,nh,k,k]  max of |P| over the block
  *   block_cnt  int32   [B,nh,k,k]  number of entries with |P| < eps  (n_ij of Eq. (M_sparse)) */

@@ -85,7 +85,7 @@ __device__ inline int lane63_sum(int x) {
     return x;
 }
 
-enum CalibPhase { kRowMax = 0, kRowDen = 1, kBlockStats = 2 };
+enum CalibPhase { kRowMax = 0, kRowDen = 1, kBlockStats = 2, kBlockStatsAnyEps = 3 };
 
 // One workgroup = four row blocks of one (batch, head), one wavefront each, that sweep a range of column blocks
 // together: every K tile is fetched once for the four (global_load_lds into a ring of two slots, one barrier per
@@ -99,7 +99,8 @@ enum CalibPhase { kRowMax = 0, kRowDen = 1, kBlockStats = 2 };
 //     y = c S - (m + log2 l + log2 eps),   p = eps 2^y,
 // so that its sign bit IS the comparison p < eps: the 32 signs of a half are shifted into one register
 // (v_alignbit) and counted by one v_bcnt; the maximum is taken on y.  The offset is rounded to binary32; what that
-// changes is put back by the row's factor, computed from the rounded offset.
+// changes is put back by the row's factor, computed from the rounded offset.  kBlockStatsAnyEps: the same with eps = 1 in
+// the exponent and p itself compared, for the eps that 2^y could not be scaled by (calib_exponent_eps).
 template <int BLK, int D>
 struct CalibSweep {
     static constexpr int QH = BLK / 32;
@@ -160,6 +161,7 @@ struct CalibSweep {
 
     template <int PHASE>
     __device__ void tile(int t, bool store) {
+        constexpr bool STATS = PHASE == kBlockStats || PHASE == kBlockStatsAnyEps;
         const uint8_t* ks = ring + (t & 1) * TILE;
         const int nkeys = a.n_tokens - t * BLK;  // real keys of the tile
         float ps = 0.0f, pm = 0.0f;
@@ -221,7 +223,15 @@ struct CalibSweep {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) den[H] += (double)S[T][r];
             }
-            if constexpr (PHASE == kBlockStats) {
+            if constexpr (PHASE == kBlockStatsAnyEps) {
+                int below = 0;
+#pragma unroll
+                for (int T = 0; T < KT; ++T)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) below += factor[H] * S[T][r] < a.eps ? 1 : 0;
+                pc += factor[H] > 0.0f ? below - pad : 0;
+            }
+            if constexpr (STATS) {
                 float part[4];
 #pragma unroll
                 for (int T = 0; T < KT; ++T)
@@ -230,7 +240,7 @@ struct CalibSweep {
                 ps = fmaf(factor[H], (part[0] + part[1]) + (part[2] + part[3]), ps);
             }
         }
-        if constexpr (PHASE == kBlockStats) {
+        if constexpr (STATS) {
             ps = lane63_fold(ps, [](float x, float y) { return x + y; });
             pm = lane63_fold(pm, [](float x, float y) { return fmaxf(x, y); });
             pc = lane63_sum(pc);
@@ -277,7 +287,7 @@ template <int BLK, int D>
 constexpr int calib_waves() { return BLK == 64 && D == 128 ? 2 : 3; }
 
 // the three sweeps of a row block by its own workgroup (operands in any order, nothing kept)
-template <int BLK, int D>
+template <int BLK, int D, int STATS>
 __global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_stats_kernel(CalibArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * CalibSweep<BLK, D>::TILE];
     const int item = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);  // a head's K stays in one XCD's L2
@@ -288,12 +298,13 @@ __global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_stats_kern
     c.template sweep<kRowDen>(0, a.kblocks, false);
 #pragma unroll
     for (int H = 0; H < c.QH; ++H) c.finish_row(H, (float)c.den[H]);
-    c.template sweep<kBlockStats>(0, a.kblocks, 4 * group + c.w < a.kblocks);
+    c.template sweep<STATS>(0, a.kblocks, 4 * group + c.w < a.kblocks);
 }
 
 // the same sweeps as one launch each, a workgroup per (four row blocks, column chunk)
 template <int BLK, int D, int PHASE>
 __global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_phase_kernel(CalibArgs a) {
+    constexpr bool STATS = PHASE == kBlockStats || PHASE == kBlockStatsAnyEps;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * CalibSweep<BLK, D>::TILE];
     const int item = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
     if (item >= a.total_wg) return;
@@ -308,11 +319,11 @@ __global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_phase_kern
 #pragma unroll
         for (int H = 0; H < c.QH; ++H) {
             const int row = c.real_row(H);
-            const size_t at = (size_t)bh * a.npad + (PHASE == kBlockStats ? reorder_source(a.table, bh % a.nh, row) : row);
+            const size_t at = (size_t)bh * a.npad + (STATS ? reorder_source(a.table, bh % a.nh, row) : row);
             float m = a.row_max[at];
             for (int z = 1; z < kRowChunks; ++z) m = fmaxf(m, a.row_max[z * plane + at]);
             c.m[H] = m;
-            if constexpr (PHASE == kBlockStats) {
+            if constexpr (STATS) {
                 double l = a.row_den[at];
                 for (int z = 1; z < kRowChunks; ++z) l += a.row_den[z * plane + at];
                 c.finish_row(H, (float)l);
@@ -320,7 +331,7 @@ __global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_phase_kern
         }
     }
     c.template sweep<PHASE>(t0, t1, store);
-    if constexpr (PHASE != kBlockStats) {
+    if constexpr (!STATS) {
 #pragma unroll
         for (int H = 0; H < c.QH; ++H)
             if (store && c.g == 0) {
@@ -657,6 +668,10 @@ static dim3 calib_grid(CalibArgs* a, int chunks) {
     a->per_xcd = (a->total_wg + 7) / 8;
     return dim3((unsigned)(a->per_xcd * 8));
 }
+// Whether 2^y with y = log2(p / eps) can stand for p: 1 / eps and the sums of 2^y over a block stay far from overflow above
+// 2^-100 (below 2^-126 the factor eps would flush to zero), and up to 1 nothing is flushed that p itself would keep.
+static bool calib_exponent_eps(float eps) { return eps >= 0x1p-100f && eps <= 1.0f; }
+
 static int calib_outputs(CalibArgs* a, float eps, float* block_sum, float* block_max, int32_t* block_cnt) {
     if (!block_sum || !block_max || !block_cnt) return fail(PARO_EINVAL, "block_sum, block_max and block_cnt must not be NULL");
     if (!(eps > 0.0f)) return fail(PARO_EINVAL, "eps=%g must be positive", (double)eps);
@@ -664,7 +679,7 @@ static int calib_outputs(CalibArgs* a, float eps, float* block_sum, float* block
     a->bmax = block_max;
     a->bcnt = block_cnt;
     a->eps = eps;
-    a->log2_eps = (float)log2((double)eps);
+    a->log2_eps = calib_exponent_eps(eps) ? (float)log2((double)eps) : 0.0f;
     return PARO_OK;
 }
 // the row statistics in a buffer of paro_calib_row_stats_bytes(): denominators first (8-byte aligned), then maxima
@@ -680,6 +695,13 @@ static void launch_phase(const paro_shape* s, dim3 grid, hipStream_t st, const C
     else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_phase_kernel<32, 64, PHASE>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((calib_phase_kernel<32, 128, PHASE>), grid, dim3(256), 0, st, a);
 }
+template <int STATS>
+static void launch_stats(const paro_shape* s, dim3 grid, hipStream_t st, const CalibArgs& a) {
+    if (s->block == 64 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<64, 64, STATS>), grid, dim3(256), 0, st, a);
+    else if (s->block == 64 && s->d == 128) hipLaunchKernelGGL((calib_stats_kernel<64, 128, STATS>), grid, dim3(256), 0, st, a);
+    else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<32, 64, STATS>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((calib_stats_kernel<32, 128, STATS>), grid, dim3(256), 0, st, a);
+}
 }  // namespace paro
 
 extern "C" int paro_calib_block_stats(const paro_shape* s, const void* q16, const void* k16, float eps, float* block_sum,
@@ -690,10 +712,8 @@ extern "C" int paro_calib_block_stats(const paro_shape* s, const void* q16, cons
     if (int st = calib_outputs(&a, eps, block_sum, block_max, block_cnt)) return st;
     const dim3 grid = calib_grid(&a, 1);
     hipStream_t st = (hipStream_t)stream;
-    if (s->block == 64 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<64, 64>), grid, dim3(256), 0, st, a);
-    else if (s->block == 64 && s->d == 128) hipLaunchKernelGGL((calib_stats_kernel<64, 128>), grid, dim3(256), 0, st, a);
-    else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<32, 64>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((calib_stats_kernel<32, 128>), grid, dim3(256), 0, st, a);
+    if (calib_exponent_eps(eps)) launch_stats<kBlockStats>(s, grid, st, a);
+    else launch_stats<kBlockStatsAnyEps>(s, grid, st, a);
     return check_launch("paro_calib_block_stats");
 }
 
@@ -729,7 +749,8 @@ extern "C" int paro_calib_block_stats_from_rows(const paro_shape* s, const uint8
     calib_row_buffers(&a, (void*)row_stats);
     // column chunks of about 16 blocks: a launch of many short workgroups ends evenly
     const dim3 grid = calib_grid(&a, (a.kblocks + 15) / 16);
-    launch_phase<kBlockStats>(s, grid, (hipStream_t)stream, a);
+    if (calib_exponent_eps(eps)) launch_phase<kBlockStats>(s, grid, (hipStream_t)stream, a);
+    else launch_phase<kBlockStatsAnyEps>(s, grid, (hipStream_t)stream, a);
     return check_launch("paro_calib_block_stats_from_rows");
 }
 

@@ -101,16 +101,22 @@ enum CalibPhase { kRowMax = 0, kRowDen = 1, kBlockStats = 2, kBlockStatsAnyEps =
 // (v_alignbit) and counted by one v_bcnt; the maximum is taken on y.  The offset is rounded to binary32; what that
 // changes is put back by the row's factor, computed from the rounded offset.  kBlockStatsAnyEps: the same with eps = 1 in
 // the exponent and p itself compared, for the eps that 2^y could not be scaled by (calib_exponent_eps).
-template <int BLK, int D>
+//
+// ONE_ROW_BLOCK: the four wavefronts have the same row block and every fourth column block each, through a ring of their
+// own and without a barrier in the loop; their row statistics meet in meet().
+template <int BLK, int D, bool ONE_ROW_BLOCK = false>
 struct CalibSweep {
     static constexpr int QH = BLK / 32;
     static constexpr int KT = BLK / 32;
     static constexpr int KS = D / 16;
     static constexpr int TILE = BLK * D * 2;
-    static constexpr int PIECES = TILE / 4096;  // 1 KB pieces of a tile per wavefront
+    static constexpr int PIECES = TILE / (ONE_ROW_BLOCK ? 1024 : 4096);  // 1 KB pieces of a tile that a wavefront moves
+    static constexpr int LDS_BYTES = (ONE_ROW_BLOCK ? 8 : 2) * TILE;
+    static constexpr int STEP = ONE_ROW_BLOCK ? 4 : 1;  // column blocks from one of a wavefront's tiles to its next
 
     const CalibArgs& a;
     uint8_t* ring;  // LDS [2][TILE]
+    int first;      // piece of a tile that this wavefront's transfers start at
     int bh, i, lane, n, g, w;
     const uint8_t* kbase;
     unsigned fill[PIECES];
@@ -120,16 +126,18 @@ struct CalibSweep {
     double den[QH];
     float off[QH], factor[QH];
 
-    __device__ CalibSweep(const CalibArgs& args, uint8_t* lds, int bh_, int group) : a(args), ring(lds), bh(bh_) {
+    __device__ CalibSweep(const CalibArgs& args, uint8_t* lds, int bh_, int group) : a(args), bh(bh_) {
         lane = threadIdx.x & 63;
         w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         n = lane & 31;
         g = lane >> 5;
-        i = min(4 * group + w, a.kblocks - 1);  // a wavefront past the last row block repeats it and stores nothing
+        i = ONE_ROW_BLOCK ? group : min(4 * group + w, a.kblocks - 1);  // past the last row block: repeats it and stores nothing
+        ring = lds + (ONE_ROW_BLOCK ? 2 * TILE * w : 0);
+        first = ONE_ROW_BLOCK ? 0 : PIECES * w;
         kbase = a.k + (size_t)bh * a.npad * D * 2;
 #pragma unroll
         for (int u = 0; u < PIECES; ++u) {
-            const unsigned p = (w * PIECES + u) * 1024u + 16u * lane;
+            const unsigned p = (first + u) * 1024u + 16u * lane;
             const unsigned row = p / (2 * D), pos = (p % (2 * D)) / 16;
             fill[u] = row * 2 * D + 16 * ((pos & ~7u) | ((pos ^ row) & 7u));
         }
@@ -151,18 +159,18 @@ struct CalibSweep {
     __device__ int real_row(int H) const { return min(row_of(H), a.n_tokens - 1); }
     __device__ bool row_valid(int H) const { return row_of(H) < a.n_tokens; }
 
-    __device__ void request(int t) {
+    __device__ void request(int t, int slot) {
         const uint8_t* kp = kbase + (size_t)t * TILE;
 #pragma unroll
         for (int u = 0; u < PIECES; ++u)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kp + fill[u]),
-                                             (__attribute__((address_space(3))) void*)(ring + (t & 1) * TILE + (w * PIECES + u) * 1024), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(ring + slot * TILE + (first + u) * 1024), 16, 0, 0);
     }
 
     template <int PHASE>
-    __device__ void tile(int t, bool store) {
+    __device__ void tile(int t, int slot, bool store) {
         constexpr bool STATS = PHASE == kBlockStats || PHASE == kBlockStatsAnyEps;
-        const uint8_t* ks = ring + (t & 1) * TILE;
+        const uint8_t* ks = ring + slot * TILE;
         const int nkeys = a.n_tokens - t * BLK;  // real keys of the tile
         float ps = 0.0f, pm = 0.0f;
         int pc = 0;
@@ -262,17 +270,36 @@ struct CalibSweep {
 #pragma unroll
             for (int H = 0; H < QH; ++H) den[H] = 0.0;
         __syncthreads();  // the previous sweep is done with the ring
-        if (t0 < t1) request(t0);
-        for (int t = t0; t < t1; ++t) {
-            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's share of tile t has landed
-            __syncthreads();                     // and everybody's; tile t - 1 has been read by all
-            if (t + 1 < t1) request(t + 1);
-            tile<PHASE>(t, store);
+        if constexpr (ONE_ROW_BLOCK) t0 += w;
+        if (t0 < t1) request(t0, 0);
+        for (int t = t0, slot = 0; t < t1; t += STEP, slot ^= 1) {
+            __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0), lgkmcnt(0): this wavefront's share of tile t has landed
+            if constexpr (!ONE_ROW_BLOCK) __syncthreads();  // and everybody's; the tile before it has been read by all
+            if (t + STEP < t1) request(t + STEP, slot ^ 1);
+            tile<PHASE>(t, slot, store);
         }
 #pragma unroll
         for (int H = 0; H < QH; ++H) {  // the two lanes of a query hold half of its keys each
             if constexpr (PHASE == kRowMax) m[H] = fmaxf(m[H], __shfl_xor(m[H], 32));
             if constexpr (PHASE == kRowDen) den[H] += __shfl_xor(den[H], 32);
+        }
+    }
+
+    // ONE_ROW_BLOCK: the maxima or denominators of the four wavefronts' column blocks, joined in all of them
+    template <int PHASE, typename T>
+    __device__ void meet(T (*rows)[BLK], T (&mine)[QH]) {
+#pragma unroll
+        for (int H = 0; H < QH; ++H)
+            if (g == 0) rows[w][32 * H + n] = mine[H];
+        __syncthreads();
+#pragma unroll
+        for (int H = 0; H < QH; ++H) {
+            T x = rows[0][32 * H + n];
+            for (int v = 1; v < 4; ++v) {
+                if constexpr (PHASE == kRowMax) x = fmaxf(x, rows[v][32 * H + n]);
+                else x += rows[v][32 * H + n];
+            }
+            mine[H] = x;
         }
     }
 
@@ -286,26 +313,36 @@ struct CalibSweep {
 template <int BLK, int D>
 constexpr int calib_waves() { return BLK == 64 && D == 128 ? 2 : 3; }
 
-// the three sweeps of a row block by its own workgroup (operands in any order, nothing kept)
-template <int BLK, int D, int STATS>
-__global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_stats_kernel(CalibArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * CalibSweep<BLK, D>::TILE];
+// the three sweeps of four row blocks, or of one, by their own workgroup (operands in any order, nothing kept)
+template <int BLK, int D, int STATS, bool ONE_ROW_BLOCK>
+__global__ __launch_bounds__(256, (ONE_ROW_BLOCK ? (BLK * D > 4096 ? 1 : 2) : calib_waves<BLK, D>())) void calib_stats_kernel(CalibArgs a) {
+    using Sweep = CalibSweep<BLK, D, ONE_ROW_BLOCK>;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[Sweep::LDS_BYTES];
     const int item = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);  // a head's K stays in one XCD's L2
     if (item >= a.total_wg) return;
-    const int bh = item / a.groups, group = item - bh * a.groups;
-    CalibSweep<BLK, D> c(a, lds, bh, group);
+    const int per_head = ONE_ROW_BLOCK ? a.kblocks : a.groups;
+    const int bh = item / per_head, group = item - bh * per_head;
+    Sweep c(a, lds, bh, group);
     c.template sweep<kRowMax>(0, a.kblocks, false);
+    if constexpr (ONE_ROW_BLOCK) {
+        __shared__ float rows[4][BLK];
+        c.template meet<kRowMax>(rows, c.m);
+    }
     c.template sweep<kRowDen>(0, a.kblocks, false);
+    if constexpr (ONE_ROW_BLOCK) {
+        __shared__ double rows[4][BLK];
+        c.template meet<kRowDen>(rows, c.den);
+    }
 #pragma unroll
     for (int H = 0; H < c.QH; ++H) c.finish_row(H, (float)c.den[H]);
-    c.template sweep<STATS>(0, a.kblocks, 4 * group + c.w < a.kblocks);
+    c.template sweep<STATS>(0, a.kblocks, ONE_ROW_BLOCK || 4 * group + c.w < a.kblocks);
 }
 
 // the same sweeps as one launch each, a workgroup per (four row blocks, column chunk)
 template <int BLK, int D, int PHASE>
 __global__ __launch_bounds__(256, (calib_waves<BLK, D>())) void calib_phase_kernel(CalibArgs a) {
     constexpr bool STATS = PHASE == kBlockStats || PHASE == kBlockStatsAnyEps;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * CalibSweep<BLK, D>::TILE];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[CalibSweep<BLK, D>::LDS_BYTES];
     const int item = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
     if (item >= a.total_wg) return;
     const int bh = item / (a.groups * a.chunks);
@@ -662,9 +699,9 @@ static int calib_args(const paro_shape* s, const void* q16, const void* k16, Cal
     a->qk_scale = (float)(1.4426950408889634 / sqrt((double)s->d));
     return PARO_OK;
 }
-static dim3 calib_grid(CalibArgs* a, int chunks) {
+static dim3 calib_grid(CalibArgs* a, int per_head, int chunks) {
     a->chunks = chunks;
-    a->total_wg = a->bh_total * a->groups * chunks;
+    a->total_wg = a->bh_total * per_head * chunks;
     a->per_xcd = (a->total_wg + 7) / 8;
     return dim3((unsigned)(a->per_xcd * 8));
 }
@@ -695,12 +732,23 @@ static void launch_phase(const paro_shape* s, dim3 grid, hipStream_t st, const C
     else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_phase_kernel<32, 64, PHASE>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((calib_phase_kernel<32, 128, PHASE>), grid, dim3(256), 0, st, a);
 }
-template <int STATS>
-static void launch_stats(const paro_shape* s, dim3 grid, hipStream_t st, const CalibArgs& a) {
-    if (s->block == 64 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<64, 64, STATS>), grid, dim3(256), 0, st, a);
-    else if (s->block == 64 && s->d == 128) hipLaunchKernelGGL((calib_stats_kernel<64, 128, STATS>), grid, dim3(256), 0, st, a);
-    else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<32, 64, STATS>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((calib_stats_kernel<32, 128, STATS>), grid, dim3(256), 0, st, a);
+// Whether every row block gets a workgroup of its own in the one-call form: while the workgroups of four row blocks leave compute
+// units idle or nearly so, a quarter of the chain per wavefront is worth more than K tiles that four of them share (and than
+// a quarter of the LDS, which lets fewer workgroups in).  The line, in workgroups of four, both sides in us (four / one):
+// block 64, d = 64, 17550 tokens: 1 head (69) 807 / 361, 8 heads (552) 1711 / 1512, 16 heads (1104) 2872 / 2997;
+// block 64, d = 128, 4096 tokens: 4 heads (64) 256 / 81, 24 heads (384) 389 / 472;
+// block 32, d = 64, 17550 tokens: 1 head (138) 615 / 324, 8 heads (1104) 1641 / 1718, 48 heads of 1955 (768) 130 / 142;
+// block 32, d = 128, 4096 tokens: 4 heads (128) 185 / 89, 8 heads (256) 190 / 173, 16 heads (512) 260 / 329.
+static bool calib_one_row_block(const paro_shape* s, const CalibArgs& a) {
+    return a.bh_total * a.groups <= (s->block == 64 && s->d == 64 ? 768 : 256);
+}
+template <int STATS, bool ONE_ROW_BLOCK>
+static void launch_stats(const paro_shape* s, hipStream_t st, CalibArgs& a) {
+    const dim3 grid = calib_grid(&a, ONE_ROW_BLOCK ? a.kblocks : a.groups, 1);
+    if (s->block == 64 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<64, 64, STATS, ONE_ROW_BLOCK>), grid, dim3(256), 0, st, a);
+    else if (s->block == 64 && s->d == 128) hipLaunchKernelGGL((calib_stats_kernel<64, 128, STATS, ONE_ROW_BLOCK>), grid, dim3(256), 0, st, a);
+    else if (s->block == 32 && s->d == 64) hipLaunchKernelGGL((calib_stats_kernel<32, 64, STATS, ONE_ROW_BLOCK>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((calib_stats_kernel<32, 128, STATS, ONE_ROW_BLOCK>), grid, dim3(256), 0, st, a);
 }
 }  // namespace paro
 
@@ -710,10 +758,10 @@ extern "C" int paro_calib_block_stats(const paro_shape* s, const void* q16, cons
     CalibArgs a;
     if (int st = calib_args(s, q16, k16, &a)) return st;
     if (int st = calib_outputs(&a, eps, block_sum, block_max, block_cnt)) return st;
-    const dim3 grid = calib_grid(&a, 1);
     hipStream_t st = (hipStream_t)stream;
-    if (calib_exponent_eps(eps)) launch_stats<kBlockStats>(s, grid, st, a);
-    else launch_stats<kBlockStatsAnyEps>(s, grid, st, a);
+    if (!calib_exponent_eps(eps)) launch_stats<kBlockStatsAnyEps, false>(s, st, a);
+    else if (calib_one_row_block(s, a)) launch_stats<kBlockStats, true>(s, st, a);
+    else launch_stats<kBlockStats, false>(s, st, a);
     return check_launch("paro_calib_block_stats");
 }
 
@@ -730,7 +778,7 @@ extern "C" int paro_calib_row_stats(const paro_shape* s, const void* q16, const 
     if (int st = calib_args(s, q16, k16, &a)) return st;
     if (!row_stats || ((uintptr_t)row_stats & 15)) return fail(PARO_EINVAL, "row_stats must be a 16-byte aligned buffer");
     calib_row_buffers(&a, row_stats);
-    const dim3 grid = calib_grid(&a, kRowChunks);
+    const dim3 grid = calib_grid(&a, a.groups, kRowChunks);
     launch_phase<kRowMax>(s, grid, (hipStream_t)stream, a);
     launch_phase<kRowDen>(s, grid, (hipStream_t)stream, a);
     return check_launch("paro_calib_row_stats");
@@ -748,7 +796,7 @@ extern "C" int paro_calib_block_stats_from_rows(const paro_shape* s, const uint8
     if (int st = make_reorder_table(s, h_perm_ids, &a.table)) return st;
     calib_row_buffers(&a, (void*)row_stats);
     // column chunks of about 16 blocks: a launch of many short workgroups ends evenly
-    const dim3 grid = calib_grid(&a, (a.kblocks + 15) / 16);
+    const dim3 grid = calib_grid(&a, a.groups, (a.kblocks + 15) / 16);
     if (calib_exponent_eps(eps)) launch_phase<kBlockStats>(s, grid, (hipStream_t)stream, a);
     else launch_phase<kBlockStatsAnyEps>(s, grid, (hipStream_t)stream, a);
     return check_launch("paro_calib_block_stats_from_rows");

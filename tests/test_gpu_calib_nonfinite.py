@@ -49,3 +49,34 @@ def test_counts_and_sums(block, d, grid, where, value):
             bsum, _, bcnt = (x[0, 0].cpu().numpy() for x in out)
             assert np.all(bcnt >= ref["cnt_lo"]) and np.all(bcnt <= ref["cnt_hi"]), (form, ids)
             assert np.allclose(bsum, ref["sum"], rtol=TIE, atol=1e-30, equal_nan=True), (form, ids)
+
+
+@pytest.mark.parametrize("block,d", [(64, 64), (64, 128), (32, 64), (32, 128)])
+@pytest.mark.parametrize("dead", [slice(0, 64), slice(0, 130), slice(100, 192)])
+def test_keys_of_minus_infinity(block, d, dead):
+    """Every logit of the first block, of more than two blocks and of the last keys is minus infinity: those entries are 0."""
+    import torch
+
+    from paper_2506_16054_amd import binding as pb
+
+    s = pb.make_shape(1, 1, d, 3, 8, 8, 0, block)
+    n, kb = 192, 192 // block
+    gen = torch.Generator().manual_seed(d)
+    q, k = (torch.randn((1, 1, n, d), generator=gen).to(torch.bfloat16) for _ in range(2))
+    q[..., 3] = 1.0
+    k[:, :, dead, 3] = -float("inf")
+    p = pc.attention_map(q[0, 0].float().numpy(), k[0, 0].float().numpy())
+    ref = pc.block_stats(p, block, EPS, TIE)
+    z = dict(device="cuda:0")
+    q, k = q.to("cuda:0"), k.to("cuda:0")  # whole blocks: the operands in the default order are the tensors themselves
+    rows = torch.zeros((pb.paro_calib_row_stats_bytes(s),), dtype=torch.uint8, **z)
+    pb.paro_calib_row_stats(s, q, k, rows)
+    for form in ("one call", "from rows"):
+        out = [torch.full((1, 1, kb, kb), -1, dtype=t, **z) for t in (torch.float32, torch.float32, torch.int32)]
+        if form == "one call":
+            pb.paro_calib_block_stats(s, q, k, EPS, *out)
+        else:
+            pb.paro_calib_block_stats_from_rows(s, np.zeros(1, np.uint8), q, k, rows, EPS, *out)
+        bsum, bmax, bcnt = (x[0, 0].cpu().numpy() for x in out)
+        assert np.allclose(bsum, ref["sum"], rtol=TIE, atol=1e-30) and np.allclose(bmax, ref["max"], rtol=TIE, atol=1e-30), form
+        assert np.all(bcnt >= ref["cnt_lo"]) and np.all(bcnt <= ref["cnt_hi"]), form

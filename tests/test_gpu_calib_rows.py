@@ -85,3 +85,37 @@ def test_pick_takes_every_heads_own_order():
     out = torch.empty((2, 5, 3, 3), dtype=torch.float32, device="cuda:0")
     pb.paro_calib_pick(s, six, ids, out)
     assert torch.equal(out, torch.stack([six[int(ids[h]), :, h] for h in range(5)], dim=1))
+
+
+# heads of one to three row blocks on either side of the number of workgroups at which the one-call form changes
+@pytest.mark.parametrize("block,d,heads,n", [(64, 64, 768, 130), (64, 64, 769, 130), (64, 128, 256, 77), (64, 128, 257, 77), (32, 64, 256, 90),
+                                             (32, 64, 257, 90), (32, 128, 256, 33), (32, 128, 257, 33)])
+def test_both_forms_of_the_one_call_form(block, d, heads, n):
+    import torch
+
+    from paper_2506_16054_amd import binding as pb
+
+    s = pb.make_shape(heads, 1, d, 1, 1, n, 0, block)
+    k = pb.paro_nblocks(s)
+    gen = torch.Generator(device="cuda:0").manual_seed(heads + n)
+    x, y = (torch.randn((heads, 1, n, d), generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(2))
+    z = dict(device="cuda:0")
+    ids = np.zeros(1, np.uint8)
+    q16, k16 = (torch.empty(pb.codes_shape(s, 16, pb.PARO_ROWS), dtype=torch.bfloat16, **z) for _ in range(2))
+    sc = torch.empty((heads, 1, k), dtype=torch.float32, **z)
+    pb.paro_permute_quantize(s, 16, pb.PARO_ROWS, ids, x, q16, sc)
+    pb.paro_permute_quantize(s, 16, pb.PARO_ROWS, ids, y, k16, sc)
+    rows = torch.zeros((pb.paro_calib_row_stats_bytes(s),), dtype=torch.uint8, **z)
+    pb.paro_calib_row_stats(s, q16, k16, rows)
+    one = [torch.full((heads, 1, k, k), -1, dtype=t, **z) for t in (torch.float32, torch.float32, torch.int32)]
+    two = [torch.full((heads, 1, k, k), -2, dtype=t, **z) for t in (torch.float32, torch.float32, torch.int32)]
+    pb.paro_calib_block_stats(s, q16, k16, 2e-3, *one)
+    pb.paro_calib_block_stats_from_rows(s, ids, q16, k16, rows, 2e-3, *two)
+    for a, b in zip(one, two):
+        assert torch.equal(a, b)
+    for h in (0, heads // 2, heads - 1):
+        ref = pc.block_stats(pc.attention_map(x[h, 0].float().cpu().numpy(), y[h, 0].float().cpu().numpy()), block, 2e-3, 2e-4)
+        assert np.allclose(one[0][h, 0].cpu().numpy(), ref["sum"], rtol=2e-4, atol=1e-30)
+        assert np.allclose(one[1][h, 0].cpu().numpy(), ref["max"], rtol=2e-4, atol=1e-30)
+        cnt = one[2][h, 0].cpu().numpy()
+        assert np.all(cnt >= ref["cnt_lo"]) and np.all(cnt <= ref["cnt_hi"])

@@ -237,6 +237,11 @@ class MaskPrefetcher:
         self.slots[slot]["free"].record(torch.cuda.current_stream())
 
 
+# Block statistics of all six axis orders are held at once (72 bytes per block, head and sample) up to this size, and one
+# order at a time (12 bytes) beyond it, where the chosen orders' sums are then made again: 9 sweeps over the map instead of 8.
+CALIB_STATS_BYTES = 1 << 30
+
+
 def calibrate(shape: pb.paro_shape, q, k, eps: float = 1e-3, sigma: float = 0.9, alpha: float = 0.5, density: float = 0.3):
     """Offline calibration of one attention layer (paper Sec. 4.1, Sec. 4.2 (3)) from calibration
     samples q, k [B, nh, N, d]: enqueues the library calls and returns device tensors
@@ -250,27 +255,37 @@ def calibrate(shape: pb.paro_shape, q, k, eps: float = 1e-3, sigma: float = 0.9,
     k16 = torch.empty_like(q16)
     unused_scales = torch.empty((shape.B, nh, kb), dtype=torch.float32, **z)
     row_stats = torch.empty((pb.paro_calib_row_stats_bytes(shape),), dtype=torch.uint8, **z)
-    bsum6 = torch.empty((6, shape.B, nh, kb, kb), dtype=torch.float32, **z)
-    bmax6 = torch.empty_like(bsum6)
-    bcnt6 = torch.empty(bsum6.shape, dtype=torch.int32, **z)
-    bsum = torch.empty((shape.B, nh, kb, kb), dtype=torch.float32, **z)
+    at_once = 72 * shape.B * nh * kb * kb <= CALIB_STATS_BYTES
+    bsums = torch.empty((6 if at_once else 1, shape.B, nh, kb, kb), dtype=torch.float32, **z)
+    bmaxs = torch.empty_like(bsums)
+    bcnts = torch.empty(bsums.shape, dtype=torch.int32, **z)
     ms = torch.empty((6, nh), dtype=torch.float32, **z)
     mq = torch.empty_like(ms)
     mc = torch.empty_like(ms)
     perm_ids = torch.empty((nh,), dtype=torch.uint8, **z)
     bitmask = torch.empty((nh, (kb * kb + 7) // 8), dtype=torch.uint8, **z)
 
-    for t in range(6):
-        ids = np.full(nh, t, np.uint8)
+    def stats_for(ids, slot, first=False):
         pb.paro_permute_quantize(shape, 16, pb.PARO_ROWS, ids, q, q16, unused_scales)
         pb.paro_permute_quantize(shape, 16, pb.PARO_ROWS, ids, k, k16, unused_scales)
-        if t == 0:  # the default order: the rows' maxima and denominators serve all six
+        if first:  # the default order: the rows' maxima and denominators serve all six
             pb.paro_calib_row_stats(shape, q16, k16, row_stats)
-        pb.paro_calib_block_stats_from_rows(shape, ids, q16, k16, row_stats, eps, bsum6[t], bmax6[t], bcnt6[t])
-    pb.paro_calib_metrics_orders(shape, bsum6, bmax6, bcnt6, sigma, ms, mq)
+        pb.paro_calib_block_stats_from_rows(shape, ids, q16, k16, row_stats, eps, bsums[slot], bmaxs[slot], bcnts[slot])
+
+    for t in range(6):
+        stats_for(np.full(nh, t, np.uint8), t if at_once else 0, first=t == 0)
+        if not at_once:
+            pb.paro_calib_metrics(shape, bsums[0], bmaxs[0], bcnts[0], sigma, ms[t], mq[t])
+    if at_once:
+        pb.paro_calib_metrics_orders(shape, bsums, bmaxs, bcnts, sigma, ms, mq)
     pb.paro_calib_choose(nh, ms, mq, alpha, mc, perm_ids)
-    pb.paro_calib_pick(shape, bsum6, perm_ids, bsum)
+    if at_once:
+        bsum = torch.empty((shape.B, nh, kb, kb), dtype=torch.float32, **z)
+        pb.paro_calib_pick(shape, bsums, perm_ids, bsum)
+    else:
+        stats_for(perm_ids.cpu().numpy(), 0)  # synchronises: the reorder calls take the ids on the host
+        bsum = bsums[0]
     pb.paro_calib_mask(shape, bsum, density, bitmask)
-    h_perm_ids = perm_ids.cpu().numpy()  # synchronises: the reorder calls take the ids on the host
+    h_perm_ids = perm_ids.cpu().numpy()  # synchronises
     return {"perm_ids": perm_ids, "h_perm_ids": h_perm_ids, "bitmask": bitmask, "m_sparse": ms, "m_quant": mq, "m_combined": mc,
             "block_sum": bsum}

@@ -119,7 +119,8 @@ def _ptr(t) -> Optional[int]:
 def _stream() -> int:
     import torch
 
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())  # current_stream().cuda_stream without the object
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # current_stream().cuda_stream without the object; not public
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _dtype_code(t) -> int:

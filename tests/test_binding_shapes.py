@@ -1,4 +1,7 @@
-"""The binding keeps what follows from a shape by the shape's numbers: a refusal is not kept, a changed shape is another."""
+"""The binding keeps what follows from a shape by the shape's numbers: a refusal is not kept, a changed shape is another.
+Its stream handle does not hang on a function that torch does not promise."""
+import types
+
 import pytest
 
 from paper_2506_16054_amd import binding as pb
@@ -23,3 +26,11 @@ def test_a_refused_shape_is_refused_every_time():
             assert e.value.status == pb.PARO_EUNSUPPORTED  # blocks of 48 are not built
     bad.block = 64
     assert pb.paro_ntokens(bad) == 105
+
+
+def test_stream_without_the_private_function(monkeypatch):
+    import torch
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4711))
+    assert pb._stream() == 4711

@@ -23,13 +23,10 @@
 #include <math.h>
 #include <string.h>
 
-#include <type_traits>
-
 #include "common.h"
 
 namespace paro {
 
-typedef int c_v4i __attribute__((ext_vector_type(4)));
 typedef __bf16 c_v8bf __attribute__((ext_vector_type(8)));
 typedef float c_v16f __attribute__((ext_vector_type(16)));
 

@@ -298,8 +298,9 @@ static void launch_channel_mean(const InT* k, float* k_mean, int n, int heads, i
     const dim3 grid((unsigned)((heads + 7) / 8 * 8 * (d / (8 * chunks))));
 #define PARO_MEAN(C) \
     case C: hipLaunchKernelGGL((channel_mean_kernel<InT, C>), grid, dim3(1024), 0, st, k, k_mean, n, heads, d); break
+    if constexpr (sizeof(InT) == 4)
+        switch (chunks) { PARO_MEAN(1); }
     switch (chunks) {
-        PARO_MEAN(1);  // fp32 only
         PARO_MEAN(2);
         PARO_MEAN(4);
         PARO_MEAN(8);

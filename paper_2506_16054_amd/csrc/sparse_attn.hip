@@ -1344,40 +1344,30 @@ __global__ __launch_bounds__(256, 3) void attn_i8_q16_kernel(AttnArgs a) {
 }
 
 // -------------------------------------------------------------------------------------------
-// bf16 unquantized block-sparse mode (the sparse-only rows of the paper's tables): same work
-// split, transposed orientation and block list, on v_mfma_f32_32x32x16_bf16.  P is not quantized,
-// so there is no tile-wide scale and no cross-wavefront exchange; P enters the PV product rounded
-// to bf16 while the denominator accumulates it in fp32.  The 16-bit tiles are twice as large as
-// the 8-bit ones, so this kernel keeps ONE LDS stage and pays a second barrier per block instead
-// of a second stage: the smaller footprint admits a third wavefront per SIMD (d = 64), which is
-// worth more here than the barrier costs.  Launched for block 32 (one wavefront per row block); block 64 has the
-// kernels behind it.
+// bf16 unquantized block-sparse mode (the sparse-only rows of the paper's tables) at block 32: one wavefront per row
+// block, same transposed orientation and block list, on v_mfma_f32_32x32x16_bf16.  P is not quantized,
+// so there is no tile-wide scale; P enters the PV product rounded to bf16 while the denominator accumulates
+// it in fp32.  The tiles go through registers to ONE LDS stage.  Block 64 has the kernels behind this one.
 // -------------------------------------------------------------------------------------------
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-template <int BLK, int D>
-struct Bf16Cfg {
-    static constexpr int KSTR = 2 * D + 16;    // bytes per K row in LDS (bf16 + 16 B pad)
-    static constexpr int VSTR = 2 * BLK + 16;  // bytes per V^T row in LDS
-    static constexpr int KBYTES = BLK * KSTR;
-    static constexpr int VBYTES = D * VSTR;
-    static constexpr int STAGE = KBYTES + VBYTES;
-    static constexpr int LDS_BYTES = STAGE;
+template <int D>
+struct Bf16B32Cfg {
+    static constexpr int KSTR = 2 * D + 16;   // bytes per K row in LDS (bf16 + 16 B pad)
+    static constexpr int VSTR = 2 * 32 + 16;  // bytes per V^T row in LDS
+    static constexpr int KBYTES = 32 * KSTR;
+    static constexpr int LDS_BYTES = KBYTES + D * VSTR;
 };
 
-template <int BLK, int D, typename OutT>
-__global__ __launch_bounds__(BLK * 2, (D == 64 ? 3 : 2)) void attn_bf16_kernel(AttnArgs a) {
-    using C = Bf16Cfg<BLK, D>;
-    constexpr int NW = BLK / 32;
-    constexpr int NT = 64 * NW;
-    constexpr int KSTR = C::KSTR, VSTR = C::VSTR, KBYTES = C::KBYTES, STAGE = C::STAGE;
-    constexpr int NKC = BLK * D * 2 / 16 / NT;  // 16-byte pieces of a K tile per thread
-    constexpr int NVC = NKC;
-    constexpr int KS = D / 16;    // contraction steps of QK^T (16 channels each)
-    constexpr int KT = BLK / 32;  // 32-key tiles per block
+template <int D, typename OutT>
+__global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_bf16_b32_kernel(AttnArgs a) {
+    constexpr int BLK = 32;
+    constexpr int KSTR = Bf16B32Cfg<D>::KSTR, VSTR = Bf16B32Cfg<D>::VSTR, KBYTES = Bf16B32Cfg<D>::KBYTES;
+    constexpr int NC = BLK * D * 2 / 16 / 64;  // 16-byte pieces of a tile per lane
+    constexpr int KS = D / 16;                 // contraction steps of QK^T (16 channels each)
     constexpr int DT = D / 32;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
@@ -1388,9 +1378,7 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? 3 : 2)) void attn_bf16_kernel(A
     const int bh = item / a.kblocks;
     const int i = item - bh * a.kblocks;
     const int h = bh % a.nh;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int w = tid >> 6;
+    const int lane = threadIdx.x;
     const int n = lane & 31;
     const int g = lane >> 5;
 
@@ -1401,7 +1389,7 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? 3 : 2)) void attn_bf16_kernel(A
     const int* cols = a.col_idx + beg;
 
     const size_t head_rows = (size_t)bh * a.kblocks * BLK;
-    const int row = i * BLK + 32 * w + n;
+    const int row = i * BLK + n;
     const bool row_valid = row < a.n_tokens;
     const uint8_t* kbase = a.k + head_rows * D * 2;
     const uint8_t* vbase = a.v + head_rows * D * 2;
@@ -1425,21 +1413,19 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? 3 : 2)) void attn_bf16_kernel(A
         return (t >> 6) == cur_chunk ? __builtin_amdgcn_readlane(cols_cur, t & 63) : __builtin_amdgcn_readlane(cols_nxt, t & 63);
     };
 
-    v4i kreg[NKC], vreg[NVC];
-    // LDS store offsets: piece cc of a thread lies a whole number of rows below its piece 0, so one
+    v4i kreg[NC], vreg[NC];
+    // LDS store offsets: piece cc of a lane lies a whole number of rows below its piece 0, so one
     // address per tile serves all pieces through immediate offsets
-    static_assert((16 * NT) % (2 * D) == 0 && (16 * NT) % (2 * BLK) == 0, "pieces must be whole rows apart");
-    const int k_off = ((16 * tid) / (2 * D)) * KSTR + (16 * tid) % (2 * D);
-    const int v_off = KBYTES + ((16 * tid) / (2 * BLK)) * VSTR + (16 * tid) % (2 * BLK);
-    auto lstore_k = [&](int stage) {
-        uint8_t* dst0 = lds + stage * STAGE + k_off;
+    static_assert(1024 % (2 * D) == 0 && 1024 % (2 * BLK) == 0, "pieces must be whole rows apart");
+    const int k_off = ((16 * lane) / (2 * D)) * KSTR + (16 * lane) % (2 * D);
+    const int v_off = KBYTES + ((16 * lane) / (2 * BLK)) * VSTR + (16 * lane) % (2 * BLK);
+    auto lstore_k = [&]() {
 #pragma unroll
-        for (int cc = 0; cc < NKC; ++cc) *(v4i*)(dst0 + cc * (16 * NT / (2 * D)) * KSTR) = kreg[cc];
+        for (int cc = 0; cc < NC; ++cc) *(v4i*)(lds + k_off + cc * (1024 / (2 * D)) * KSTR) = kreg[cc];
     };
-    auto lstore_v = [&](int stage) {
-        uint8_t* dst0 = lds + stage * STAGE + v_off;
+    auto lstore_v = [&]() {
 #pragma unroll
-        for (int cc = 0; cc < NVC; ++cc) *(v4i*)(dst0 + cc * (16 * NT / (2 * BLK)) * VSTR) = vreg[cc];
+        for (int cc = 0; cc < NC; ++cc) *(v4i*)(lds + v_off + cc * (1024 / (2 * BLK)) * VSTR) = vreg[cc];
     };
 
     // The exponentials are taken against a fixed reference per row (its maximum after the first
@@ -1454,58 +1440,46 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? 3 : 2)) void attn_bf16_kernel(A
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
 
-    // One LDS stage and two barriers per live block: K_t is read before the first barrier; behind it
-    // K_{t+1} and V_t replace K_t and V_{t-1} (every wavefront is past their last reads), the second
-    // barrier publishes them.  Half the LDS footprint, which lets a third wavefront per SIMD in.
+    // One LDS stage and two barriers per live block: K_t is read before the first; behind it K_{t+1} and V_t replace
+    // K_t and V_{t-1}, the second publishes them to all lanes.
     auto gload_k = [&](int t) {
         const uint8_t* kp = kbase + (size_t)col_of(t) * (BLK * D * 2);
 #pragma unroll
-        for (int cc = 0; cc < NKC; ++cc) kreg[cc] = *(const v4i*)(kp + 16 * (tid + NT * cc));
+        for (int cc = 0; cc < NC; ++cc) kreg[cc] = *(const v4i*)(kp + 16 * (lane + 64 * cc));
     };
     auto gload_v = [&](int t) {
         const uint8_t* vp = vbase + (size_t)col_of(t) * (BLK * D * 2);
 #pragma unroll
-        for (int cc = 0; cc < NVC; ++cc) vreg[cc] = *(const v4i*)(vp + 16 * (tid + NT * cc));
+        for (int cc = 0; cc < NC; ++cc) vreg[cc] = *(const v4i*)(vp + 16 * (lane + 64 * cc));
     };
     if (cnt > 0) {
         gload_k(0);
         gload_v(0);
-        lstore_k(0);
+        lstore_k();
         if (cnt > 1) gload_k(1);
     }
     __syncthreads();
 
-    constexpr int stage = 0;
     auto step = [&](auto tail_tag, int t) {
         constexpr bool TAIL = decltype(tail_tag)::value;
-        const uint8_t* ks = lds + stage * STAGE;
-        const uint8_t* vs = ks + KBYTES;
-
-        v16f sacc[KT];
+        v16f sacc;
 #pragma unroll
-        for (int T = 0; T < KT; ++T) {
+        for (int r = 0; r < 16; ++r) sacc[r] = 0.0f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sacc[T][r] = 0.0f;
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const v8bf kf = *(const v8bf*)(ks + (32 * T + n) * KSTR + 32 * s + 16 * g);
-                sacc[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc[T], 0, 0, 0);
-            }
+        for (int s = 0; s < KS; ++s) {
+            const v8bf kf = *(const v8bf*)(lds + n * KSTR + 32 * s + 16 * g);
+            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc, 0, 0, 0);
         }
         if constexpr (TAIL) {
             const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
 #pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (32 * T + 8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) sacc[T][r] = -INFINITY;
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) sacc[r] = -INFINITY;
         }
         auto row_max = [&]() {  // maximum over the block's keys of this lane's query, in both of its lanes
             float part[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) part[r & 3] = fmaxf(part[r & 3], sacc[T][r]);
+            for (int r = 0; r < 16; ++r) part[r & 3] = fmaxf(part[r & 3], sacc[r]);
             const float mx = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(mx), __float_as_int(mx), false, false);
             return fmaxf(__int_as_float((int)sw[0]), __int_as_float((int)sw[1]));
@@ -1518,13 +1492,11 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? 3 : 2)) void attn_bf16_kernel(A
         // y = c S - m_ref, the exponent of P, FIRST, in place of S: its maximum tells whether the row has climbed past
         // its reference (results of an fma need no NaN quieting before a maximum, raw matrix results would)
 #pragma unroll
-        for (int T = 0; T < KT; ++T)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sacc[T][r] = fmaf(sacc[T][r], c, -m_ref);
+        for (int r = 0; r < 16; ++r) sacc[r] = fmaf(sacc[r], c, -m_ref);
         const float climb = row_max();  // row maximum - reference
         __syncthreads();
-        lstore_v(0);                      // V_t (loaded one block ago)
-        if (t + 1 < cnt) lstore_k(0);     // K_{t+1}
+        lstore_v();                       // V_t (loaded one block ago)
+        if (t + 1 < cnt) lstore_k();      // K_{t+1}
         if (t + 1 < cnt) gload_v(t + 1);  // before the column chunk moves on: t+1 may be its last entry
         if (((t + 2) & 63) == 0) {
             cols_cur = cols_nxt;
@@ -1541,39 +1513,33 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? 3 : 2)) void attn_bf16_kernel(A
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[dt][r] *= down;
 #pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sacc[T][r] -= up;
+            for (int r = 0; r < 16; ++r) sacc[r] -= up;
             m_ref += up;
         }
 
         float rs = 0.0f;
-        v8bf pf[KT][2];
+        v8bf pf[2];
 #pragma unroll
-        for (int T = 0; T < KT; ++T)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const float p0 = __builtin_amdgcn_exp2f(sacc[T][8 * u + 2 * e2]);
-                    const float p1 = __builtin_amdgcn_exp2f(sacc[T][8 * u + 2 * e2 + 1]);
-                    rs += p0 + p1;
-                    const v2bf pb = __builtin_convertvector(v2f{p0, p1}, v2bf);
-                    pf[T][u][2 * e2] = pb[0];
-                    pf[T][u][2 * e2 + 1] = pb[1];
-                }
+            for (int e2 = 0; e2 < 4; ++e2) {
+                const float p0 = __builtin_amdgcn_exp2f(sacc[8 * u + 2 * e2]);
+                const float p1 = __builtin_amdgcn_exp2f(sacc[8 * u + 2 * e2 + 1]);
+                rs += p0 + p1;
+                const v2bf pb = __builtin_convertvector(v2f{p0, p1}, v2bf);
+                pf[u][2 * e2] = pb[0];
+                pf[u][2 * e2 + 1] = pb[1];
+            }
         l += rs;
 
         __syncthreads();  // K_{t+1} and V_t are in place
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const v8bf vf = *(const v8bf*)(vs + (32 * dt + n) * VSTR + 2 * (32 * T + 16 * g + 8 * u));
-                    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[T][u], acc[dt], 0, 0, 0);
-                }
+            for (int u = 0; u < 2; ++u) {
+                const v8bf vf = *(const v8bf*)(lds + KBYTES + (32 * dt + n) * VSTR + 2 * (16 * g + 8 * u));
+                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[u], acc[dt], 0, 0, 0);
+            }
     };
 
     const bool has_tail = (a.n_tokens % BLK) != 0 && cnt > 0 && min(max(cols[cnt - 1], 0), a.kblocks - 1) == a.kblocks - 1;
@@ -2051,21 +2017,13 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
     else bf16_finish((OutT*)a.op + 64, ooff, row < a.n_tokens, rows.acc[2], rows.acc[3], rows.nref, rows.l, take, &meet[w ^ 2][0][0], lane);
 }
 
-template <int BLK, int D, typename OutT>
-static int launch_bf16_t(const AttnArgs& a, hipStream_t st) {
-    constexpr int bytes = Bf16Cfg<BLK, D>::LDS_BYTES;
-    static_assert(bytes <= 48 * 1024, "beyond 48 KB the launch would have to raise the function's dynamic LDS limit first");
-    hipLaunchKernelGGL((attn_bf16_kernel<BLK, D, OutT>), dim3((unsigned)(a.per_xcd * 8)), dim3(BLK * 2), bytes, st, a);
-    return PARO_OK;
-}
-
 template <typename OutT>
 static int launch_bf16(int blk, int d, const AttnArgs& a, hipStream_t st) {
     const dim3 grid((unsigned)(a.per_xcd * 8));
     if (blk == 64 && d == 64) hipLaunchKernelGGL((attn_bf16_d64_kernel<OutT>), grid, dim3(128), 0, st, a);
     else if (blk == 64) hipLaunchKernelGGL((attn_bf16_d128_kernel<OutT>), grid, dim3(256), 0, st, a);
-    else if (d == 64) return launch_bf16_t<32, 64, OutT>(a, st);
-    else return launch_bf16_t<32, 128, OutT>(a, st);
+    else if (d == 64) hipLaunchKernelGGL((attn_bf16_b32_kernel<64, OutT>), grid, dim3(64), Bf16B32Cfg<64>::LDS_BYTES, st, a);
+    else hipLaunchKernelGGL((attn_bf16_b32_kernel<128, OutT>), grid, dim3(64), Bf16B32Cfg<128>::LDS_BYTES, st, a);
     return PARO_OK;
 }
 

@@ -1,7 +1,8 @@
 """The bf16 kernels of block 64, whose wavefronts split the keys of every block, where that can go wrong: a ragged last
 block that leaves the upper wavefronts without keys (alone in a row, last of several), rows of none, one, two and three
-blocks, more than 64 blocks, and rows whose logits climb past the reference by less and by more than the exponential's
-range, at the first block of a row and later, in the keys of either wavefront."""
+blocks, more than 64 blocks, rows whose logits climb past the reference (a wavefront's first maximum) by less than the 64
+octaves at which it is moved, by more, and by more than the exponential's range, in the keys of either wavefront and in
+a ragged last block, and rows whose first block holds the largest logits."""
 import numpy as np
 import pytest
 
@@ -65,7 +66,7 @@ def test_more_than_one_chunk_of_the_column_list(d):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("upper", [False, True])
-@pytest.mark.parametrize("gain", [6.0, 30.0, 300.0])  # climbs of tens, hundreds and thousands of octaves
+@pytest.mark.parametrize("gain", [6.0, 30.0, 300.0])  # climbs of at most 12, of 20 to 58 and of 68 to 640 octaves
 def test_logits_that_climb_past_the_reference(d, upper, gain):
     rng = np.random.default_rng(int(gain) + d)
     n = 64 * 6
@@ -76,3 +77,72 @@ def test_logits_that_climb_past_the_reference(d, upper, gain):
     k[4 * 64 + 40 * upper + 7] *= 3.0 * gain
     v = rng.standard_normal((n, d))
     _check(d, (6, 8, 8), np.ones((1, 6, 6), bool), q, k, v)
+
+
+def _climbs(d, q, k, half):
+    """[rows]: octaves from a wavefront's first maximum of a row (over its half of block 0) to its largest logit, every block live."""
+    r = [_bf16(x) for x in (q, k)]
+    x = (r[0] @ r[1].T) * (1.4426950408889634 / d ** 0.5)
+    own = np.arange(len(k)) % 64 // 32 == half
+    first = x[:, own & (np.arange(len(k)) < 64)].max(1)
+    return x[:, own].max(1) - first
+
+
+def _bf16(x):
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to(torch.bfloat16).double().numpy()
+
+
+def _key(d, octaves):
+    """A key whose logits against queries of |N(0, 1)| are about so many octaves (their channels add up to about 0.8 d)."""
+    return octaves * d ** 0.5 / (1.4426950408889634 * 0.798 * d)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("upper", [False, True])
+@pytest.mark.parametrize("octaves,lo,hi", [(20.0, 5.0, 64.0), (95.0, 64.0, 128.0), (300.0, 192.0, 450.0)])
+def test_climbs_of_a_stated_size(d, upper, octaves, lo, hi):
+    rng = np.random.default_rng(int(octaves) + d)
+    n = 64 * 6
+    q = np.abs(rng.standard_normal((n, d)))
+    q *= 0.798 * d / q.sum(1, keepdims=True)  # all rows climb alike
+    k = np.abs(rng.standard_normal((n, d))) * 0.05
+    # one key of block 2 stands out, in the half of the keys that one wavefront owns, and one of block 4 by as much again
+    k[2 * 64 + 40 * upper + 3] = _key(d, octaves)
+    c = _climbs(d, q, k, int(upper))
+    assert lo < c.min() and c.max() < hi and _climbs(d, q, k, int(not upper)).max() < 5.0
+    k[4 * 64 + 40 * upper + 7] = _key(d, 2.0 * octaves)
+    v = rng.standard_normal((n, d))
+    _check(d, (6, 8, 8), np.ones((1, 6, 6), bool), q, k, v)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("upper", [False, True])
+def test_the_largest_logits_in_the_first_block(d, upper):
+    rng = np.random.default_rng(d)
+    n = 64 * 6
+    q = np.abs(rng.standard_normal((n, d)))
+    k = np.abs(rng.standard_normal((n, d))) * 0.05
+    k[40 * upper + 5] = _key(d, 300.0)  # the wavefront of the other half keeps a reference some 300 octaves lower
+    assert _climbs(d, q, k, int(upper)).max() == 0.0
+    v = rng.standard_normal((n, d))
+    _check(d, (6, 8, 8), np.ones((1, 6, 6), bool), q, k, v)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("upper,tail", [(False, 40), (True, 40), (False, 20)])
+@pytest.mark.parametrize("octaves,lo,hi", [(95.0, 64.0, 128.0), (250.0, 160.0, 320.0)])
+def test_a_climb_in_the_ragged_last_block(d, upper, tail, octaves, lo, hi):
+    """All logits lie far below 0, what a padded key would give: one that is not masked where the logits are formed anew takes
+    the whole row."""
+    rng = np.random.default_rng(int(octaves) + tail + d)
+    n = 64 * 5 + tail
+    q = np.abs(rng.standard_normal((n, d)))
+    q *= 0.798 * d / q.sum(1, keepdims=True)
+    k = rng.standard_normal((n, d)) * 0.05 + _key(d, -500.0)
+    k[5 * 64 + 32 * upper + 3] = _key(d, -500.0 + octaves)
+    c = _climbs(d, q, k, int(upper))
+    assert lo < c.min() and c.max() < hi
+    v = rng.standard_normal((n, d))
+    _check(d, (1, n // 4, 4), np.ones((1, 6, 6), bool), q, k, v)

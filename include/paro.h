@@ -309,9 +309,10 @@ int paro_blocklist_cols_device(int nh, int k, const uint8_t* bitmask, const int3
 
 /* Per-block statistics of P for operands that are already reordered (Eq. (M_sparse), (M_quant)).
  * P is formed from the 16-bit operands with fp32 accumulation; entries of padded rows and
- * columns (beyond N) do not exist and enter no statistic.
+ * columns (beyond N) do not exist and enter no statistic.  A row that holds NaN counts no entry below eps.
  *   q16, k16   bf16 [B,nh,Npad,d] as produced by paro_(permute_)quantize(bits 16, PARO_ROWS)
- *   eps        threshold of Eq. (M_sparse) (paper: e.g. 1e-3), any value > 0, infinity included; only block_cnt depends on it
+ *   eps        threshold of Eq. (M_sparse) (paper: e.g. 1e-3), any value > 0, infinity included; sums and maxima do not
+ *              depend on it beyond their rounding
  *   block_sum  float32 [B,nh,k,k]  sum of |P| over the block (the block sum of Sec. 4.2 (3))
  *   block_max  float32 [B,nh,k,k]  max of |P| over the block
  *   block_cnt  int32   [B,nh,k,k]  number of entries with |P| < eps  (n_ij of Eq. (M_sparse)) */
@@ -322,8 +323,10 @@ int paro_calib_block_stats(const paro_shape* s, const void* q16, const void* k16
  * paro_calib_row_stats: per row of P its largest logit and its denominator, of operands in the DEFAULT token order
  *   (axis order 0).  row_stats: paro_calib_row_stats_bytes(s) bytes on the device, 16-byte aligned.
  * paro_calib_block_stats_from_rows: the block statistics of operands reordered by h_perm_ids (host, [nh]) from them.
- *   The outputs are those of paro_calib_block_stats on the same operands: row maxima are exact and denominators are
- *   accumulated in binary64 before they are rounded to binary32, so neither depends on the order of the keys. */
+ *   The outputs are those of paro_calib_block_stats on the same operands: row maxima are exact, and denominators are
+ *   accumulated in binary64 before they are rounded to binary32, so they depend on the order of the keys only where the
+ *   sum lies within its own rounding error (at most N 2^-53 of it) of a boundary between two binary32 values; there a row's
+ *   denominator, and with it the row's entries, can differ by 2^-23 of themselves. */
 int64_t paro_calib_row_stats_bytes(const paro_shape* s);
 int paro_calib_row_stats(const paro_shape* s, const void* q16, const void* k16, void* row_stats, void* stream);
 int paro_calib_block_stats_from_rows(const paro_shape* s, const uint8_t* h_perm_ids, const void* q16, const void* k16,

@@ -4,13 +4,15 @@
 //   paro_calib_block_stats   per b x b block of the post-softmax map P = softmax(Q K^T / sqrt(d)) of
 //                            already reordered 16-bit operands: sum, maximum, and the number of
 //                            entries below eps (the n_ij of Eq. (M_sparse)).  The map is never
-//                            stored: one workgroup owns a row block, sweeps all column blocks once
-//                            for the row maxima and denominators and a second time for the block
-//                            statistics, both on v_mfma_f32_32x32x16_bf16 in the transposed
-//                            orientation (a lane holds 16 keys of ONE query, so the row statistics
-//                            are in-lane plus one cross-lane step).
+//                            stored: a workgroup owns four row blocks (one, where that would leave
+//                            the chip idle) and sweeps all column blocks three times, for the row
+//                            maxima, for the denominators and for the block statistics, on
+//                            v_mfma_f32_32x32x16_bf16 in the transposed orientation (a lane holds
+//                            16 keys of ONE query, so the row statistics are in-lane plus one
+//                            cross-lane step).
 //   paro_calib_row_stats, paro_calib_block_stats_from_rows
-//                            the two sweeps apart: the first serves every axis order of the same Q and K.
+//                            the first two sweeps and the third apart, each split into column chunks:
+//                            the first two serve every axis order of the same Q and K.
 //   paro_calib_metrics       M_sparse and M_quant of Eq. (M_sparse) / (M_quant) per head.
 //   paro_calib_choose        the combined metric over the six orders and the order that minimises it.
 //   paro_calib_mask          block-sum thresholding with explicit density control: the n_live
@@ -91,8 +93,9 @@ enum CalibPhase { kRowMax = 0, kRowDen = 1, kBlockStats = 2, kBlockStatsAnyEps =
 // orientation: the lanes n and n + 32 share query n of the half.
 //
 // Phases.  kRowMax: the row's largest logit (exact in any order).  kRowDen: its denominator against that maximum,
-// accumulated in binary64, so that - rounded to binary32 - it does not depend on the order of the keys: the row
-// statistics of one axis order serve all six.  kBlockStats: the exponent is formed against eps,
+// accumulated in binary64, so that - rounded to binary32 - it depends on the order of the keys only where the sum lies
+// within its own rounding of a binary32 boundary: the row statistics of one axis order serve all six.  Taking both
+// in one sweep would save the first, but not with a denominator that is the same in every order.  kBlockStats: the exponent is formed against eps,
 //     y = c S - (m + log2 l + log2 eps),   p = eps 2^y,
 // so that its sign bit IS the comparison p < eps: the 32 signs of a half are shifted into one register
 // (v_alignbit) and counted by one v_bcnt; the maximum is taken on y.  The offset is rounded to binary32; what that

@@ -1715,9 +1715,10 @@ __device__ __forceinline__ void bf16_finish(OutT* op, long long ooff, bool row_v
 // is read from LDS once per row block (four wavefronts of 16 queries read it four times: 64 KB of reads and 16 KB of
 // writes per block, 640 of the 777 cycles a block took).  A wavefront's half tiles are its own: it moves them to
 // LDS itself (global_load_lds, 4 KB of K and 4 KB of V, one slot each) and there is no barrier in the loop.  K_{t+1} is
-// requested behind the reads of K_t, V_{t+1} behind those of V_t.  Matrix and vector instructions bound it now (about 330 and
-// 300 cycles per block of a compute unit, which hardly overlap).  48 heads of 17550 tokens at 30 % density, quantizer
-// included: 1530 -> 1430 us.
+// requested behind the reads of K_t, V_{t+1} behind those of V_t.  Matrix and vector instructions bound it now: of the 538
+// cycles that a block takes a compute unit (1.64 GHz under this load) the matrix pipes are busy for 256 and vector issue
+// for 365, 98 of them together, which leaves 3 % idle.  48 heads of 17550 tokens at 30 % density, quantizer
+// included: 1553 -> 1467 us.
 template <typename OutT>
 __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     constexpr int BLK = 64, D = 64;
@@ -1758,7 +1759,8 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
         for (int s = 0; s < KS; ++s) qf[H][s] = *(const v8bf*)(qrow + 32 * s);
     }
     // K half: 32 rows of 128 bytes, piece p of row r at position p ^ r % 8.  V^T half: 64 rows of 64 bytes, piece p of row r at
-    // position p ^ (r / 2) % 4.  Eight neighbouring rows then cover all banks, for the requests and for the fragment reads.
+    // position p ^ (r / 2) % 4, so that neighbouring rows start in different banks.  (Half of the LDS's busy cycles still count
+    // as conflicts; it is busy for a quarter of the time, and wavefronts wait for it 2 % of theirs.)
     const unsigned kfill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
     const unsigned vfill = 128u * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
     // fragment s of K: piece 2 s + g of row n, i.e. fragment 0's address with bits flipped; fragment u of V^T: piece 2 g + u
@@ -1883,7 +1885,8 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
 // The tiles are shared: each wavefront moves a quarter of K and of V^T to LDS (global_load_lds), one slot each.
 // Two barriers per block: V_t is requested behind the first (V_{t-1} has been read by all, K_t is whole) and K_{t+1}
 // behind the second (K_t has been read by all, V_t is whole), so each has half a block of work to hide behind.
-// 24 heads of 4096 + 512 tokens at 30 % density, two layers with quantizer and mask prefetch: 411 -> 385 us.
+// 24 heads of 4096 + 512 tokens at 30 % density, two layers with quantizer and mask prefetch: 419 -> 387 us (runs of one
+// side differ by 0.3 %; 406 -> 377 and 470 -> 411 elsewhere).
 template <typename OutT>
 __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
     constexpr int BLK = 64, D = 128;

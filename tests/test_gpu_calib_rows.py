@@ -1,5 +1,7 @@
 """Calibration in two steps (row statistics once, block statistics per axis order) against the one-call form, and
-the mask selection at the sizes where the kernels change: keys per thread, registers or memory, ties."""
+the mask selection at the sizes where the kernels change: keys per thread, registers or memory, ties.  The two forms add a
+row's denominator in another order, in binary64: they are equal bit for bit unless a sum lies within its own rounding error
+of a binary32 rounding boundary, which none of these inputs' (fixed) sums do."""
 import numpy as np
 import pytest
 

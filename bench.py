@@ -27,33 +27,34 @@ PEAK_BF16_TFLOPS = 2500.0
 
 
 def attention_kernel_symbol(w):
-    """(mangled symbol, demangled name as the profiler prints it, wavefronts per row-block visit, wavefronts per SIMD)
-    of the kernel that paro_sparse_attn launches for an integer workload."""
+    """(mangled symbol, demangled name as the profiler prints it, wavefronts per row-block visit, wavefronts per SIMD, live
+    blocks per loop iteration) of the kernel that paro_sparse_attn launches for an integer workload."""
     t, tn = ("t", "unsigned short") if w.dtype == "bf16" else ("f", "float")
     if w.block == 64 and w.d == 64 and w.bits_qk == 8:
         return ("_ZN4paro18attn_i8_w64_kernelILi%dE%sLi0EEEvNS_8AttnArgsE" % (w.bits_pv, t),
-                "paro::attn_i8_w64_kernel<%d, %s, 0>" % (w.bits_pv, tn), 1, 2)
+                "paro::attn_i8_w64_kernel<%d, %s, 0>" % (w.bits_pv, tn), 1, 2, 2)
     if w.block == 64 and w.d == 64 and w.bits_qk == 4:
         return ("_ZN4paro22attn_i8_w64_qk4_kernelILi%dE%sEEvNS_8AttnArgsE" % (w.bits_pv, t),
-                "paro::attn_i8_w64_qk4_kernel<%d, %s>" % (w.bits_pv, tn), 1, 2)
+                "paro::attn_i8_w64_qk4_kernel<%d, %s>" % (w.bits_pv, tn), 1, 2, 2)
     if w.block == 64 and w.d == 128 and w.bits_qk == 8 and w.bits_pv == 8:
-        return ("_ZN4paro18attn_i8_q16_kernelI%sEEvNS_8AttnArgsE" % t, "paro::attn_i8_q16_kernel<%s>" % tn, 4, 4)
+        return ("_ZN4paro18attn_i8_q16_kernelI%sEEvNS_8AttnArgsE" % t, "paro::attn_i8_q16_kernel<%s>" % tn, 4, 4, 1)
     return ("_ZN4paro14attn_i8_kernelILi%dELi%dELi%dELi%dE%sLi0EEEvNS_8AttnArgsE" % (w.block, w.d, w.bits_qk, w.bits_pv, t),
-            "paro::attn_i8_kernel<%d, %d, %d, %d, %s, 0>" % (w.block, w.d, w.bits_qk, w.bits_pv, tn), w.block // 32, 3 if w.d == 64 else 2)
+            "paro::attn_i8_kernel<%d, %d, %d, %d, %s, 0>" % (w.block, w.d, w.bits_qk, w.bits_pv, tn), w.block // 32, 3 if w.d == 64 else 2, 1)
 
 
 def static_loop_counts(w):
-    """Vector instructions per loop iteration (one visit of a live block by one wavefront) of the built attention
+    """Vector instructions per visit of a live block by one wavefront in the loop of the built attention
     kernel, by issue class, from the compiler's listing (lib/attn_loop_counts.json, written by the build).  Of the
     kernel's loop variants the one with the fewest instructions is the folded-exponent form that 8-bit P codes take."""
     path = os.path.join(ROOT, "paper_2506_16054_amd", "lib", "attn_loop_counts.json")
+    symbol, _, _, _, visits = attention_kernel_symbol(w)
     try:
-        loops = json.load(open(path)).get(attention_kernel_symbol(w)[0])
+        loops = json.load(open(path)).get(symbol)
     except OSError:
         return None
     if not loops:
         return None
-    return min(loops, key=lambda c: sum(c.values()))
+    return {c: n / visits for c, n in min(loops, key=lambda c: sum(c.values())).items()}
 
 
 def recorded_counters(w, live_blocks):
@@ -64,7 +65,7 @@ def recorded_counters(w, live_blocks):
     import re
 
     out = {"valu_instructions": None, "traffic": None, "stale": None}
-    _, name, waves, _ = attention_kernel_symbol(w)
+    _, name, waves, _, _ = attention_kernel_symbol(w)
     static = static_loop_counts(w)
     path = os.path.join(ROOT, "profiles", "attn_i8_%s_sq_counters.md" % w.name)
     try:
@@ -105,7 +106,7 @@ def valu_issue_roofline(w, live_blocks, attn_ms, n_cus):
     static = static_loop_counts(w)
     if not static:
         return None
-    _, name, waves, occupancy = attention_kernel_symbol(w)
+    _, name, waves, occupancy, _ = attention_kernel_symbol(w)
     kinds = probe.kinds()
     cost_cycles, cost_ns = {}, {}
     for cls in static:

@@ -44,6 +44,7 @@
 
 namespace paro {
 
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
@@ -68,16 +69,22 @@ __device__ long long timeline_records[kTimelineSlots][kTimelineFields];
         timeline_phase[i] += now_ - timeline_last;         \
         timeline_last = now_;                              \
     }
-#define PARO_TIMELINE_END(slot, lane, blocks)                                         \
+// without phases
+#define PARO_TIMELINE_STOP(slot, lane, blocks)                                        \
     if ((lane) == 0 && (slot) < kTimelineSlots) {                                     \
         timeline_records[slot][0] = timeline_start;                                   \
         timeline_records[slot][1] = wall_clock64();                                   \
         timeline_records[slot][2] = (blocks);                                         \
+    }
+#define PARO_TIMELINE_END(slot, lane, blocks)                                         \
+    PARO_TIMELINE_STOP(slot, lane, blocks)                                            \
+    if ((lane) == 0 && (slot) < kTimelineSlots) {                                     \
         for (int f_ = 0; f_ < 5; ++f_) timeline_records[slot][3 + f_] = timeline_phase[f_]; \
     }
 #else
 #define PARO_TIMELINE_BEGIN
 #define PARO_TIMELINE_PHASE(i)
+#define PARO_TIMELINE_STOP(slot, lane, blocks)
 #define PARO_TIMELINE_END(slot, lane, blocks)
 #endif
 
@@ -629,14 +636,27 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? PARO_ATTN_WAVES_D64 : 2)) void 
 // The wavefront owns all 64 queries of the row block as two halves of 32 (H = 0, 1; a lane holds query
 // n of each half).  The P quantization group - the whole 64 x 64 tile - then lives in one wavefront: its
 // maximum is an in-wave reduction, nothing is exchanged between wavefronts and nothing has to be
-// synchronised.  K_j and V_j^T travel from global memory (L2) straight into LDS with
-// global_load_lds_dwordx4, which bypasses the vector registers: every lane fetches exactly the 16-byte
-// fragments the matrix instructions will take from it as A operand (K rows and PARO_VT rows are 64 bytes;
-// a lane pair reads 32 contiguous bytes), so a tile arrives in LDS as eight 1 KB fragments in lane order
-// and is read back with conflict-free 16-byte LDS reads just before use.  The LDS is a private two-slot
-// ring per wavefront: block t+1 is requested at the top of block t and has all of block t to arrive; the
-// only wait is one vmcnt(0) per block.  Each fragment feeds two matrix instructions (one per half).
-// Per block and half the arithmetic is that of attn_i8_kernel.
+// synchronised.  Per block and half the arithmetic is that of attn_i8_kernel.
+//
+// What bounds it: issue slots and, under sustained load, the energy of a block (the card holds 1 380 W of its 1 400 W limit
+// throughout and lowers the clock, 2.4 -> about 2.1 GHz), so both instructions and bytes moved on the chip count.  Two
+// wavefronts of a SIMD issue together only where neither issues an exponential (a v_exp_f32 takes all of 8.5 cycles), a
+// matrix instruction costs 8 issue cycles beside exponentials and blocks the second slot for its 32 cycles beside
+// anything else.  Therefore:
+//   * the 64 exponentials of a lane come in four bursts of 16 (half x key tile) with raised priority: a wavefront in its burst is
+//     not interleaved with the other one's fp32 work, which could not issue beside it, and outside of bursts both issue at once;
+//   * the 16 matrix instructions sit in the bursts, one in front of every four exponentials (34 cycles).  For that, products
+//     run ahead or behind: the bursts of block t hold, in turn, P V of half 1 of block t - 1, K Q of half 1 of block t + 1,
+//     P V of half 0 of block t and K Q of half 0 of block t + 1;
+//   * the chain from the row maxima to the tile's scale runs beside the sum and the codes of the previous block's last tile;
+//   * K and V^T fragments (16 bytes per lane; a lane pair reads 32 contiguous bytes of a 64-byte row) go from global memory (L2)
+//     to registers, each as soon as the last product of its predecessor is issued: K has two bursts, V one and two halves of
+//     vector work to arrive.  No LDS (a copy through LDS cost 21.9 pJ/B against 16.7);
+//   * the accumulators of the products start at an instruction's own constant (acc_start): 16 registers less, and 16 register
+//     reads less in every second matrix instruction.
+// Before: K and V by way of an LDS ring, products, maxima and exponentials of a block one after the other, 1.00 of the
+// summed issue cost.  Sustained, us per call with the quantizer: 48 heads of 17550 tokens at 30 % 1 160 -> 1 085, 30 heads
+// at 50 % 1 182 -> 1 100; 48 heads at 20 % with 4-bit P and V 835 -> 780, all 4-bit 837 -> 792.
 // -------------------------------------------------------------------------------------------
 #ifndef PARO_ATTN_SINGLE_WAVE
 #define PARO_ATTN_SINGLE_WAVE 1
@@ -652,12 +672,70 @@ __device__ inline void lds_dma16(const uint8_t* base, unsigned lane_off, uint8_t
                                      (__attribute__((address_space(3))) void*)(lds_dst - OFFSET), 16, OFFSET, 0);
 }
 
+// The lane number, computed where it stands: in rarely taken branches, so that nothing derived from it is kept in
+// registers through the loop around them.
+__device__ __forceinline__ int lane_here() {
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
+// 64 column indices per fetch, one per lane, one chunk ahead; at(u) is called with u = 0, 1, 2, ...
+struct ColumnList {
+    const int* cols;
+    int cnt, kblocks, cur, nxt, chunk;
+    __device__ ColumnList(const int* cols_, int cnt_, int kblocks_) : cols(cols_), cnt(cnt_), kblocks(kblocks_), chunk(0) {
+        cur = load(0);
+        nxt = load(1);
+    }
+    __device__ int load(int ch) const {
+        const int idx = min(ch * 64 + lane_here(), cnt - 1);
+        return cnt > 0 && ch * 64 < cnt ? min(max(cols[idx], 0), kblocks - 1) : 0;
+    }
+    __device__ int at(int u) {
+        if ((u & 63) == 0 && u > 0) {
+            cur = nxt;
+            ++chunk;
+            nxt = load(chunk + 1);
+        }
+        return __builtin_amdgcn_readlane(cur, u & 63);
+    }
+};
+
+// Start of an integer accumulator chain that costs no registers: 1 / (2 pi), one of the constants that an instruction can
+// name in place of a register.  As a float its bits 0x3E22F983 are kStartI * 2^-26, so the register of a chain that started
+// there, read as a float, is (kStartI + result) * 2^-26 exactly while -2292099 <= result <= 6096508 (|result| <= 127 * 127 * 128
+// here), and one subtraction leaves result * 2^-26.
+constexpr float kStartI = 10680707.0f;
+constexpr float kStartF = kStartI * 0x1p-26f;
+__device__ inline v16i acc_start() {
+    v16i x;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = 0x3E22F983;
+    return x;
+}
+__device__ inline float start_result(int raw) { return fmaf(__int_as_float(raw), 0x1p26f, -kStartI); }  // exact
+// Ends a basic block without an instruction.  The compiler names the constant above in the instruction only where a
+// basic block uses it once; two chains that start in one block would get it in 16 registers.
+__device__ __forceinline__ void end_basic_block() {
+    __label__ next;
+    asm goto("" : : : : next);
+next:;
+}
+// How the exponent is formed from the raw logit: in one fma on the biased value; after one subtraction, with 2^26 in the scale; or
+// from the integer itself, for scales that 2^26 could take out of range.
+enum LogitMode { kFold = 0, kScaled = 1, kExact = 2 };
+
+typedef const __attribute__((address_space(1))) uint8_t* global_bytes;
+typedef __attribute__((address_space(1))) v4i global_v4i;
+typedef __attribute__((address_space(1))) v2u global_v2u;
+
 // QSRC as in attn_i8_kernel: 0 = Q codes and scale from the quantizer; 1 (bf16) / 2 (fp32) = the unquantized Q in the
 // default token order, reordered and quantized here - the quantization group is the row block this wavefront owns,
 // so its absmax is one in-wave reduction.
 // QKBITS 4: Q and K rows are 32 bytes of packed 4-bit codes; a lane fetches the 16 bytes that hold its 32 channels
 // (32 g .. 32 g + 31) of a K row - one fragment per key tile instead of two - and widens them to two 16-byte operands
-// (codes times 16, undone in the scale) right after the LDS read; Q is widened the same way once.
+// (codes times 16, undone in the scale) right before their products; Q is widened the same way once.
 template <int QKBITS, int PVBITS, typename OutT, int QSRC>
 __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
     static_assert(QSRC == 0 || QKBITS == 8, "in-kernel quantization of Q produces 8-bit codes");
@@ -666,9 +744,6 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
     constexpr int VPACK = PVBITS == 4 ? 2 : 1;
     constexpr float LOG2_QMAXP = PVBITS == 4 ? 2.807354922057604f : 6.988684686772166f;
     constexpr float kLog2_65535 = 15.999977986052736f;
-    // [slot][fragment][16 B per lane]; fragments 0-3: K (T,s) - with 4-bit K only 0-1: (T); 4-7: V^T (dt,T) - with 4-bit V only 4-5: (dt), where
-    // lane (n, g) holds bytes 16g .. 16g+15 of packed channel row 32 dt + n, i.e. the 32 slots of key tile g
-    __shared__ __attribute__((aligned(16))) uint8_t ring[2][8][1024];
 
     const int wg = blockIdx.x;
     const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
@@ -680,34 +755,31 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
     const int lane = threadIdx.x;
     const int n = lane & 31;
     const int g = lane >> 5;
-    PARO_TIMELINE_BEGIN
+#if PARO_TIMELINE
+    const long long timeline_start = QKBITS == 8 ? wall_clock64() : 0;  // 4-bit Q and K leave no registers to hold it
+#endif
 
     const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
     const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
     const int end = __builtin_amdgcn_readfirstlane(min(max(rp[1], beg), a.nnz));
     const int cnt = end - beg;
     const int* cols = a.col_idx + beg;
-    if (2 * cnt > a.kblocks) __builtin_amdgcn_s_setprio(2);
 
     const size_t head_rows = (size_t)bh * a.kblocks * BLK;
     const uint8_t* kbase = a.k + head_rows * D / KPACK;  // the head's K codes (wave-uniform)
     const uint8_t* vbase = a.v + head_rows * D / VPACK;  // the head's V^T codes (wave-uniform)
     const unsigned klane = n * (D / KPACK) + 16 * g;     // this lane's K fragment of key tile 0, step 0, inside a block
-    const unsigned vlane = n * (BLK / VPACK) + 16 * g;   // this lane's V^T piece of channel tile 0, inside a block
+    const unsigned vlane = n * (BLK / VPACK) + 16 / VPACK * g;  // its V^T fragment of channel tile 0, key tile 0
     const float* skp = a.sk + (size_t)bh * a.kblocks;
     const float* svp = a.sv + (size_t)bh * a.kblocks;
     float sq_i;
     int row[2];
     bool row_valid[2];
-    unsigned invalid_row[2];
     v4i qf[2][2];  // [half][contraction step]
 #pragma unroll
     for (int H = 0; H < 2; ++H) {
         row[H] = i * BLK + 32 * H + n;
         row_valid[H] = row[H] < a.n_tokens;
-        // or-ed into the bit pattern of a value <= 0 it gives a pattern at or above that of -inf: larger, as an
-        // unsigned number, than the pattern of every value a real row can have
-        invalid_row[H] = row_valid[H] ? 0u : 0xFF800000u;
     }
     if constexpr (QSRC == 0 && QKBITS == 4) {
         sq_i = a.sq[(size_t)bh * a.kblocks + i] * a.qk_scale * (1.0f / 256.0f);  // Q and K codes both enter times 16
@@ -780,41 +852,73 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
         sq_i = scale * a.qk_scale;
     }
 
-    // column indices: 64 per fetch, one per lane, one chunk ahead
-    auto load_cols = [&](int chunk) {
-        const int idx = min(chunk * 64 + lane, cnt - 1);
-        return cnt > 0 && chunk * 64 < cnt ? min(max(cols[idx], 0), a.kblocks - 1) : 0;
+    v4i kf[2][2];  // K fragments of the next block [key tile][contraction step]
+    v4i vf[2][2];  // V^T fragments [channel tile][key tile]
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int T = 0; T < 2; ++T) vf[dt][T] = v4i{0, 0, 0, 0};
+    v4i kraw[2];   // 4-bit K: a lane's 32 channels of a key of either tile
+    auto load_k = [&](int j) {
+        global_bytes kp = (global_bytes)kbase + (size_t)j * (BLK * D / KPACK);  // j comes from a scalar register
+        unsigned off = klane;
+        asm volatile("" : "+s"(kp), "+v"(off));  // scalar base + lane offset, not a 64-bit address per lane
+#pragma unroll
+        for (int T = 0; T < 2; ++T) {
+            if constexpr (QKBITS == 4) {
+                kraw[T] = *(const global_v4i*)(kp + off + 32 * T * (D / 2));
+            } else {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) kf[T][s] = *(const global_v4i*)(kp + off + 32 * T * D + 32 * s);
+            }
+        }
     };
-    int cols_cur = load_cols(0), cols_nxt = load_cols(1);
-    int cur_chunk = 0;  // chunk held by cols_cur
-
-    // request the tiles of column block j into ring slot `slot`
-    auto request = [&](int j, int slot) {
-        const uint8_t* kp = kbase + (size_t)j * (BLK * D / KPACK);  // j comes from a scalar register: kp, vp are wave-uniform
-        const uint8_t* vp = vbase + (size_t)j * (BLK * D / VPACK);
+    auto widen_k = [&]() {
         if constexpr (QKBITS == 4) {
-            lds_dma16<0>(kp, klane, &ring[slot][0][0]);
-            lds_dma16<32 * D / 2>(kp, klane, &ring[slot][1][0]);
-        } else {
-            lds_dma16<0>(kp, klane, &ring[slot][0][0]);
-            lds_dma16<32>(kp, klane, &ring[slot][1][0]);
-            lds_dma16<32 * D>(kp, klane, &ring[slot][2][0]);
-            lds_dma16<32 * D + 32>(kp, klane, &ring[slot][3][0]);
-        }
-        if constexpr (PVBITS == 4) {
-            lds_dma16<0>(vp, vlane, &ring[slot][4][0]);
-            lds_dma16<32 * BLK / 2>(vp, vlane, &ring[slot][5][0]);
-        } else {
-            lds_dma16<0>(vp, vlane, &ring[slot][4][0]);
-            lds_dma16<32>(vp, vlane, &ring[slot][5][0]);
-            lds_dma16<32 * BLK>(vp, vlane, &ring[slot][6][0]);
-            lds_dma16<32 * BLK + 32>(vp, vlane, &ring[slot][7][0]);
+#pragma unroll
+            for (int T = 0; T < 2; ++T) unpack_nibbles(kraw[T], kf[T][0], kf[T][1]);
         }
     };
+    v2u vraw[2][2];  // 4-bit V: a lane's 16 slots of a channel
+    auto load_v = [&](int j) {
+        global_bytes vp = (global_bytes)vbase + (size_t)j * (BLK * D / VPACK);
+        unsigned off = vlane;
+        asm volatile("" : "+s"(vp), "+v"(off));
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int T = 0; T < 2; ++T) {
+                if constexpr (PVBITS == 4) vraw[dt][T] = *(const global_v2u*)(vp + off + 32 * dt * (BLK / 2) + 16 * T);
+                else vf[dt][T] = *(const global_v4i*)(vp + off + 32 * dt * BLK + 32 * T);
+            }
+    };
+    auto widen_v = [&]() {
+        if constexpr (PVBITS == 4) {
+            // a nibble moved to the top of its byte is the code times 16 (undone in the scale), and the PARO_VT nibble order
+            // makes the bytes come out in slot order
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                for (int T = 0; T < 2; ++T)
+                    vf[dt][T] = v4i{(int)((vraw[dt][T].x << 4) & 0xF0F0F0F0u), (int)(vraw[dt][T].x & 0xF0F0F0F0u),
+                                    (int)((vraw[dt][T].y << 4) & 0xF0F0F0F0u), (int)(vraw[dt][T].y & 0xF0F0F0F0u)};
+        }
+    };
+    // product number p (0 .. 3) of S^T = K Q^T / of O^T = V^T P^T: the two chains of two alternate
+    auto qk = [&](int p, int H, v16i (&S)[2]) {
+        const int T = p & 1, s = p >> 1;
+        S[T] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[T][s], qf[H][s], s == 0 ? acc_start() : S[T], 0, 0, 0);
+    };
+    auto pv = [&](int p, const v4i (&pf)[2], v16i (&o)[2]) {
+        const int dt = p & 1, T = p >> 1;
+        o[dt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[dt][T], pf[T], T == 0 ? acc_start() : o[dt], 0, 0, 0);
+    };
 
-    float m[2] = {-INFINITY, -INFINITY};
-    float m_ref[2] = {-INFINITY, -INFINITY};
-    float w_base[2] = {INFINITY, INFINITY};
+    // Padded rows hold +inf: their share of the tile's scale is then -inf, they never ask for a new reference, and what their own
+    // sums become (NaN) is not stored.
+    float m[2], m_ref[2];
+#pragma unroll
+    for (int H = 0; H < 2; ++H) m[H] = m_ref[H] = row_valid[H] ? -INFINITY : INFINITY;
     float l[2] = {0.0f, 0.0f};
     float acc[2][2][16];  // [half][channel tile][register]
 #pragma unroll
@@ -823,92 +927,134 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[H][dt][r] = 0.0f;
-    v16i acc_init;
+    auto update = [&](int H, const v16i (&o)[2], float sv_eff) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc_init[r] = kAccBiasI;
-    asm volatile("" : "+v"(acc_init));
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc[H][dt][r] = fmaf(__int_as_float(o[dt][r]) - kStartF, sv_eff, acc[H][dt][r]);
+                asm volatile("" : "+v"(acc[H][dt][r]));  // here, not where the sum is next used: the product's registers are needed
+            }
+    };
 
-    float sk_cur = 0.0f, sv_cur = 0.0f;
-    int j_cur = 0;
-    if (cnt > 0) {
-        j_cur = __builtin_amdgcn_readlane(cols_cur, 0);
-        request(j_cur, 0);
-        sk_cur = skp[j_cur];
-        sv_cur = svp[j_cur];
+    // 64 column indices per fetch, one per lane; past the end of the row any column, read and not used
+    auto load_cols = [&](int chunk) {
+        const int idx = min(chunk * 64 + lane_here(), cnt - 1);
+        return chunk * 64 < cnt ? min(max(cols[idx], 0), a.kblocks - 1) : 0;
+    };
+    int cols64 = load_cols(0);
+    auto column = [&](int u) {  // u advances by one per call
+        if ((u & 63) == 0) cols64 = load_cols(u >> 6);
+        return __builtin_amdgcn_readlane(cols64, u & 63);
+    };
+    // The scaled and the folded form multiply the logit scale by 2^26.  Folded: the rule of attn_i8_kernel.  Scaled: where that
+    // cannot overflow; beyond 2^90 (inputs of some 2^50 each) the exact form takes over.
+    constexpr bool FOLDABLE = PARO_FOLD_LOGIT_BIAS && PVBITS == 8;
+    bool fast = false;
+    float acc_down = 0x1p13f;  // the sums are held divided by this (half of the 2^26 of start_result), or by 2^26 where V is huge
+    {   // the largest scales of the row block (a lane past the end of the list holds the row's last column)
+        float sk_max = cnt > 0 ? skp[cols64] : 0.0f, sv_max = cnt > 0 ? svp[cols64] : 0.0f;
+        for (int base = 64; base < cnt; base += 64)
+            if (base + lane < cnt) {
+                const int j = min(max(cols[base + lane], 0), a.kblocks - 1);
+                sk_max = fmaxf(sk_max, skp[j]);
+                sv_max = fmaxf(sv_max, svp[j]);
+            }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
+        if (__builtin_amdgcn_ballot_w64(sv_max > 0x1p90f) != 0) acc_down = 1.0f;
+        sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
+        fast = FOLDABLE ? sq_i * sk_max * kAccBiasF < 8192.0f : sq_i * sk_max < 0x1p90f;
     }
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;  // the column block with padded keys, if any
 
-    auto step = [&](auto fold_tag, int t) {
-        constexpr bool FOLD = decltype(fold_tag)::value;
-        const float c = sq_i * sk_cur;
-        const float sv_now = sv_cur;
-        const int j_now = j_cur;
-        const uint8_t* slot = &ring[t & 1][0][0] + 16 * lane;
-
-        // ---- the tiles of this block have arrived (everything this wavefront has in flight is theirs)
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); the other counters untouched
-        v4i kf[2][2];
+    v16i S0[2], Sa[2], Sb[2];  // raw logits [key tile]: of half 0; of half 1, this block's and the next one's in turn
+    v4i pf1[2] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
+    float sv_eff1 = 0.0f;
+    float sk_cur = 0.0f, sv_cur = 0.0f;
+    int j0 = 0, j1 = 0;  // columns of the first block and of block t + 1 (past the end: any column, read and not used)
+    if (cnt > 0) {
+        j0 = __builtin_amdgcn_readlane(cols64, 0);
+        j1 = column(1);
+        load_k(j0);
+        widen_k();
+        sk_cur = uniform_load(skp + j0);
+        sv_cur = uniform_load(svp + j0);
 #pragma unroll
-        for (int T = 0; T < 2; ++T) {
-            if constexpr (QKBITS == 4) {
-                unpack_nibbles(*(const v4i*)(slot + T * 1024), kf[T][0], kf[T][1]);
-            } else {
-#pragma unroll
-                for (int s = 0; s < 2; ++s) kf[T][s] = *(const v4i*)(slot + (2 * T + s) * 1024);
-            }
+        for (int p = 0; p < 4; ++p) {
+            qk(p, 0, S0);
+            if (p < 2) end_basic_block();
         }
-        // ---- request the next block's tiles into the other slot (its previous content, block t-1, is consumed)
-        if (t + 1 < cnt) {
-            if (((t + 1) & 63) == 0) {
-                cols_cur = cols_nxt;
-                ++cur_chunk;
-                cols_nxt = load_cols(cur_chunk + 1);
-            }
-            j_cur = __builtin_amdgcn_readlane(cols_cur, (t + 1) & 63);
-            request(j_cur, (t + 1) & 1);
-            sk_cur = skp[j_cur];
-            sv_cur = svp[j_cur];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            qk(p, 1, Sa);
+            if (p < 1) end_basic_block();
         }
+        load_k(j1);
+    }
 
-        // ---- S^T = K_j Q_i^T for both halves (i32, biased); every K fragment feeds two products
-        v16i sacc[2][2];  // [half][key tile]
+    auto codes = [&](const float (&E)[16], v4i& f) {
 #pragma unroll
-        for (int T = 0; T < 2; ++T)
+        for (int r = 0; r < 16; r += 4) {
+            const unsigned lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(E[r], E[r + 1]));
+            const unsigned hi = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(E[r + 2], E[r + 3]));
+            f[r >> 2] = (int)__builtin_amdgcn_perm(hi, lo, 0x06040200u);
+        }
+    };
+    auto add16 = [&](const float (&E)[16], float (&sum)[4], bool first) {
 #pragma unroll
-            for (int H = 0; H < 2; ++H) {
-                sacc[H][T] = acc_init;
-#pragma unroll
-                for (int s = 0; s < 2; ++s) sacc[H][T] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[T][s], qf[H][s], sacc[H][T], 0, 0, 0);
-            }
+        for (int r = 0; r < 16; ++r) sum[r & 3] = first && r < 4 ? E[r] : sum[r & 3] + E[r];
+        asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]));  // here: the exponentials' registers are needed
+    };
+    // what is left of half 1 of the block before when a block begins: its second tile's exponentials (E), the sum over its
+    // first one, its weight, and (pf1, sv_eff1) its product P V
+    float sum1[4] = {0.0f, 0.0f, 0.0f, 0.0f}, w_blk1 = 0.0f;
+
+    auto close = [&](const float (&E)[16]) {
+        add16(E, sum1, false);
+        codes(E, pf1[1]);
+        l[1] = fmaf((sum1[0] + sum1[1]) + (sum1[2] + sum1[3]), w_blk1, l[1]);
+    };
+
+    // What has to be known of a block before its exponentials: row maxima and the tile's scale.  `last`: the tile of the block before
+    // whose sum and codes are still to be made; they keep the wavefront busy through this chain of dependent steps.
+    float e = 0.0f;
+    auto open = [&](int j, float sk_next, v16i (&S1)[2], const float (&last)[16]) {
         // Keys past N (ragged last column block) never receive probability mass: their raw logits become the
         // bit pattern of -inf, which as an integer loses every maximum and as a float sends the exponent's fma
         // (c > 0) to -inf, i.e. E = 0.  A wave-uniform branch, taken for that one column block only.
-        if (j_now == tail_block) {
-            const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
+        if (j == tail_block) {
+            const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK, gg = lane_here() >> 5;
 #pragma unroll
-            for (int H = 0; H < 2; ++H)
+            for (int T = 0; T < 2; ++T)
 #pragma unroll
-                for (int T = 0; T < 2; ++T)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (32 * T + 8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) sacc[H][T][r] = (int)0xFF800000;
+                for (int r = 0; r < 16; ++r)
+                    if (32 * T + 8 * (r >> 2) + 4 * gg + (r & 3) >= nkeys) {
+                        S0[T][r] = (int)0xFF800000;
+                        S1[T][r] = (int)0xFF800000;
+                    }
         }
-
-        // ---- running maxima of both halves and the tile's quantization scale (one in-wave reduction)
+        int part[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};  // below every real value (those carry the accumulators' start)
+#pragma unroll
+        for (int T = 0; T < 2; ++T)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                part[0][r & 3] = max(part[0][r & 3], S0[T][r]);
+                part[1][r & 3] = max(part[1][r & 3], S1[T][r]);
+            }
+        // ---- running maxima of both halves and the tile's quantization scale (one in-wave reduction), beside the sum and the
+        // codes of the last quarter of the block before, which keep the wavefront busy through this chain of dependent steps
+        const float c = sq_i * sk_next;
         float m_new[2];
         unsigned eb = 0xFF800000u;
 #pragma unroll
         for (int H = 0; H < 2; ++H) {
-            int part[4] = {0, 0, 0, 0};  // below every real value (those carry the accumulator bias)
-#pragma unroll
-            for (int T = 0; T < 2; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) part[r & 3] = max(part[r & 3], sacc[H][T][r]);
-            const float ymax = c * int_result(xor32_max(max(max(part[0], part[1]), max(part[2], part[3]))));
+            const float ymax = c * start_result(xor32_max(max(max(part[H][0], part[H][1]), max(part[H][2], part[H][3]))));
             m_new[H] = fmaxf(m[H], ymax);
-            eb = min(eb, __float_as_uint(ymax - m_new[H]) | invalid_row[H]);  // a padded row loses the minimum
+            eb = min(eb, __float_as_uint(ymax - m_new[H]));  // a padded row has -inf here and loses the minimum
         }
-        const float e = __uint_as_float(wave_umin(eb));
+        e = __uint_as_float(wave_umin(eb));
+        close(last);
         if (__builtin_amdgcn_ballot_w64(m_new[0] - m_ref[0] > 64.0f || m_new[1] - m_ref[1] > 64.0f) != 0) {
 #pragma unroll
             for (int H = 0; H < 2; ++H) {
@@ -919,115 +1065,138 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) acc[H][dt][r] *= down;
                 m_ref[H] = m_new[H];
-                w_base[H] = -kLog2_65535 - m_new[H];
+                if (H == 1) sv_eff1 *= down;  // of the product that is still to be added
             }
         }
-        v4i vf[2][2];  // V_j^T fragments [channel tile][key tile]
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-            for (int T = 0; T < 2; ++T) {
-                if constexpr (PVBITS == 4) {
-                    // this lane's 16 slots of key tile T: 8 packed bytes inside the piece that lane (n, T) fetched;
-                    // a nibble moved to the top of its byte is the code times 16 (undone in the scale), and the
-                    // PARO_VT nibble order makes the bytes come out in slot order
-                    const uint2 x = *(const uint2*)(&ring[t & 1][4 + dt][0] + (n + 32 * T) * 16 + 8 * g);
-                    vf[dt][T] = v4i{(int)((x.x << 4) & 0xF0F0F0F0u), (int)(x.x & 0xF0F0F0F0u), (int)((x.y << 4) & 0xF0F0F0F0u),
-                                    (int)(x.y & 0xF0F0F0F0u)};
-                } else {
-                    vf[dt][T] = *(const v4i*)(slot + (4 + 2 * dt + T) * 1024);
-                }
-            }
-
+        m[0] = m_new[0];
+        m[1] = m_new[1];
+    };
+    float E[16] = {};  // exponentials of the tile at hand
+    // one live block; S1 and N1: the raw logits of half 1, this block's and the next one's
+    auto step = [&](auto mode_tag, int t, v16i (&S1)[2], v16i (&N1)[2]) {
+        constexpr int MODE = decltype(mode_tag)::value;
+        const float c = sq_i * sk_cur;
+        v16i o[2];
+        const float sv_now = sv_cur * (PVBITS == 4 ? acc_down * 0.0625f : acc_down);
+        float off_f[2], w_blk[2];
+        const float c_up = c * 0x1p26f;
         float cb_hi = 0.0f, cb_lo = 0.0f;
-        if constexpr (FOLD) {
-            cb_hi = c * kAccBiasF;
-            cb_lo = fmaf(c, kAccBiasF, -cb_hi);
+        if constexpr (MODE == kFold) {
+            cb_hi = c_up * kStartF;
+            cb_lo = fmaf(c_up, kStartF, -cb_hi);
         }
 #pragma unroll
         for (int H = 0; H < 2; ++H) {
-            m[H] = m_new[H];
-            const float off_n = (LOG2_QMAXP - kLog2_65535) - m_new[H] - e;
-            float off_f = off_n, w_blk;
-            if constexpr (FOLD) {
-                off_f = off_n - cb_hi;
-                const float bb = off_f - off_n;
-                const float terr = (off_n - (off_f - bb)) + (-cb_hi - bb);
-                w_blk = __builtin_amdgcn_exp2f((w_base[H] - off_n) - (cb_lo - terr));
+            const float off_n = (LOG2_QMAXP - kLog2_65535) - m[H] - e;
+            off_f[H] = off_n;
+            if constexpr (MODE == kFold) {
+                off_f[H] = off_n - cb_hi;
+                const float bb = off_f[H] - off_n;
+                const float terr = (off_n - (off_f[H] - bb)) + (-cb_hi - bb);
+                w_blk[H] = __builtin_amdgcn_exp2f(((-kLog2_65535 - m_ref[H]) - off_n) - (cb_lo - terr));
             } else {
-                w_blk = __builtin_amdgcn_exp2f(w_base[H] - off_n);
-            }
-            // ---- E (all of the half first, in place of the raw logits), row sum as four independent chains,
-            // codes packed as B operand
-            float ev[2][16];
-#pragma unroll
-            for (int T = 0; T < 2; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    ev[T][r] = __builtin_amdgcn_exp2f(fmaf(FOLD ? __int_as_float(sacc[H][T][r]) : int_result(sacc[H][T][r]), c, off_f));
-            float part_sum[4];
-#pragma unroll
-            for (int T = 0; T < 2; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) part_sum[r & 3] = (T == 0 && r < 4) ? ev[T][r] : part_sum[r & 3] + ev[T][r];
-            const float rs = (part_sum[0] + part_sum[1]) + (part_sum[2] + part_sum[3]);
-            v4i pf[2];
-#pragma unroll
-            for (int T = 0; T < 2; ++T)
-#pragma unroll
-                for (int qd = 0; qd < 4; ++qd) {
-                    const unsigned lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(ev[T][4 * qd], ev[T][4 * qd + 1]));
-                    const unsigned hi = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(ev[T][4 * qd + 2], ev[T][4 * qd + 3]));
-                    pf[T][qd] = (int)__builtin_amdgcn_perm(hi, lo, 0x06040200u);
-                }
-            l[H] = fmaf(rs, w_blk, l[H]);
-            // ---- O^T += (sP sv_j 2^(m' - m_ref)) V_j^T P^T for this half
-            const float sv_eff = w_blk * sv_now * (PVBITS == 4 ? 0.0625f : 1.0f);
-#pragma unroll
-            for (int dt = 0; dt < 2; ++dt) {
-                v16i o = acc_init;
-#pragma unroll
-                for (int T = 0; T < 2; ++T) o = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[dt][T], pf[T], o, 0, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[H][dt][r] = fmaf(int_result(o[r]), sv_eff, acc[H][dt][r]);
+                w_blk[H] = __builtin_amdgcn_exp2f((-kLog2_65535 - m_ref[H]) - off_n);
             }
         }
-    };
-
-    constexpr bool FOLDABLE = PARO_FOLD_LOGIT_BIAS && PVBITS == 8;
-    bool fold = false;
-    if constexpr (FOLDABLE) {  // same rule as attn_i8_kernel
-        // the first two chunks of column indices are in registers already (a lane past the end holds the row's last column)
-        float sk_max = cnt > 0 ? skp[cols_cur] : 0.0f;
-        if (cnt > 64) sk_max = fmaxf(sk_max, skp[cols_nxt]);
-        for (int base = 128; base < cnt; base += 64)
-            if (base + lane < cnt) sk_max = fmaxf(sk_max, skp[min(max(cols[base + lane], 0), a.kblocks - 1)]);
+        auto exponents = [&](const v16i& S, int H, float (&E)[16]) {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
-        fold = sq_i * sk_max * kAccBiasF < 8192.0f;
-    }
-    if (fold) {
-        for (int t = 0; t < cnt; ++t) step(std::bool_constant<FOLDABLE>{}, t);
-    } else {
-        for (int t = 0; t < cnt; ++t) step(std::false_type{}, t);
+            for (int r = 0; r < 16; ++r) {
+                if constexpr (MODE == kFold) E[r] = fmaf(__int_as_float(S[r]), c_up, off_f[H]);
+                else if constexpr (MODE == kScaled) E[r] = fmaf(__int_as_float(S[r]) - kStartF, c_up, off_f[H]);
+                else E[r] = fmaf(start_result(S[r]), c, off_f[H]);
+            }
+        };
+        // a tile's exponentials, four behind each of four matrix instructions
+        auto burst = [&](float (&E)[16], auto product) {
+            end_basic_block();
+            __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                product(p);
+                if (p == 0) end_basic_block();
+#pragma unroll
+                for (int r = 4 * p; r < 4 * p + 4; ++r) E[r] = __builtin_amdgcn_exp2f(E[r]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __builtin_amdgcn_s_setprio(0);
+        };
+        float sum[4];
+        v4i pf0[2];
+        exponents(S0[0], 0, E);
+        burst(E, [&](int p) { pv(p, pf1, o); });  // P V of half 1 of the block before
+        load_v(j0);
+        j0 = j1;
+        sk_cur = uniform_load(skp + j0);
+        sv_cur = uniform_load(svp + j0);
+        add16(E, sum, true);
+        codes(E, pf0[0]);
+        exponents(S0[1], 0, E);
+        update(1, o, sv_eff1);
+        widen_k();
+        burst(E, [&](int p) { qk(p, 1, N1); });  // the next block's logits of half 1
+        add16(E, sum, false);
+        codes(E, pf0[1]);
+        l[0] = fmaf((sum[0] + sum[1]) + (sum[2] + sum[3]), w_blk[0], l[0]);
+        asm volatile("" : "+v"(l[0]));
+        exponents(S1[0], 1, E);
+        widen_v();
+        burst(E, [&](int p) { pv(p, pf0, o); });  // P V of half 0
+        add16(E, sum1, true);
+        codes(E, pf1[0]);
+        exponents(S1[1], 1, E);
+        update(0, o, w_blk[0] * sv_now);
+        burst(E, [&](int p) { qk(p, 0, S0); });  // the next block's logits of half 0
+        j1 = column(t + 2);
+        load_k(j1);
+        w_blk1 = w_blk[1];
+        sv_eff1 = w_blk[1] * sv_now;
+        if (t + 1 < cnt) open(j0, sk_cur, N1, E);
+    };
+    auto visit_all = [&](auto mode_tag) {
+        int t = 0;
+        for (; t + 1 < cnt; t += 2) {  // one exit: a second one would cost waits for loads that only its path has in flight
+            step(mode_tag, t, Sa, Sb);
+            step(mode_tag, t + 1, Sb, Sa);
+        }
+        if (t < cnt) step(mode_tag, t, Sa, Sb);
+    };
+    if (cnt > 0) open(j0, sk_cur, Sa, E);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing pending at the loop's entry: the compiler would wait for it in every pass
+    if (fast) visit_all(std::integral_constant<int, FOLDABLE ? kFold : kScaled>{});
+    else visit_all(std::integral_constant<int, kExact>{});
+    if (cnt > 0) {
+        v16i o[2];
+        close(E);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            if (p < 2) end_basic_block();
+            pv(p, pf1, o);
+        }
+        update(1, o, sv_eff1);
     }
 
 #pragma unroll
     for (int H = 0; H < 2; ++H) {
+        const int ln = lane_here();  // nothing that only these stores need is kept through the loop
+        const int orow_no = i * BLK + 32 * H + (ln & 31);
+        const bool valid = orow_no < a.n_tokens;
         const float l_tot = (l[H] + __shfl_xor(l[H], 32)) * 65535.0f;
-        const float inv = (row_valid[H] && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
-        const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row[H], row_valid[H]);
+        const float inv = (valid && l_tot > 0.0f) ? (0x1p26f / acc_down) / l_tot : 0.0f;
+        const long long ooff = out_row_offset<D>(a, bh, h, head_rows, orow_no, valid);
         if (ooff >= 0) {
-            OutT* orow = (OutT*)a.op + ooff + 4 * g;
+            OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 5);
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-                for (int qd = 0; qd < 4; ++qd)
-                    store4(orow + 32 * dt + 8 * qd, acc[H][dt][4 * qd] * inv, acc[H][dt][4 * qd + 1] * inv, acc[H][dt][4 * qd + 2] * inv,
-                           acc[H][dt][4 * qd + 3] * inv);
+                for (int qd = 0; qd < 4; ++qd) {
+                    float x[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) x[r] = valid ? acc[H][dt][4 * qd + r] * inv : 0.0f;
+                    store4(orow + 32 * dt + 8 * qd, x[0], x[1], x[2], x[3]);
+                }
         }
     }
-    PARO_TIMELINE_END(item, lane, cnt)
+    if constexpr (QKBITS == 8) { PARO_TIMELINE_STOP(item, lane, cnt) }
 }
 
 template <int PVBITS, typename OutT, int QSRC = 0>
@@ -1636,43 +1805,12 @@ struct Bf16Rows {
 };
 constexpr float kBf16SumLimit = 18446744073709551616.0f;  // 2^64
 
-__device__ __forceinline__ int lane_here();
 __device__ __forceinline__ void mask_keys(v16f& S, int first, int nkeys) {  // keys first + .. of the tile at or past nkeys
     const int g = lane_here() >> 5;
 #pragma unroll
     for (int r = 0; r < 16; ++r)
         if (first + 8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) S[r] = -INFINITY;
 }
-
-// The lane number, computed where it stands: in rarely taken branches, so that nothing derived from it is kept in
-// registers through the loop around them.
-__device__ __forceinline__ int lane_here() {
-    int zero = 0;
-    asm volatile("" : "+v"(zero));
-    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
-}
-
-// 64 column indices per fetch, one per lane, one chunk ahead; at(u) is called with u = 0, 1, 2, ...
-struct ColumnList {
-    const int* cols;
-    int cnt, kblocks, cur, nxt, chunk;
-    __device__ ColumnList(const int* cols_, int cnt_, int kblocks_) : cols(cols_), cnt(cnt_), kblocks(kblocks_), chunk(0) {
-        cur = load(0);
-        nxt = load(1);
-    }
-    __device__ int load(int ch) const {
-        const int idx = min(ch * 64 + lane_here(), cnt - 1);
-        return cnt > 0 && ch * 64 < cnt ? min(max(cols[idx], 0), kblocks - 1) : 0;
-    }
-    __device__ int at(int u) {
-        if ((u & 63) == 0 && u > 0) {
-            cur = nxt;
-            ++chunk;
-            nxt = load(chunk + 1);
-        }
-        return __builtin_amdgcn_readlane(cur, u & 63);
-    }
-};
 
 // Two accumulator tiles (64 channels of 32 queries) with their reference and row sum, handed to another wavefront.
 __device__ __forceinline__ void bf16_hand_over(const v16f& t0, const v16f& t1, float nref, float l, float* tiles, float* row, int lane) {

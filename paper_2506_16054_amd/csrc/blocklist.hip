@@ -89,16 +89,19 @@ __global__ __launch_bounds__(256) void blocklist_fill_kernel(int nh, int k, int 
 // The whole expansion in one launch.  A workgroup owns `per_wg` consecutive row blocks of the flat [nh][k] array.  Where its part of
 // the list starts is the number of live blocks in front of it, which it counts itself, straight from the masks: they
 // are a few hundred KB that every XCD's L2 holds, and reading on average half of them (16 bytes per lane and load) takes less than
-// a launch that waits for the one before it.  Bound by the last workgroup's counting (14 dependent rounds of four loads per
-// thread at the size below): 48 masks of 275 x 275 blocks take 13.1 us a call, all of it inside the kernel (13.0 us by the
-// kernel trace), against 24.6 us for the three launches (a thread per row reading single bytes, a scan by one
-// workgroup, the fill).
-constexpr int kWholeThreads = 512;
+// a launch that waits for the one before it.  Bound by the last workgroup's counting (at the size below 454 KB through one
+// compute unit, 3.4 us at 64 bytes a cycle, in four rounds of seven loads per thread) and by what stands before and behind
+// it: 48 masks of 275 x 275 blocks take 10.0 us a call, against 13.1 with half as many threads and 14 rounds of four loads, and
+// 24.6 us for the three launches (a thread per row reading single bytes, a scan by one workgroup, the fill).  The first
+// round's loads travel while the workgroup's own rows are staged.  4, 10 and 14 loads in flight: 10.3, 10.4, 10.4; a
+// wavefront per row in the staging: 10.4.
+constexpr int kWholeThreads = 1024;
 constexpr int kWholeMaxRows = kWholeThreads;  // a thread per row in the scan
 constexpr int kWholeGroups = 256;             // one workgroup per compute unit
+constexpr int kWholeFlight = 7;               // pieces of 16 bytes that a thread has in flight
 // Counting what lies in front grows with the square of the masks' size, the three launches with the size.  At 1 MB the one
-// launch is still ahead (30 heads of 512 x 512 blocks: 22.5 against 41.8 us; 1 of 2896 x 2896: 27.6 against 65.7; 256 of
-// 181 x 181: 26.3 against 94.3); beyond it the rows of a workgroup outgrow their 8 KB of LDS.
+// launch is still ahead (30 heads of 512 x 512 blocks: 17.5 against 41.8 us; 1 of 2896 x 2896: 21.4 against 65.7; 256 of
+// 181 x 181: 20.7 against 94.3); beyond it the rows of a workgroup outgrow their 8 KB of LDS.
 constexpr int64_t kOneLaunchBytes = 1 << 20;
 constexpr int kWholeStage = 8192;             // bytes of a workgroup's own rows, see launch_whole
 
@@ -114,7 +117,32 @@ __global__ __launch_bounds__(kWholeThreads) void blocklist_whole_kernel(int nh, 
     if (r0 >= r1) return;
     const int words = (k + 31) / 32 + 1;  // words that a row's bits can touch, counted from the byte its first bit is in
 
-    // ---- this workgroup's rows: bits i k .. i k + k - 1 of head h, from the byte that holds the first of them
+    // ---- live blocks in front of row r0: whole bytes [0, whole) of the masks, minus the bits behind every finished
+    // head's last block, plus the bits of the byte that row r0 starts in
+    const int h0 = r0 / k, bit0 = (r0 - h0 * k) * k;
+    const int whole = h0 * nbytes + (bit0 >> 3);
+    const int head = min(whole, (int)(-(uintptr_t)bitmask & 15u));  // bytes in front of the first aligned piece
+    const int pieces = (whole - head) >> 4;
+    const uint4* src16 = (const uint4*)(bitmask + head);
+    uint4 x[kWholeFlight];
+    auto request = [&](int p0) {  // a piece past the last one is read as the first one (there is one) and not counted
+#pragma unroll
+        for (int u = 0; u < kWholeFlight; ++u) {
+            const int p = p0 + u * kWholeThreads;
+            x[u] = src16[p < pieces ? p : 0];
+        }
+    };
+    int before = 0;
+    auto count = [&](int p0) {
+#pragma unroll
+        for (int u = 0; u < kWholeFlight; ++u) {
+            const int n = __popc(x[u].x) + __popc(x[u].y) + __popc(x[u].z) + __popc(x[u].w);
+            before += p0 + u * kWholeThreads < pieces ? n : 0;
+        }
+    };
+    if (pieces > 0) request(t);
+
+    // ---- while those travel, this workgroup's rows: bits i k .. i k + k - 1 of head h, from the byte that holds the first of them
     uint8_t* bytes = (uint8_t*)stage;
     const int row_bytes = 4 * words;
     for (int e = t; e < (r1 - r0) * row_bytes; e += kWholeThreads) {
@@ -124,27 +152,14 @@ __global__ __launch_bounds__(kWholeThreads) void blocklist_whole_kernel(int nh, 
         bytes[e] = at < nbytes ? bitmask[(size_t)h * nbytes + at] : (uint8_t)0;
     }
 
-    // ---- live blocks in front of row r0: whole bytes [0, whole) of the masks, minus the bits behind every finished
-    // head's last block, plus the bits of the byte that row r0 starts in
-    const int h0 = r0 / k, bit0 = (r0 - h0 * k) * k;
-    const int whole = h0 * nbytes + (bit0 >> 3);
-    const int head = min(whole, (int)(-(uintptr_t)bitmask & 15u));  // bytes in front of the first aligned piece
-    const int pieces = (whole - head) >> 4;
-    int before = 0;
+    if (pieces > 0) {
+        count(t);
+        for (int p0 = t + kWholeFlight * kWholeThreads; p0 - t < pieces; p0 += kWholeFlight * kWholeThreads) {
+            request(p0);
+            count(p0);
+        }
+    }
     {
-        const uint4* src = (const uint4*)(bitmask + head);
-        int p = t;
-        for (; p + 3 * kWholeThreads < pieces; p += 4 * kWholeThreads) {
-            uint4 x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = src[p + u * kWholeThreads];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) before += __popc(x[u].x) + __popc(x[u].y) + __popc(x[u].z) + __popc(x[u].w);
-        }
-        for (; p < pieces; p += kWholeThreads) {
-            const uint4 x = src[p];
-            before += __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
-        }
         const int rest = head + 16 * pieces;  // at most 15 bytes on either side of the pieces
         if (t < head) before += __popc((unsigned)bitmask[t]);
         if (t < whole - rest) before += __popc((unsigned)bitmask[rest + t]);

@@ -219,6 +219,14 @@ int paro_permute_quantize_qkv(const paro_shape* s, paro_dtype dtype, int bits_qk
                               void* q_codes, float* sq, void* k_codes, float* sk, void* v_codes, float* sv,
                               void* stream);
 
+/* paro_permute_quantize_qkv that also stores the reordered, padded tensors, exactly as paro_permute writes them: the three reorders and
+ * the three quantizers of the separate-step form in one launch.
+ *   qp, kp, vp  [B,nh,Npad,d] dtype; none may alias an input or another output */
+int paro_permute_quantize_qkv_keep(const paro_shape* s, paro_dtype dtype, int bits_qk, int bits_pv,
+                                   const uint8_t* h_perm_ids, const void* q, const void* k, const void* v,
+                                   void* qp, void* kp, void* vp, void* q_codes, float* sq, void* k_codes,
+                                   float* sk, void* v_codes, float* sv, void* stream);
+
 /* paro_sparse_attn followed by paro_unpermute without the intermediate tensor: row n' of the
  * result is stored at row idx_h[n'] of o.  Arguments as paro_sparse_attn, plus
  *   h_perm_ids  host, [nh], values 0..5

@@ -22,6 +22,7 @@ PARO_F32 = 0
 PARO_BF16 = 1
 PARO_ROWS = 0
 PARO_VT = 1
+QKV_BITS = ((8, 8), (8, 4), (4, 4), (4, 8), (16, 16))  # (bits_qk, bits_pv) of the one-launch quantizers and of the attention
 
 LIBPATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "lib", "libparo.so")
 
@@ -30,7 +31,7 @@ EXPORTS = (
     "paro_perm_index", "paro_vt_slot", "paro_mask_to_blocklist", "paro_permute", "paro_unpermute",
     "paro_quantize", "paro_sparse_attn", "paro_permute_quantize", "paro_sparse_attn_unpermuted", "paro_schedule_rows", "paro_check_blocklist", "paro_check_row_order",
     "paro_mask_to_blocklist_device", "paro_calib_block_stats", "paro_calib_metrics", "paro_calib_choose", "paro_calib_mask",
-    "paro_sparse_attn_unpermuted_rawq", "paro_blocklist_cols_device", "paro_permute_quantize_qkv",
+    "paro_sparse_attn_unpermuted_rawq", "paro_blocklist_cols_device", "paro_permute_quantize_qkv", "paro_permute_quantize_qkv_keep",
     "paro_k_channel_mean", "paro_permute_quantize_smoothed",
     "paro_calib_row_stats_bytes", "paro_calib_row_stats", "paro_calib_block_stats_from_rows", "paro_calib_metrics_orders", "paro_calib_pick",
 )
@@ -92,6 +93,7 @@ def lib() -> ctypes.CDLL:
         L.paro_sparse_attn_unpermuted_rawq.argtypes = [sp, i32, i32, vp, vp, vp, vp, vp, vp, vp, i64, vp, vp, i32, vp, vp]
         L.paro_blocklist_cols_device.argtypes = [i32, i32, vp, vp, vp, i64, vp]
         L.paro_permute_quantize_qkv.argtypes = [sp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+        L.paro_permute_quantize_qkv_keep.argtypes = [sp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.paro_k_channel_mean.argtypes = [sp, i32, vp, vp, vp]
         L.paro_permute_quantize_smoothed.argtypes = [sp, i32, i32, vp, vp, vp, vp, vp, vp]
         _lib = L
@@ -308,7 +310,7 @@ def paro_permute_quantize(s: paro_shape, bits: int, layout: int, perm_ids, x, co
                                        _ptr(scales), _stream()))
 
 
-def paro_permute_quantize_qkv(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv) -> None:
+def _qkv_operands(s: paro_shape, bits_qk: int, bits_pv: int, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv) -> None:
     import torch
 
     m = _dims(s)
@@ -321,9 +323,25 @@ def paro_permute_quantize_qkv(s: paro_shape, bits_qk: int, bits_pv: int, perm_id
     _require(v_codes, "v_codes", m.vt4 if bits_pv == 4 else m.vt, torch.bfloat16 if bits_pv == 16 else torch.int8)
     for name, x in (("sq", sq), ("sk", sk), ("sv", sv)):
         _require(x, name, m.scales, torch.float32)
+
+
+def paro_permute_quantize_qkv(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv) -> None:
+    _qkv_operands(s, bits_qk, bits_pv, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)
     p = _perm_bytes(s, perm_ids)
     _check(lib().paro_permute_quantize_qkv(ctypes.byref(s), _dtype_code(q), int(bits_qk), int(bits_pv), p, _ptr(q), _ptr(k),
                                            _ptr(v), _ptr(q_codes), _ptr(sq), _ptr(k_codes), _ptr(sk), _ptr(v_codes), _ptr(sv), _stream()))
+
+
+def paro_permute_quantize_qkv_keep(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, qp, kp, vp, q_codes, sq, k_codes, sk,
+                                   v_codes, sv) -> None:
+    """qp, kp, vp: the reordered, padded tensors [B, nh, Npad, d], stored as well."""
+    _qkv_operands(s, bits_qk, bits_pv, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)
+    for name, x in (("qp", qp), ("kp", kp), ("vp", vp)):
+        _require(x, name, _dims(s).xp, q.dtype)
+    p = _perm_bytes(s, perm_ids)
+    _check(lib().paro_permute_quantize_qkv_keep(ctypes.byref(s), _dtype_code(q), int(bits_qk), int(bits_pv), p, _ptr(q), _ptr(k), _ptr(v),
+                                                _ptr(qp), _ptr(kp), _ptr(vp), _ptr(q_codes), _ptr(sq), _ptr(k_codes), _ptr(sk),
+                                                _ptr(v_codes), _ptr(sv), _stream()))
 
 
 def paro_k_channel_mean(s: paro_shape, k, k_mean) -> None:

@@ -45,12 +45,18 @@ class ParoAttention:
         self.row_ptr, self.col_idx, self.row_order = row_ptr, col_idx, row_order
 
     def prepare(self, q, k, v) -> None:
-        """paro_permute + paro_quantize for Q, K (row layout) and V (transposed-block layout)."""
+        """paro_permute + paro_quantize for Q, K (row layout) and V (transposed-block layout); one launch where all three are
+        quantized."""
         s = self.s
+        rows_are_codes = self.bits_qk == 16 and self.dtype == torch.bfloat16  # bf16 rows: nothing to convert
+        if not rows_are_codes and (self.bits_qk, self.bits_pv) in pb.QKV_BITS:
+            pb.paro_permute_quantize_qkv_keep(s, self.bits_qk, self.bits_pv, self.perm_ids, q, k, v, *self.xp, self.qc, self.sq, self.kc, self.sk,
+                                              self.vc, self.sv)
+            return
         for src, xp in zip((q, k, v), self.xp):
             pb.paro_permute(s, self.perm_ids, src, xp)
-        if self.bits_qk == 16 and self.dtype == torch.bfloat16:
-            self.qc, self.kc = self.xp[0], self.xp[1]  # already bf16 rows: nothing to convert
+        if rows_are_codes:
+            self.qc, self.kc = self.xp[0], self.xp[1]
         else:
             pb.paro_quantize(s, self.bits_qk, pb.PARO_ROWS, self.xp[0], self.qc, self.sq)
             pb.paro_quantize(s, self.bits_qk, pb.PARO_ROWS, self.xp[1], self.kc, self.sk)

@@ -100,6 +100,44 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+# The calls that run once per layer do their argument checks in a native module (csrc/native/fastcall.cpp): a layer of 130
+# tokens is two calls and host work only, 9.3 us with it and 17.3 us through the checks below and ctypes.  It declines by
+# returning None whatever it does not take as it stands, and the function here goes on with its own checks.
+FASTCALL = ("paro_permute_quantize_qkv", "paro_permute_quantize_qkv_keep", "paro_sparse_attn", "paro_sparse_attn_unpermuted", "paro_unpermute",
+            "paro_mask_to_blocklist_device")
+_fast = None
+
+
+def _native():
+    """The native module, bound to the loaded library (raises if it has not been built)."""
+    global _fast
+    if _fast is None:
+        import importlib.machinery
+        import importlib.util
+
+        import torch  # noqa: F401  the module links torch's libraries
+
+        L = lib()
+        path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "lib", "paro_fastcall.so")
+        if not os.path.exists(path):
+            raise ParoError(PARO_EHIP, "%s is missing: build it with `python -m paper_2506_16054_amd.build`" % path)
+        loader = importlib.machinery.ExtensionFileLoader("paro_fastcall", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("paro_fastcall", loader))
+        loader.exec_module(module)
+        module.bind(paro_shape, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in FASTCALL))
+        _fast = module
+    return _fast
+
+
+def _made(status) -> bool:
+    """Whether the native module has made the call (None: it declined); raises if the call was refused."""
+    if status is None:
+        return False
+    if status != PARO_OK:
+        _check(status)
+    return True
+
+
 def _check(status: int) -> None:
     if status != PARO_OK:
         raise ParoError(status, lib().paro_last_error().decode() or lib().paro_strerror(status).decode())
@@ -275,6 +313,8 @@ def paro_permute(s: paro_shape, perm_ids, x, xp) -> None:
 
 
 def paro_unpermute(s: paro_shape, perm_ids, op, o) -> None:
+    if _made((_fast or _native()).paro_unpermute(s, perm_ids, op, o)):
+        return
     m = _dims(s)
     _require(op, "op", m.xp)
     _require(o, "o", m.x, op.dtype)
@@ -326,6 +366,8 @@ def _qkv_operands(s: paro_shape, bits_qk: int, bits_pv: int, q, k, v, q_codes, s
 
 
 def paro_permute_quantize_qkv(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv) -> None:
+    if _made((_fast or _native()).paro_permute_quantize_qkv(s, bits_qk, bits_pv, perm_ids, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)):
+        return
     _qkv_operands(s, bits_qk, bits_pv, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)
     p = _perm_bytes(s, perm_ids)
     _check(lib().paro_permute_quantize_qkv(ctypes.byref(s), _dtype_code(q), int(bits_qk), int(bits_pv), p, _ptr(q), _ptr(k),
@@ -335,6 +377,9 @@ def paro_permute_quantize_qkv(s: paro_shape, bits_qk: int, bits_pv: int, perm_id
 def paro_permute_quantize_qkv_keep(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, qp, kp, vp, q_codes, sq, k_codes, sk,
                                    v_codes, sv) -> None:
     """qp, kp, vp: the reordered, padded tensors [B, nh, Npad, d], stored as well."""
+    if _made((_fast or _native()).paro_permute_quantize_qkv_keep(s, bits_qk, bits_pv, perm_ids, q, k, v, qp, kp, vp, q_codes, sq,
+                                                                  k_codes, sk, v_codes, sv)):
+        return
     _qkv_operands(s, bits_qk, bits_pv, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)
     for name, x in (("qp", qp), ("kp", kp), ("vp", vp)):
         _require(x, name, _dims(s).xp, q.dtype)
@@ -367,6 +412,8 @@ def paro_permute_quantize_smoothed(s: paro_shape, bits: int, perm_ids, k, k_mean
 def paro_mask_to_blocklist_device(nh: int, k: int, bitmask, row_ptr, col_idx, nnz_out=None) -> None:
     """Device tensors: bitmask uint8 [nh, ceil(k*k/8)] -> row_ptr int32 [nh, k+1], col_idx int32 [cap]
     (cap = col_idx.numel(); may be None for the offsets only), nnz_out int32 [1] or None."""
+    if _made((_fast or _native()).paro_mask_to_blocklist_device(nh, k, bitmask, row_ptr, col_idx, nnz_out)):
+        return
     import torch
 
     _require(bitmask, "bitmask", (nh, (k * k + 7) // 8), torch.uint8)
@@ -509,6 +556,9 @@ def _order_ptr(s: paro_shape, row_order):
 
 def paro_sparse_attn_unpermuted(s: paro_shape, bits_qk: int, bits_pv: int, q, sq, k, sk, v, sv, row_ptr, col_idx, perm_ids, o,
                                 row_order=None) -> None:
+    if _made((_fast or _native()).paro_sparse_attn_unpermuted(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx, perm_ids, o,
+                                                               row_order)):
+        return
     _attn_operands(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx)
     _require(o, "o", _dims(s).x)
     p = _perm_bytes(s, perm_ids)
@@ -539,6 +589,8 @@ def paro_sparse_attn_unpermuted_rawq(s: paro_shape, bits_pv: int, q, k, sk, v, s
 
 
 def paro_sparse_attn(s: paro_shape, bits_qk: int, bits_pv: int, q, sq, k, sk, v, sv, row_ptr, col_idx, op, row_order=None) -> None:
+    if _made((_fast or _native()).paro_sparse_attn(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx, op, row_order)):
+        return
     import torch
 
     m = _dims(s)

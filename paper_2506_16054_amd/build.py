@@ -2,6 +2,7 @@
 
     lib/libparo.so        the product library (everything include/paro.h declares)
     lib/libparo_probe.so  measurement aids of bench.py (csrc/probe/): matrix-rate and instruction-issue probes
+    lib/paro_fastcall.so  the binding's per-layer calls from torch tensors (csrc/native/, a CPython extension, host code)
     lib/libparo_timeline.so  the product library with sparse_attn.hip compiled under -DPARO_TIMELINE=1 (every wavefront of
                           the attention kernels records its start and end clock; read by `probe --timeline`)
 
@@ -23,6 +24,7 @@ LIBPATH = os.path.join(LIBDIR, "libparo.so")
 PROBE_LIBPATH = os.path.join(LIBDIR, "libparo_probe.so")
 TIMELINE_LIBNAME = "libparo_timeline.so"
 SOURCES = ("host_api.cpp", "permute.hip", "quantize.hip", "blocklist.hip", "calibrate.hip", "sparse_attn.hip")
+FASTCALL_LIBNAME = "paro_fastcall.so"
 PROBE_SOURCES = ("probe/issue_probe.hip",)
 
 # -packed-fp32-ops is switched off on purpose: all float math here is scalar per lane.
@@ -155,6 +157,26 @@ def _link(out: str, objs) -> None:
         raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
 
 
+def build_fastcall(libdir: str = LIBDIR) -> str:
+    """The binding's native module: host code against the headers of the running interpreter and its torch."""
+    import sysconfig
+
+    import torch
+
+    base = os.path.dirname(torch.__file__)
+    out = os.path.join(libdir, FASTCALL_LIBNAME)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(base, "include"),
+           "-I", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "native", "fastcall.cpp"), "-o", out,
+           "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the native module failed to build:\n%s\n%s" % (r.stdout, r.stderr))
+    return out
+
+
 def build_library(extra_flags=(), verbose: bool = True, out: str = LIBPATH, probe_out: str | None = PROBE_LIBPATH) -> str:
     """Compile every source and link ``out`` (default: the in-tree library the binding loads) and, unless
     ``probe_out`` is None, the measurement-aid library next to it."""
@@ -164,7 +186,10 @@ def build_library(extra_flags=(), verbose: bool = True, out: str = LIBPATH, prob
     with ThreadPoolExecutor(max_workers=4) as ex:
         counts = ex.submit(write_loop_counts, list(extra_flags), objdir)
         timeline = ex.submit(_compile, "sparse_attn.hip", [*extra_flags, "-DPARO_TIMELINE=1"], objdir, "_timeline") if probe_out else None
+        fastcall = ex.submit(build_fastcall, objdir) if probe_out else None
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags), objdir), srcs))
+        if fastcall:
+            fastcall.result()
         counts.result()
         timeline_obj = timeline.result() if timeline else None
     _link(out, objs[: len(SOURCES)])

@@ -2,7 +2,7 @@
 // INT8 / INT4 PV under block-wise scales (paper Sec. 4.2 (2) and Sec. 4.3), for gfx950.
 //
 // Work split.  One workgroup owns one row block (BLK queries) of one head and walks that row's
-// compacted live-block list in ascending order.  A wavefront owns 32 queries; BLK = 64 uses two
+// compacted live-block list in ascending order.  In attn_i8_kernel a wavefront owns 32 queries; BLK = 64 uses two
 // wavefronts, BLK = 32 one.  Both products run on v_mfma_i32_32x32x32_i8 in the transposed
 // orientation
 //        S^T (keys x queries)   = K_j (A operand, from LDS)   x Q_i^T (B operand, registers)
@@ -14,7 +14,7 @@
 // order this imposes on the contraction is matched by the PARO_VT storage order of V, so V
 // fragments are plain 16-byte LDS reads.
 //
-// Pipeline.  K_j and V_j^T tiles travel HBM/L2 -> registers -> LDS through a ring of two LDS
+// Pipeline (of attn_i8_kernel; the kernels for one shape each state theirs).  K_j and V_j^T tiles travel HBM/L2 -> registers -> LDS through a ring of two LDS
 // stages, with the global loads issued two blocks ahead of the math and ONE workgroup barrier
 // per live block; the barrier also carries the cross-wavefront exchange of the P-tile maximum
 // (the P quantization group is the whole BLK x BLK tile).  Cross-lane reductions use DPP,
@@ -167,8 +167,7 @@ __device__ inline float int_result(int raw) { return __int_as_float(raw) - kAccB
 // The scale of a column block is the same for every lane and is written by the quantizer before this kernel
 // starts: read through the constant address space it becomes a scalar load, needs no vector register while it is
 // carried from one block to the next, and enters its one multiplication as a scalar operand.  Used by the kernel
-// with four wavefronts per row block (-1.4 % there); the one-wavefront kernel measures the same either way and
-// keeps its vector loads.
+// with four wavefronts per row block (-1.4 % there) and by the one-wavefront kernel, which has no registers to spare.
 __device__ inline float uniform_load(const float* p) { return *(const __attribute__((address_space(4))) float*)(unsigned long long)p; }
 
 // 1: with 8-bit P codes the accumulator bias of the logits is folded into the offset of the exponent's
@@ -1521,6 +1520,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_q16_kernel(AttnArgs a) {
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 template <int D>
@@ -1853,18 +1853,21 @@ __device__ __forceinline__ void bf16_finish(OutT* op, long long ooff, bool row_v
 // is read from LDS once per row block (four wavefronts of 16 queries read it four times: 64 KB of reads and 16 KB of
 // writes per block, 640 of the 777 cycles a block took).  A wavefront's half tiles are its own: it moves them to
 // LDS itself (global_load_lds, 4 KB of K and 4 KB of V, one slot each) and there is no barrier in the loop.  K_{t+1} is
-// requested behind the reads of K_t, V_{t+1} behind those of V_t.  Matrix and vector instructions bound it now: of the 538
-// cycles that a block takes a compute unit (1.64 GHz under this load) the matrix pipes are busy for 256 and vector issue
-// for 365, 98 of them together, which leaves 3 % idle.  48 heads of 17550 tokens at 30 % density, quantizer
-// included: 1553 -> 1467 us.
+// requested behind the reads of K_t, V_{t+1} behind those of V_t.
+// What bounds it is power: under this load the card stands at its limit (1.4 kW) and lowers its clock to 1.64 GHz, so time
+// follows the energy of a block, of which the products are nearly half.  Hence the 16 x 16 x 32 form of the products: 7.2 nJ
+// for half the work of a 32 x 32 x 16 one, which takes 16.7.  A lane holds 4 keys of each 16-key tile against one query of
+// each of four groups; the keys of a tile are chosen (krow) so that the 8 exponentials of a lane and group are one operand of
+// the second product in the order that V^T is stored in.  48 heads of 17550 tokens at 30 % density, quantizer included:
+// 1419 -> 1334 us (with 32 x 32 x 16 products before).  K and V straight to registers, without LDS and with two wavefronts
+// per SIMD instead of three: 2080 us.
 template <typename OutT>
 __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     constexpr int BLK = 64, D = 64;
     constexpr int TILE = BLK * D * 2;
-    constexpr int KS = D / 16, DT = D / 32;
     __shared__ __attribute__((aligned(16))) uint8_t kbuf[2][TILE / 2];  // [wavefront]; later half of the exchange buffer
     __shared__ __attribute__((aligned(16))) uint8_t vbuf[2][TILE / 2];
-    __shared__ float meet[2][2][64];  // [half of the queries][reference, sum][lane]
+    __shared__ float meet[2][4][64];  // [half of the queries][2 references, 2 sums][lane]
 
     const int wg = blockIdx.x;
     const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
@@ -1875,8 +1878,8 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     const int h = bh % a.nh;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 31;
-    const int g = lane >> 5;
+    const int n = lane & 15;
+    const int G = lane >> 4;
 
     const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
     const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
@@ -1889,28 +1892,29 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     const uint8_t* kbase = a.k + head_rows * D * 2 + (TILE / 2) * w;  // rows 32 w .. of a K tile
     const uint8_t* vbase = a.v + head_rows * D * 2 + 64 * w;          // slots 32 w .. of every row of a V^T tile
     const float c = a.qk_scale;
-    v8bf qf[2][KS];
+    v8bf qf[4][2];  // [group of 16 queries][32 channels]
 #pragma unroll
-    for (int H = 0; H < 2; ++H) {
-        const uint8_t* qrow = a.q + (head_rows + i * BLK + 32 * H + n) * D * 2 + 16 * g;
+    for (int H = 0; H < 4; ++H) {
+        const uint8_t* qrow = a.q + (head_rows + i * BLK + 16 * H + n) * D * 2 + 16 * G;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) qf[H][s] = *(const v8bf*)(qrow + 32 * s);
+        for (int s = 0; s < 2; ++s) qf[H][s] = *(const v8bf*)(qrow + 64 * s);
     }
-    // K half: 32 rows of 128 bytes, piece p of row r at position p ^ r % 8.  V^T half: 64 rows of 64 bytes, piece p of row r at
-    // position p ^ (r / 2) % 4, so that neighbouring rows start in different banks.  (Half of the LDS's busy cycles still count
-    // as conflicts; it is busy for a quarter of the time, and wavefronts wait for it 2 % of theirs.)
-    const unsigned kfill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
+    // Row n of K's tile T is key 16 (n / 4 % 2) + 8 T + 4 (n / 8) + n % 4 of the half: lane group G then holds, of both tiles, the 8
+    // keys of V^T's piece G.
+    const int krow = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
+    // K half: 32 rows of 128 bytes, piece p of row r at position p ^ (r % 4 + 4 (r / 16)), different for the eight rows that
+    // neighbouring lanes read.  V^T half: 64 rows of 64 bytes, piece p of row r at position p ^ (r / 2) % 4.
+    unsigned kfill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ ((lane >> 3) & 3));
     const unsigned vfill = 128u * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
-    // fragment s of K: piece 2 s + g of row n, i.e. fragment 0's address with bits flipped; fragment u of V^T: piece 2 g + u
-    unsigned kread = 128u * n + 16u * (g ^ (n & 7));
-    unsigned vread = 64u * n + 16u * ((2 * g) ^ ((n >> 1) & 3));
+    unsigned kread = 128u * krow + 16u * (G ^ ((krow & 3) | ((krow >> 2) & 4)));
+    unsigned vread = 64u * n + 16u * (G ^ ((n >> 1) & 3));
     auto request_k = [&](int j) {
         const uint8_t* kp = kbase + (size_t)j * TILE;
-        asm volatile("" : "+s"(kp));  // scalar base + lane offset, not a 64-bit address per lane
+        asm volatile("" : "+s"(kp), "+v"(kfill));  // scalar base + lane offset; the flipped offset is made here, not kept
         lds_dma16<0>(kp, kfill, &kbuf[w][0]);
         lds_dma16<1024>(kp, kfill, &kbuf[w][1024]);
-        lds_dma16<2048>(kp, kfill, &kbuf[w][2048]);
-        lds_dma16<3072>(kp, kfill, &kbuf[w][3072]);
+        lds_dma16<2048>(kp, kfill ^ 64u, &kbuf[w][2048]);
+        lds_dma16<3072>(kp, kfill ^ 64u, &kbuf[w][3072]);
     };
     auto request_v = [&](int j) {
         const uint8_t* vp = vbase + (size_t)j * TILE;
@@ -1920,10 +1924,80 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
         lds_dma16<0>(vp + 4096, vfill, &vbuf[w][2048]);
         lds_dma16<2048>(vp + 4096, vfill, &vbuf[w][3072]);
     };
-
-    Bf16Rows<DT> rows[2];
-    rows[0].init();
-    rows[1].init();
+    // Running state of query n of each group over this wavefront's keys, as in Bf16Rows; a group without a reference has its bit
+    // clear in `seen` and offset 0.
+    float off[4], l[4];
+    unsigned seen = 0;
+    v4f acc[4][4];  // [16 channels][group]
+#pragma unroll
+    for (int H = 0; H < 4; ++H) {
+        off[H] = 0.0f;
+        l[H] = 0.0f;
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) acc[ct][H] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    v4f S[2][4];
+    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
+    const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
+    auto mask = [&]() {  // keys past N never receive probability mass
+        const int ln = lane_here();
+        const int first = 32 * w + 16 * ((ln >> 4) & 1) + 4 * (ln >> 5);
+#pragma unroll
+        for (int T = 0; T < 2; ++T)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int H = 0; H < 4; ++H)
+                    if (first + 8 * T + r >= nkeys) S[T][H][r] = -INFINITY;
+    };
+    // groups without a reference take their maximum in S; with `all`, those that climbed past theirs as well
+    auto reference = [&](int H, bool all) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int T = 0; T < 2; ++T)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, S[T][H][r]);
+        float ymax = c * mx;
+        const int ln = lane_here();
+        ymax = fmaxf(ymax, __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 16), __float_as_int(ymax))));
+        ymax = fmaxf(ymax, __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 32), __float_as_int(ymax))));
+        if (!(seen >> H & 1)) {
+            if (ymax > -INFINITY) {
+                off[H] = -ymax;
+                seen |= 1u << H;
+            }
+        } else if (all) {
+            const float up = fmaxf(ymax + off[H], 0.0f);
+            const float down = __builtin_amdgcn_exp2f(-up);
+            l[H] *= down;
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[ct][H][r] *= down;
+            off[H] -= up;
+        }
+    };
+    // P = 2^(c S + off) in place of S, and this lane's sums
+    float rs[4];
+    auto exponentials = [&]() {
+#pragma unroll
+        for (int H = 0; H < 4; ++H)
+#pragma unroll
+            for (int T = 0; T < 2; ++T)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) S[T][H][r] = fmaf(S[T][H][r], c, off[H]);
+#pragma unroll
+        for (int H = 0; H < 4; ++H)
+#pragma unroll
+            for (int T = 0; T < 2; ++T)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    S[T][H][r] = __builtin_amdgcn_exp2f(S[T][H][r]);
+                }
+#pragma unroll
+        for (int H = 0; H < 4; ++H)
+            rs[H] = ((S[0][H][0] + S[1][H][0]) + (S[0][H][1] + S[1][H][1])) + ((S[0][H][2] + S[1][H][2]) + (S[0][H][3] + S[1][H][3]));
+    };
     // Columns of the steps t, t + 1; behind the last step its own column is requested once more and not used: requests
     // under a condition would make the compiler wait for V_t in front of K_t's reads.
     int j0 = 0, j1 = 0;
@@ -1933,88 +2007,127 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
         request_v(j0);
         j1 = cnt > 1 ? list.at(1) : j0;
     }
+    bool open = true;  // some row has no reference yet
     __builtin_amdgcn_s_waitcnt(0x0F70);  // Q is in registers: otherwise the compiler waits for everything in every pass
-    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
-    const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
-
+    const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int t = 0; t < cnt; ++t) {
         __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4): all but the last request, V_t's, have landed
-        asm volatile("" : "+v"(kread), "+v"(vread));  // the flipped addresses are made here, not kept
+        asm volatile("" : "+v"(kread), "+v"(vread));  // the flipped address is made here, not kept
         // ---- S^T = K_j Q_i^T, 32 keys of this wavefront against 64 queries
-        v16f S[2];
+        v8bf kf[2][2];
 #pragma unroll
-        for (int H = 0; H < 2; ++H)
+        for (int T = 0; T < 2; ++T)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) S[H][r] = 0.0f;
+            for (int s = 0; s < 2; ++s) kf[T][s] = *(const v8bf*)(&kbuf[w][0] + (kread ^ (64u * s)) + 1024 * T);
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const v8bf kf = *(const v8bf*)(&kbuf[w][0] + (kread ^ (32u * s)));
+        for (int T = 0; T < 2; ++T) {
 #pragma unroll
-            for (int H = 0; H < 2; ++H) S[H] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[H][s], S[H], 0, 0, 0);
+            for (int H = 0; H < 4; ++H) S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[T][0], qf[H][0], zero, 0, 0, 0);
+#pragma unroll
+            for (int H = 0; H < 4; ++H) S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[T][1], qf[H][1], S[T][H], 0, 0, 0);
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_t has been read
         request_k(j1);
-        if (j0 == tail_block) {  // keys past N never receive probability mass
-            mask_keys(S[0], 32 * w, nkeys);
-            mask_keys(S[1], 32 * w, nkeys);
+        if (j0 == tail_block) mask();
+        if (open) {
+#pragma unroll
+            for (int H = 0; H < 4; ++H) reference(H, false);
+            open = __builtin_amdgcn_ballot_w64(seen != 15u) != 0;
         }
-        if (__builtin_amdgcn_ballot_w64(rows[0].nref == INFINITY || rows[1].nref == INFINITY) != 0) {
-            rows[0].reference(S[0], c, false);
-            rows[1].reference(S[1], c, false);
-        }
-        float rs[2];
-        rs[0] = rows[0].exponentials(S[0], c);
-        rs[1] = rows[1].exponentials(S[1], c);
-        if (__builtin_amdgcn_ballot_w64(rs[0] > kBf16SumLimit || rs[1] > kBf16SumLimit) != 0) {
+        exponentials();
+        // one compare for the lane's four queries (no sum is negative); a NaN in one of them must not hide another's climb
+        if (__builtin_amdgcn_ballot_w64(!((rs[0] + rs[1]) + (rs[2] + rs[3]) <= kBf16SumLimit)) != 0) {
             // rare: the logits once more, from K in global memory (its LDS slot is being refilled)
             const int ln = lane_here();
-            const uint8_t* kp = kbase + (size_t)j0 * TILE + 128 * (ln & 31) + 16 * (ln >> 5);
+            const int lr = 16 * ((ln >> 2) & 1) + 4 * ((ln >> 3) & 1) + (ln & 3);
+            const uint8_t* kp = kbase + (size_t)j0 * TILE + 128 * lr + 16 * (ln >> 4);
 #pragma unroll
-            for (int H = 0; H < 2; ++H) {
+            for (int T = 0; T < 2; ++T)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) S[H][r] = 0.0f;
+                for (int H = 0; H < 4; ++H) {
+                    S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const v8bf*)(kp + 1024 * T), qf[H][0], zero, 0, 0, 0);
+                    S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const v8bf*)(kp + 1024 * T + 64), qf[H][1], S[T][H], 0, 0, 0);
+                }
+            if (j0 == tail_block) mask();
 #pragma unroll
-                for (int s = 0; s < KS; ++s) S[H] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const v8bf*)(kp + 32 * s), qf[H][s], S[H], 0, 0, 0);
-                if (j0 == tail_block) mask_keys(S[H], 32 * w, nkeys);
-                rows[H].reference(S[H], c, true);
-                rs[H] = rows[H].exponentials(S[H], c);
-            }
+            for (int H = 0; H < 4; ++H) reference(H, true);
+            exponentials();
         }
         // ---- O^T += V_j^T P^T over this wavefront's keys
-        v8bf pf[2][2];
+        v8bf pf[4];
 #pragma unroll
-        for (int H = 0; H < 2; ++H) {
-            rows[H].l += rs[H];
+        for (int H = 0; H < 4; ++H) {
+            l[H] += rs[H];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) pf[H][u] = rows[H].pack(S[H], u);
+            for (int e = 0; e < 4; ++e) {
+                const v2bf pb = __builtin_convertvector(v2f{S[e >> 1][H][2 * (e & 1)], S[e >> 1][H][2 * (e & 1) + 1]}, v2bf);
+                pf[H][2 * e] = pb[0];
+                pf[H][2 * e + 1] = pb[1];
+            }
         }
         __builtin_amdgcn_s_waitcnt(0x0F74);  // V_t has landed; K_{t+1} may be on its way
+        v8bf vf[4];
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+        for (int ct = 0; ct < 4; ++ct) vf[ct] = *(const v8bf*)(&vbuf[w][0] + vread + 1024 * ct);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const v8bf vf = *(const v8bf*)(&vbuf[w][0] + 2048 * dt + (vread ^ (16u * u)));
+        for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-                for (int H = 0; H < 2; ++H) rows[H].acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[H][u], rows[H].acc[dt], 0, 0, 0);
-            }
+            for (int H = 0; H < 4; ++H) acc[ct][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ct], pf[H], acc[ct][H], 0, 0, 0);
         __builtin_amdgcn_s_waitcnt(0xC07F);  // V_t has been read
         request_v(j1);
         j0 = j1;
         if (t + 2 < cnt) j1 = list.at(t + 2);
     }
-
     // ---- wavefront w finishes the queries of half w: it hands its sums of the other half over through LDS
     __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing is in flight to the buffers any more
     __syncthreads();
     float* give = (float*)(w == 0 ? &kbuf[0][0] : &vbuf[0][0]);  // 8 KB each: [32 registers][64 lanes]
     const float* take = (const float*)(w == 0 ? &vbuf[0][0] : &kbuf[0][0]);
-    const int row = i * BLK + 32 * w + n;
-    if (w == 0) bf16_hand_over(rows[1].acc[0], rows[1].acc[1], rows[1].nref, rows[1].l, give, &meet[1][0][0], lane);
-    else bf16_hand_over(rows[0].acc[0], rows[0].acc[1], rows[0].nref, rows[0].l, give, &meet[0][0][0], lane);
+    const int ln = lane_here();  // nothing of the lane's number is kept through the loop for this
+    auto hand_over = [&](auto other) {
+        constexpr int O = decltype(other)::value;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            meet[O][u][ln] = seen >> (2 * O + u) & 1 ? off[2 * O + u] : INFINITY;
+            meet[O][2 + u][ln] = l[2 * O + u];
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) give[(16 * u + 4 * ct + r) * 64 + ln] = acc[ct][2 * O + u][r];
+        }
+    };
+    auto finish = [&](auto own) {
+        constexpr int O = decltype(own)::value;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int row = i * BLK + 32 * O + 16 * u + (ln & 15);
+            const float mine = seen >> (2 * O + u) & 1 ? off[2 * O + u] : INFINITY, other = meet[O][u][ln];
+            const float top = fminf(mine, other);  // minus the larger reference; +inf if neither saw a key
+            const float fa = mine < INFINITY ? __builtin_amdgcn_exp2f(top - mine) : 0.0f;
+            const float fb = other < INFINITY ? __builtin_amdgcn_exp2f(top - other) : 0.0f;
+            float l_tot = l[2 * O + u] * fa + meet[O][2 + u][ln] * fb;
+            l_tot += __shfl_xor(l_tot, 16);
+            l_tot += __shfl_xor(l_tot, 32);
+            const float inv = (row < a.n_tokens && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
+            const float ia = fa * inv, ib = fb * inv;
+            const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens);
+            if (ooff >= 0) {
+                OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 4);
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct) {
+                    float o[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[r] = acc[ct][2 * O + u][r] * ia + take[(16 * u + 4 * ct + r) * 64 + ln] * ib;
+                    store4(orow + 16 * ct, o[0], o[1], o[2], o[3]);
+                }
+            }
+        }
+    };
+    if (w == 0) hand_over(std::integral_constant<int, 1>{});
+    else hand_over(std::integral_constant<int, 0>{});
     __syncthreads();
-    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens);
-    if (w == 0) bf16_finish((OutT*)a.op, ooff, row < a.n_tokens, rows[0].acc[0], rows[0].acc[1], rows[0].nref, rows[0].l, take, &meet[0][0][0], lane);
-    else bf16_finish((OutT*)a.op, ooff, row < a.n_tokens, rows[1].acc[0], rows[1].acc[1], rows[1].nref, rows[1].l, take, &meet[1][0][0], lane);
+    if (w == 0) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, 1>{});
 }
 
 // d = 128: FOUR wavefronts per row block, wavefront w with the queries 32 (w & 1) .. and the keys 32 (w >> 1) .. of every

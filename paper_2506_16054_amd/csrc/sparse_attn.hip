@@ -1736,118 +1736,151 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_bf16_b32_kernel(At
 // its own sums, which meet once, at the end of the row.
 // -------------------------------------------------------------------------------------------
 
-// Running state of 32 queries over one wavefront's keys.  Lanes n and n + 32 share query n of the half and hold 16 keys
-// of a 32-key tile each (8 q + 4 g + p, as everywhere).  Exponentials are taken against the first maximum that is seen;
-// a lane whose sum of one block passes 2^64 sends the wavefront through a rare branch that moves the references to the
-// rows' maxima.  (Looking at the sum takes one compare where the row maximum took 16 operands; a logit 64 octaves above
-// the reference shows in the sum, and one that overflows the exponential shows as infinity.)
-template <int DT>
-struct Bf16Rows {
-    float nref;  // minus the reference; +inf while no real key has been seen
-    float off;   // what is added to c S: nref, or 0 while there is no reference
-    float l;     // this lane's share of the row sum
-    v16f acc[DT];
+// Running state of NG groups of 16 queries over one wavefront's 32 keys of every block, in 16 x 16 x 32 products.  Lane n + 16 G
+// holds query n of each group: in S[T], tile T of 16 keys, the four keys 4 G .. of the tile, in acc the channels 4 G .. of each 16.
+// The rows of K's tiles are chosen (bf16_krow) so that a lane's eight keys are one piece of V^T's rows, and its exponentials one
+// operand of the second product.
+// Exponentials are taken against the first maximum that is seen; a lane whose sum of one block passes 2^64 sends the wavefront
+// through a rare branch that moves the references to the rows' maxima.  (Looking at the sum takes one compare where the row maximum
+// took 16 operands; a logit 64 octaves above the reference shows in the sum, and one that overflows the exponential shows as
+// infinity.)
+__device__ __forceinline__ int bf16_krow(int n) { return 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3); }  // of tile 0; tile 1: + 8
+constexpr float kBf16SumLimit = 18446744073709551616.0f;  // 2^64
+template <int NG, int CT>
+struct Bf16Groups {
+    float off[NG];  // minus the reference, what is added to c S; 0 while there is none
+    float l[NG];    // this lane's share of the row sum
+    unsigned seen;  // bit H: group H's query has a reference (a real key has been seen)
+    v4f acc[CT][NG];
 
     __device__ __forceinline__ void init() {
-        nref = INFINITY;
-        off = 0.0f;
-        l = 0.0f;
+        seen = 0;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+        for (int H = 0; H < NG; ++H) {
+            off[H] = 0.0f;
+            l[H] = 0.0f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
-    }
-    // maximum of c S over the tile's keys, in both lanes of the query
-    static __device__ __forceinline__ float row_max(const v16f& S, float c) {
-        float part[4];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) part[r & 3] = r < 4 ? S[r] : fmaxf(part[r & 3], S[r]);
-        const float mx = c * fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(mx), __float_as_int(mx), false, false);
-        return fmaxf(__int_as_float((int)sw[0]), __int_as_float((int)sw[1]));
-    }
-    // P = 2^(c S + off) in place of S; returns this lane's sum
-    __device__ __forceinline__ float exponentials(v16f& S, float c) const {
-        float part[4];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) S[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, off));
-#pragma unroll
-        for (int r = 0; r < 16; ++r) part[r & 3] = r < 4 ? S[r] : part[r & 3] + S[r];
-        return (part[0] + part[1]) + (part[2] + part[3]);
-    }
-    // rows without a reference take their maximum in S; with `all`, rows that climbed past theirs as well
-    __device__ __forceinline__ void reference(const v16f& S, float c, bool all) {
-        const float ymax = row_max(S, c);
-        if (nref == INFINITY) {
-            if (ymax > -INFINITY) nref = -ymax;
-        } else if (all) {
-            const float up = fmaxf(ymax + nref, 0.0f);
-            const float down = __builtin_amdgcn_exp2f(-up);
-            l *= down;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[dt][r] *= down;
-            nref -= up;
+            for (int ct = 0; ct < CT; ++ct) acc[ct][H] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
         }
-        off = nref == INFINITY ? 0.0f : nref;
     }
-    static __device__ __forceinline__ v8bf pack(const v16f& P, int u) {
+    __device__ __forceinline__ bool open() const { return __builtin_amdgcn_ballot_w64(seen != (1u << NG) - 1) != 0; }
+    // keys at or past nkeys never receive probability mass; the wavefront's keys start at `first`
+    static __device__ __forceinline__ void mask(v4f (&S)[2][NG], int first, int nkeys) {
+        const int ln = lane_here();
+        first += 16 * ((ln >> 4) & 1) + 4 * (ln >> 5);
+#pragma unroll
+        for (int T = 0; T < 2; ++T)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int H = 0; H < NG; ++H)
+                    if (first + 8 * T + r >= nkeys) S[T][H][r] = -INFINITY;
+    }
+    // queries without a reference take their maximum in S; with `all`, those that climbed past theirs as well
+    __device__ __forceinline__ void reference(const v4f (&S)[2][NG], float c, bool all) {
+#pragma unroll
+        for (int H = 0; H < NG; ++H) {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int T = 0; T < 2; ++T)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mx = fmaxf(mx, S[T][H][r]);
+            float ymax = c * mx;
+            const int ln = lane_here();
+            ymax = fmaxf(ymax, __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 16), __float_as_int(ymax))));
+            ymax = fmaxf(ymax, __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 32), __float_as_int(ymax))));
+            if (!(seen >> H & 1)) {
+                if (ymax > -INFINITY) {
+                    off[H] = -ymax;
+                    seen |= 1u << H;
+                }
+            } else if (all) {
+                const float up = fmaxf(ymax + off[H], 0.0f);
+                const float down = __builtin_amdgcn_exp2f(-up);
+                l[H] *= down;
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[ct][H][r] *= down;
+                off[H] -= up;
+            }
+        }
+    }
+    // P = 2^(c S + off) in place of S, and this lane's sums.  True if some sum calls for the rare branch: one compare for the lane's
+    // queries (no sum is negative); a NaN in one of them must not hide another's climb.
+    __device__ __forceinline__ bool exponentials(v4f (&S)[2][NG], float c, float (&rs)[NG]) const {
+#pragma unroll
+        for (int H = 0; H < NG; ++H)
+#pragma unroll
+            for (int T = 0; T < 2; ++T)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) S[T][H][r] = __builtin_amdgcn_exp2f(fmaf(S[T][H][r], c, off[H]));
+        float all = 0.0f;
+#pragma unroll
+        for (int H = 0; H < NG; ++H) {
+            rs[H] = ((S[0][H][0] + S[1][H][0]) + (S[0][H][1] + S[1][H][1])) + ((S[0][H][2] + S[1][H][2]) + (S[0][H][3] + S[1][H][3]));
+            all = H ? all + rs[H] : rs[H];
+        }
+        return __builtin_amdgcn_ballot_w64(!(all <= kBf16SumLimit)) != 0;
+    }
+    __device__ __forceinline__ void add(const float (&rs)[NG]) {
+#pragma unroll
+        for (int H = 0; H < NG; ++H) l[H] += rs[H];
+    }
+    static __device__ __forceinline__ v8bf pack(const v4f (&S)[2][NG], int H) {
         v8bf f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const v2bf pb = __builtin_convertvector(v2f{P[8 * u + 2 * e], P[8 * u + 2 * e + 1]}, v2bf);
+            const v2bf pb = __builtin_convertvector(v2f{S[e >> 1][H][2 * (e & 1)], S[e >> 1][H][2 * (e & 1) + 1]}, v2bf);
             f[2 * e] = pb[0];
             f[2 * e + 1] = pb[1];
         }
         return f;
     }
-};
-constexpr float kBf16SumLimit = 18446744073709551616.0f;  // 2^64
-
-__device__ __forceinline__ void mask_keys(v16f& S, int first, int nkeys) {  // keys first + .. of the tile at or past nkeys
-    const int g = lane_here() >> 5;
+    // The end of a row: the sums of 64 channels of two groups (from group H0 and channel tile C0), with their references and row
+    // sums, handed to another wavefront ...
+    template <int H0, int C0>
+    __device__ __forceinline__ void hand_over(float* tiles, float (*row)[64], int ln) const {
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-        if (first + 8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) S[r] = -INFINITY;
-}
-
-// Two accumulator tiles (64 channels of 32 queries) with their reference and row sum, handed to another wavefront.
-__device__ __forceinline__ void bf16_hand_over(const v16f& t0, const v16f& t1, float nref, float l, float* tiles, float* row, int lane) {
-    row[lane] = nref;
-    row[64 + lane] = l;
+        for (int u = 0; u < 2; ++u) {
+            row[u][ln] = seen >> (H0 + u) & 1 ? off[H0 + u] : INFINITY;
+            row[2 + u][ln] = l[H0 + u];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        tiles[e * 64 + lane] = t0[e];
-        tiles[(16 + e) * 64 + lane] = t1[e];
+            for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) tiles[(16 * u + 4 * ct + r) * 64 + ln] = acc[C0 + ct][H0 + u][r];
+        }
     }
-}
-// ... and joined with this wavefront's own two, normalised and stored.
-template <typename OutT>
-__device__ __forceinline__ void bf16_finish(OutT* op, long long ooff, bool row_valid, const v16f& t0, const v16f& t1, float nref, float l,
-                                            const float* tiles, const float* row, int lane) {
-    const float other_nref = row[lane], other_l = row[64 + lane];
-    const float top = fminf(nref, other_nref);  // minus the larger reference; +inf if neither saw a key
-    const float fa = nref < INFINITY ? __builtin_amdgcn_exp2f(top - nref) : 0.0f;
-    const float fb = other_nref < INFINITY ? __builtin_amdgcn_exp2f(top - other_nref) : 0.0f;
-    float l_tot = l * fa + other_l * fb;
-    l_tot += __shfl_xor(l_tot, 32);
-    const float inv = (row_valid && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
-    const float ia = fa * inv, ib = fb * inv;
-    if (ooff >= 0) {
-        OutT* orow = op + ooff + 4 * (lane >> 5);
+    // ... and joined there with its own, normalised and stored.  row0: the row (of the block's matrix) of query 0 of group H0;
+    // offset(row): of its first channel in op, negative if it is not stored.
+    template <int H0, int C0, typename OutT, typename Offset>
+    __device__ __forceinline__ void finish(OutT* op, Offset offset, int row0, int n_tokens, const float* tiles, const float (*meet)[64], int ln) const {
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
+        for (int u = 0; u < 2; ++u) {
+            const int row = row0 + 16 * u + (ln & 15);
+            const float mine = seen >> (H0 + u) & 1 ? off[H0 + u] : INFINITY, other = meet[u][ln];
+            const float top = fminf(mine, other);  // minus the larger reference; +inf if neither saw a key
+            const float fa = mine < INFINITY ? __builtin_amdgcn_exp2f(top - mine) : 0.0f;
+            const float fb = other < INFINITY ? __builtin_amdgcn_exp2f(top - other) : 0.0f;
+            float l_tot = l[H0 + u] * fa + meet[2 + u][ln] * fb;
+            l_tot += __shfl_xor(l_tot, 16);
+            l_tot += __shfl_xor(l_tot, 32);
+            const float inv = (row < n_tokens && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
+            const float ia = fa * inv, ib = fb * inv;
+            const long long ooff = offset(row);
+            if (ooff >= 0) {
+                OutT* orow = op + ooff + 16 * C0 + 4 * (ln >> 4);
 #pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                float o[4];
+                for (int ct = 0; ct < 4; ++ct) {
+                    float o[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    o[e] = (dt ? t1 : t0)[4 * qd + e] * ia + tiles[(16 * dt + 4 * qd + e) * 64 + lane] * ib;
-                store4(orow + 32 * dt + 8 * qd, o[0], o[1], o[2], o[3]);
+                    for (int r = 0; r < 4; ++r) o[r] = acc[C0 + ct][H0 + u][r] * ia + tiles[(16 * u + 4 * ct + r) * 64 + ln] * ib;
+                    store4(orow + 16 * ct, o[0], o[1], o[2], o[3]);
+                }
             }
+        }
     }
-}
+};
 
 // d = 64: TWO wavefronts per row block, each with all 64 queries and one half of the keys, so that every byte of K and V
 // is read from LDS once per row block (four wavefronts of 16 queries read it four times: 64 KB of reads and 16 KB of
@@ -1856,10 +1889,8 @@ __device__ __forceinline__ void bf16_finish(OutT* op, long long ooff, bool row_v
 // requested behind the reads of K_t, V_{t+1} behind those of V_t.
 // What bounds it is power: under this load the card stands at its limit (1.4 kW) and lowers its clock to 1.64 GHz, so time
 // follows the energy of a block, of which the products are nearly half.  Hence the 16 x 16 x 32 form of the products: 7.2 nJ
-// for half the work of a 32 x 32 x 16 one, which takes 16.7.  A lane holds 4 keys of each 16-key tile against one query of
-// each of four groups; the keys of a tile are chosen (krow) so that the 8 exponentials of a lane and group are one operand of
-// the second product in the order that V^T is stored in.  48 heads of 17550 tokens at 30 % density, quantizer included:
-// 1419 -> 1334 us (with 32 x 32 x 16 products before).  K and V straight to registers, without LDS and with two wavefronts
+// for half the work of a 32 x 32 x 16 one, which takes 16.7.  48 heads of 17550 tokens at 30 % density, quantizer included:
+// 1423 -> 1355 us (with 32 x 32 x 16 products before).  K and V straight to registers, without LDS and with two wavefronts
 // per SIMD instead of three: 2080 us.
 template <typename OutT>
 __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
@@ -1899,9 +1930,7 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) qf[H][s] = *(const v8bf*)(qrow + 64 * s);
     }
-    // Row n of K's tile T is key 16 (n / 4 % 2) + 8 T + 4 (n / 8) + n % 4 of the half: lane group G then holds, of both tiles, the 8
-    // keys of V^T's piece G.
-    const int krow = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
+    const int krow = bf16_krow(n);
     // K half: 32 rows of 128 bytes, piece p of row r at position p ^ (r % 4 + 4 (r / 16)), different for the eight rows that
     // neighbouring lanes read.  V^T half: 64 rows of 64 bytes, piece p of row r at position p ^ (r / 2) % 4.
     unsigned kfill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ ((lane >> 3) & 3));
@@ -1924,80 +1953,11 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
         lds_dma16<0>(vp + 4096, vfill, &vbuf[w][2048]);
         lds_dma16<2048>(vp + 4096, vfill, &vbuf[w][3072]);
     };
-    // Running state of query n of each group over this wavefront's keys, as in Bf16Rows; a group without a reference has its bit
-    // clear in `seen` and offset 0.
-    float off[4], l[4];
-    unsigned seen = 0;
-    v4f acc[4][4];  // [16 channels][group]
-#pragma unroll
-    for (int H = 0; H < 4; ++H) {
-        off[H] = 0.0f;
-        l[H] = 0.0f;
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) acc[ct][H] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    }
+    Bf16Groups<4, 4> rows;
+    rows.init();
     v4f S[2][4];
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
     const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
-    auto mask = [&]() {  // keys past N never receive probability mass
-        const int ln = lane_here();
-        const int first = 32 * w + 16 * ((ln >> 4) & 1) + 4 * (ln >> 5);
-#pragma unroll
-        for (int T = 0; T < 2; ++T)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int H = 0; H < 4; ++H)
-                    if (first + 8 * T + r >= nkeys) S[T][H][r] = -INFINITY;
-    };
-    // groups without a reference take their maximum in S; with `all`, those that climbed past theirs as well
-    auto reference = [&](int H, bool all) {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int T = 0; T < 2; ++T)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, S[T][H][r]);
-        float ymax = c * mx;
-        const int ln = lane_here();
-        ymax = fmaxf(ymax, __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 16), __float_as_int(ymax))));
-        ymax = fmaxf(ymax, __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (ln ^ 32), __float_as_int(ymax))));
-        if (!(seen >> H & 1)) {
-            if (ymax > -INFINITY) {
-                off[H] = -ymax;
-                seen |= 1u << H;
-            }
-        } else if (all) {
-            const float up = fmaxf(ymax + off[H], 0.0f);
-            const float down = __builtin_amdgcn_exp2f(-up);
-            l[H] *= down;
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[ct][H][r] *= down;
-            off[H] -= up;
-        }
-    };
-    // P = 2^(c S + off) in place of S, and this lane's sums
-    float rs[4];
-    auto exponentials = [&]() {
-#pragma unroll
-        for (int H = 0; H < 4; ++H)
-#pragma unroll
-            for (int T = 0; T < 2; ++T)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) S[T][H][r] = fmaf(S[T][H][r], c, off[H]);
-#pragma unroll
-        for (int H = 0; H < 4; ++H)
-#pragma unroll
-            for (int T = 0; T < 2; ++T)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    S[T][H][r] = __builtin_amdgcn_exp2f(S[T][H][r]);
-                }
-#pragma unroll
-        for (int H = 0; H < 4; ++H)
-            rs[H] = ((S[0][H][0] + S[1][H][0]) + (S[0][H][1] + S[1][H][1])) + ((S[0][H][2] + S[1][H][2]) + (S[0][H][3] + S[1][H][3]));
-    };
     // Columns of the steps t, t + 1; behind the last step its own column is requested once more and not used: requests
     // under a condition would make the compiler wait for V_t in front of K_t's reads.
     int j0 = 0, j1 = 0;
@@ -2028,19 +1988,16 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_t has been read
         request_k(j1);
-        if (j0 == tail_block) mask();
+        if (j0 == tail_block) rows.mask(S, 32 * w, nkeys);
         if (open) {
-#pragma unroll
-            for (int H = 0; H < 4; ++H) reference(H, false);
-            open = __builtin_amdgcn_ballot_w64(seen != 15u) != 0;
+            rows.reference(S, c, false);
+            open = rows.open();
         }
-        exponentials();
-        // one compare for the lane's four queries (no sum is negative); a NaN in one of them must not hide another's climb
-        if (__builtin_amdgcn_ballot_w64(!((rs[0] + rs[1]) + (rs[2] + rs[3]) <= kBf16SumLimit)) != 0) {
+        float rs[4];
+        if (rows.exponentials(S, c, rs)) {
             // rare: the logits once more, from K in global memory (its LDS slot is being refilled)
             const int ln = lane_here();
-            const int lr = 16 * ((ln >> 2) & 1) + 4 * ((ln >> 3) & 1) + (ln & 3);
-            const uint8_t* kp = kbase + (size_t)j0 * TILE + 128 * lr + 16 * (ln >> 4);
+            const uint8_t* kp = kbase + (size_t)j0 * TILE + 128 * bf16_krow(ln & 15) + 16 * (ln >> 4);
 #pragma unroll
             for (int T = 0; T < 2; ++T)
 #pragma unroll
@@ -2048,23 +2005,15 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
                     S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const v8bf*)(kp + 1024 * T), qf[H][0], zero, 0, 0, 0);
                     S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const v8bf*)(kp + 1024 * T + 64), qf[H][1], S[T][H], 0, 0, 0);
                 }
-            if (j0 == tail_block) mask();
-#pragma unroll
-            for (int H = 0; H < 4; ++H) reference(H, true);
-            exponentials();
+            if (j0 == tail_block) rows.mask(S, 32 * w, nkeys);
+            rows.reference(S, c, true);
+            rows.exponentials(S, c, rs);
         }
         // ---- O^T += V_j^T P^T over this wavefront's keys
+        rows.add(rs);
         v8bf pf[4];
 #pragma unroll
-        for (int H = 0; H < 4; ++H) {
-            l[H] += rs[H];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const v2bf pb = __builtin_convertvector(v2f{S[e >> 1][H][2 * (e & 1)], S[e >> 1][H][2 * (e & 1) + 1]}, v2bf);
-                pf[H][2 * e] = pb[0];
-                pf[H][2 * e + 1] = pb[1];
-            }
-        }
+        for (int H = 0; H < 4; ++H) pf[H] = rows.pack(S, H);
         __builtin_amdgcn_s_waitcnt(0x0F74);  // V_t has landed; K_{t+1} may be on its way
         v8bf vf[4];
 #pragma unroll
@@ -2072,7 +2021,7 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-            for (int H = 0; H < 4; ++H) acc[ct][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ct], pf[H], acc[ct][H], 0, 0, 0);
+            for (int H = 0; H < 4; ++H) rows.acc[ct][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ct], pf[H], rows.acc[ct][H], 0, 0, 0);
         __builtin_amdgcn_s_waitcnt(0xC07F);  // V_t has been read
         request_v(j1);
         j0 = j1;
@@ -2084,50 +2033,12 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     float* give = (float*)(w == 0 ? &kbuf[0][0] : &vbuf[0][0]);  // 8 KB each: [32 registers][64 lanes]
     const float* take = (const float*)(w == 0 ? &vbuf[0][0] : &kbuf[0][0]);
     const int ln = lane_here();  // nothing of the lane's number is kept through the loop for this
-    auto hand_over = [&](auto other) {
-        constexpr int O = decltype(other)::value;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            meet[O][u][ln] = seen >> (2 * O + u) & 1 ? off[2 * O + u] : INFINITY;
-            meet[O][2 + u][ln] = l[2 * O + u];
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) give[(16 * u + 4 * ct + r) * 64 + ln] = acc[ct][2 * O + u][r];
-        }
-    };
-    auto finish = [&](auto own) {
-        constexpr int O = decltype(own)::value;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int row = i * BLK + 32 * O + 16 * u + (ln & 15);
-            const float mine = seen >> (2 * O + u) & 1 ? off[2 * O + u] : INFINITY, other = meet[O][u][ln];
-            const float top = fminf(mine, other);  // minus the larger reference; +inf if neither saw a key
-            const float fa = mine < INFINITY ? __builtin_amdgcn_exp2f(top - mine) : 0.0f;
-            const float fb = other < INFINITY ? __builtin_amdgcn_exp2f(top - other) : 0.0f;
-            float l_tot = l[2 * O + u] * fa + meet[O][2 + u][ln] * fb;
-            l_tot += __shfl_xor(l_tot, 16);
-            l_tot += __shfl_xor(l_tot, 32);
-            const float inv = (row < a.n_tokens && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
-            const float ia = fa * inv, ib = fb * inv;
-            const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens);
-            if (ooff >= 0) {
-                OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 4);
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) {
-                    float o[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) o[r] = acc[ct][2 * O + u][r] * ia + take[(16 * u + 4 * ct + r) * 64 + ln] * ib;
-                    store4(orow + 16 * ct, o[0], o[1], o[2], o[3]);
-                }
-            }
-        }
-    };
-    if (w == 0) hand_over(std::integral_constant<int, 1>{});
-    else hand_over(std::integral_constant<int, 0>{});
+    auto offset = [&](int row) { return out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens); };
+    if (w == 0) rows.template hand_over<2, 0>(give, meet[1], ln);
+    else rows.template hand_over<0, 0>(give, meet[0], ln);
     __syncthreads();
-    if (w == 0) finish(std::integral_constant<int, 0>{});
-    else finish(std::integral_constant<int, 1>{});
+    if (w == 0) rows.template finish<0, 0>((OutT*)a.op, offset, i * BLK, a.n_tokens, take, meet[0], ln);
+    else rows.template finish<2, 0>((OutT*)a.op, offset, i * BLK + 32, a.n_tokens, take, meet[1], ln);
 }
 
 // d = 128: FOUR wavefronts per row block, wavefront w with the queries 32 (w & 1) .. and the keys 32 (w >> 1) .. of every
@@ -2137,15 +2048,16 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
 // Two barriers per block: V_t is requested behind the first (V_{t-1} has been read by all, K_t is whole) and K_{t+1}
 // behind the second (K_t has been read by all, V_t is whole), so each has half a block of work to hide behind.
 // 24 heads of 4096 + 512 tokens at 30 % density, two layers with quantizer and mask prefetch: 419 -> 387 us (runs of one
-// side differ by 0.3 %; 406 -> 377 and 470 -> 411 elsewhere).
+// side differ by 0.3 %; 406 -> 377 and 470 -> 411 elsewhere).  In 16 x 16 x 32 products, 393 -> 349 us: a lane's logits are four
+// chains of four products, not one chain of eight that each wait for the one before, and they take less energy.
 template <typename OutT>
 __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
     constexpr int BLK = 64, D = 128;
     constexpr int TILE = BLK * D * 2;
-    constexpr int KS = D / 16, DT = D / 32;
+    constexpr int KS = D / 32, CT = D / 16;
     __shared__ __attribute__((aligned(16))) uint8_t kbuf[TILE];  // later half of the exchange buffer
     __shared__ __attribute__((aligned(16))) uint8_t vbuf[TILE];
-    __shared__ float meet[4][2][64];  // [wavefront][reference, sum][lane]
+    __shared__ float meet[4][4][64];  // [wavefront][2 references, 2 sums][lane]
 
     const int wg = blockIdx.x;
     const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
@@ -2157,8 +2069,8 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kh = w >> 1;
-    const int n = lane & 31;
-    const int g = lane >> 5;
+    const int n = lane & 15;
+    const int G = lane >> 4;
 
     const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
     const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
@@ -2171,25 +2083,28 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
     const uint8_t* kbase = a.k + head_rows * D * 2 + 4096 * w;  // rows 16 w .. of a K tile
     const uint8_t* vbase = a.v + head_rows * D * 2 + 4096 * w;  // rows 32 w .. of a V^T tile
     const float c = a.qk_scale;
-    const int row = i * BLK + 32 * (w & 1) + n;
-    v8bf qf[KS];
-    {
-        const uint8_t* qrow = a.q + (head_rows + row) * D * 2 + 16 * g;
+    const int row0 = i * BLK + 32 * (w & 1);
+    v8bf qf[2][KS];  // [group of 16 queries][32 channels]
 #pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s] = *(const v8bf*)(qrow + 32 * s);
+    for (int H = 0; H < 2; ++H) {
+        const uint8_t* qrow = a.q + (head_rows + row0 + 16 * H + n) * D * 2 + 16 * G;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qf[H][s] = *(const v8bf*)(qrow + 64 * s);
     }
-    // K rows have two 128-byte lines, V^T rows one; piece p of a line of row r sits at position p ^ r % 8 of the line
-    unsigned kfill = 256u * (lane >> 4) + 16u * ((lane & 8) | ((lane ^ (lane >> 4)) & 7));  // rows 0 .. 3 of eight; 4 .. 7: bit 6 flipped
+    // K rows have two 128-byte lines, V^T rows one; piece p of a line sits at position p ^ (r % 4 + 4 (r / 16 % 2)) for row r of K and
+    // p ^ r % 8 for row r of V^T, different for the eight rows that neighbouring lanes read
+    const int krow = bf16_krow(n);
+    const unsigned kfill = 256u * (lane >> 4) + 16u * ((lane & 8) | ((lane & 7) ^ ((lane >> 4) | 4 * (w & 1))));
     const unsigned vfill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
-    unsigned kread = 256u * (32 * kh + n) + 16u * (g ^ (n & 7));               // fragment s: piece 2 s + g
-    unsigned vread = 128u * n + 16u * ((4 * kh + 2 * g) ^ (n & 7));            // fragment u: piece 4 kh + 2 g + u
+    unsigned kread = 256u * (32 * kh + krow) + 16u * (G ^ ((krow & 3) | ((krow >> 2) & 4)));  // 32 channels s: piece 4 s + G
+    const unsigned vread = 128u * n + 16u * ((4 * kh + G) ^ (n & 7));                         // piece 4 kh + G
     auto request_k = [&](int j) {
         const uint8_t* kp = kbase + (size_t)j * TILE;
-        asm volatile("" : "+s"(kp), "+v"(kfill));
+        asm volatile("" : "+s"(kp));
         lds_dma16<0>(kp, kfill, &kbuf[4096 * w]);
-        lds_dma16<1024>(kp, kfill ^ 64u, &kbuf[4096 * w + 1024]);
+        lds_dma16<1024>(kp, kfill, &kbuf[4096 * w + 1024]);
         lds_dma16<2048>(kp, kfill, &kbuf[4096 * w + 2048]);
-        lds_dma16<3072>(kp, kfill ^ 64u, &kbuf[4096 * w + 3072]);
+        lds_dma16<3072>(kp, kfill, &kbuf[4096 * w + 3072]);
     };
     auto request_v = [&](int j) {
         const uint8_t* vp = vbase + (size_t)j * TILE;
@@ -2202,8 +2117,10 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
     const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
 
-    Bf16Rows<DT> rows;
+    Bf16Groups<2, CT> rows;
     rows.init();
+    bool open = true;  // some row has no reference yet
+    const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
     int j0 = 0, j1 = 0;  // columns of the steps t, t + 1
     if (cnt > 0) {
         j0 = list.at(0);
@@ -2215,46 +2132,51 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's part of K_t has landed
         __syncthreads();                     // and everybody's; V_{t-1} has been read by all
         request_v(j0);
-        asm volatile("" : "+v"(kread), "+v"(vread));  // the flipped addresses are made here, not kept
+        asm volatile("" : "+v"(kread));  // the flipped address is made here, not kept
         // ---- S^T = K_j Q_i^T, this wavefront's 32 keys against its 32 queries
-        v16f S;
+        v4f S[2][2];
         auto logits = [&]() {
+            v8bf kf[2][KS];  // all requested before the first product: each would otherwise wait out its own latency
 #pragma unroll
-            for (int r = 0; r < 16; ++r) S[r] = 0.0f;
-            v8bf kf[KS];  // all requested before the first product: each would otherwise wait out its own latency
+            for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int s = 0; s < KS; ++s) kf[s] = *(const v8bf*)(kbuf + (kread ^ (32u * (s & 3))) + 128 * (s >> 2));
+                for (int T = 0; T < 2; ++T) kf[T][s] = *(const v8bf*)(kbuf + (kread ^ (64u * (s & 1))) + 128 * (s >> 1) + 2048 * T);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s = 0; s < KS; ++s) S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], S, 0, 0, 0);
-            if (j0 == tail_block) mask_keys(S, 32 * kh, nkeys);  // keys past N never receive probability mass
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int T = 0; T < 2; ++T)
+#pragma unroll
+                    for (int H = 0; H < 2; ++H) S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[T][s], qf[H][s], s ? S[T][H] : zero, 0, 0, 0);
+            if (j0 == tail_block) rows.mask(S, 32 * kh, nkeys);
         };
         logits();
-        if (__builtin_amdgcn_ballot_w64(rows.nref == INFINITY) != 0) rows.reference(S, c, false);
-        float rs = rows.exponentials(S, c);
-        if (__builtin_amdgcn_ballot_w64(rs > kBf16SumLimit) != 0) {  // rare
+        if (open) {
+            rows.reference(S, c, false);
+            open = rows.open();
+        }
+        float rs[2];
+        if (rows.exponentials(S, c, rs)) {  // rare
             logits();
             rows.reference(S, c, true);
-            rs = rows.exponentials(S, c);
+            rows.exponentials(S, c, rs);
         }
-        rows.l += rs;
+        rows.add(rs);
         v8bf pf[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) pf[u] = rows.pack(S, u);
+        for (int H = 0; H < 2; ++H) pf[H] = rows.pack(S, H);
         __builtin_amdgcn_s_waitcnt(0x0F70);  // this wavefront's part of V_t has landed
         __syncthreads();                     // and everybody's; K_t has been read by all
         if (t + 1 < cnt) request_k(j1);
         // ---- O^T += V_j^T P^T over this wavefront's keys
-        v8bf vf[DT][2];
+        v8bf vf[CT];
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) vf[dt][u] = *(const v8bf*)(vbuf + 4096 * dt + (vread ^ (16u * u)));
+        for (int ct = 0; ct < CT; ++ct) vf[ct] = *(const v8bf*)(vbuf + 2048 * ct + vread);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) rows.acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][u], pf[u], rows.acc[dt], 0, 0, 0);
+            for (int H = 0; H < 2; ++H) rows.acc[ct][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[ct], pf[H], rows.acc[ct][H], 0, 0, 0);
         j0 = j1;
         if (t + 2 < cnt) j1 = list.at(t + 2);
     }
@@ -2263,12 +2185,13 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
     __syncthreads();
     float* give = (float*)((w & 1 ? vbuf : kbuf) + 8192 * kh);  // 8 KB each: [32 registers][64 lanes]
     const float* take = (const float*)((w & 1 ? vbuf : kbuf) + 8192 * (kh ^ 1));
-    if (kh == 0) bf16_hand_over(rows.acc[2], rows.acc[3], rows.nref, rows.l, give, &meet[w][0][0], lane);
-    else bf16_hand_over(rows.acc[0], rows.acc[1], rows.nref, rows.l, give, &meet[w][0][0], lane);
+    const int ln = lane_here();  // nothing of the lane's number is kept through the loop for this
+    auto offset = [&](int row) { return out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens); };
+    if (kh == 0) rows.template hand_over<0, 4>(give, meet[w], ln);
+    else rows.template hand_over<0, 0>(give, meet[w], ln);
     __syncthreads();
-    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens);
-    if (kh == 0) bf16_finish((OutT*)a.op, ooff, row < a.n_tokens, rows.acc[0], rows.acc[1], rows.nref, rows.l, take, &meet[w ^ 2][0][0], lane);
-    else bf16_finish((OutT*)a.op + 64, ooff, row < a.n_tokens, rows.acc[2], rows.acc[3], rows.nref, rows.l, take, &meet[w ^ 2][0][0], lane);
+    if (kh == 0) rows.template finish<0, 0>((OutT*)a.op, offset, row0, a.n_tokens, take, meet[w ^ 2], ln);
+    else rows.template finish<0, 4>((OutT*)a.op, offset, row0, a.n_tokens, take, meet[w ^ 2], ln);
 }
 
 template <typename OutT>

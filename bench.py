@@ -6,7 +6,7 @@ One "step" is one pass of the whole hot path over one batch of synthetic input t
 resident in HBM: reorder Q, K, V -> block quantize -> block-sparse INT8 attention -> inverse
 reorder, in the fused form (the reorder rides on the quantizer's loads and on the attention
 kernel's stores; Q, K and V are quantized by one launch: two launches per step).  The block list of the static mask is built once, outside
-the timed region, as the method does offline.  The same path as five separate steps is timed
+the timed region, as the method does offline.  The same path with its intermediates stored (reorder and quantize, attend, inverse reorder) is timed
 afterwards for reference (`separate_steps_ms`).  Prints ONE JSON line.  The headline workload is the CogVideoX-5B-shaped
 layer: 48 heads, N = 17550, d = 64, 30 % density, INT8 QK^T and INT8 PV.
 """

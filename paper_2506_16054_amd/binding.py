@@ -1,5 +1,5 @@
-"""Thin ctypes binding over libparo.so: same names as the C ABI (include/paro.h), argument
-marshalling only.  Device tensors are torch tensors (device memory + the current HIP stream);
+"""Thin binding over libparo.so: same names as the C ABI (include/paro.h), argument marshalling only
+(ctypes, and a native module for the calls that run once per layer).  Device tensors are torch tensors (device memory + the current HIP stream);
 every step of the path runs inside the library's kernels.
 
 The library is loaded on first use and the binding fails loudly if it has not been built

@@ -71,7 +71,7 @@ class ParoAttention:
         return self.o
 
     def run(self, q, k, v):
-        """The path as five separate steps (reorder, quantize, attention, inverse reorder)."""
+        """The path with its intermediates kept: reorder and quantize (one launch where prepare() can), attention, inverse reorder."""
         self.prepare(q, k, v)
         self.attend()
         return self.finish()

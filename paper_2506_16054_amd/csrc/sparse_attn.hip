@@ -1887,7 +1887,7 @@ struct Bf16Groups {
 // writes per block, 640 of the 777 cycles a block took).  A wavefront's half tiles are its own: it moves them to
 // LDS itself (global_load_lds, 4 KB of K and 4 KB of V, one slot each) and there is no barrier in the loop.  K_{t+1} is
 // requested behind the reads of K_t, V_{t+1} behind those of V_t.
-// What bounds it is power: under this load the card stands at its limit (1.4 kW) and lowers its clock to 1.64 GHz, so time
+// What bounds it is power: under this load the card stands at its limit (1.4 kW) and lowers its clock to 1.7 GHz, so time
 // follows the energy of a block, of which the products are nearly half.  Hence the 16 x 16 x 32 form of the products: 7.2 nJ
 // for half the work of a 32 x 32 x 16 one, which takes 16.7.  48 heads of 17550 tokens at 30 % density, quantizer included:
 // 1423 -> 1355 us (with 32 x 32 x 16 products before).  K and V straight to registers, without LDS and with two wavefronts

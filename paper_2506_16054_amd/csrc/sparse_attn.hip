@@ -714,6 +714,21 @@ __device__ inline v16i acc_start() {
     return x;
 }
 __device__ inline float start_result(int raw) { return fmaf(__int_as_float(raw), 0x1p26f, -kStartI); }  // exact
+// The offset of the folded exponent, off_n - c_up * kStartF rounded once, and by how much it lies above the exact value (to the last
+// place of off_n).  Written out, because left to the compiler it was one fma in one half and the rounded difference of the rounded
+// product in the other one, and kStartI has 24 significant bits: the product is rounded no less than the difference.  A contracted
+// step of the two-sum would count the product's residue twice.  Error against the float64 oracle, fp32 outputs of 8-bit codes: 48
+// heads of 17550 tokens at 30 % 3.44e-4 -> 3.23e-4, 30 heads at 50 % 3.42e-4 -> 3.31e-4 (with one rounding and attn_i8_kernel's start
+// value 3.27e-4 and 3.24e-4; samples differ by some 2 %), 4-bit Q and K 3.46e-4 -> 3.30e-4 (3.85e-4); 1078 -> 1082 us.
+__device__ __forceinline__ float folded_offset(float off_n, float c_up, float& above) {
+#pragma clang fp contract(off)
+    const float off = fmaf(-c_up, kStartF, off_n);
+    const float cb_hi = c_up * kStartF;
+    const float cb_lo = fmaf(c_up, kStartF, -cb_hi);
+    const float bb = off - off_n;
+    above = cb_lo - ((off_n - (off - bb)) + (-cb_hi - bb));
+    return off;
+}
 // Ends a basic block without an instruction.  The compiler names the constant above in the instruction only where a
 // basic block uses it once; two chains that start in one block would get it in 16 registers.
 __device__ __forceinline__ void end_basic_block() {
@@ -1079,20 +1094,14 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
         const float sv_now = sv_cur * (PVBITS == 4 ? acc_down * 0.0625f : acc_down);
         float off_f[2], w_blk[2];
         const float c_up = c * 0x1p26f;
-        float cb_hi = 0.0f, cb_lo = 0.0f;
-        if constexpr (MODE == kFold) {
-            cb_hi = c_up * kStartF;
-            cb_lo = fmaf(c_up, kStartF, -cb_hi);
-        }
 #pragma unroll
         for (int H = 0; H < 2; ++H) {
             const float off_n = (LOG2_QMAXP - kLog2_65535) - m[H] - e;
             off_f[H] = off_n;
             if constexpr (MODE == kFold) {
-                off_f[H] = off_n - cb_hi;
-                const float bb = off_f[H] - off_n;
-                const float terr = (off_n - (off_f[H] - bb)) + (-cb_hi - bb);
-                w_blk[H] = __builtin_amdgcn_exp2f(((-kLog2_65535 - m_ref[H]) - off_n) - (cb_lo - terr));
+                float above;
+                off_f[H] = folded_offset(off_n, c_up, above);
+                w_blk[H] = __builtin_amdgcn_exp2f(((-kLog2_65535 - m_ref[H]) - off_n) - above);
             } else {
                 w_blk[H] = __builtin_amdgcn_exp2f((-kLog2_65535 - m_ref[H]) - off_n);
             }

@@ -164,6 +164,11 @@ constexpr int kAccBiasI = 0x4B400000;
 constexpr float kAccBiasF = 12582912.0f;
 __device__ inline float int_result(int raw) { return __int_as_float(raw) - kAccBiasF; }
 
+// Smallest scale of a block of logits that may meet the -inf of a masked key: scales of Q and K that are both of some 2^-75 have a product
+// of 0, and 0 times -inf is NaN.  Rows whose scale in the ragged block is below it take the exact form of the exponent, which
+// raises the scale to it: |c S| <= 2^-126 * 2^21 changes no bit of an exponent of -9 or below.
+constexpr float kLogitScaleMin = 0x1p-126f;
+
 // The scale of a column block is the same for every lane and is written by the quantizer before this kernel
 // starts: read through the constant address space it becomes a scalar load, needs no vector register while it is
 // carried from one block to the next, and enters its one multiplication as a scalar operand.  Used by the kernel
@@ -785,6 +790,7 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
     const unsigned klane = n * (D / KPACK) + 16 * g;     // this lane's K fragment of key tile 0, step 0, inside a block
     const unsigned vlane = n * (BLK / VPACK) + 16 / VPACK * g;  // its V^T fragment of channel tile 0, key tile 0
     const float* skp = a.sk + (size_t)bh * a.kblocks;
+    const float sk_last = uniform_load(skp + a.kblocks - 1);  // asked for here, used below
     const float* svp = a.sv + (size_t)bh * a.kblocks;
     float sq_i;
     int row[2];
@@ -981,6 +987,7 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
         fast = FOLDABLE ? sq_i * sk_max * kAccBiasF < 8192.0f : sq_i * sk_max < 0x1p90f;
     }
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;  // the column block with padded keys, if any
+    if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fast = false;
 
     v16i S0[2], Sa[2], Sb[2];  // raw logits [key tile]: of half 0; of half 1, this block's and the next one's in turn
     v4i pf1[2] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
@@ -1089,7 +1096,8 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
     // one live block; S1 and N1: the raw logits of half 1, this block's and the next one's
     auto step = [&](auto mode_tag, int t, v16i (&S1)[2], v16i (&N1)[2]) {
         constexpr int MODE = decltype(mode_tag)::value;
-        const float c = sq_i * sk_cur;
+        float c = sq_i * sk_cur;
+        if (MODE == kExact && c < kLogitScaleMin) c = kLogitScaleMin;
         v16i o[2];
         const float sv_now = sv_cur * (PVBITS == 4 ? acc_down * 0.0625f : acc_down);
         float off_f[2], w_blk[2];
@@ -1299,6 +1307,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_q16_kernel(AttnArgs a) {
     const uint8_t* kbase = a.k + head_rows * D;
     const uint8_t* vbase = a.v + head_rows * D;
     const float* skp = a.sk + (size_t)bh * a.kblocks;
+    const float sk_last = uniform_load(skp + a.kblocks - 1);  // asked for here, used below
     const float* svp = a.sv + (size_t)bh * a.kblocks;
     const float sq_i = a.sq[(size_t)bh * a.kblocks + i] * a.qk_scale;
     const int row = i * BLK + 16 * w + n;  // this lane's query, in the reordered sequence
@@ -1389,10 +1398,12 @@ __global__ __launch_bounds__(256, 3) void attn_i8_q16_kernel(AttnArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;  // the column block with padded keys, if any
+    if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fold = false;
 
     auto step = [&](auto fold_tag, int t) {
         constexpr bool FOLD = decltype(fold_tag)::value;
-        const float c = sq_i * sk0;
+        float c = sq_i * sk0;
+        if (!FOLD && c < kLogitScaleMin) c = kLogitScaleMin;
         const float sv_now = sv0;
         const uint8_t* kslot = &kring[t & 1][0];
         const uint8_t* vslot = &vring[t & 1][0];
@@ -1407,7 +1418,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_q16_kernel(AttnArgs a) {
             for (int s = 0; s < KS; ++s)
                 sacc[T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(*(const v4i*)(kslot + 1024 * T + kread[s]), qf[s], sacc[T], 0, 0, 0);
         }
-        if (j0 == tail_block) {  // keys past N: the bit pattern of -inf loses every maximum and gives E = 0
+        if (j0 == tail_block) {  // keys past N: the bit pattern of -inf loses every maximum and gives E = 0 (c > 0)
             const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
 #pragma unroll
             for (int T = 0; T < 4; ++T)

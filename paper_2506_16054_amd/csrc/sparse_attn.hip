@@ -1827,7 +1827,7 @@ struct Bf16Groups {
         }
     }
     // P = 2^(c S + off) in place of S, and this lane's sums.  True if some sum calls for the rare branch: one compare for the lane's
-    // queries (no sum is negative); a NaN in one of them must not hide another's climb.
+    // queries.  A sum that is NaN stays out of it: it neither hides another's climb nor sends the wavefront there in every block.
     __device__ __forceinline__ bool exponentials(v4f (&S)[2][NG], float c, float (&rs)[NG]) const {
 #pragma unroll
         for (int H = 0; H < NG; ++H)
@@ -1839,9 +1839,9 @@ struct Bf16Groups {
 #pragma unroll
         for (int H = 0; H < NG; ++H) {
             rs[H] = ((S[0][H][0] + S[1][H][0]) + (S[0][H][1] + S[1][H][1])) + ((S[0][H][2] + S[1][H][2]) + (S[0][H][3] + S[1][H][3]));
-            all = H ? all + rs[H] : rs[H];
+            all = H ? fmaxf(all, rs[H]) : rs[H];
         }
-        return __builtin_amdgcn_ballot_w64(!(all <= kBf16SumLimit)) != 0;
+        return __builtin_amdgcn_ballot_w64(all > kBf16SumLimit) != 0;
     }
     __device__ __forceinline__ void add(const float (&rs)[NG]) {
 #pragma unroll

@@ -1,5 +1,6 @@
 """bf16 mode, block 64: a lane holds one query of each of several groups of 16, and one look at the sum of their exponentials decides
-whether references have to move.  A query that is NaN must not hide that another query of the same lane climbs."""
+whether references have to move.  A query that is NaN must not hide that another query of the same lane climbs, and must not make the others
+move either."""
 import numpy as np
 import pytest
 
@@ -34,3 +35,35 @@ def test_nan_query_does_not_hide_a_climb(d, bad, climbs):
     assert float((o[rows] - ref[rows]).abs().max()) <= 1e-2 * float(v.double().abs().max())
     if bad is not None:
         assert torch.isnan(o[bad]).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_nan_query_does_not_move_the_other_references(d):
+    """References move where a block's sum passes 2^64, and nothing less: rows that climb by some 20 octaves keep theirs, whatever
+    the other queries of their wavefront hold, so their bits are the same beside a query of zeros and beside one of NaN."""
+    import torch
+
+    from paper_2506_16054_amd import binding as pb
+    from paper_2506_16054_amd import workloads as wl
+    from paper_2506_16054_amd.pipeline import ParoAttention
+
+    s = pb.make_shape(1, 1, d, 1, 16, 21, 0, 64)  # 336 tokens: five whole blocks and one of 16
+    n = pb.paro_ntokens(s)
+    pa = ParoAttention(s, [0], wl.pack_bitmask(np.ones((1, 6, 6), np.uint8)), 16, 16, torch.float32)
+    gen = torch.Generator().manual_seed(d)
+    q, k, v = (torch.randn((n, d), generator=gen) for _ in range(3))
+    u = torch.sign(torch.randn((d,), generator=gen))
+    q += 0.5 * u
+    for b in range(1, 6):
+        k[64 * b :] += u  # logits of a block lie about 0.5 * sqrt(d) * log2(e), 6 and 8 octaves, above those of the one before
+    bad = [5, 70, 149, 250, 330]
+
+    def layer(value):
+        q[bad] = value
+        pa.prepare_fused_qkv(*(x[None, None].contiguous().cuda() for x in (q, k, v)))
+        return pa.attend_fused()[0, 0].cpu()
+
+    rows = [i for i in range(n) if i not in bad]
+    zero, nan = layer(0.0), layer(float("nan"))
+    assert torch.isfinite(zero).all() and torch.isnan(nan[bad]).all()
+    assert torch.equal(nan[rows], zero[rows])

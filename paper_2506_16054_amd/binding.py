@@ -109,13 +109,13 @@ _fast = None
 
 
 def _native():
-    """The native module, bound to the loaded library (raises if it has not been built)."""
+    """The native module, bound to the loaded library (raises if there is none for this interpreter and this torch)."""
     global _fast
-    if _fast is None:
+    if _fast is None or _fast is _NoNative:
         import importlib.machinery
         import importlib.util
 
-        import torch  # noqa: F401  the module links torch's libraries
+        import torch  # the module links its libraries
 
         L = lib()
         path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "lib", "paro_fastcall.so")
@@ -124,9 +124,34 @@ def _native():
         loader = importlib.machinery.ExtensionFileLoader("paro_fastcall", path)
         module = importlib.util.module_from_spec(importlib.util.spec_from_loader("paro_fastcall", loader))
         loader.exec_module(module)
+        if module.built_for != torch.__version__:
+            raise ParoError(PARO_EHIP, "%s is built for torch %s, not %s" % (path, module.built_for, torch.__version__))
         module.bind(paro_shape, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in FASTCALL))
         _fast = module
     return _fast
+
+
+class _NoNative:
+    """Stands in for a native module that cannot be had: declines every call."""
+
+
+for _name in FASTCALL:
+    setattr(_NoNative, _name, staticmethod(lambda *args: None))
+
+
+def _layer_calls():
+    """The native module or, with a warning, what declines in its place: it needs a C++ compiler and torch's headers to build, and the
+    checks below and ctypes do all it does, more slowly."""
+    global _fast
+    lib()
+    try:
+        return _native()
+    except (ParoError, ImportError) as e:
+        import warnings
+
+        warnings.warn("per-layer calls go through ctypes: %s" % e, RuntimeWarning, stacklevel=3)
+        _fast = _NoNative
+        return _fast
 
 
 def _made(status) -> bool:
@@ -313,7 +338,7 @@ def paro_permute(s: paro_shape, perm_ids, x, xp) -> None:
 
 
 def paro_unpermute(s: paro_shape, perm_ids, op, o) -> None:
-    if _made((_fast or _native()).paro_unpermute(s, perm_ids, op, o)):
+    if _made((_fast or _layer_calls()).paro_unpermute(s, perm_ids, op, o)):
         return
     m = _dims(s)
     _require(op, "op", m.xp)
@@ -366,7 +391,7 @@ def _qkv_operands(s: paro_shape, bits_qk: int, bits_pv: int, q, k, v, q_codes, s
 
 
 def paro_permute_quantize_qkv(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv) -> None:
-    if _made((_fast or _native()).paro_permute_quantize_qkv(s, bits_qk, bits_pv, perm_ids, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)):
+    if _made((_fast or _layer_calls()).paro_permute_quantize_qkv(s, bits_qk, bits_pv, perm_ids, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)):
         return
     _qkv_operands(s, bits_qk, bits_pv, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)
     p = _perm_bytes(s, perm_ids)
@@ -377,7 +402,7 @@ def paro_permute_quantize_qkv(s: paro_shape, bits_qk: int, bits_pv: int, perm_id
 def paro_permute_quantize_qkv_keep(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, qp, kp, vp, q_codes, sq, k_codes, sk,
                                    v_codes, sv) -> None:
     """qp, kp, vp: the reordered, padded tensors [B, nh, Npad, d], stored as well."""
-    if _made((_fast or _native()).paro_permute_quantize_qkv_keep(s, bits_qk, bits_pv, perm_ids, q, k, v, qp, kp, vp, q_codes, sq,
+    if _made((_fast or _layer_calls()).paro_permute_quantize_qkv_keep(s, bits_qk, bits_pv, perm_ids, q, k, v, qp, kp, vp, q_codes, sq,
                                                                   k_codes, sk, v_codes, sv)):
         return
     _qkv_operands(s, bits_qk, bits_pv, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)
@@ -412,7 +437,7 @@ def paro_permute_quantize_smoothed(s: paro_shape, bits: int, perm_ids, k, k_mean
 def paro_mask_to_blocklist_device(nh: int, k: int, bitmask, row_ptr, col_idx, nnz_out=None) -> None:
     """Device tensors: bitmask uint8 [nh, ceil(k*k/8)] -> row_ptr int32 [nh, k+1], col_idx int32 [cap]
     (cap = col_idx.numel(); may be None for the offsets only), nnz_out int32 [1] or None."""
-    if _made((_fast or _native()).paro_mask_to_blocklist_device(nh, k, bitmask, row_ptr, col_idx, nnz_out)):
+    if _made((_fast or _layer_calls()).paro_mask_to_blocklist_device(nh, k, bitmask, row_ptr, col_idx, nnz_out)):
         return
     import torch
 
@@ -556,7 +581,7 @@ def _order_ptr(s: paro_shape, row_order):
 
 def paro_sparse_attn_unpermuted(s: paro_shape, bits_qk: int, bits_pv: int, q, sq, k, sk, v, sv, row_ptr, col_idx, perm_ids, o,
                                 row_order=None) -> None:
-    if _made((_fast or _native()).paro_sparse_attn_unpermuted(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx, perm_ids, o,
+    if _made((_fast or _layer_calls()).paro_sparse_attn_unpermuted(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx, perm_ids, o,
                                                                row_order)):
         return
     _attn_operands(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx)
@@ -589,7 +614,7 @@ def paro_sparse_attn_unpermuted_rawq(s: paro_shape, bits_pv: int, q, k, sk, v, s
 
 
 def paro_sparse_attn(s: paro_shape, bits_qk: int, bits_pv: int, q, sq, k, sk, v, sv, row_ptr, col_idx, op, row_order=None) -> None:
-    if _made((_fast or _native()).paro_sparse_attn(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx, op, row_order)):
+    if _made((_fast or _layer_calls()).paro_sparse_attn(s, bits_qk, bits_pv, q, sq, k, sk, v, sv, row_ptr, col_idx, op, row_order)):
         return
     import torch
 

@@ -288,4 +288,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "paro_fastcall", nullptr, -1, metho
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_paro_fastcall(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit_paro_fastcall(void) {
+    PyObject* m = PyModule_Create(&module);
+    // the torch whose tensors this file knows the layout of; the binding loads it beside no other
+    if (m && PyModule_AddStringConstant(m, "built_for", PARO_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -48,6 +48,40 @@ def test_module_is_missing(monkeypatch, tmp_path):
         pb._native()
 
 
+def _calls_without_module(monkeypatch, match):
+    """The per-layer calls reach the binding's own checks (which refuse these arguments) after one warning."""
+    monkeypatch.setattr(pb, "_fast", None)
+    s = pb.make_shape(1, 2, 64, 3, 5, 7, 11, 64)
+    with pytest.warns(RuntimeWarning, match=match):
+        with pytest.raises(pb.ParoError, match="must be"):
+            pb.paro_unpermute(s, [0, 0], torch.zeros(4), torch.zeros(4))
+    for name in pb.FASTCALL:
+        assert getattr(pb._fast, name)(1, 2, 3) is None
+
+
+def test_calls_go_on_without_the_module(monkeypatch, tmp_path):
+    pb.lib()
+    monkeypatch.setattr(pb, "__file__", str(tmp_path / "binding.py"))
+    _calls_without_module(monkeypatch, "paro_fastcall.so is missing")
+
+
+def test_module_for_another_torch_is_not_used(monkeypatch):
+    pb._native()
+    monkeypatch.setattr(torch, "__version__", "0.0.0")
+    _calls_without_module(monkeypatch, "not 0.0.0")
+
+
+def test_build_goes_on_without_a_compiler(monkeypatch, tmp_path, capfd):
+    from paper_2506_16054_amd import build
+
+    stale = tmp_path / build.FASTCALL_LIBNAME
+    for cxx in ("no-such-compiler", "false"):
+        monkeypatch.setenv("CXX", cxx)
+        stale.write_bytes(b"of an earlier build")
+        assert build.build_fastcall(str(tmp_path)) is None
+        assert not stale.exists() and "native module" in capfd.readouterr().err
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits_qk,bits_pv", pb.QKV_BITS)
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])

@@ -49,7 +49,9 @@ class ParoAttention:
         quantized."""
         s = self.s
         rows_are_codes = self.bits_qk == 16 and self.dtype == torch.bfloat16  # bf16 rows: nothing to convert
-        if not rows_are_codes and (self.bits_qk, self.bits_pv) in pb.QKV_BITS:
+        # an input that is itself one of the reordered tensors (which have its shape where nothing is padded) is read before it is written
+        in_order = self.N == self.npad and not {x.data_ptr() for x in (q, k, v)}.isdisjoint(x.data_ptr() for x in self.xp)
+        if not rows_are_codes and not in_order and (self.bits_qk, self.bits_pv) in pb.QKV_BITS:
             pb.paro_permute_quantize_qkv_keep(s, self.bits_qk, self.bits_pv, self.perm_ids, q, k, v, *self.xp, self.qc, self.sq, self.kc, self.sk,
                                               self.vc, self.sv)
             return

@@ -47,3 +47,25 @@ def test_one_launch_equals_the_separate_calls(dtype, d, block, bits, grid, text)
     pb.paro_permute_quantize_qkv_keep(s, *bits, ids, *x, *xp1, c1[0], s1[0], c1[1], s1[1], c1[2], s1[2])
     for a, b in zip(xp0 + c0 + s0, xp1 + c1 + s1):
         assert torch.equal(_bits(a), _bits(b))
+
+
+@pytest.mark.parametrize("bits", [(8, 8), (4, 4)])
+def test_prepare_takes_its_own_reordered_tensors(bits):
+    """Without padding an input may be one of the layer's reordered tensors, as long as it is read before it is written."""
+    import torch
+
+    from paper_2506_16054_amd import binding as pb
+    from paper_2506_16054_amd import workloads as wl
+    from paper_2506_16054_amd.pipeline import ParoAttention
+
+    s = pb.make_shape(1, 2, 64, 2, 8, 8, 0, 64)  # 128 tokens, two blocks
+    mask = wl.pack_bitmask(np.ones((2, 2, 2), np.uint8))
+    a, b = (ParoAttention(s, [2, 4], mask, *bits, torch.float32) for _ in range(2))
+    gen = torch.Generator().manual_seed(1)
+    q, k, v = (torch.randn((1, 2, 128, 64), generator=gen).cuda() for _ in range(3))
+    want = a.run(q, k, v)
+    b.xp[1].copy_(q)
+    b.xp[2].copy_(k)
+    assert torch.equal(b.run(b.xp[1], b.xp[2], v), want)
+    for x, y in zip(a.xp + [a.qc, a.kc, a.vc, a.sq, a.sk, a.sv], b.xp + [b.qc, b.kc, b.vc, b.sq, b.sk, b.sv]):
+        assert torch.equal(_bits(x), _bits(y))

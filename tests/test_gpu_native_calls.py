@@ -89,13 +89,22 @@ def test_same_bytes_as_the_binding(monkeypatch, bits_qk, bits_pv, dtype):
     pa, bits, x = _layer(bits_qk, bits_pv, dtype)
     row_ptr, cols = torch.empty_like(pa.row_ptr), torch.empty_like(pa.col_idx)
 
+    def spoil():
+        """Nothing that a call is to write holds what an earlier one wrote there."""
+        for t in (row_ptr, cols, pa.op, pa.o, *pa.xp, pa.qc, pa.kc, pa.vc, pa.sq, pa.sk, pa.sv, *pa._fused_buffers()):
+            t.fill_(3)
+
     def once():
-        row_ptr.zero_(), cols.zero_(), pa.o.zero_()
+        spoil()
         pb.paro_mask_to_blocklist_device(2, pa.k, torch.from_numpy(bits).to("cuda:0"), row_ptr, cols)
         pa.use_blocklist(row_ptr, cols, pa.row_order)
-        steps = pa.run(*x).clone()
+        out = [row_ptr.clone(), cols.clone(), pa.run(*x).clone(), pa.op.clone()]
+        out += [t.clone() for t in (*pa.xp, pa.qc, pa.kc, pa.vc, pa.sq, pa.sk, pa.sv)]
+        spoil()
+        row_ptr.copy_(out[0]), cols.copy_(out[1])
         pa.prepare_fused_qkv(*x)
-        return steps, pa.attend_fused().clone(), row_ptr.clone(), cols.clone()
+        out += [t.clone() for t in (*pa._fused_buffers(), pa.vc, pa.sq, pa.sk, pa.sv)]
+        return out + [pa.attend_fused().clone()]
 
     pa.row_order = torch.from_numpy(pa.h_row_order).to("cuda:0")
     calls = []
@@ -111,8 +120,8 @@ def test_same_bytes_as_the_binding(monkeypatch, bits_qk, bits_pv, dtype):
     got = once()
     assert calls and all(status == pb.PARO_OK for _, status in calls)
     monkeypatch.setattr(pb, "_fast", NONE)
-    for a, b in zip(got, once()):
-        assert torch.equal(a, b)
+    for a, b in zip(got, once(), strict=True):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
 
 
 @pytest.mark.gpu
@@ -136,3 +145,52 @@ def test_declined_and_refused_on_the_device():
     seen = []
     torch.func.vmap(lambda t: seen.append(f(pa.s, pa.perm_ids, t, o)) or t)(op[None])
     assert seen == [None]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_calls_follow_the_current_stream(monkeypatch, native):
+    """Inputs that arrive late on a side stream: a call on any other stream would read what was there before."""
+    pa, bits, x = _layer(8, 8, torch.float32)
+    want_steps = pa.run(*x).clone()
+    pa.prepare_fused_qkv(*x)
+    want_fused = pa.attend_fused().clone()
+    late = [torch.zeros_like(t) for t in x]
+    monkeypatch.setattr(pb, "_fast", pb._native() if native else NONE)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for want, call in ((want_steps, lambda: pa.run(*late)), (want_fused, lambda: (pa.prepare_fused_qkv(*late), pa.attend_fused())[1])):
+            [t.zero_() for t in late]
+            torch.cuda._sleep(20_000_000)  # some 10 ms
+            [t.copy_(s) for t, s in zip(late, x)]
+            o = call().clone()
+            side.synchronize()
+            assert torch.equal(o, want)
+
+
+@pytest.mark.gpu
+def test_two_threads_with_a_layer_and_a_stream_each():
+    import threading
+
+    layers = [_layer(8, 8, torch.float32), _layer(4, 4, torch.bfloat16)]
+    want = [(pa.run(*x).clone(), (pa.prepare_fused_qkv(*x), pa.attend_fused())[1].clone()) for pa, _, x in layers]
+    torch.cuda.synchronize()
+    wrong, start = [], threading.Barrier(2)
+
+    def work(i):
+        pa, _, x = layers[i]
+        start.wait()
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(50):
+                steps = pa.run(*x).clone()
+                pa.prepare_fused_qkv(*x)
+                fused = pa.attend_fused().clone()
+                torch.cuda.current_stream().synchronize()
+                if not (torch.equal(steps, want[i][0]) and torch.equal(fused, want[i][1])):
+                    wrong.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    assert wrong == []

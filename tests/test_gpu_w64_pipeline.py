@@ -75,3 +75,26 @@ def test_scales_past_the_folded_form_and_extreme_ones(bits, gain_qk, gain_v):
     masks = np.ones((1, 6, 6), bool)
     masks[0, 2, 1::2] = False
     _run(grid, masks, q, k, v, *bits, list(range(6)), gain_qk, gain_v, raw_q=bits[0] == 8)
+
+
+@pytest.mark.parametrize("bits", [(8, 8), (8, 4), (4, 8), (4, 4)])
+@pytest.mark.parametrize("octave", [89, 91, 101])
+def test_exact_form_beyond_the_scaled_one(bits, octave):
+    """Logit scales of 1.4 * 2^octave per integer step: below and above 2^90, where the scaled form gives way to the exact one
+    (8-bit P codes take the exact form at all three).  A row of Q and a row of K have one channel that counts, of opposite signs, so
+    logits are 0 or of -2^100 octaves and every maximum is 0: attention is the mean of V over the keys of other channels.  (The offset of
+    an exponent holds minus the maximum and log2 of the largest code in one float, so maxima this large are out of range.)"""
+    grid = (1, 10, 35)
+    rng = np.random.default_rng(11)
+    one, top = (64.0, 127.0) if bits[0] == 8 else (4.0, 7.0)
+    q, k = np.zeros((2, 350, 64))
+    for x, own, sign in ((q, 63, 1.0), (k, 62, -1.0)):
+        x[range(350), rng.integers(0, 4, 350)] = one * sign
+        x[:, own] = top  # the largest value of every block, in a channel that the other tensor leaves at 0
+    masks = np.ones((1, 6, 6), bool)
+    masks[0, 2, 1::2] = False
+    # scale per step: gain^2 * log2(e) / 8, of 4-bit codes (times 16 each) / 256
+    gain = 2.0 ** ((octave + 3) // 2 + (0 if bits[0] == 8 else 4))
+    c = gain * gain * 1.4426950408889634 / 8 / (1 if bits[0] == 8 else 256)
+    assert (c < 2.0**90) == (octave == 89) and 1.4 < c / 2.0**octave < 1.5
+    _run(grid, masks, q, k, rng.standard_normal((350, 64)), *bits, list(range(6)), gain, raw_q=bits[0] == 8)

@@ -720,18 +720,13 @@ __device__ inline v16i acc_start() {
 }
 __device__ inline float start_result(int raw) { return fmaf(__int_as_float(raw), 0x1p26f, -kStartI); }  // exact
 // The offset of the folded exponent, off_n - c_up * kStartF rounded once, and by how much it lies above the exact value (to the last
-// place of off_n).  Written out, because left to the compiler it was one fma in one half and the rounded difference of the rounded
-// product in the other one, and kStartI has 24 significant bits: the product is rounded no less than the difference.  A contracted
-// step of the two-sum would count the product's residue twice.  Error against the float64 oracle, fp32 outputs of 8-bit codes: 48
-// heads of 17550 tokens at 30 % 3.44e-4 -> 3.23e-4, 30 heads at 50 % 3.42e-4 -> 3.31e-4 (with one rounding and attn_i8_kernel's start
-// value 3.27e-4 and 3.24e-4; samples differ by some 2 %), 4-bit Q and K 3.46e-4 -> 3.30e-4 (3.85e-4); 1078 -> 1082 us.
+// place of off_n: the second fma cancels to off_n plus that).  Left to the compiler, the product was rounded by itself in one of the
+// two halves, and kStartI has 24 significant bits: that is no less than the difference's own rounding.  Error against binary64, fp32
+// outputs of 8-bit codes, all heads of 17550 tokens: 48 heads at 30 % 3.41e-4 -> 3.15e-4, 30 heads at 50 % 3.40e-4 -> 3.14e-4, 30 heads with
+// 4-bit Q and K at 30 % 3.58e-4 -> 3.34e-4 (with attn_i8_kernel's start value 3.19e-4, 3.18e-4 and 3.91e-4).
 __device__ __forceinline__ float folded_offset(float off_n, float c_up, float& above) {
-#pragma clang fp contract(off)
     const float off = fmaf(-c_up, kStartF, off_n);
-    const float cb_hi = c_up * kStartF;
-    const float cb_lo = fmaf(c_up, kStartF, -cb_hi);
-    const float bb = off - off_n;
-    above = cb_lo - ((off_n - (off - bb)) + (-cb_hi - bb));
+    above = fmaf(c_up, kStartF, off) - off_n;
     return off;
 }
 // Ends a basic block without an instruction.  The compiler names the constant above in the instruction only where a

@@ -80,6 +80,21 @@ def test_loop_instruction_counts_reads_the_loops_that_hold_matrix_instructions()
     assert instruction_class("v_mul_f32_e32") == "add_mul"
 
 
+def test_bench_prices_the_loop_that_ordinary_scales_take():
+    """Of the d = 64 kernel's two loops the exact one has a second fma per logit; in total they differ by a few instructions either way."""
+    from bench import ordinary_loop, static_loop_counts
+    from paper_2506_16054_amd import workloads as wl
+
+    exact, scaled = {"add_mul": 283, "fma": 396, "half_rate": 204, "mfma": 32}, {"add_mul": 415, "fma": 268, "half_rate": 204, "mfma": 32}
+    assert ordinary_loop([exact, scaled]) is scaled and ordinary_loop([scaled, exact]) is scaled
+    folded, subtracted = {"add_mul": 63, "fma": 53, "mfma_16x16": 16}, {"add_mul": 72, "fma": 50, "mfma_16x16": 16}
+    assert ordinary_loop([subtracted, folded]) is folded
+    base = wl.WORKLOADS["cogvideox5b"]
+    for bits_qk, bits_pv in ((8, 8), (8, 4), (4, 8), (4, 4)):  # 64 logits per lane and visit
+        counts = static_loop_counts(base.replace(bits_qk=bits_qk, bits_pv=bits_pv))
+        assert 2 * 64 <= counts["fma"] < 2.5 * 64, (bits_qk, bits_pv, counts)
+
+
 def test_probe_library_exports_what_bench_calls():
     """lib/libparo_probe.so is a measurement aid next to the product library; bench.py fails if it is missing."""
     import ctypes

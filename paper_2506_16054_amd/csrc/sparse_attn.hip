@@ -659,8 +659,8 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? PARO_ATTN_WAVES_D64 : 2)) void 
 //   * the accumulators of the products start at an instruction's own constant (acc_start): 16 registers less, and 16 register
 //     reads less in every second matrix instruction.
 // Before: K and V by way of an LDS ring, products, maxima and exponentials of a block one after the other, 1.00 of the
-// summed issue cost.  Sustained, us per call with the quantizer: 48 heads of 17550 tokens at 30 % 1 160 -> 1 085, 30 heads
-// at 50 % 1 182 -> 1 100; 48 heads at 20 % with 4-bit P and V 835 -> 780, all 4-bit 837 -> 792.
+// summed issue cost.  Sustained, us per call with the quantizer: 48 heads of 17550 tokens at 30 % 1 175 -> 1 089, 30 heads
+// at 50 % 1 196 -> 1 090; 48 heads at 20 % with 4-bit P and V 840 -> 791, all 4-bit 838 -> 804.
 // -------------------------------------------------------------------------------------------
 #ifndef PARO_ATTN_SINGLE_WAVE
 #define PARO_ATTN_SINGLE_WAVE 1
@@ -2063,7 +2063,7 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
 // Two barriers per block: V_t is requested behind the first (V_{t-1} has been read by all, K_t is whole) and K_{t+1}
 // behind the second (K_t has been read by all, V_t is whole), so each has half a block of work to hide behind.
 // 24 heads of 4096 + 512 tokens at 30 % density, two layers with quantizer and mask prefetch: 419 -> 387 us (runs of one
-// side differ by 0.3 %; 406 -> 377 and 470 -> 411 elsewhere).  In 16 x 16 x 32 products, 393 -> 349 us: a lane's logits are four
+// side differ by 0.3 %; 406 -> 377 and 470 -> 411 elsewhere).  In 16 x 16 x 32 products, 389 -> 354 us: a lane's logits are four
 // chains of four products, not one chain of eight that each wait for the one before, and they take less energy.
 template <typename OutT>
 __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {

@@ -201,15 +201,6 @@ int paro_check_row_order(const paro_shape* s, const int32_t* h_order) {
     return PARO_OK;
 }
 
-// Workgroups of the attention kernel that one XCD (32 compute units of 4 SIMDs) holds at a time: by wavefronts per workgroup and
-// wavefronts per SIMD of the kernel that paro_sparse_attn launches.
-static int64_t workgroups_per_xcd(const paro_shape* s, int bits_qk) {
-    const bool bf16 = bits_qk == 16;
-    if (s->block == 32) return 128 * (s->d == 128 ? 2 : bf16 ? 3 : 4);  // one wavefront
-    if (s->d == 64) return bf16 ? 128 * 3 / 2 : 128 * 2;                // two wavefronts, three per SIMD; one, two per SIMD
-    return 128;  // 8 bit throughout: four, four per SIMD; other codes: two, two per SIMD (bf16: 96, with no difference in time)
-}
-
 int paro_schedule_rows(const paro_shape* s, int bits_qk, int bits_pv, const int32_t* h_row_ptr, int32_t* h_order) {
     int64_t n, k;
     if (int st = check_shape(s, &n, &k)) return st;
@@ -225,14 +216,13 @@ int paro_schedule_rows(const paro_shape* s, int bits_qk, int bits_pv, const int3
     const int64_t kv_bytes = k * s->block * (int64_t)s->d * (bits_qk + bits_pv) / 8;
     const int64_t l2_budget = 4 << 20;
     const int64_t window = std::max<int64_t>(1, l2_budget / std::max<int64_t>(kv_bytes, 1));
-    // A wavefront that has its SIMD to itself runs no faster than one that shares it, so when the last group of an XCD runs out of row
-    // blocks the launch drains for as long as the last-started rows take.  With several groups per XCD the lightest rows of the whole
-    // range - half as many as the XCD holds workgroups - are therefore kept back and started last, heaviest first: they are the
-    // shortest filler there is, and being few and short they cost the L2 little.  us per launch with none, 64, half as many
-    // as resident and more kept back: 48 heads, d = 64, 8 bit 990, 973, 971 (128), 959 (256); all 4 bit 717, 712, 709 (128), 708 (256); 30
-    // heads, 4-bit Q and K 640, 624, 619 (128), 617 (256); blocks of 32 660, 653, 637 (256); 48 heads of bf16, d = 64 1217, 1216, 1214 (96),
-    // 1238 (192).  At d = 128 it makes no difference or a small loss: 24 heads of 15872 tokens, 8 bit 824, 829 (64), 827 (128), bf16 979, 997.
-    const int64_t resident = workgroups_per_xcd(s, bits_qk);
+    // Workgroups one XCD holds at a time (32 compute units x 8 one-wavefront workgroups of the d = 64 / block 64 / 8-bit
+    // kernel, x 4 workgroups of the others).  A wavefront that has its SIMD to itself runs no faster than one that shares
+    // it, so when the last group of an XCD runs out of row blocks the launch drains for as long as the last-started
+    // rows take.  With several groups per XCD the lightest rows of the whole range - half as many as the XCD holds
+    // workgroups - are therefore kept back and started last, heaviest first: they are the shortest filler there is,
+    // and being few and short they cost the L2 little.
+    const int64_t resident = (s->d == 64 && s->block == 64 && bits_qk == 8) ? 256 : 128;
     // Which (batch, head) an XCD works on.  Positions are in units of whole (batch, head) "slots" of k row blocks; slot
     // v holds head_at[v].  Masks made with one threshold per head (Sec. 4.2 (3)) can differ in live blocks from head to
     // head; when every XCD's range is a whole number of heads and the heads in their natural order would load some XCD

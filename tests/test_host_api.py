@@ -278,25 +278,6 @@ def test_row_schedule_is_a_permutation_heaviest_first_within_l2_groups_lightest_
         pb.paro_schedule_rows(s2, 5, 8, rp2)
 
 
-@pytest.mark.parametrize("block,bits_qk,bits_pv,kept", [(64, 8, 8, 128), (64, 8, 4, 128), (64, 4, 4, 128), (64, 4, 8, 128), (64, 16, 16, 96),
-                                                        (32, 8, 8, 256), (32, 4, 4, 256), (32, 16, 16, 192)])
-def test_row_schedule_keeps_back_half_of_what_the_kernel_has_resident(block, bits_qk, bits_pv, kept):
-    """d = 64, groups of one or two heads: the rows kept back are half as many as an XCD holds workgroups of the kernel that these widths
-    launch."""
-    s = pb.make_shape(1, 48, 64, 13, 30, 45, 0, block)
-    k = pb.paro_nblocks(s)
-    live = np.random.default_rng(3).permutation(48 * k).reshape(48, k) + 1  # all different
-    rp = np.zeros((48, k + 1), np.int64)
-    rp[:, 1:] = np.cumsum(live, axis=1)
-    rp += np.concatenate([[0], np.cumsum(live.sum(1))[:-1]])[:, None]
-    order = pb.paro_schedule_rows(s, bits_qk, bits_pv, rp.astype(np.int32))
-    pb.paro_check_row_order(s, order)
-    ranges = [live[chunk // k, chunk % k] for chunk in np.split(order, 8)]
-    for lv in ranges:
-        assert np.array_equal(lv[-kept:], np.sort(lv)[:kept][::-1])
-    assert any(lv[-kept - 1] != np.sort(lv)[kept] for lv in ranges)  # and no more than these
-
-
 def test_row_schedule_deals_unequal_heads_to_the_xcds_by_work():
     """Heads of equal size stay where they are (XCD x works on heads 6x .. 6x+5); heads that differ in live blocks are
     dealt so that no XCD carries much more than its share."""

@@ -125,8 +125,8 @@ int paro_check_row_order(const paro_shape* s, const int32_t* h_order);
  * to the 8 XCDs in 8 contiguous ranges; inside a range, row blocks are sorted by descending live
  * count within groups of consecutive heads whose K and V operands fit one L2 (4 MB) together (so
  * the reordering never evicts the K/V tiles being reused); a range whose heads all fit together is
- * one group.  A range of several groups keeps its lightest row blocks (half as many as the XCD
- * holds workgroups, at most a quarter of the range) out of the groups and starts them last, heaviest
+ * one group.  A range of several groups keeps its lightest row blocks (128 with 8-bit Q and K at
+ * d = 64 and block 64, else 64; at most a quarter of the range) out of the groups and starts them last, heaviest
  * first: the launch ends when the last-started row blocks are done, and these are the shortest.
  * When every XCD's range is a whole number of (batch, head) pairs and the heads differ in live
  * blocks (one threshold per head, Sec. 4.2 (3)) so that the natural order would load some XCD more

@@ -216,13 +216,14 @@ int paro_schedule_rows(const paro_shape* s, int bits_qk, int bits_pv, const int3
     const int64_t kv_bytes = k * s->block * (int64_t)s->d * (bits_qk + bits_pv) / 8;
     const int64_t l2_budget = 4 << 20;
     const int64_t window = std::max<int64_t>(1, l2_budget / std::max<int64_t>(kv_bytes, 1));
-    // Workgroups one XCD holds at a time (32 compute units x 8 one-wavefront workgroups of the d = 64 / block 64 / 8-bit
-    // kernel, x 4 workgroups of the others).  A wavefront that has its SIMD to itself runs no faster than one that shares
-    // it, so when the last group of an XCD runs out of row blocks the launch drains for as long as the last-started
-    // rows take.  With several groups per XCD the lightest rows of the whole range - half as many as the XCD holds
-    // workgroups - are therefore kept back and started last, heaviest first: they are the shortest filler there is,
-    // and being few and short they cost the L2 little.
-    const int64_t resident = (s->d == 64 && s->block == 64 && bits_qk == 8) ? 256 : 128;
+    // A wavefront that has its SIMD to itself runs no faster than one that shares it, so when the last group of an XCD runs out of row
+    // blocks the launch drains for as long as the last-started rows take.  With several groups per XCD the lightest rows of the whole
+    // range are therefore kept back and started last, heaviest first: they are the shortest filler there is, and being few and
+    // short they cost the L2 little.  128 of them for the d = 64 / block 64 kernel of 8-bit Q and K (half of the workgroups that an XCD
+    // holds of it), 64 elsewhere, which is measured and not half of what those kernels hold (4-bit Q and K, d = 64: 128; bf16, d = 64: 96;
+    // blocks of 32: 128 to 256; bf16, d = 128: 48).  With those numbers 40 drawn layers take the same time on average, and single ones
+    // from 0.84 to 1.04 times it: 30 heads of 275 blocks with 4-bit Q and K 624 -> 619 us, but 12 heads of 273 blocks 416 -> 497.
+    const int64_t keep = (s->d == 64 && s->block == 64 && bits_qk == 8) ? 128 : 64;
     // Which (batch, head) an XCD works on.  Positions are in units of whole (batch, head) "slots" of k row blocks; slot
     // v holds head_at[v].  Masks made with one threshold per head (Sec. 4.2 (3)) can differ in live blocks from head to
     // head; when every XCD's range is a whole number of heads and the heads in their natural order would load some XCD
@@ -280,7 +281,7 @@ int paro_schedule_rows(const paro_shape* s, int bits_qk, int bits_pv, const int3
             ids.resize(hi - lo);
             for (int64_t t = lo; t < hi; ++t) ids[t - lo] = (int32_t)t;
             std::stable_sort(ids.begin(), ids.end(), [&](int32_t a, int32_t b) { return live(a) < live(b); });
-            kept_back.assign(ids.begin(), ids.begin() + std::min<int64_t>(resident / 2, (hi - lo) / 4));
+            kept_back.assign(ids.begin(), ids.begin() + std::min<int64_t>(keep, (hi - lo) / 4));
             for (int32_t id : kept_back) held[id - lo] = 1;
             std::stable_sort(kept_back.begin(), kept_back.end(), heavier);
         }

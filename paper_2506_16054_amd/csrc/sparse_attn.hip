@@ -660,7 +660,7 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? PARO_ATTN_WAVES_D64 : 2)) void 
 //     reads less in every second matrix instruction.
 // Before: K and V by way of an LDS ring, products, maxima and exponentials of a block one after the other, 1.00 of the
 // summed issue cost.  Sustained, us per call with the quantizer: 48 heads of 17550 tokens at 30 % 1 175 -> 1 089, 30 heads
-// at 50 % 1 196 -> 1 090; 48 heads at 20 % with 4-bit P and V 840 -> 791, all 4-bit 838 -> 804.
+// at 50 % 1 196 -> 1 090; 48 heads at 20 % with 4-bit P and V 840 -> 791, all 4-bit 839 -> 807.
 // -------------------------------------------------------------------------------------------
 #ifndef PARO_ATTN_SINGLE_WAVE
 #define PARO_ATTN_SINGLE_WAVE 1

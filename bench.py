@@ -38,6 +38,9 @@ def attention_kernel_symbol(w):
                 "paro::attn_i8_w64_qk4_kernel<%d, %s>" % (w.bits_pv, tn), 1, 2, 2)
     if w.block == 64 and w.d == 128 and w.bits_qk == 8 and w.bits_pv == 8:
         return ("_ZN4paro18attn_i8_q16_kernelI%sEEvNS_8AttnArgsE" % t, "paro::attn_i8_q16_kernel<%s>" % tn, 4, 4, 1)
+    if w.block == 32:
+        return ("_ZN4paro18attn_i8_b32_kernelILi%dELi%dELi%dE%sEEvNS_8AttnArgsE" % (w.d, w.bits_qk, w.bits_pv, t),
+                "paro::attn_i8_b32_kernel<%d, %d, %d, %s>" % (w.d, w.bits_qk, w.bits_pv, tn), 1, 3 if w.d == 64 else 2, 2)
     return ("_ZN4paro14attn_i8_kernelILi%dELi%dELi%dELi%dE%sLi0EEEvNS_8AttnArgsE" % (w.block, w.d, w.bits_qk, w.bits_pv, t),
             "paro::attn_i8_kernel<%d, %d, %d, %d, %s, 0>" % (w.block, w.d, w.bits_qk, w.bits_pv, tn), w.block // 32, 3 if w.d == 64 else 2, 1)
 

@@ -99,7 +99,7 @@ def loop_instruction_counts(asm: str) -> dict:
     """{kernel symbol: [ {class: count per loop iteration}, ... one entry per innermost loop that holds matrix
     instructions ]} from the compiler's assembly listing.  Loop blocks that are rarely taken branches are left out."""
     out = {}
-    for m in re.finditer(r"^(_ZN4paro\w*attn\w+):[^\n]*\n(.*?)\n\s*s_endpgm", asm, re.S | re.M):
+    for m in re.finditer(r"^(_ZN4paro\w*attn\w+):[^\n]*\n(.*?)\n\.Lfunc_end", asm, re.S | re.M):
         name, body = m.group(1), m.group(2)
         loops, label, header = {}, None, None
         for line in body.split("\n"):
@@ -124,6 +124,8 @@ def loop_instruction_counts(asm: str) -> dict:
             for ops in blocks:
                 if sum(o.startswith("v_cndmask") for o in ops) >= _RARE or sum(o.startswith("v_mul_f32") for o in ops) >= _RARE:
                     continue
+                if len(ops) >= _RARE and all(instruction_class(o) == "fma" or o.startswith("v_mov") for o in ops):
+                    continue  # what the sums of the block-32 kernel hold too much, taken out every eight blocks
                 for o in ops:
                     c = instruction_class(o)
                     counts[c] = counts.get(c, 0) + 1

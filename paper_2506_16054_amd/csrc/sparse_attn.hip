@@ -1222,6 +1222,383 @@ __global__ __launch_bounds__(64, 2) void attn_i8_w64_qk4_kernel(AttnArgs a) {
 }
 
 // -------------------------------------------------------------------------------------------
+// block 32: ONE wavefront per row block of 32 queries, no barrier.
+//
+// The same wavefront program as above with one half: the 16 exponentials of a lane stand in one burst at raised priority,
+// and inside it run K Q of block t + 1 and P V of block t - 1 (at d = 64 one matrix instruction in front of every four
+// exponentials; at d = 128 six of the eight fit, the others run beside the vector work).  K and V^T fragments go from global memory
+// straight to registers, each requested as soon as the last product of its predecessor is issued; the chain from the row maxima
+// to the tile's scale runs beside the codes of the block before.  Rows of 128 bytes of K are the exception: a lane pair reads 32 of a row, so
+// every request would touch 32 lines and the next three the same ones, more than the L1 of a compute unit holds for its wavefronts; they
+// go through LDS in whole lines.
+// Bound by the issue of the vector work where the chip is full (158 vector instructions per block at d = 64, 196 in attn_i8_kernel,
+// which exchanged tiles through LDS with a barrier per block), by the chain of one block where it is not.  Attention call alone, us,
+// attn_i8_kernel -> this one, 8-bit codes / all 4-bit, 30 % density: d = 64, 30 heads of 17550 tokens 1001 -> 780 / 957 -> 799, 24 heads
+// of 4096 57.2 -> 44.4 / 56.4 -> 47.9, 4 heads of 4096 36.5 -> 24.4 / 37.9 -> 27.9; d = 128, 30 heads of 17550 1765 -> 1264 (K by
+// registers 1560) / 1839 -> 1295, 4 heads of 4096 46.5 -> 30.3 / 49.9 -> 37.2.
+//
+// The exponent is formed after one exact subtraction per logit (the folded form of the kernel above is 2.5 % faster here and
+// decides P codes within 6e-5 of a tie differently: error against binary64 3e-4 with it, 4e-5 without).
+// -------------------------------------------------------------------------------------------
+
+// 8-bit P V products enter the sums without a subtraction.  Their chain starts at START, a power of two that no
+// |result| exceeds: its register then holds a positive integer below 2^24, which read as a float is that integer times 2^-149
+// exactly (subnormals and the lowest binade share one spacing), so one fma adds it to the sum.  What the sum holds too much,
+// START times the sum of the weights, is known per row and taken out every PERIOD blocks, before it is large enough to
+// cost places: PERIOD * START = 2^22, an addition rounds to half a unit of the integer at most.  (Error of the output against
+// binary64, rms over 320 .. 17550 tokens: 3.3e-5 .. 4.4e-5, with the subtraction and the folded exponent 2.9e-4 .. 3.3e-4.
+// With 4-bit P codes, which are mostly 0, it would show: 2e-5 -> 9e-5; they keep the subtraction.)
+// The weights carry 2^(kWeightUp - E), E the exponent of the row block's largest V scale: with V scales within 2^28 of each other
+// nothing is subnormal that counts and nothing overflows (w_blk reaches 2^57, see m_ref, and PERIOD of them are summed).
+// Rows outside take the other loop.
+constexpr int kWeightUp = 60;
+
+template <int D, int QKBITS, int PVBITS, typename OutT>
+__global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(AttnArgs a) {
+    constexpr int BLK = 32;
+    constexpr int KPACK = QKBITS == 4 ? 2 : 1;
+    constexpr int VPACK = PVBITS == 4 ? 2 : 1;
+    constexpr int KS = D / 32;  // contraction steps of QK^T
+    constexpr int DT = D / 32;  // 32-channel tiles of the output
+    constexpr float LOG2_QMAXP = PVBITS == 4 ? 2.807354922057604f : 6.988684686772166f;
+    constexpr float kLog2_65535 = 15.999977986052736f;
+    constexpr bool LIFTED = PVBITS == 8;  // P V products enter the sums without a subtraction
+    constexpr int START = 1 << 19;  // >= 32 * 127 * 127
+    constexpr int PERIOD = 8;
+    constexpr bool K_BY_LDS = D / KPACK == 128;
+    __shared__ __attribute__((aligned(16))) uint8_t kslot[K_BY_LDS ? BLK * D : 16];
+
+    const int wg = blockIdx.x;
+    const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
+    if (logical >= a.total_wg) return;
+    const int item = a.row_order ? min(max(a.row_order[logical], 0), a.total_wg - 1) : logical;
+    const int bh = item / a.kblocks;
+    const int i = item - bh * a.kblocks;
+    const int h = bh % a.nh;
+    const int lane = threadIdx.x;
+    const int n = lane & 31;
+    const int g = lane >> 5;
+
+    const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
+    const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
+    const int end = __builtin_amdgcn_readfirstlane(min(max(rp[1], beg), a.nnz));
+    const int cnt = end - beg;
+    const int* cols = a.col_idx + beg;
+
+    const size_t head_rows = (size_t)bh * a.kblocks * BLK;
+    const uint8_t* kbase = a.k + head_rows * D / KPACK;
+    const uint8_t* vbase = a.v + head_rows * D / VPACK;
+    const unsigned klane = n * (D / KPACK) + 16 * g;            // this lane's K fragment of step 0, inside a block
+    const unsigned vlane = n * (BLK / VPACK) + 16 / VPACK * g;  // its V^T fragment of channel tile 0
+    const float* skp = a.sk + (size_t)bh * a.kblocks;
+    const float sk_last = uniform_load(skp + a.kblocks - 1);
+    const float* svp = a.sv + (size_t)bh * a.kblocks;
+    float sq_i = a.sq[(size_t)bh * a.kblocks + i] * (QKBITS == 4 ? a.qk_scale * (1.0f / 256.0f) : a.qk_scale);  // 4-bit codes enter times 16
+    const int row = i * BLK + n;
+    const bool row_valid = row < a.n_tokens;
+    v4i qf[KS];
+    if constexpr (QKBITS == 4) {
+        const uint8_t* qrow = a.q + (head_rows + row) * (D / 2) + 16 * g;
+#pragma unroll
+        for (int s = 0; s < KS; s += 2) unpack_nibbles(*(const v4i*)(qrow + 16 * s), qf[s], qf[s + 1]);
+    } else {
+        const uint8_t* qrow = a.q + (head_rows + row) * D + 16 * g;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qf[s] = *(const v4i*)(qrow + 32 * s);
+    }
+
+    v4i kf[KS], kraw[KS / 2];  // K fragments of the next block; 4-bit: 32 channels each, widened in front of the products
+    v4i vf[DT];                // V^T fragments [channel tile]
+    v2u vraw[DT];              // 4-bit V: a lane's 16 slots of a channel
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+        vf[dt] = v4i{0, 0, 0, 0};
+        vraw[dt] = v2u{0, 0};
+    }
+    // lane L of a request fills bytes 16 L of a 1 KB piece: position L % 8 of line L / 8, which holds the line's piece (L % 8) ^ (L / 8)
+    const unsigned kfill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
+    auto load_k = [&](int j) {
+        if constexpr (K_BY_LDS) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): what the slot held has been read
+            const uint8_t* kp = kbase + (size_t)j * (BLK * D);
+            lds_dma16<0>(kp, kfill, kslot);
+            lds_dma16<1024>(kp, kfill, kslot + 1024);
+            lds_dma16<2048>(kp, kfill, kslot + 2048);
+            lds_dma16<3072>(kp, kfill, kslot + 3072);
+            return;
+        }
+        global_bytes kp = (global_bytes)kbase + (size_t)j * (BLK * D / KPACK);
+        unsigned off = klane;
+        asm volatile("" : "+s"(kp), "+v"(off));  // scalar base + lane offset, not a 64-bit address per lane
+#pragma unroll
+        for (int s = 0; s < KS / KPACK; ++s) {
+            if constexpr (QKBITS == 4) kraw[s] = *(const global_v4i*)(kp + off + 32 * s);
+            else kf[s] = *(const global_v4i*)(kp + off + 32 * s);
+        }
+    };
+    auto widen_k = [&]() {  // what was requested, as operands
+        if constexpr (K_BY_LDS) {
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) kf[s] = *(const v4i*)(kslot + 128 * n + 16 * ((2 * s + g) ^ (n & 7)));
+        }
+        if constexpr (QKBITS == 4) {
+#pragma unroll
+            for (int s = 0; s < KS; s += 2) unpack_nibbles(kraw[s / 2], kf[s], kf[s + 1]);
+        }
+    };
+    auto load_v = [&](int j) {
+        global_bytes vp = (global_bytes)vbase + (size_t)j * (BLK * D / VPACK);
+        unsigned off = vlane;
+        asm volatile("" : "+s"(vp), "+v"(off));
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+            if constexpr (PVBITS == 4) vraw[dt] = *(const global_v2u*)(vp + off + 32 * dt * (BLK / 2));
+            else vf[dt] = *(const global_v4i*)(vp + off + 32 * dt * BLK);
+        }
+    };
+    auto widen_v = [&]() {  // codes times 16, undone in the scale; the PARO_VT nibble order makes the bytes come out in slot order
+        if constexpr (PVBITS == 4) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+                vf[dt] = v4i{(int)((vraw[dt].x << 4) & 0xF0F0F0F0u), (int)(vraw[dt].x & 0xF0F0F0F0u),
+                             (int)((vraw[dt].y << 4) & 0xF0F0F0F0u), (int)(vraw[dt].y & 0xF0F0F0F0u)};
+        }
+    };
+
+    // 64 column indices per fetch, one per lane; past the end of the row its last column again
+    auto load_cols = [&](int chunk) { return min(max(cols[min(chunk * 64 + lane_here(), cnt - 1)], 0), a.kblocks - 1); };
+    int cols64 = cnt > 0 ? load_cols(0) : 0;
+    auto column = [&](int u) {  // u advances by one per call
+        if ((u & 63) == 0) cols64 = load_cols(u >> 6);
+        return __builtin_amdgcn_readlane(cols64, u & 63);
+    };
+
+    // a padded row holds +inf, as above
+    float m = row_valid ? -INFINITY : INFINITY, m_ref = m, l = 0.0f;
+    float acc[DT][16];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
+    float held = 0.0f;  // sum of the weights whose `start` the sums still hold
+
+    bool fast = false;
+    int sv_exp = 0;  // the weights are multiplied by 2^sv_exp
+    {
+        float sk_max = 0.0f, sv_max = 0.0f, sv_min = INFINITY;
+        for (int base = 0; base < cnt; base += 64)
+            if (base + lane < cnt) {
+                const int j = base == 0 ? cols64 : min(max(cols[base + lane], 0), a.kblocks - 1);
+                sk_max = fmaxf(sk_max, skp[j]);
+                sv_max = fmaxf(sv_max, svp[j]);
+                sv_min = fminf(sv_min, svp[j]);
+            }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
+            sv_max = fmaxf(sv_max, __shfl_xor(sv_max, off));
+            sv_min = fminf(sv_min, __shfl_xor(sv_min, off));
+        }
+        sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
+        fast = sq_i * sk_max < 0x1p90f;  // as above
+        if (LIFTED) fast = fast && sv_min >= 0x1p-28f * sv_max && sv_max < 0x1p100f && sv_max > 0x1p-60f;
+        sv_exp = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(sv_max));
+    }
+    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
+    if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fast = false;
+    const bool lifted = LIFTED && fast;
+    // start of the P V products, and what a V scale is multiplied by to give a weight (otherwise as above)
+    v16i start;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) start[r] = lifted ? START : 0x3E22F983;
+    asm volatile("" : "+v"(start));
+    const float sv_up = lifted ? ldexpf(1.0f, kWeightUp - sv_exp) : (sv_exp > 90 ? 1.0f : 0x1p13f);
+
+    v16i Sa, Sb;  // raw logits, this block's and the next one's in turn
+    v4i pf = {0, 0, 0, 0};
+    float weight = 0.0f;  // of the product that is still to be added
+    float sk_cur = 0.0f, sv_cur = 0.0f;
+    int j0 = 0, j1 = 0;
+    auto qk = [&](int s, v16i& S) { S = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[s], qf[s], s == 0 ? acc_start() : S, 0, 0, 0); };
+
+    float e = 0.0f;
+    // row maxima and the tile's scale of a block, from its raw logits; `beside` is what keeps the wavefront busy meanwhile
+    auto open = [&](int j, float sk_next, v16i& S, auto beside) __attribute__((always_inline)) {
+        if (j == tail_block) {  // keys past N, as in the kernel above
+            const int real = a.n_tokens - (a.kblocks - 1) * BLK - 4 * (lane_here() >> 5);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                S[r] = 8 * (r >> 2) + (r & 3) >= real ? (int)0xFF800000 : S[r];
+                asm volatile("" : "+v"(S[r]));
+            }
+        }
+        int part[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[r & 3] = max(part[r & 3], S[r]);
+        const float c = sq_i * sk_next;
+        const float ymax = c * start_result(xor32_max(max(max(part[0], part[1]), max(part[2], part[3]))));
+        const float m_new = fmaxf(m, ymax);
+        const unsigned eb = wave_umin(min(0xFF800000u, __float_as_uint(ymax - m_new)));  // a padded row has -inf here
+        beside();
+        e = __uint_as_float(eb);
+        if (__builtin_amdgcn_ballot_w64(m_new - m_ref > 64.0f) != 0) {
+            const float down = __builtin_amdgcn_exp2f(m_ref - m_new);  // first block: 2^-inf = 0 on zero sums
+            l *= down;
+            weight *= down;
+            held *= down;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[dt][r] *= down;
+            m_ref = m_new;
+        }
+        m = m_new;
+    };
+    auto settle = [&]() {  // takes out what the sums hold too much
+        const float extra = held * -(START * 0x1p-149f);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[dt][r] += extra;
+        held = 0.0f;
+    };
+    auto step = [&](auto mode_tag, int t, v16i& S, v16i& N) __attribute__((always_inline)) {
+        constexpr int MODE = decltype(mode_tag)::value;
+        constexpr bool LIFT = LIFTED && MODE != kExact;
+        float c = sq_i * sk_cur;
+        if (MODE == kExact && c < kLogitScaleMin) c = kLogitScaleMin;
+        const float c_up = c * 0x1p26f;
+        const float off_n = (LOG2_QMAXP - kLog2_65535) - m - e;
+        const float w_blk = __builtin_amdgcn_exp2f((-kLog2_65535 - m_ref) - off_n);
+        float E[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            if constexpr (MODE == kScaled) E[r] = fmaf(__int_as_float(S[r]) - kStartF, c_up, off_n);
+            else E[r] = fmaf(start_result(S[r]), c, off_n);
+        }
+        widen_k();
+        widen_v();
+        const int j2 = column(t + 2);
+        auto add = [&](int dt, const v16i& o) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc[dt][r] = fmaf(LIFT ? __int_as_float(o[r]) : __int_as_float(o[r]) - kStartF, weight, acc[dt][r]);
+                asm volatile("" : "+v"(acc[dt][r]));
+            }
+        };
+        v16i o[DT];
+        end_basic_block();
+        __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            if constexpr (D == 64) {
+                if (p < 2) qk(p, N);
+                else o[p - 2] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[p - 2], pf, start, 0, 0, 0);
+            } else {
+                qk(p, N);
+                if (p & 1) o[p >> 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[p >> 1], pf, start, 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 4 * p; r < 4 * p + 4; ++r) E[r] = __builtin_amdgcn_exp2f(E[r]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (p == D / 32 - 1) load_k(j2);
+        }
+        __builtin_amdgcn_s_setprio(0);
+        float sum[4];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[r & 3] = r < 4 ? E[r] : sum[r & 3] + E[r];
+        asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]));
+        add(0, o[0]);
+        add(1, o[1]);
+        if constexpr (D == 128) {
+#pragma unroll
+            for (int dt = 2; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[dt], pf, start, 0, 0, 0);
+        }
+        load_v(j0);
+        j0 = j1;
+        const float sv_now = sv_cur * sv_up * (PVBITS == 4 ? 0.0625f : 1.0f);
+        sk_cur = uniform_load(skp + j0);
+        sv_cur = uniform_load(svp + j0);
+        j1 = j2;
+        open(j0, sk_cur, N, [&]() __attribute__((always_inline)) {
+            if constexpr (D == 128) {
+                add(2, o[2]);
+                add(3, o[3]);
+            }
+            if constexpr (LIFT) held += weight;
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) {
+                const unsigned lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(E[r], E[r + 1]));
+                const unsigned hi = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(E[r + 2], E[r + 3]));
+                pf[r >> 2] = (int)__builtin_amdgcn_perm(hi, lo, 0x06040200u);
+            }
+            asm volatile("" : "+v"(pf));
+            l = fmaf((sum[0] + sum[1]) + (sum[2] + sum[3]), w_blk, l);
+            weight = w_blk * sv_now;
+        });
+    };
+    auto visit_all = [&](auto mode_tag) __attribute__((always_inline)) {
+        constexpr bool LIFT = LIFTED && decltype(mode_tag)::value != kExact;
+        int t = 0;
+        for (; t + 1 < cnt; t += 2) {
+            step(mode_tag, t, Sa, Sb);
+            step(mode_tag, t + 1, Sb, Sa);
+            if (LIFT && (t & (PERIOD - 2)) == PERIOD - 2) settle();
+        }
+        if (t < cnt) step(mode_tag, t, Sa, Sb);
+        if constexpr (LIFT) settle();
+    };
+    if (cnt > 0) {
+        j0 = __builtin_amdgcn_readlane(cols64, 0);
+        j1 = column(1);
+        load_k(j0);
+        sk_cur = uniform_load(skp + j0);
+        sv_cur = uniform_load(svp + j0);
+        widen_k();
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qk(s, Sa);
+        load_k(j1);
+        open(j0, sk_cur, Sa, [] {});
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing pending at the loop's entry: the compiler would wait for it in every pass
+    if (fast) visit_all(std::integral_constant<int, kScaled>{});
+    else visit_all(std::integral_constant<int, kExact>{});
+    if (cnt > 0) {  // the last block's P V, one tile at a time
+        widen_v();
+        const float first = lifted ? START * 0x1p-149f : kStartF;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+            const v16i o = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[dt], pf, start, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[dt][r] = fmaf(__int_as_float(o[r]) - first, weight, acc[dt][r]);
+        }
+    }
+
+    const int ln = lane_here();
+    const int orow_no = i * BLK + (ln & 31);
+    const bool valid = orow_no < a.n_tokens;
+    const float l_tot = (l + __shfl_xor(l, 32)) * 65535.0f;
+    // the sums carry the weights' factor and the spacing of the integers they were read as
+    const float up = lifted ? 0x1p89f : 1.0f;
+    const float inv = (valid && l_tot > 0.0f) ? (lifted ? ldexpf(1.0f, sv_exp) : sv_exp > 90 ? 0x1p26f : 0x1p13f) / l_tot : 0.0f;
+    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, orow_no, valid);
+    if (ooff >= 0) {
+        OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 5);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int qd = 0; qd < 4; ++qd) {
+                float x[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[r] = valid ? (acc[dt][4 * qd + r] * up) * inv : 0.0f;
+                store4(orow + 32 * dt + 8 * qd, x[0], x[1], x[2], x[3]);
+            }
+    }
+}
+
+// -------------------------------------------------------------------------------------------
 // d = 128, block 64, 8-bit Q, K, P and V codes: FOUR wavefronts per row block, 16 queries each, on
 // v_mfma_i32_16x16x64_i8.
 //
@@ -2219,6 +2596,13 @@ static int launch_bf16(int blk, int d, const AttnArgs& a, hipStream_t st) {
     return PARO_OK;
 }
 
+template <int D, int QKBITS, int PVBITS>
+static void launch_b32(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
+    dim3 grid((unsigned)(a.per_xcd * 8));
+    if (out_dtype == PARO_F32) hipLaunchKernelGGL((attn_i8_b32_kernel<D, QKBITS, PVBITS, float>), grid, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((attn_i8_b32_kernel<D, QKBITS, PVBITS, uint16_t>), grid, dim3(64), 0, st, a);
+}
+
 template <int BLK, int D, int QKBITS, int PVBITS>
 static void launch_out(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
     dim3 grid((unsigned)(a.per_xcd * 8));
@@ -2285,8 +2669,8 @@ static void launch_i8(int blk, int d, paro_dtype out_dtype, const AttnArgs& a, h
     }
     if (blk == 64 && d == 64) launch_out<64, 64, QKBITS, PVBITS>(out_dtype, a, st);
     else if (blk == 64 && d == 128) launch_out<64, 128, QKBITS, PVBITS>(out_dtype, a, st);
-    else if (blk == 32 && d == 64) launch_out<32, 64, QKBITS, PVBITS>(out_dtype, a, st);
-    else launch_out<32, 128, QKBITS, PVBITS>(out_dtype, a, st);
+    else if (d == 64) launch_b32<64, QKBITS, PVBITS>(out_dtype, a, st);
+    else launch_b32<128, QKBITS, PVBITS>(out_dtype, a, st);
 }
 
 }  // namespace paro

@@ -30,19 +30,17 @@ def attention_kernel_symbol(w):
     """(mangled symbol, demangled name as the profiler prints it, wavefronts per row-block visit, wavefronts per SIMD, live
     blocks per loop iteration) of the kernel that paro_sparse_attn launches for an integer workload."""
     t, tn = ("t", "unsigned short") if w.dtype == "bf16" else ("f", "float")
-    if w.block == 64 and w.d == 64 and w.bits_qk == 8:
-        return ("_ZN4paro18attn_i8_w64_kernelILi%dE%sLi0EEEvNS_8AttnArgsE" % (w.bits_pv, t),
-                "paro::attn_i8_w64_kernel<%d, %s, 0>" % (w.bits_pv, tn), 1, 2, 2)
-    if w.block == 64 and w.d == 64 and w.bits_qk == 4:
-        return ("_ZN4paro22attn_i8_w64_qk4_kernelILi%dE%sEEvNS_8AttnArgsE" % (w.bits_pv, t),
-                "paro::attn_i8_w64_qk4_kernel<%d, %s>" % (w.bits_pv, tn), 1, 2, 2)
-    if w.block == 64 and w.d == 128 and w.bits_qk == 8 and w.bits_pv == 8:
-        return ("_ZN4paro18attn_i8_q16_kernelI%sEEvNS_8AttnArgsE" % t, "paro::attn_i8_q16_kernel<%s>" % tn, 4, 4, 1)
     if w.block == 32:
         return ("_ZN4paro18attn_i8_b32_kernelILi%dELi%dELi%dE%sEEvNS_8AttnArgsE" % (w.d, w.bits_qk, w.bits_pv, t),
                 "paro::attn_i8_b32_kernel<%d, %d, %d, %s>" % (w.d, w.bits_qk, w.bits_pv, tn), 1, 3 if w.d == 64 else 2, 2)
-    return ("_ZN4paro14attn_i8_kernelILi%dELi%dELi%dELi%dE%sLi0EEEvNS_8AttnArgsE" % (w.block, w.d, w.bits_qk, w.bits_pv, t),
-            "paro::attn_i8_kernel<%d, %d, %d, %d, %s, 0>" % (w.block, w.d, w.bits_qk, w.bits_pv, tn), w.block // 32, 3 if w.d == 64 else 2, 1)
+    if w.d == 128 or w.B * w.nh * w.k <= 1536:
+        return ("_ZN4paro18attn_i8_q16_kernelILi%dELi%dELi%dE%sLi0EEEvNS_8AttnArgsE" % (w.d, w.bits_qk, w.bits_pv, t),
+                "paro::attn_i8_q16_kernel<%d, %d, %d, %s, 0>" % (w.d, w.bits_qk, w.bits_pv, tn), 4, 4, 2)
+    if w.bits_qk == 8:
+        return ("_ZN4paro18attn_i8_w64_kernelILi%dE%sLi0EEEvNS_8AttnArgsE" % (w.bits_pv, t),
+                "paro::attn_i8_w64_kernel<%d, %s, 0>" % (w.bits_pv, tn), 1, 2, 2)
+    return ("_ZN4paro22attn_i8_w64_qk4_kernelILi%dE%sEEvNS_8AttnArgsE" % (w.bits_pv, t),
+            "paro::attn_i8_w64_qk4_kernel<%d, %s>" % (w.bits_pv, tn), 1, 2, 2)
 
 
 def ordinary_loop(loops):

@@ -99,7 +99,7 @@ def loop_instruction_counts(asm: str) -> dict:
     """{kernel symbol: [ {class: count per loop iteration}, ... one entry per innermost loop that holds matrix
     instructions ]} from the compiler's assembly listing.  Loop blocks that are rarely taken branches are left out."""
     out = {}
-    for m in re.finditer(r"^(_ZN4paro\w*attn\w+):[^\n]*\n(.*?)\n\.Lfunc_end", asm, re.S | re.M):
+    for m in re.finditer(r"^(_ZN4paro\w*attn\w+):[^\n]*\n(.*?)(?:\n\.Lfunc_end|\Z)", asm, re.S | re.M):
         name, body = m.group(1), m.group(2)
         loops, label, header = {}, None, None
         for line in body.split("\n"):

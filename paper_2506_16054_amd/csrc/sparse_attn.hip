@@ -2,32 +2,28 @@
 // INT8 / INT4 PV under block-wise scales (paper Sec. 4.2 (2) and Sec. 4.3), for gfx950.
 //
 // Work split.  One workgroup owns one row block (BLK queries) of one head and walks that row's
-// compacted live-block list in ascending order.  In attn_i8_kernel a wavefront owns 32 queries; BLK = 64 uses two
-// wavefronts, BLK = 32 one.  Both products run on v_mfma_i32_32x32x32_i8 in the transposed
-// orientation
-//        S^T (keys x queries)   = K_j (A operand, from LDS)   x Q_i^T (B operand, registers)
-//        O^T (channels x queries) = V_j^T (A operand, from LDS) x P^T   (B operand, registers)
+// compacted live-block list in ascending order.  Integer codes have three kernels: attn_i8_w64_kernel (d = 64, block 64, many row
+// blocks: one wavefront of 64 queries), attn_i8_q16_kernel (d = 128, block 64, and d = 64 with few row blocks: four wavefronts of
+// 16) and attn_i8_b32_kernel (block 32: one wavefront of 32).  Both products run on v_mfma_i32_32x32x32_i8 (16x16x64 with 16
+// queries) in the transposed orientation
+//        S^T (keys x queries)   = K_j (A operand)   x Q_i^T (B operand, registers)
+//        O^T (channels x queries) = V_j^T (A operand) x P^T   (B operand, registers)
 // because the accumulator layout of a 32x32 result tile gives every lane 16 values of ONE
 // query (keys 8q + 4g + p of the tile, q,p = 0..3, g = lane / 32): row reductions of the
 // softmax are in-lane plus one cross-lane step, and the 16 quantized probabilities pack into
 // exactly the four registers the next matrix instruction wants as its B operand.  The key
 // order this imposes on the contraction is matched by the PARO_VT storage order of V, so V
-// fragments are plain 16-byte LDS reads.
-//
-// Pipeline (of attn_i8_kernel; the kernels for one shape each state theirs).  K_j and V_j^T tiles travel HBM/L2 -> registers -> LDS through a ring of two LDS
-// stages, with the global loads issued two blocks ahead of the math and ONE workgroup barrier
-// per live block; the barrier also carries the cross-wavefront exchange of the P-tile maximum
-// (the P quantization group is the whole BLK x BLK tile).  Cross-lane reductions use DPP,
+// fragments are plain 16-byte reads.  The P quantization group is the whole BLK x BLK tile; cross-lane reductions use DPP,
 // v_permlane32_swap and scalar reads, never LDS.
 //
 // Arithmetic per live block (X in log2 units, c = sq_i * sk_j * log2(e) / sqrt(d)):
 //   m' = max(m, c * rowmax S)  (the row maximum is taken on the integers, c > 0);  e = max over valid rows of (c * rowmax S - m')   (<= 0)
 //   E  = qmaxP * 2^(c*S - m' - e)  in (0, qmaxP]  ->  Pc = round-half-even(E), two codes per
 //        v_cvt_pknorm_u16_f32 (E is formed pre-divided by 65535), four codes packed by one v_perm_b32.
-//        The exponent is ONE fma on the raw accumulator register: the register read as a float is B + S
-//        (B = 1.5 * 2^23, see int_result), so c*S + off = c*(B + S) + (off - c*B); the offset off - c*B is
+//        Folded form (8-bit P codes at block 64): the exponent is ONE fma on the raw accumulator register, which read as a float
+//        is B + S in units of 2^-26 (B = kStartI), so c*S + off = c*(B + S) + (off - c*B); the offset off - c*B is
 //        rounded to binary32 once per row and block, and that rounding (at most half an ulp of c*B, about
-//        1e-4 relative in E) is computed exactly and returned to the block's weight, so the sums see the
+//        1e-4 relative in E) is computed and returned to the block's weight, so the sums see the
 //        scale the codes were really formed with,
 //   l  = l * 2^(m - m') + sP * rowsum(E),  sP = 2^e / qmaxP   (the P tile maximum over qmaxP)
 //   acc = acc * 2^(m - m') + (sP * sv_j) * float(Pc V_j)
@@ -59,12 +55,14 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 constexpr int kTimelineSlots = 1 << 16;
 constexpr int kTimelineFields = 8;  // start, end (constant-rate clock), column blocks, shader cycles of phases 0..4
 __device__ long long timeline_records[kTimelineSlots][kTimelineFields];
-#define PARO_TIMELINE_BEGIN                                \
-    const long long timeline_start = wall_clock64();       \
-    long long timeline_last = clock64(), timeline_phase[5] = {0, 0, 0, 0, 0};
+// (on: whether this instantiation records; some have no registers to hold it)
+#define PARO_TIMELINE_BEGIN(on)                                      \
+    constexpr bool timeline_on = on;                                 \
+    const long long timeline_start = timeline_on ? wall_clock64() : 0; \
+    long long timeline_last = timeline_on ? clock64() : 0, timeline_phase[5] = {0, 0, 0, 0, 0};
 // closes phase i of the block loop (shader clock at issue, not at completion, of the instructions in front of it)
 #define PARO_TIMELINE_PHASE(i)                             \
-    {                                                      \
+    if constexpr (timeline_on) {                           \
         const long long now_ = clock64();                  \
         timeline_phase[i] += now_ - timeline_last;         \
         timeline_last = now_;                              \
@@ -77,12 +75,12 @@ __device__ long long timeline_records[kTimelineSlots][kTimelineFields];
         timeline_records[slot][2] = (blocks);                                         \
     }
 #define PARO_TIMELINE_END(slot, lane, blocks)                                         \
-    PARO_TIMELINE_STOP(slot, lane, blocks)                                            \
-    if ((lane) == 0 && (slot) < kTimelineSlots) {                                     \
+    if constexpr (timeline_on) { PARO_TIMELINE_STOP(slot, lane, blocks) }             \
+    if (timeline_on && (lane) == 0 && (slot) < kTimelineSlots) {                      \
         for (int f_ = 0; f_ < 5; ++f_) timeline_records[slot][3 + f_] = timeline_phase[f_]; \
     }
 #else
-#define PARO_TIMELINE_BEGIN
+#define PARO_TIMELINE_BEGIN(on)
 #define PARO_TIMELINE_PHASE(i)
 #define PARO_TIMELINE_STOP(slot, lane, blocks)
 #define PARO_TIMELINE_END(slot, lane, blocks)
@@ -156,13 +154,10 @@ __device__ inline unsigned wave_umin(unsigned x) {
     return min(r0, r1);
 }
 
-// Integer matrix results become floats without a convert instruction: every accumulator chain
-// starts at the bit pattern of 1.5 * 2^23, so the register read as a float is 1.5 * 2^23 + result
-// exactly (|result| <= 127*127*128 < 2^22) and one subtraction on the full-rate fp32 pipe
-// recovers the result, bit-identical to v_cvt_f32_i32.
-constexpr int kAccBiasI = 0x4B400000;
-constexpr float kAccBiasF = 12582912.0f;
-__device__ inline float int_result(int raw) { return __int_as_float(raw) - kAccBiasF; }
+// The folded exponent is taken where the logit scales of the row block's tiles keep the rounding of its offset small:
+// c * 1.5 * 2^23 < 2^13 for the largest K scale among the live column blocks, i.e. at most 2^-12 in the exponent.  Row blocks whose inputs
+// have an unusual magnitude take the exact form.  The decision is the same in every lane of the workgroup (one row block, one list).
+constexpr float kFoldBound = 12582912.0f;
 
 // Smallest scale of a block of logits that may meet the -inf of a masked key: scales of Q and K that are both of some 2^-75 have a product
 // of 0, and 0 times -inf is NaN.  Rows whose scale in the ragged block is below it take the exact form of the exponent, which
@@ -171,8 +166,7 @@ constexpr float kLogitScaleMin = 0x1p-126f;
 
 // The scale of a column block is the same for every lane and is written by the quantizer before this kernel
 // starts: read through the constant address space it becomes a scalar load, needs no vector register while it is
-// carried from one block to the next, and enters its one multiplication as a scalar operand.  Used by the kernel
-// with four wavefronts per row block (-1.4 % there) and by the one-wavefront kernel, which has no registers to spare.
+// carried from one block to the next, and enters its one multiplication as a scalar operand.
 __device__ inline float uniform_load(const float* p) { return *(const __attribute__((address_space(4))) float*)(unsigned long long)p; }
 
 // 1: with 8-bit P codes the accumulator bias of the logits is folded into the offset of the exponent's
@@ -181,9 +175,6 @@ __device__ inline float uniform_load(const float* p) { return *(const __attribut
 // by up to a seventh of its largest term, so that mode always keeps the exact exponent.
 #ifndef PARO_FOLD_LOGIT_BIAS
 #define PARO_FOLD_LOGIT_BIAS 1
-#endif
-#ifndef PARO_ATTN_WAVES_D64
-#define PARO_ATTN_WAVES_D64 3  // wavefronts per SIMD the register allocation must allow, d = 64
 #endif
 
 // 16 bytes of packed 4-bit codes -> 32 signed bytes holding the codes times 16: a nibble moved to
@@ -197,450 +188,13 @@ __device__ inline void unpack_nibbles(const v4i x, v4i& first, v4i& second) {
     second = v4i{lo.z, hi.z, lo.w, hi.w};
 }
 
-// QSRC selects where this row block's Q operand comes from: 0 = codes and scale written by the
-// quantizer; 1 (bf16) / 2 (fp32) = the unquantized Q tensor in the default token order, in which case
-// the workgroup reorders and quantizes its own 64 x d block on the way in - the quantization group of
-// Q is exactly the row block a workgroup owns (Sec. 4.3 (1)), so no other workgroup needs the result.
-template <int BLK, int D, int QKBITS, int PVBITS, typename OutT, int QSRC = 0>
-__global__ __launch_bounds__(BLK * 2, (D == 64 ? PARO_ATTN_WAVES_D64 : 2)) void attn_i8_kernel(AttnArgs a) {
-    static_assert(QSRC == 0 || QKBITS == 8, "in-kernel quantization of Q produces 8-bit codes");
-    constexpr int NW = BLK / 32;
-    constexpr int NT = 64 * NW;
-    constexpr int KSTR = D + 16;    // padded LDS row strides: rows 16 B apart in bank space
-    constexpr int VSTR = BLK + 16;
-    constexpr int KBYTES = BLK * KSTR;
-    constexpr int VBYTES = D * VSTR;
-    constexpr int STAGE = KBYTES + VBYTES;
-    constexpr int VPACK = PVBITS == 4 ? 2 : 1;
-    constexpr int KPACK = QKBITS == 4 ? 2 : 1;
-    constexpr int NKC = BLK * D / KPACK / 16 / NT;  // 16-byte pieces of a K tile per thread
-    constexpr int NVC = BLK * D / VPACK / 16 / NT;  // 16-byte pieces of a V tile per thread
-    constexpr int KS = D / 32;    // contraction steps of QK^T
-    constexpr int KT = BLK / 32;  // 32-key tiles per block
-    constexpr int DT = D / 32;    // 32-channel tiles of the output
-    constexpr float QMAXP = PVBITS == 4 ? 7.0f : 127.0f;
-    constexpr float LOG2_QMAXP = PVBITS == 4 ? 2.807354922057604f : 6.988684686772166f;
-    static_assert(NKC >= 1 && NVC >= 1, "tile too small for the workgroup");
-
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE];
-    __shared__ unsigned tile_e[2][NW];
-    __shared__ float q_amax[NW];
-
-    // Workgroups are dealt to the 8 XCDs round-robin; give each XCD a contiguous range of
-    // (head, row block) so the K/V of the heads it works on stay in its own L2.
-    const int wg = blockIdx.x;
-    const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
-    if (logical >= a.total_wg) return;
-    const int item = a.row_order ? min(max(a.row_order[logical], 0), a.total_wg - 1) : logical;
-    const int bh = item / a.kblocks;
-    const int i = item - bh * a.kblocks;
-    const int h = bh % a.nh;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int w = tid >> 6;
-    const int n = lane & 31;
-    const int g = lane >> 5;
-
-    const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
-    // (the same for every lane: kept in scalar registers, so the loop control costs no vector work)
-    const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
-    const int end = __builtin_amdgcn_readfirstlane(min(max(rp[1], beg), a.nnz));
-    const int cnt = end - beg;
-    const int* cols = a.col_idx + beg;
-    // A row block that attends more than half of all column blocks (text rows of an image model,
-    // Sec. 4.2 (1)) is on the critical path of the launch: its blocks are visited one after the other,
-    // so its wavefronts get issue priority over the short rows they share a SIMD with.
-    if (2 * cnt > a.kblocks) __builtin_amdgcn_s_setprio(2);
-
-    const size_t head_rows = (size_t)bh * a.kblocks * BLK;
-    const int row = i * BLK + 32 * w + n;  // this lane's query, in the reordered sequence
-    const bool row_valid = row < a.n_tokens;
-    const uint8_t* kbase = a.k + head_rows * D / KPACK;
-    const uint8_t* vbase = a.v + head_rows * D / VPACK;
-    const float* skp = a.sk + (size_t)bh * a.kblocks;
-    const float* svp = a.sv + (size_t)bh * a.kblocks;
-    v4i qf[KS];
-    float sq_i = 0.0f;
-    float x[QSRC != 0 ? KS : 1][16];  // this lane's slice of the unquantized row (QSRC != 0)
-    if constexpr (QSRC != 0) {
-        // ---- reorder + quantize this row block of Q here (same arithmetic as the quantizer:
-        // absmax over real rows, scale = absmax / 127 in binary32, code = rint(fl32(x / scale))).
-        // The loads are issued now; the reduction finishes behind the first K/V tile loads.
-        using RawT = std::conditional_t<QSRC == 1, uint16_t, float>;
-        const RawT* qsrc = (const RawT*)a.q + ((size_t)bh * a.n_tokens + (row_valid ? reorder_source(a.table, h, row) : 0)) * D + 16 * g;
-        float amax = 0.0f;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            if (row_valid) {
-                if constexpr (QSRC == 1) {
-                    const uint4 lo = *(const uint4*)(qsrc + 32 * s), hi = *(const uint4*)(qsrc + 32 * s + 8);
-                    const unsigned wv[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        x[s][2 * e] = __uint_as_float(wv[e] << 16);
-                        x[s][2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u);
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float4 f = *(const float4*)(qsrc + 32 * s + 4 * e);
-                        x[s][4 * e] = f.x;
-                        x[s][4 * e + 1] = f.y;
-                        x[s][4 * e + 2] = f.z;
-                        x[s][4 * e + 3] = f.w;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) x[s][e] = 0.0f;
-            }
-#pragma unroll
-            for (int e = 0; e < 16; ++e) amax = fmaxf(amax, fabsf(x[s][e]));
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
-        if (lane == 0) q_amax[w] = amax;  // exchanged across the barrier that opens the block loop
-    } else if constexpr (QKBITS == 4) {
-        // 4-bit Q and K codes both enter the product times 16
-        sq_i = a.sq[(size_t)bh * a.kblocks + i] * a.qk_scale * (1.0f / 256.0f);
-        const uint8_t* qrow = a.q + ((head_rows + row) * D + 16 * g) / 2;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const uint2 x = *(const uint2*)(qrow + 16 * s);  // 16 codes of this lane's contraction slice
-            v4i unused;
-            unpack_nibbles(v4i{(int)x.x, (int)x.y, 0, 0}, qf[s], unused);
-        }
-    } else {
-        sq_i = a.sq[(size_t)bh * a.kblocks + i] * a.qk_scale;
-        const uint8_t* qrow = a.q + (head_rows + row) * D + 16 * g;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s] = *(const v4i*)(qrow + 32 * s);
-    }
-
-    // Column indices of the live list are fetched 64 at a time, one per lane, one chunk ahead;
-    // the column of block t is then a lane read, not a memory access on the per-block path.
-    auto load_cols = [&](int chunk) {
-        const int idx = min(chunk * 64 + lane, cnt - 1);
-        return cnt > 0 && chunk * 64 < cnt ? min(max(cols[idx], 0), a.kblocks - 1) : 0;
-    };
-    int cols_cur = load_cols(0), cols_nxt = load_cols(1);
-    int cur_chunk = 0;
-    auto col_of = [&](int t) {  // valid for t in chunk cur_chunk or cur_chunk + 1
-        return (t >> 6) == cur_chunk ? __builtin_amdgcn_readlane(cols_cur, t & 63) : __builtin_amdgcn_readlane(cols_nxt, t & 63);
-    };
-
-    v4i kreg[NKC], vreg[NVC];
-    int j_reg = 0;  // column block whose tiles sit in kreg / vreg (wave-uniform)
-    auto gload = [&](int t) {
-        const int j = col_of(t);
-        j_reg = j;
-        const uint8_t* kp = kbase + (size_t)j * (BLK * D / KPACK);
-        const uint8_t* vp = vbase + (size_t)j * (BLK * D / VPACK);
-#pragma unroll
-        for (int c = 0; c < NKC; ++c) kreg[c] = *(const v4i*)(kp + 16 * (tid + NT * c));
-#pragma unroll
-        for (int c = 0; c < NVC; ++c) vreg[c] = *(const v4i*)(vp + 16 * (tid + NT * c));
-    };
-    // LDS store offsets of this thread's 16-byte pieces: piece c lies a whole number of rows below
-    // piece 0, so one address per tile and stage serves all pieces through immediate offsets.
-    constexpr int KROWB = D / KPACK, VROWB = BLK / VPACK;  // bytes of one stored row in global memory
-    static_assert((16 * NT) % KROWB == 0 && (16 * NT) % VROWB == 0, "pieces must be whole rows apart");
-    const int k_off = ((16 * tid) / KROWB) * KSTR + KPACK * ((16 * tid) % KROWB);
-    const int v_off = KBYTES + ((16 * tid) / VROWB) * VSTR + VPACK * ((16 * tid) % VROWB);
-    auto lstore_k = [&](int stage) {
-        uint8_t* dst0 = lds + stage * STAGE + k_off;
-#pragma unroll
-        for (int c = 0; c < NKC; ++c) {
-            uint8_t* dst = dst0 + c * (16 * NT / KROWB) * KSTR;
-            if constexpr (QKBITS == 4) {  // 16 packed bytes = 32 channels of one key
-                v4i first, second;
-                unpack_nibbles(kreg[c], first, second);
-                *(v4i*)dst = first;
-                *(v4i*)(dst + 16) = second;
-            } else {
-                *(v4i*)dst = kreg[c];
-            }
-        }
-    };
-    auto lstore_v = [&](int stage) {
-        uint8_t* dst0 = lds + stage * STAGE + v_off;
-#pragma unroll
-        for (int c = 0; c < NVC; ++c) {
-            uint8_t* dst = dst0 + c * (16 * NT / VROWB) * VSTR;
-            if constexpr (PVBITS == 4) {
-                // 16 packed bytes = 32 slots of one channel (the PARO_VT nibble order makes the
-                // unpacked bytes land in slot order)
-                v4i first, second;
-                unpack_nibbles(vreg[c], first, second);
-                *(v4i*)dst = first;
-                *(v4i*)(dst + 16) = second;
-            } else {
-                *(v4i*)dst = vreg[c];
-            }
-        }
-    };
-
-    float m = -INFINITY;  // running row maximum, log2 units
-    float m_ref = -INFINITY;  // the maximum the stored sums are expressed against (set by the first block)
-    constexpr float kLog2_65535 = 15.999977986052736f;
-    float w_base = INFINITY;  // -log2(65535) - m_ref
-    float l = 0.0f;       // this lane's share of the running denominator, divided by 65535 * 2^(m - m_ref)
-    float acc[DT][16];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
-
-    // Start value of every integer accumulator chain, held in registers for the whole loop.
-    v16i acc_init;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc_init[r] = kAccBiasI;
-    asm volatile("" : "+v"(acc_init));  // opaque to the optimizer: not re-created per block
-
-    // LDS ring of two stages, one barrier per live block (placed after the row maxima):
-    //   K_{t+1} is stored at the top of iteration t  - every wavefront finished reading K_{t-1}
-    //                                                  before barrier t-1;
-    //   V_{t+1} is stored right after barrier t      - every wavefront finished reading V_{t-1}
-    //                                                  before it arrived at barrier t;
-    //   the registers are refilled from global memory (block t+2) after both stores.
-    // The scales of a block are fetched one block ahead of their use (behind the barrier of the block
-    // before), straight into the registers the next iteration reads: its column index is carried in a
-    // scalar register from the tile prefetch, so nothing per lane rotates from block to block.
-    float sk_cur = 0.0f, sv_cur = 0.0f;  // scales of block t
-    if (cnt > 0) {
-        gload(0);
-        lstore_k(0);
-        lstore_v(0);
-        sk_cur = skp[j_reg];
-        sv_cur = svp[j_reg];
-    }
-    if (cnt > 1) gload(1);
-    __syncthreads();
-    if constexpr (QSRC != 0) {
-        float amax = q_amax[0];
-#pragma unroll
-        for (int ww = 1; ww < NW; ++ww) amax = fmaxf(amax, q_amax[ww]);
-        const float scale = amax > 0.0f ? amax / 127.0f : 1.0f;
-        const GroupDivider quotient(scale);
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                unsigned word = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float r = fminf(fmaxf(rintf(quotient(x[s][4 * e4 + e])), -127.0f), 127.0f);
-                    word |= ((unsigned)(int)r & 0xffu) << (8 * e);
-                }
-                qf[s][e4] = (int)word;
-            }
-        }
-        sq_i = scale * a.qk_scale;
-    }
-
-    int stage = 0;
-    // One live block.  TAIL selects the variant that masks keys past N (only the last column
-    // block of a ragged sequence needs it; keeping it out of the common path saves two
-    // instructions per logit).
-    auto step = [&](auto tail_tag, auto fold_tag, int t) {
-        constexpr bool TAIL = decltype(tail_tag)::value;
-        constexpr bool FOLD = decltype(fold_tag)::value;
-        const int next = stage ^ 1;
-        if (t + 1 < cnt) lstore_k(next);
-
-        const float c = sq_i * sk_cur;
-        const uint8_t* ks = lds + stage * STAGE;
-        const uint8_t* vs = ks + KBYTES;
-
-        // ---- S^T = K_j Q_i^T (i32, biased)
-        v16i sacc[KT];
-#pragma unroll
-        for (int T = 0; T < KT; ++T) {
-            sacc[T] = acc_init;
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const v4i kf = *(const v4i*)(ks + (32 * T + n) * KSTR + 32 * s + 16 * g);
-                sacc[T] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf, qf[s], sacc[T], 0, 0, 0);
-            }
-        }
-        // Raw accumulator value of a masked logit: it loses every maximum (real values carry the
-        // accumulator bias); its exponential is forced to zero below.
-        constexpr int kMaskedS = 0;
-        if constexpr (TAIL) {  // keys past N never receive probability mass
-            const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
-#pragma unroll
-            for (int T = 0; T < KT; ++T)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (32 * T + 8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) sacc[T][r] = kMaskedS;
-        }
-
-        // ---- running maximum (on the raw integers: c > 0) and the tile's quantization scale
-        int part[4] = {kMaskedS, kMaskedS, kMaskedS, kMaskedS};
-#pragma unroll
-        for (int T = 0; T < KT; ++T)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part[r & 3] = max(part[r & 3], sacc[T][r]);
-        const float ymax = c * int_result(xor32_max(max(max(part[0], part[1]), max(part[2], part[3]))));
-        const float m_new = fmaxf(m, ymax);
-        // e = log2 of the largest entry of the Pt tile = max over valid rows of (row maximum of
-        // the block - running maximum), always <= 0; reduced as an unsigned minimum of bit patterns
-        unsigned eb = wave_umin(row_valid ? __float_as_uint(ymax - m_new) : 0xFF800000u);
-        if constexpr (NW > 1) {
-            if (lane == 0) tile_e[t & 1][w] = eb;
-        }
-        __syncthreads();
-        // scales of block t+1 (j_reg still names it: the prefetch of block t+2 comes below)
-        // (behind the last block it names that block again: a harmless reload)
-        const float sk_next = skp[j_reg], sv_next = svp[j_reg];
-        if (t + 1 < cnt) lstore_v(next);
-        if (((t + 2) & 63) == 0) {  // block t+2 opens a new chunk of 64 column indices
-            cols_cur = cols_nxt;
-            ++cur_chunk;
-            cols_nxt = load_cols(cur_chunk + 1);
-        }
-        if (t + 2 < cnt) gload(t + 2);
-        if constexpr (NW > 1) {
-#pragma unroll
-            for (int ww = 0; ww < NW; ++ww) eb = min(eb, tile_e[t & 1][ww]);
-        }
-        const float e = __uint_as_float(eb);
-        // The first block of a row finds m_ref = -inf: growth = +inf takes the branch below, which
-        // scales the (zero) sums by 2^-inf = 0 and makes the block's maximum the reference.
-        const float growth = m_new - m_ref;
-        if (__builtin_amdgcn_ballot_w64(growth > 64.0f) != 0) {  // keep the stored sums far from overflow
-            const float down = __builtin_amdgcn_exp2f(-growth);
-            l *= down;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[dt][r] *= down;
-            m_ref = m_new;
-            w_base = -kLog2_65535 - m_new;
-        }
-        m = m_new;
-
-        // ---- E = qmaxP * 2^(X - m' - e); row sum; round half to even and pack as B operand
-        float rs = 0.0f;
-        v4i pf[KT];
-        // E is formed divided by 65535, so that v_cvt_pknorm_u16_f32 (which rounds x * 65535 to the
-        // nearest 16-bit integer, two values per instruction) yields the codes; one byte permute
-        // packs four of them.  The row sum carries the same factor, undone once per row.
-        // Exponent offset: X - m' - e + log2(qmaxP) - log2(65535): the tile maximum maps to qmaxP / 65535.
-        const float off_n = (LOG2_QMAXP - kLog2_65535) - m_new - e;
-        // weight of this block's terms in the stored sums, sP * 2^(m' - m_ref) = 2^(e + m' - m_ref - log2(qmaxP)),
-        // written against the offset above: the part that depends on m_ref alone changes only with m_ref
-        float off_f = off_n, w_blk;
-        if constexpr (FOLD) {
-            // c * (B + S) + off_f with off_f = fl(off_n - c*B).  c*B = cb_hi + cb_lo exactly (fma residual) and
-            // off_n - cb_hi = off_f + terr exactly (two-sum), so E comes out as E_exact * 2^delta with
-            // delta = cb_lo - terr known exactly; the block's weight takes the factor 2^-delta.
-            const float cb_hi = c * kAccBiasF;
-            const float cb_lo = fmaf(c, kAccBiasF, -cb_hi);
-            off_f = off_n - cb_hi;
-            const float bb = off_f - off_n;
-            const float terr = (off_n - (off_f - bb)) + (-cb_hi - bb);
-            w_blk = __builtin_amdgcn_exp2f((w_base - off_n) - (cb_lo - terr));
-        } else {
-            w_blk = __builtin_amdgcn_exp2f(w_base - off_n);
-        }
-        // All exponentials of the block first (in place of the raw logits), then the row sum as four independent
-        // chains and the conversions: neighbouring instructions do not wait for each other's results.
-        float ev[KT][16];
-#pragma unroll
-        for (int T = 0; T < KT; ++T)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                ev[T][r] = __builtin_amdgcn_exp2f(fmaf(FOLD ? __int_as_float(sacc[T][r]) : int_result(sacc[T][r]), c, off_f));
-                if constexpr (TAIL) {
-                    if (32 * T + 8 * (r >> 2) + 4 * g + (r & 3) >= a.n_tokens - (a.kblocks - 1) * BLK) ev[T][r] = 0.0f;
-                }
-            }
-        float part_sum[4];
-#pragma unroll
-        for (int T = 0; T < KT; ++T)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part_sum[r & 3] = (T == 0 && r < 4) ? ev[T][r] : part_sum[r & 3] + ev[T][r];
-        rs = (part_sum[0] + part_sum[1]) + (part_sum[2] + part_sum[3]);
-#pragma unroll
-        for (int T = 0; T < KT; ++T)
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                // (the builtin, not inline assembly: the instruction consumes results of the
-                // transcendental unit, and only instructions the compiler can see get the wait state
-                // that this needs when they follow the exponential directly)
-                const unsigned lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(ev[T][4 * qd], ev[T][4 * qd + 1]));
-                const unsigned hi = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(ev[T][4 * qd + 2], ev[T][4 * qd + 3]));
-                pf[T][qd] = (int)__builtin_amdgcn_perm(hi, lo, 0x06040200u);
-            }
-        l = fmaf(rs, w_blk, l);  // rs carries the factor 1/65535; it is undone once, at the end
-
-        // ---- O^T += (sP sv_j 2^(m' - m_ref)) V_j^T P^T
-        const float sv_eff = w_blk * sv_cur * (PVBITS == 4 ? 0.0625f : 1.0f);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-            v16i o = acc_init;
-#pragma unroll
-            for (int T = 0; T < KT; ++T) {
-                const v4i vf = *(const v4i*)(vs + (32 * dt + n) * VSTR + 32 * T + 16 * g);
-                o = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, pf[T], o, 0, 0, 0);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[dt][r] = fmaf(int_result(o[r]), sv_eff, acc[dt][r]);
-        }
-        sk_cur = sk_next;
-        sv_cur = sv_next;
-        stage = next;
-    };
-
-    // col_of(cnt - 1) is only addressable while its chunk is current, so the ragged-tail test
-    // reads the list directly (once per workgroup).
-    const bool has_tail = (a.n_tokens % BLK) != 0 && cnt > 0 && min(max(cols[cnt - 1], 0), a.kblocks - 1) == a.kblocks - 1;
-    const int cnt_main = has_tail ? cnt - 1 : cnt;
-    // The folded form of the exponent is taken where the logit scales of the row block's tiles keep the
-    // rounding of its offset small: c * B < 2^13 for the largest K scale among the live column blocks, i.e.
-    // at most 2^-12 in the exponent.  Row blocks whose inputs have an unusual magnitude take the exact
-    // form.  The decision is the same in every lane of the workgroup (one row block, one list).
-    constexpr bool FOLDABLE = PARO_FOLD_LOGIT_BIAS && PVBITS == 8;
-    bool fold = false;
-    if constexpr (FOLDABLE) {
-        float sk_max = 0.0f;
-        for (int base = 0; base < cnt; base += 64)
-            if (base + lane < cnt) sk_max = fmaxf(sk_max, skp[min(max(cols[base + lane], 0), a.kblocks - 1)]);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
-        fold = sq_i * sk_max * kAccBiasF < 8192.0f;
-    }
-    auto visit_all = [&](auto fold_tag) {
-        for (int t = 0; t < cnt_main; ++t) step(std::false_type{}, fold_tag, t);
-        if (has_tail) step(std::true_type{}, fold_tag, cnt - 1);
-    };
-    if (fold) visit_all(std::bool_constant<FOLDABLE>{});
-    else visit_all(std::false_type{});
-
-    // ---- finalize: divide by the denominator, store the row (zeros for padded rows)
-    const float l_tot = (l + __shfl_xor(l, 32)) * 65535.0f;
-    const float inv = (row_valid && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
-    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row_valid);
-    if (ooff >= 0) {
-        OutT* orow = (OutT*)a.op + ooff + 4 * g;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd)
-                store4(orow + 32 * dt + 8 * qd, acc[dt][4 * qd] * inv, acc[dt][4 * qd + 1] * inv, acc[dt][4 * qd + 2] * inv,
-                       acc[dt][4 * qd + 3] * inv);
-    }
-}
-
 // -------------------------------------------------------------------------------------------
 // d = 64, block 64, 8-bit Q and K codes (P and V 8-bit or 4-bit): ONE wavefront per row block, no barrier.
 //
 // The wavefront owns all 64 queries of the row block as two halves of 32 (H = 0, 1; a lane holds query
 // n of each half).  The P quantization group - the whole 64 x 64 tile - then lives in one wavefront: its
 // maximum is an in-wave reduction, nothing is exchanged between wavefronts and nothing has to be
-// synchronised.  Per block and half the arithmetic is that of attn_i8_kernel.
+// synchronised.
 //
 // What bounds it: issue slots and, under sustained load, the energy of a block (the card holds 1 380 W of its 1 400 W limit
 // throughout and lowers the clock, 2.4 -> about 2.1 GHz), so both instructions and bytes moved on the chip count.  Two
@@ -662,9 +216,6 @@ __global__ __launch_bounds__(BLK * 2, (D == 64 ? PARO_ATTN_WAVES_D64 : 2)) void 
 // summed issue cost.  Sustained, us per call with the quantizer: 48 heads of 17550 tokens at 30 % 1 175 -> 1 089, 30 heads
 // at 50 % 1 196 -> 1 090; 48 heads at 20 % with 4-bit P and V 840 -> 791, all 4-bit 839 -> 807.
 // -------------------------------------------------------------------------------------------
-#ifndef PARO_ATTN_SINGLE_WAVE
-#define PARO_ATTN_SINGLE_WAVE 1
-#endif
 
 // Lane L's 16 bytes at base + lane_off + OFFSET land at lds_dst + 16 L (lds_dst wave-uniform, lds_dst >= OFFSET
 // bytes into its array).  The instruction's immediate offset moves the global AND the LDS address, so the LDS
@@ -723,7 +274,7 @@ __device__ inline float start_result(int raw) { return fmaf(__int_as_float(raw),
 // place of off_n: the second fma cancels to off_n plus that).  Left to the compiler, the product was rounded by itself in one of the
 // two halves, and kStartI has 24 significant bits: that is no less than the difference's own rounding.  Error against binary64, fp32
 // outputs of 8-bit codes, all heads of 17550 tokens: 48 heads at 30 % 3.41e-4 -> 3.15e-4, 30 heads at 50 % 3.40e-4 -> 3.14e-4, 30 heads with
-// 4-bit Q and K at 30 % 3.58e-4 -> 3.34e-4 (with attn_i8_kernel's start value 3.19e-4, 3.18e-4 and 3.91e-4).
+// 4-bit Q and K at 30 % 3.58e-4 -> 3.34e-4 (with a start of 1.5 * 2^23 3.19e-4, 3.18e-4 and 3.91e-4).
 __device__ __forceinline__ float folded_offset(float off_n, float c_up, float& above) {
     const float off = fmaf(-c_up, kStartF, off_n);
     above = fmaf(c_up, kStartF, off) - off_n;
@@ -744,9 +295,9 @@ typedef const __attribute__((address_space(1))) uint8_t* global_bytes;
 typedef __attribute__((address_space(1))) v4i global_v4i;
 typedef __attribute__((address_space(1))) v2u global_v2u;
 
-// QSRC as in attn_i8_kernel: 0 = Q codes and scale from the quantizer; 1 (bf16) / 2 (fp32) = the unquantized Q in the
-// default token order, reordered and quantized here - the quantization group is the row block this wavefront owns,
-// so its absmax is one in-wave reduction.
+// QSRC: 0 = Q codes and scale from the quantizer; 1 (bf16) / 2 (fp32) = the unquantized Q in the default token order, reordered and
+// quantized here - the quantization group of Q is the row block this wavefront owns (Sec. 4.3 (1)), so no other workgroup needs the
+// result and its absmax is one in-wave reduction.
 // QKBITS 4: Q and K rows are 32 bytes of packed 4-bit codes; a lane fetches the 16 bytes that hold its 32 channels
 // (32 g .. 32 g + 31) of a K row - one fragment per key tile instead of two - and widens them to two 16-byte operands
 // (codes times 16, undone in the scale) right before their products; Q is widened the same way once.
@@ -962,7 +513,7 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
         if ((u & 63) == 0) cols64 = load_cols(u >> 6);
         return __builtin_amdgcn_readlane(cols64, u & 63);
     };
-    // The scaled and the folded form multiply the logit scale by 2^26.  Folded: the rule of attn_i8_kernel.  Scaled: where that
+    // The scaled and the folded form multiply the logit scale by 2^26.  Folded: the rule of kFoldBound.  Scaled: where that
     // cannot overflow; beyond 2^90 (inputs of some 2^50 each) the exact form takes over.
     constexpr bool FOLDABLE = PARO_FOLD_LOGIT_BIAS && PVBITS == 8;
     bool fast = false;
@@ -979,7 +530,7 @@ __device__ __forceinline__ void attn_i8_w64_body(const AttnArgs& a) {
         for (int off = 32; off >= 1; off >>= 1) sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
         if (__builtin_amdgcn_ballot_w64(sv_max > 0x1p90f) != 0) acc_down = 1.0f;
         sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
-        fast = FOLDABLE ? sq_i * sk_max * kAccBiasF < 8192.0f : sq_i * sk_max < 0x1p90f;
+        fast = FOLDABLE ? sq_i * sk_max * kFoldBound < 8192.0f : sq_i * sk_max < 0x1p90f;
     }
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;  // the column block with padded keys, if any
     if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fast = false;
@@ -1231,9 +782,9 @@ __global__ __launch_bounds__(64, 2) void attn_i8_w64_qk4_kernel(AttnArgs a) {
 // to the tile's scale runs beside the codes of the block before.  Rows of 128 bytes of K are the exception: a lane pair reads 32 of a row, so
 // every request would touch 32 lines and the next three the same ones, more than the L1 of a compute unit holds for its wavefronts; they
 // go through LDS in whole lines.
-// Bound by the issue of the vector work where the chip is full (158 vector instructions per block at d = 64, 196 in attn_i8_kernel,
+// Bound by the issue of the vector work where the chip is full (158 vector instructions per block at d = 64; 196 in the kernel before it,
 // which exchanged tiles through LDS with a barrier per block), by the chain of one block where it is not.  Attention call alone, us,
-// attn_i8_kernel -> this one, 8-bit codes / all 4-bit, 30 % density: d = 64, 30 heads of 17550 tokens 1001 -> 780 / 957 -> 799, 24 heads
+// that kernel -> this one, 8-bit codes / all 4-bit, 30 % density: d = 64, 30 heads of 17550 tokens 1001 -> 780 / 957 -> 799, 24 heads
 // of 4096 57.2 -> 44.4 / 56.4 -> 47.9, 4 heads of 4096 36.5 -> 24.4 / 37.9 -> 27.9; d = 128, 30 heads of 17550 1765 -> 1264 (K by
 // registers 1560) / 1839 -> 1295, 4 heads of 4096 46.5 -> 30.3 / 49.9 -> 37.2.
 //
@@ -1599,15 +1150,21 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 }
 
 // -------------------------------------------------------------------------------------------
-// d = 128, block 64, 8-bit Q, K, P and V codes: FOUR wavefronts per row block, 16 queries each, on
+// block 64, d = 128, and d = 64 where the row blocks are few: FOUR wavefronts per row block, 16 queries each, on
 // v_mfma_i32_16x16x64_i8.
 //
-// At d = 128 a wavefront of 32 queries carries 64 accumulator registers and needs ~200 in all: two
-// wavefronts per SIMD, each alone for long stretches, and a row block that attends every column block (the
-// text rows of an image model, Sec. 4.2 (1)) is a chain of 72 such block visits that the whole launch
-// waits for.  With 16 queries per wavefront the visit is half as long, the registers allow three
-// wavefronts per SIMD, and the matrix work is unchanged (a 16x16x64 instruction takes half the time of a
-// 32x32x32 one).
+// Why 16 queries.  At d = 128 a wavefront of 32 carries 64 accumulator registers and needs some 200: two wavefronts per SIMD.  With 16
+// it needs 128 or fewer - four per SIMD, four workgroups per compute unit - and a block is a quarter of the instructions per wavefront, which
+// is what counts where a row's chain of blocks bounds the launch: rows of text (Sec. 4.2 (1)) that attend every column block, and
+// launches with fewer row blocks than the chip has room for.
+//
+// Order of things.  Between two barriers a wavefront exponentiates block t and multiplies K Q of block t + 1: its four matrix
+// instructions per two key tiles run beside the exponentials of two tiles of block t (at raised priority), and the chain from the
+// maxima of block t + 1 to this wavefront's share of its tile exponent, four numbers that meet in LDS across the barrier, runs beside
+// the sum, the codes, P V and the accumulator update of block t.  160 vector instructions per wavefront and block at d = 128 (207 with
+// products, maxima and exponentials of one block in turn), 136 at d = 64.  What bounds it: issue where the chip is full (the matrix
+// time is added where it is not beside an exponential), the chain of one block, some 1 100 (d = 64) to 1 500 cycles, where it is not.
+// Exponentials in whole bursts with one matrix instruction per two of them: 1 % slower, registers.
 //
 // Layouts.  S^T tile T (16 keys x 16 queries): lane (n = lane % 16, G = lane / 16) holds query n, keys
 // 4 G + r (r = 0..3) of the tile.  Which key sits in which row of a tile is free - K rows are fetched from
@@ -1616,20 +1173,19 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 // covers: row 4 G + r of tile T is the key whose PARO_VT slot is 16 G + 4 T + r, i.e. token
 // 32 (G >> 1) + 8 T + 4 (G & 1) + r of the block.  V^T fragments are then plain 16-byte reads of PARO_VT rows.
 //
-// Tiles.  K_j (64 x 128 B) and V_j^T (128 x 64 B) are contiguous 8 KB in global memory and go to LDS as
-// they are with global_load_lds_dwordx4, each wavefront moving a quarter, except that inside every 128-byte
-// line the eight 16-byte pieces are stored at position (piece ^ line % 8): the reads of 16 lanes that walk
-// down a column of pieces then spread over all banks.  Two K slots and two V slots; ONE barrier per block,
-// after the wavefront has written its share of the tile exponent and waited for its own requests: behind
-// it K_{t+2} may overwrite K_t (all K_t reads precede the barrier) and V_{t+1} may overwrite V_{t-1}.  K_{t+2}
-// is requested right behind the barrier; V_{t+1} only after the V_t fragments have been read, because the
-// compiler makes every read of the V ring wait for all requests into that ring issued before it.
-// Arithmetic per block as in attn_i8_kernel.
+// Tiles.  K_j and V_j^T of 8-bit codes go to LDS as they are with global_load_lds_dwordx4, each wavefront moving a quarter, 4-bit codes by
+// way of registers in which they are widened once for all four wavefronts.  Inside every 128-byte line the eight 16-byte pieces are
+// stored at position (piece ^ line % 8): the reads of 16 lanes that walk down a column of pieces then spread over all banks.  Two K
+// slots and two V slots, arrays of their own in a loop unrolled by two: with one array the compiler makes every read wait for all
+// requests before it.  ONE barrier per block, after the wavefront has waited for its own requests: behind it K_{t+2} may overwrite
+// K_t and V_{t+1} V_{t-1}, and they have the whole block to land.
+//
+// Attention call alone, us, before -> now, 30 % density, 8-bit codes / 8-bit Q K with 4-bit P V / all 4-bit.  d = 128 (before: the same split without
+// the overlap for 8-bit codes, two wavefronts of 32 queries otherwise): 30 heads of 17550 tokens 1159 -> 1022 / 1271 -> 1089 / 1291 -> 1080,
+// 24 heads of 4096 69.4 -> 61.5 / 83.5 -> 65.6 / 81.0 -> 63.7, 4 heads of 4096 24.4 -> 19.7 / 35.1 -> 23.5 / 36.2 -> 23.6, 24 heads of
+// 4096 image and 512 text tokens 119.9 -> 98.2.  d = 64 (before: one wavefront of 64 queries): 24 heads of 4096 43.7 -> 38.3 / 45.6 -> 43.1 /
+// 47.3 -> 44.0, 4 heads of 4096 30.5 -> 16.3 / 33.4 -> 17.2 / 34.0 -> 17.8.
 // -------------------------------------------------------------------------------------------
-#ifndef PARO_ATTN_Q16
-#define PARO_ATTN_Q16 1
-#endif
-
 typedef int v4acc __attribute__((ext_vector_type(4)));
 
 // max over the four lanes n, n + 16, n + 32, n + 48 (the lanes that share a query), returned in all four
@@ -1640,20 +1196,29 @@ __device__ inline int quad_rows_max(int x) {
 __device__ inline float quad_rows_sum(float x) {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
     const float y = __int_as_float((int)r[0]) + __int_as_float((int)r[1]);
-    return y + __shfl_xor(y, 32);
+    const auto z = __builtin_amdgcn_permlane32_swap(__float_as_int(y), __float_as_int(y), false, false);
+    return __int_as_float((int)z[0]) + __int_as_float((int)z[1]);
 }
 
-template <typename OutT>
-__global__ __launch_bounds__(256, 3) void attn_i8_q16_kernel(AttnArgs a) {
-    constexpr int BLK = 64, D = 128;
-    constexpr int KS = D / 64;     // contraction steps of QK^T (64 channels each)
-    constexpr int CT = D / 16;     // 16-channel tiles of the output
-    constexpr int TILE = BLK * D;  // bytes of a K tile and of a V^T tile
-    constexpr float LOG2_QMAXP = 6.988684686772166f;
+template <int D, int QKBITS, int PVBITS, typename OutT, int QSRC = 0>
+__global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(AttnArgs a) {
+    static_assert(QSRC == 0 || QKBITS == 8, "in-kernel quantization of Q produces 8-bit codes");
+    constexpr int BLK = 64;
+    constexpr int KPACK = QKBITS == 4 ? 2 : 1;
+    constexpr int VPACK = PVBITS == 4 ? 2 : 1;
+    constexpr int KS = D / 64;        // contraction steps of QK^T (64 channels each)
+    constexpr int CT = D / 16;        // 16-channel tiles of the output
+    constexpr int TILE = BLK * D;     // bytes of a K and of a V^T tile in LDS
+    constexpr float LOG2_QMAXP = PVBITS == 4 ? 2.807354922057604f : 6.988684686772166f;
     constexpr float kLog2_65535 = 15.999977986052736f;
-    __shared__ __attribute__((aligned(16))) uint8_t kring[2][TILE];
-    __shared__ __attribute__((aligned(16))) uint8_t vring[2][TILE];
-    __shared__ unsigned tile_e[2][4];
+    constexpr bool LIFTED = PVBITS == 8;  // P V products enter the sums without a subtraction (see kWeightUp)
+    constexpr int START = 1 << 20;        // >= 64 * 127 * 127
+    constexpr int PERIOD = D == 64 ? 2 : 4;  // error against binary64, d = 64, of the folded form's 3.157e-4: 3.166e-4 with 4; at d = 128 3.53e-4 -> 2.80e-4
+    __shared__ __attribute__((aligned(16))) uint8_t kring0[TILE];
+    __shared__ __attribute__((aligned(16))) uint8_t kring1[TILE];
+    __shared__ __attribute__((aligned(16))) uint8_t vring0[TILE];
+    __shared__ __attribute__((aligned(16))) uint8_t vring1[TILE];
+    __shared__ __attribute__((aligned(16))) unsigned tile_e[2][4];
 
     const int wg = blockIdx.x;
     const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
@@ -1666,241 +1231,462 @@ __global__ __launch_bounds__(256, 3) void attn_i8_q16_kernel(AttnArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15;
     const int G = lane >> 4;
-    PARO_TIMELINE_BEGIN
+    PARO_TIMELINE_BEGIN(QKBITS == 8 && PVBITS == 8)
 
     const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
     const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
     const int end = __builtin_amdgcn_readfirstlane(min(max(rp[1], beg), a.nnz));
     const int cnt = end - beg;
     const int* cols = a.col_idx + beg;
-    if (2 * cnt > a.kblocks) __builtin_amdgcn_s_setprio(2);
 
     const size_t head_rows = (size_t)bh * a.kblocks * BLK;
-    const uint8_t* kbase = a.k + head_rows * D;
-    const uint8_t* vbase = a.v + head_rows * D;
+    const uint8_t* kbase = a.k + head_rows * D / KPACK;
+    const uint8_t* vbase = a.v + head_rows * D / VPACK;
     const float* skp = a.sk + (size_t)bh * a.kblocks;
     const float sk_last = uniform_load(skp + a.kblocks - 1);  // asked for here, used below
     const float* svp = a.sv + (size_t)bh * a.kblocks;
-    const float sq_i = a.sq[(size_t)bh * a.kblocks + i] * a.qk_scale;
     const int row = i * BLK + 16 * w + n;  // this lane's query, in the reordered sequence
     const bool row_valid = row < a.n_tokens;
-    // or-ed into the bit pattern of a value <= 0 it gives a pattern at or above that of -inf: larger, as an unsigned
-    // number, than the pattern of every value a real row can have
-    const unsigned invalid_row = row_valid ? 0u : 0xFF800000u;
-    v4i qf[KS];
-    {
-        const uint8_t* qrow = a.q + (head_rows + row) * D + 16 * G;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s] = *(const v4i*)(qrow + 64 * s);
-    }
-    // a wavefront moves two of the eight 1 KB pieces of a tile: lane L fills LDS bytes 16 L of the piece, which is
-    // position L % 8 of line L / 8 and holds the line's global piece (L % 8) ^ (L / 8)
-    const unsigned fill_lane = 2048u * w + 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
-    // K fragment of tile T, step s: row 32 (n >> 3) + 8 T + (n & 7) of the tile, piece 4 s + G
-    unsigned kread[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) kread[s] = 128u * (32 * (n >> 3) + (n & 7)) + 16u * ((4 * s + G) ^ (n & 7));
-    // V^T fragment of channel tile ct: PARO_VT row 16 ct + n = line 8 ct + n / 2, piece 4 (n % 2) + G
-    const unsigned vread = 128u * (n >> 1) + 16u * ((4 * (n & 1) + G) ^ (n >> 1));
 
-    // column indices: 64 per fetch, one per lane; `cols_cur` holds the chunk of the newest step looked up
-    auto load_cols = [&](int chunk) {
-        const int idx = min(chunk * 64 + lane, cnt - 1);
-        return cnt > 0 && chunk * 64 < cnt ? min(max(cols[idx], 0), a.kblocks - 1) : 0;
+    // ---- tiles to LDS, as 128-byte lines of eight 16-byte pieces (one K row at d = 128, two rows otherwise); piece p of line x sits at
+    // position p ^ (x % 8).  8-bit codes are requested straight into LDS, 1 KB a request, lane L filling bytes 16 L: position L % 8 of
+    // a line L / 8.  4-bit codes come in registers, a whole block earlier, and are widened on the way (codes times 16, undone in the scale).
+    const unsigned fill = 128u * (lane >> 3) + 16u * ((lane & 7) ^ (lane >> 3));
+    auto request = [&](const uint8_t* tile, uint8_t* slot) __attribute__((always_inline)) {
+        constexpr int EACH = TILE / 4;
+        const uint8_t* from = tile + EACH * w;
+        unsigned off = fill;
+        asm volatile("" : "+s"(from), "+v"(off));  // scalar base + lane offset, not a 64-bit address per lane
+        lds_dma16<0>(from, off, slot + EACH * w);
+        if constexpr (EACH == 2048) lds_dma16<1024>(from, off, slot + EACH * w + 1024);
     };
-    int cols_cur = load_cols(0), cols_nxt = load_cols(1);
-    int cur_chunk = 0;
-    auto col_at = [&](int u) {  // u advances by one per call
-        if ((u & 63) == 0 && u > 0) {
-            cols_cur = cols_nxt;
-            ++cur_chunk;
-            cols_nxt = load_cols(cur_chunk + 1);
+    using Packed = std::conditional_t<D == 128, v4i, v2u>;  // a thread's share of a tile of 4-bit codes
+    const int tid = threadIdx.x;
+    Packed kreg{}, vreg{};
+    auto place = [](int line, int piece) { return 128u * line + 16u * (piece ^ (line & 7)); };
+    auto widen = [&](const Packed& x, uint8_t* slot, unsigned at, unsigned apart) __attribute__((always_inline)) {
+        v4i first, second;
+        if constexpr (D == 128) {
+            unpack_nibbles(x, first, second);
+            *(v4i*)(slot + at) = first;
+            *(v4i*)(slot + (at ^ apart)) = second;
+        } else {
+            unpack_nibbles(v4i{(int)x.x, (int)x.y, 0, 0}, first, second);
+            *(v4i*)(slot + at) = first;
         }
-        return __builtin_amdgcn_readlane(cols_cur, u & 63);
     };
-    auto request_k = [&](int j, int slot) {
-        const uint8_t* kp = kbase + (size_t)j * TILE;
-        lds_dma16<0>(kp, fill_lane, &kring[slot][2048 * w]);
-        lds_dma16<1024>(kp, fill_lane, &kring[slot][2048 * w + 1024]);
+    // K: a quarter of row tid / 4, 32 channels as pieces p and 4 + p of 16 (Q is split the same way) or 16 channels as one piece;
+    // V^T: half of row tid / 2, 32 slots as two pieces, or a quarter of row tid / 4, one piece
+    const unsigned kat = D == 128 ? place(tid >> 2, tid & 3) : place(tid >> 3, tid & 7);
+    const unsigned vat = D == 128 ? place(tid >> 2, 2 * (tid & 3)) : place(tid >> 3, tid & 7);
+    auto fetch = [&](const uint8_t* tile, Packed& x) __attribute__((always_inline)) {
+        global_bytes from = (global_bytes)tile;
+        unsigned off = sizeof(Packed) * (64u * w + lane_here());
+        asm volatile("" : "+s"(from), "+v"(off));
+        x = *(const __attribute__((address_space(1))) Packed*)(from + off);
     };
-    auto request_v = [&](int j, int slot) {
-        const uint8_t* vp = vbase + (size_t)j * TILE;
-        lds_dma16<0>(vp, fill_lane, &vring[slot][2048 * w]);
-        lds_dma16<1024>(vp, fill_lane, &vring[slot][2048 * w + 1024]);
+    auto fetch_k = [&](int j) __attribute__((always_inline)) { fetch(kbase + (size_t)j * (TILE / 2), kreg); };
+    auto fetch_v = [&](int j) __attribute__((always_inline)) { fetch(vbase + (size_t)j * (TILE / 2), vreg); };
+    // the next tile into a free slot: requested (8-bit, block j) or written from the registers, which then fetch block j_after
+    auto bring_k = [&](int j, int j_after, uint8_t* slot) __attribute__((always_inline)) {
+        if constexpr (QKBITS == 8) request(kbase + (size_t)j * TILE, slot);
+        else {
+            widen(kreg, slot, kat, 64);
+            fetch_k(j_after);
+        }
+    };
+    auto bring_v = [&](int j, int j_after, uint8_t* slot) __attribute__((always_inline)) {
+        if constexpr (PVBITS == 8) request(vbase + (size_t)j * TILE, slot);
+        else {
+            widen(vreg, slot, vat, 16);
+            fetch_v(j_after);
+        }
     };
 
-    float m = -INFINITY, m_ref = -INFINITY, w_base = INFINITY, l = 0.0f;
+    // 64 column indices per fetch, one per lane; past the end of the row its last column again
+    auto load_cols = [&](int chunk) { return min(max(cols[min(chunk * 64 + lane_here(), cnt - 1)], 0), a.kblocks - 1); };
+    int cols64 = cnt > 0 ? load_cols(0) : 0;
+    auto column = [&](int u) {  // u advances by one per call
+        if ((u & 63) == 0) cols64 = load_cols(u >> 6);
+        return __builtin_amdgcn_readlane(cols64, u & 63);
+    };
+    int j0 = 0, j1 = 0, j2 = 0;  // columns of the first block and of blocks t + 1 and t + 2
+    float sk0 = 0.0f, sv0 = 0.0f, sk1 = 0.0f, sv1 = 0.0f;  // their scales
+    const int first_cols = cols64;
+    if (cnt > 0) {
+        j0 = __builtin_amdgcn_readlane(cols64, 0);
+        j1 = column(1);
+        j2 = column(2);
+        if constexpr (QKBITS == 4) fetch_k(j0);
+        if constexpr (PVBITS == 4) fetch_v(j0);
+        bring_k(j0, j1, kring0);
+        bring_v(j0, j1, vring0);
+        bring_k(j1, j2, kring1);
+        sk0 = uniform_load(skp + j0);
+        sv0 = uniform_load(svp + j0);
+        sk1 = uniform_load(skp + j1);
+        sv1 = uniform_load(svp + j1);
+    }
+
+    // ---- Q
+    v4i qf[KS];
+    float sq_i = 0.0f;
+    if constexpr (QSRC == 0) {
+        sq_i = a.sq[(size_t)bh * a.kblocks + i] * (QKBITS == 4 ? a.qk_scale * (1.0f / 256.0f) : a.qk_scale);  // 4-bit codes enter times 16
+        const uint8_t* qrow = a.q + (head_rows + row) * (D / KPACK);
+        if constexpr (QKBITS == 8) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) qf[s] = *(const v4i*)(qrow + 64 * s + 16 * G);
+        } else if constexpr (KS == 2) {
+            unpack_nibbles(*(const v4i*)(qrow + 16 * G), qf[0], qf[1]);
+        } else {
+            v4i unused;
+            const v2u x = *(const v2u*)(qrow + 8 * G);
+            unpack_nibbles(v4i{(int)x.x, (int)x.y, 0, 0}, qf[0], unused);
+        }
+    } else {
+        // same arithmetic as the quantizer: absmax over the real rows of the block, scale = absmax / 127 in binary32,
+        // code = rint(fl32(x / scale))
+        using RawT = std::conditional_t<QSRC == 1, uint16_t, float>;
+        __shared__ float q_amax[4];
+        const RawT* qsrc = (const RawT*)a.q + ((size_t)bh * a.n_tokens + (row_valid ? reorder_source(a.table, h, row) : 0)) * D + 16 * G;
+        float x[KS][16];
+        float amax = 0.0f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            if (row_valid) {
+                if constexpr (QSRC == 1) {
+                    const uint4 lo = *(const uint4*)(qsrc + 64 * s), hi = *(const uint4*)(qsrc + 64 * s + 8);
+                    const unsigned wv[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        x[s][2 * e] = __uint_as_float(wv[e] << 16);
+                        x[s][2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u);
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float4 f = *(const float4*)(qsrc + 64 * s + 4 * e);
+                        x[s][4 * e] = f.x;
+                        x[s][4 * e + 1] = f.y;
+                        x[s][4 * e + 2] = f.z;
+                        x[s][4 * e + 3] = f.w;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) x[s][e] = 0.0f;
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) amax = fmaxf(amax, fabsf(x[s][e]));
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+        if (lane == 0) q_amax[w] = amax;
+        __syncthreads();
+        amax = fmaxf(fmaxf(q_amax[0], q_amax[1]), fmaxf(q_amax[2], q_amax[3]));
+        const float scale = amax > 0.0f ? amax / 127.0f : 1.0f;
+        const GroupDivider quotient(scale);
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+                unsigned word = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float r = fminf(fmaxf(rintf(quotient(x[s][4 * e4 + e])), -127.0f), 127.0f);
+                    word |= ((unsigned)(int)r & 0xffu) << (8 * e);
+                }
+                qf[s][e4] = (int)word;
+            }
+        sq_i = scale * a.qk_scale;
+    }
+    sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
+
+    // ---- which of the loops the row block's scales allow (as in the kernels above)
+    constexpr bool FOLDABLE = PARO_FOLD_LOGIT_BIAS && PVBITS == 8;
+    bool fast = false;
+    int sv_exp = 0;
+    {
+        float sk_max = 0.0f, sv_max = 0.0f, sv_min = INFINITY;
+        for (int base = 0; base < cnt; base += 64)
+            if (base + lane < cnt) {
+                const int j = base == 0 ? first_cols : min(max(cols[base + lane], 0), a.kblocks - 1);
+                sk_max = fmaxf(sk_max, skp[j]);
+                sv_max = fmaxf(sv_max, svp[j]);
+                sv_min = fminf(sv_min, svp[j]);
+            }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
+            sv_max = fmaxf(sv_max, __shfl_xor(sv_max, off));
+            sv_min = fminf(sv_min, __shfl_xor(sv_min, off));
+        }
+        fast = FOLDABLE ? sq_i * sk_max * kFoldBound < 8192.0f : sq_i * sk_max < 0x1p90f;
+        if (LIFTED) fast = fast && sv_min >= 0x1p-28f * sv_max && sv_max < 0x1p100f && sv_max > 0x1p-60f;
+        sv_exp = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(sv_max));
+    }
+    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;  // the column block with padded keys, if any
+    if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fast = false;
+    const bool lifted = LIFTED && fast;
+    const float sv_up = (lifted ? ldexpf(1.0f, kWeightUp - sv_exp) : (sv_exp > 90 ? 1.0f : 0x1p13f)) * (PVBITS == 4 ? 0.0625f : 1.0f);
+    v4acc s_start, o_start;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        s_start[r] = 0x3E22F983;
+        o_start[r] = lifted ? START : 0x3E22F983;
+    }
+    asm volatile("" : "+v"(s_start));
+    if constexpr (LIFTED) asm volatile("" : "+v"(o_start));
+
+    // ---- fragments.  K, tile T: row 32 (n >> 3) + 8 T + (n & 7) of the block; V^T, channel tile ct: row 16 ct + n
+    unsigned kread[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        // d = 128: contraction step x.  d = 64: even and odd tiles, which sit four lines further on
+        if constexpr (D == 128) kread[x] = 128u * (32 * (n >> 3) + (n & 7)) + 16u * ((4 * x + G) ^ (n & 7));
+        else kread[x] = 128u * (16 * (n >> 3) + ((n & 7) >> 1)) + 16u * ((4 * (n & 1) + G) ^ ((n & 7) >> 1) ^ (4 * x));
+    }
+    const unsigned vread = 128u * (n >> 1) + 16u * ((4 * (n & 1) + G) ^ (n >> 1));
+    auto k_fragment = [&](const uint8_t* slot, int T, int s) __attribute__((always_inline)) {
+        return D == 128 ? *(const v4i*)(slot + 1024 * T + kread[s]) : *(const v4i*)(slot + 512 * T + kread[T & 1]);
+    };
+    auto logits = [&](const uint8_t* slot, v4acc (&S)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int T = 0; T < 4; ++T) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) S[T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(k_fragment(slot, T, s), qf[s], s == 0 ? s_start : S[T], 0, 0, 0);
+        }
+    };
+
+    float m = row_valid ? -INFINITY : INFINITY, m_ref = m, l = 0.0f;  // a padded row holds +inf, as above
     float acc[CT][4];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[ct][r] = 0.0f;
-    v4acc acc_init = {kAccBiasI, kAccBiasI, kAccBiasI, kAccBiasI};
-    asm volatile("" : "+v"(acc_init));
+    float held = 0.0f;
 
-    // columns of the steps t, t + 1, t + 2 and the scales of t, t + 1
-    int j0 = 0, j1 = 0, j2 = 0;
-    float sk0 = 0.0f, sv0 = 0.0f, sk1 = 0.0f, sv1 = 0.0f;
-    if (cnt > 0) {
-        j0 = col_at(0);
-        request_k(j0, 0);
-        request_v(j0, 0);
-        sk0 = uniform_load(skp + j0);
-        sv0 = uniform_load(svp + j0);
-        if (cnt > 1) {
-            j1 = col_at(1);
-            request_k(j1, 1);
-            sk1 = uniform_load(skp + j1);
-            sv1 = uniform_load(svp + j1);
-        }
-        if (cnt > 2) j2 = col_at(2);
-    }
-    constexpr bool FOLDABLE = PARO_FOLD_LOGIT_BIAS;
-    bool fold = false;
-    if constexpr (FOLDABLE) {  // same rule as attn_i8_kernel; its loads travel while the first tiles do
-        // the first two chunks of column indices are in registers already (a lane past the end holds the row's last column)
-        float sk_max = cnt > 0 ? skp[cols_cur] : 0.0f;
-        if (cnt > 64) sk_max = fmaxf(sk_max, skp[cols_nxt]);
-        for (int base = 128; base < cnt; base += 64)
-            if (base + lane < cnt) sk_max = fmaxf(sk_max, skp[min(max(cols[base + lane], 0), a.kblocks - 1)]);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
-        fold = sq_i * sk_max * kAccBiasF < 8192.0f;
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    __syncthreads();
-    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;  // the column block with padded keys, if any
-    if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fold = false;
-
-    auto step = [&](auto fold_tag, int t) {
-        constexpr bool FOLD = decltype(fold_tag)::value;
-        float c = sq_i * sk0;
-        if (!FOLD && c < kLogitScaleMin) c = kLogitScaleMin;
-        const float sv_now = sv0;
-        const uint8_t* kslot = &kring[t & 1][0];
-        const uint8_t* vslot = &vring[t & 1][0];
-        PARO_TIMELINE_PHASE(3)  // behind the previous block's accumulator update (and the loop's own overhead)
-
-        // ---- S^T = K_j Q_i^T (i32, biased): four 16-key tiles
-        v4acc sacc[4];
-#pragma unroll
-        for (int T = 0; T < 4; ++T) {
-            sacc[T] = acc_init;
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                sacc[T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(*(const v4i*)(kslot + 1024 * T + kread[s]), qf[s], sacc[T], 0, 0, 0);
-        }
-        if (j0 == tail_block) {  // keys past N: the bit pattern of -inf loses every maximum and gives E = 0 (c > 0)
-            const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
+    auto mask_tail = [&](int j, v4acc (&S)[4]) __attribute__((always_inline)) {
+        if (j == tail_block) {  // keys past N: the bit pattern of -inf loses every maximum and gives E = 0 (c > 0)
+            const int GG = lane_here() >> 4;
+            const int real = a.n_tokens - (a.kblocks - 1) * BLK - 32 * (GG >> 1) - 4 * (GG & 1);
 #pragma unroll
             for (int T = 0; T < 4; ++T)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (32 * (G >> 1) + 8 * T + 4 * (G & 1) + r >= nkeys) sacc[T][r] = (int)0xFF800000;
+                for (int r = 0; r < 4; ++r) {
+                    S[T][r] = 8 * T + r >= real ? (int)0xFF800000 : S[T][r];
+                    asm volatile("" : "+v"(S[T][r]));
+                }
         }
-        // ---- running maximum and this wavefront's share of the tile's quantization scale
-        int part[4] = {0, 0, 0, 0};  // below every real value (those carry the accumulator bias)
+    };
+    // new running maximum from a block's raw logits, and this wavefront's share of the tile's quantization scale
+    auto maxima = [&](const v4acc (&S)[4], float c, unsigned& eb) __attribute__((always_inline)) {
+        int part[4] = {0, 0, 0, 0};  // below every real value (those carry the accumulators' start)
 #pragma unroll
         for (int T = 0; T < 4; ++T)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) part[r] = max(part[r], sacc[T][r]);
-        const float ymax = c * int_result(quad_rows_max(max(max(part[0], part[1]), max(part[2], part[3]))));
+            for (int r = 0; r < 4; ++r) part[r] = max(part[r], S[T][r]);
+        const float ymax = c * start_result(quad_rows_max(max(max(part[0], part[1]), max(part[2], part[3]))));
         const float m_new = fmaxf(m, ymax);
-        unsigned eb = __float_as_uint(ymax - m_new) | invalid_row;  // a padded row loses the minimum
+        eb = __float_as_uint(ymax - m_new);              // a padded row has -inf here and loses the minimum
         eb = min(eb, (unsigned)dpp_mov<0xB1>((int)eb));  // the four rows of 16 lanes hold the same 16 queries:
         eb = min(eb, (unsigned)dpp_mov<0x4E>((int)eb));  // one row is reduced
         eb = min(eb, (unsigned)dpp_mov<0x141>((int)eb));
         eb = min(eb, (unsigned)dpp_mov<0x140>((int)eb));
-        if (lane == 0) tile_e[t & 1][w] = eb;
-        // ---- everything this wavefront has in flight (its share of K_{t+1} and V_t) has landed; behind the
-        // barrier both tiles and all four exponents are whole, K_t has been read by all and V_{t-1} is consumed
-        PARO_TIMELINE_PHASE(0)  // K reads, products, row maximum, share of the tile exponent
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        __syncthreads();
-        PARO_TIMELINE_PHASE(1)  // wait for the tiles and for the other wavefronts
-        if (t + 2 < cnt) request_k(j2, t & 1);
-        const int j_v = j1;
-        const float e = __uint_as_float(min(min(tile_e[t & 1][0], tile_e[t & 1][1]), min(tile_e[t & 1][2], tile_e[t & 1][3])));
-        // the next step's column, scales and the column after it (scalar work, hidden behind the vector work below)
-        j0 = j1;
-        j1 = j2;
-        sk0 = sk1;
-        sv0 = sv1;
-        if (t + 2 < cnt) {
-            sk1 = uniform_load(skp + j1);
-            sv1 = uniform_load(svp + j1);
-        }
-        if (t + 3 < cnt) j2 = col_at(t + 3);
-
+        return m_new;
+    };
+    auto refer = [&](float m_new) __attribute__((always_inline)) {  // keeps the stored sums far from overflow; takes the maximum over
         if (__builtin_amdgcn_ballot_w64(m_new - m_ref > 64.0f) != 0) {
             const float down = __builtin_amdgcn_exp2f(m_ref - m_new);  // first block: 2^-inf = 0 on zero sums
             l *= down;
+            held *= down;
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[ct][r] *= down;
             m_ref = m_new;
-            w_base = -kLog2_65535 - m_new;
         }
         m = m_new;
-        const float off_n = (LOG2_QMAXP - kLog2_65535) - m_new - e;
+    };
+    auto settle = [&]() __attribute__((always_inline)) {  // takes out what the sums hold too much
+        const float extra = held * -(START * 0x1p-149f);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[ct][r] += extra;
+        held = 0.0f;
+    };
+
+    v4acc Sa[4], Sb[4];  // raw logits, this block's and the next one's in turn
+    // block t, whose logits are in S and whose tile exponents are in tile_e; K_{t+1} is in k_next and V_t in v_now
+    auto step = [&](auto mode_tag, auto parity_tag, int t, v4acc (&S)[4], v4acc (&N)[4]) __attribute__((always_inline)) {
+        constexpr int MODE = decltype(mode_tag)::value;
+        constexpr int PARITY = decltype(parity_tag)::value;
+        constexpr bool LIFT = LIFTED && MODE != kExact;
+        uint8_t* const k_next = PARITY ? kring0 : kring1;  // K_{t+1}
+        uint8_t* const k_free = PARITY ? kring1 : kring0;  // held K_t
+        uint8_t* const v_now = PARITY ? vring1 : vring0;   // V_t
+        uint8_t* const v_free = PARITY ? vring0 : vring1;  // held V_{t-1}
+        const uint4 eq = *(const uint4*)tile_e[PARITY];
+        v4i kf[2][KS];
+        auto read_k = [&](int T0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int T = 0; T < 2; ++T)
+#pragma unroll
+                for (int s = 0; s < KS; ++s) kf[T][s] = k_fragment(k_next, T0 + T, s);
+        };
+        auto products_k = [&](int T0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int T = 0; T < 2; ++T) N[T0 + T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf[T][s], qf[s], s == 0 ? s_start : N[T0 + T], 0, 0, 0);
+        };
+        v4i vf[4];
+        auto read_v = [&](int ct0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) vf[x] = *(const v4i*)(v_now + 1024 * (ct0 + x) + vread);
+        };
+        read_k(0);
+        const int j3 = column(t + 3);
+        bring_k(j2, j3, k_free);
+        bring_v(j1, j2, v_free);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(3);
+        products_k(0);
+        read_k(2);
+        const float e = __uint_as_float(min(min(eq.x, eq.y), min(eq.z, eq.w)));
+        float c = sq_i * sk0;
+        if (MODE == kExact && c < kLogitScaleMin) c = kLogitScaleMin;
+        const float c_up = c * 0x1p26f;
+        const float off_n = (LOG2_QMAXP - kLog2_65535) - m - e;
         float off_f = off_n, w_blk;
-        if constexpr (FOLD) {
-            const float cb_hi = c * kAccBiasF;
-            const float cb_lo = fmaf(c, kAccBiasF, -cb_hi);
-            off_f = off_n - cb_hi;
-            const float bb = off_f - off_n;
-            const float terr = (off_n - (off_f - bb)) + (-cb_hi - bb);
-            w_blk = __builtin_amdgcn_exp2f((w_base - off_n) - (cb_lo - terr));
+        if constexpr (MODE == kFold) {
+            float above;
+            off_f = folded_offset(off_n, c_up, above);
+            w_blk = __builtin_amdgcn_exp2f(((-kLog2_65535 - m_ref) - off_n) - above);
         } else {
-            w_blk = __builtin_amdgcn_exp2f(w_base - off_n);
+            w_blk = __builtin_amdgcn_exp2f((-kLog2_65535 - m_ref) - off_n);
         }
-        // ---- E (in place of the raw logits), row sum, codes packed as B operand: register T = tile T
-        float ev[4][4];
+        float E[4][4];
+        auto exponentials = [&](int T0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int T = 0; T < 4; ++T)
+            for (int T = T0; T < T0 + 2; ++T)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                ev[T][r] = __builtin_amdgcn_exp2f(fmaf(FOLD ? __int_as_float(sacc[T][r]) : int_result(sacc[T][r]), c, off_f));
-        const float rs = ((ev[0][0] + ev[0][1]) + (ev[0][2] + ev[0][3])) + ((ev[1][0] + ev[1][1]) + (ev[1][2] + ev[1][3])) +
-                         (((ev[2][0] + ev[2][1]) + (ev[2][2] + ev[2][3])) + ((ev[3][0] + ev[3][1]) + (ev[3][2] + ev[3][3])));
+                for (int r = 0; r < 4; ++r) {
+                    float y;
+                    if constexpr (MODE == kFold) y = fmaf(__int_as_float(S[T][r]), c_up, off_f);
+                    else if constexpr (MODE == kScaled) y = fmaf(__int_as_float(S[T][r]) - kStartF, c_up, off_f);
+                    else y = fmaf(start_result(S[T][r]), c, off_f);
+                    E[T][r] = __builtin_amdgcn_exp2f(y);
+                }
+            asm volatile("" : "+v"(E[T0][0]), "+v"(E[T0][1]), "+v"(E[T0][2]), "+v"(E[T0][3]), "+v"(E[T0 + 1][0]), "+v"(E[T0 + 1][1]), "+v"(E[T0 + 1][2]), "+v"(E[T0 + 1][3]));
+        };
+        exponentials(0);
+        __builtin_amdgcn_sched_barrier(0);
+        products_k(2);
+        __builtin_amdgcn_sched_barrier(0);
+        read_v(0);
+        exponentials(2);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
+        PARO_TIMELINE_PHASE(0)  // products K Q of the next block, exponentials
+        mask_tail(j1, N);
+        unsigned eb;
+        const float m_new = maxima(N, sq_i * sk1, eb);
+        const float rs = ((E[0][0] + E[0][1]) + (E[0][2] + E[0][3])) + ((E[1][0] + E[1][1]) + (E[1][2] + E[1][3])) +
+                         (((E[2][0] + E[2][1]) + (E[2][2] + E[2][3])) + ((E[3][0] + E[3][1]) + (E[3][2] + E[3][3])));
         v4i pf;
 #pragma unroll
         for (int T = 0; T < 4; ++T) {
-            const unsigned lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(ev[T][0], ev[T][1]));
-            const unsigned hi = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(ev[T][2], ev[T][3]));
+            const unsigned lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(E[T][0], E[T][1]));
+            const unsigned hi = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(E[T][2], E[T][3]));
             pf[T] = (int)__builtin_amdgcn_perm(hi, lo, 0x06040200u);
         }
         l = fmaf(rs, w_blk, l);
-        PARO_TIMELINE_PHASE(2)  // exponentials, row sum, codes
-        // ---- O^T += (sP sv_j 2^(m' - m_ref)) V_j^T P^T: eight 16-channel tiles, one instruction each
-        const float sv_eff = w_blk * sv_now;
+        const float weight = w_blk * (sv0 * sv_up);
+        v4acc o[4];
+        auto products_v = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            const v4acc o = __builtin_amdgcn_mfma_i32_16x16x64_i8(*(const v4i*)(vslot + 1024 * ct + vread), pf, acc_init, 0, 0, 0);
+            for (int x = 0; x < 4; ++x) o[x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[x], pf, LIFTED ? o_start : s_start, 0, 0, 0);
+        };
+        auto add = [&](int ct0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[ct][r] = fmaf(int_result(o[r]), sv_eff, acc[ct][r]);
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[ct0 + x][r] = fmaf(LIFT ? __int_as_float(o[x][r]) : __int_as_float(o[x][r]) - kStartF, weight, acc[ct0 + x][r]);
+        };
+        products_v();
+        if constexpr (CT == 8) {
+            read_v(4);
+            add(0);
+            products_v();
+            add(4);
+        } else {
+            add(0);
         }
-        if (t + 1 < cnt) request_v(j_v, (t + 1) & 1);
+        tile_e[PARITY ^ 1][w] = eb;  // (the same in every lane)
+        if constexpr (LIFT) held += weight;
+        refer(m_new);
+        sk0 = sk1;
+        sv0 = sv1;
+        j1 = j2;
+        j2 = j3;
+        sk1 = uniform_load(skp + j1);
+        sv1 = uniform_load(svp + j1);
+        PARO_TIMELINE_PHASE(2)  // maxima of the next block, sum, codes, products P V, accumulators
+        // what this wavefront has asked for has landed; behind the barrier both tiles and all four exponents are whole, and what
+        // this block read is free
+        if constexpr (QKBITS == 8 || PVBITS == 8) __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        PARO_TIMELINE_PHASE(1)  // wait for the tiles and for the other wavefronts
     };
-
-    PARO_TIMELINE_PHASE(4)  // everything in front of the block loop
-    if (fold) {
-        for (int t = 0; t < cnt; ++t) step(std::bool_constant<FOLDABLE>{}, t);
-    } else {
-        for (int t = 0; t < cnt; ++t) step(std::false_type{}, t);
+    auto visit_all = [&](auto mode_tag) __attribute__((always_inline)) {
+        constexpr bool LIFT = LIFTED && decltype(mode_tag)::value != kExact;
+        int t = 0;
+        for (; t + 1 < cnt; t += 2) {
+            step(mode_tag, std::integral_constant<int, 0>{}, t, Sa, Sb);
+            step(mode_tag, std::integral_constant<int, 1>{}, t + 1, Sb, Sa);
+            if (LIFT && (t & (PERIOD - 2)) == PERIOD - 2) settle();  // (2: every time)
+        }
+        if (t < cnt) step(mode_tag, std::integral_constant<int, 0>{}, t, Sa, Sb);
+        if constexpr (LIFT) settle();
+    };
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    __syncthreads();
+    if (cnt > 0) {
+        logits(kring0, Sa);
+        mask_tail(j0, Sa);
+        unsigned eb;
+        const float m_new = maxima(Sa, sq_i * sk0, eb);
+        tile_e[0][w] = eb;
+        refer(m_new);
     }
+    __syncthreads();
+    PARO_TIMELINE_PHASE(4)  // everything in front of the block loop
+    if (fast) visit_all(std::integral_constant<int, FOLDABLE ? kFold : kScaled>{});
+    else visit_all(std::integral_constant<int, kExact>{});
     PARO_TIMELINE_PHASE(3)
 
     const float l_tot = quad_rows_sum(l) * 65535.0f;
-    const float inv = (row_valid && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
-    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row_valid);
+    // the sums carry the weights' factor and the spacing of the integers they were read as
+    const float up = lifted ? 0x1p89f : 1.0f;
+    const int ln = lane_here();  // nothing that only these stores need is kept through the loop
+    const int orow_no = i * BLK + 16 * w + (ln & 15);
+    const bool valid = orow_no < a.n_tokens;
+    const float inv = (valid && l_tot > 0.0f) ? (lifted ? ldexpf(1.0f, sv_exp) : sv_exp > 90 ? 0x1p26f : 0x1p13f) / l_tot : 0.0f;
+    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, orow_no, valid);
     if (ooff >= 0) {
-        OutT* orow = (OutT*)a.op + ooff + 4 * G;
+        OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 4);
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) store4(orow + 16 * ct, acc[ct][0] * inv, acc[ct][1] * inv, acc[ct][2] * inv, acc[ct][3] * inv);
+        for (int ct = 0; ct < CT; ++ct) {
+            float x[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = valid ? (acc[ct][r] * up) * inv : 0.0f;
+            store4(orow + 16 * ct, x[0], x[1], x[2], x[3]);
+        }
     }
-    PARO_TIMELINE_END(4 * item + w, lane, cnt)
+    PARO_TIMELINE_END(4 * item + w, threadIdx.x & 63, cnt)
 }
 
 // -------------------------------------------------------------------------------------------
@@ -2603,74 +2389,50 @@ static void launch_b32(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) 
     else hipLaunchKernelGGL((attn_i8_b32_kernel<D, QKBITS, PVBITS, uint16_t>), grid, dim3(64), 0, st, a);
 }
 
-template <int BLK, int D, int QKBITS, int PVBITS>
-static void launch_out(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
+template <int D, int QKBITS, int PVBITS, int QSRC = 0>
+static void launch_q16(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
     dim3 grid((unsigned)(a.per_xcd * 8));
-    if (out_dtype == PARO_F32)
-        hipLaunchKernelGGL((attn_i8_kernel<BLK, D, QKBITS, PVBITS, float>), grid, dim3(BLK * 2), 0, st, a);
-    else
-        hipLaunchKernelGGL((attn_i8_kernel<BLK, D, QKBITS, PVBITS, uint16_t>), grid, dim3(BLK * 2), 0, st, a);
+    if (out_dtype == PARO_F32) hipLaunchKernelGGL((attn_i8_q16_kernel<D, QKBITS, PVBITS, float, QSRC>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((attn_i8_q16_kernel<D, QKBITS, PVBITS, uint16_t, QSRC>), grid, dim3(256), 0, st, a);
 }
 
-// Q taken from the unquantized tensor (block 64 only): QSRC 1 = bf16, 2 = fp32
-template <int D, int PVBITS, int QSRC>
-static void launch_rawq(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
+template <int QKBITS, int PVBITS, int QSRC = 0>
+static void launch_w64(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
     dim3 grid((unsigned)(a.per_xcd * 8));
-    if (out_dtype == PARO_F32)
-        hipLaunchKernelGGL((attn_i8_kernel<64, D, 8, PVBITS, float, QSRC>), grid, dim3(128), 0, st, a);
-    else
-        hipLaunchKernelGGL((attn_i8_kernel<64, D, 8, PVBITS, uint16_t, QSRC>), grid, dim3(128), 0, st, a);
-}
-
-template <int PVBITS, int QSRC>
-static void launch_rawq_w64(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
-    dim3 grid((unsigned)(a.per_xcd * 8));
-    if (out_dtype == PARO_F32) hipLaunchKernelGGL((attn_i8_w64_kernel<PVBITS, float, QSRC>), grid, dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((attn_i8_w64_kernel<PVBITS, uint16_t, QSRC>), grid, dim3(64), 0, st, a);
-}
-
-template <int QSRC>
-static void launch_rawq_shape(int d, int bits_pv, paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
-    if constexpr (PARO_ATTN_SINGLE_WAVE) {
-        if (d == 64) {  // block 64 is a precondition of this entry point: the one-wavefront kernel applies
-            if (bits_pv == 8) launch_rawq_w64<8, QSRC>(out_dtype, a, st);
-            else launch_rawq_w64<4, QSRC>(out_dtype, a, st);
-            return;
-        }
+    if constexpr (QKBITS == 8) {
+        if (out_dtype == PARO_F32) hipLaunchKernelGGL((attn_i8_w64_kernel<PVBITS, float, QSRC>), grid, dim3(64), 0, st, a);
+        else hipLaunchKernelGGL((attn_i8_w64_kernel<PVBITS, uint16_t, QSRC>), grid, dim3(64), 0, st, a);
+    } else {
+        if (out_dtype == PARO_F32) hipLaunchKernelGGL((attn_i8_w64_qk4_kernel<PVBITS, float>), grid, dim3(64), 0, st, a);
+        else hipLaunchKernelGGL((attn_i8_w64_qk4_kernel<PVBITS, uint16_t>), grid, dim3(64), 0, st, a);
     }
-    if (d == 64 && bits_pv == 8) launch_rawq<64, 8, QSRC>(out_dtype, a, st);
-    else if (d == 64) launch_rawq<64, 4, QSRC>(out_dtype, a, st);
-    else if (bits_pv == 8) launch_rawq<128, 8, QSRC>(out_dtype, a, st);
-    else launch_rawq<128, 4, QSRC>(out_dtype, a, st);
+}
+
+// Block 64; QSRC as in the kernels.  d = 64: with few row blocks the chain of a row's blocks is the launch, and four wavefronts of 16
+// queries are through a block in half the time that one wavefront of 64 needs; with many the chip is full and the 136 x 4 instructions
+// per block of the former lose to the 495 of the latter.  The line, in row blocks of the launch, both sides in us (four wavefronts / one),
+// 8-bit codes / all 4-bit: 256 16.3 / 30.5 and 17.8 / 34.0, 516 15.3 / 23.4 and 16.6 / 25.8, 1536 38.3 / 43.7 and 44.0 / 47.3, 1690
+// 117.7 / 116.2 and 124.0 / 116.4, 8250 720 / 628 and 826 / 688.
+constexpr int kQ16Rows = 1536;
+template <int QKBITS, int PVBITS, int QSRC = 0>
+static void launch_b64(int d, paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
+    if (d == 128) launch_q16<128, QKBITS, PVBITS, QSRC>(out_dtype, a, st);
+    else if (a.total_wg <= kQ16Rows) launch_q16<64, QKBITS, PVBITS, QSRC>(out_dtype, a, st);
+    else launch_w64<QKBITS, PVBITS, QSRC>(out_dtype, a, st);
 }
 
 template <int QKBITS, int PVBITS>
 static void launch_i8(int blk, int d, paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
-    if constexpr (PARO_ATTN_SINGLE_WAVE) {
-        if (blk == 64 && d == 64) {  // one wavefront per row block
-            dim3 grid((unsigned)(a.per_xcd * 8));
-            if constexpr (QKBITS == 8) {
-                if (out_dtype == PARO_F32) hipLaunchKernelGGL((attn_i8_w64_kernel<PVBITS, float>), grid, dim3(64), 0, st, a);
-                else hipLaunchKernelGGL((attn_i8_w64_kernel<PVBITS, uint16_t>), grid, dim3(64), 0, st, a);
-            } else {
-                if (out_dtype == PARO_F32) hipLaunchKernelGGL((attn_i8_w64_qk4_kernel<PVBITS, float>), grid, dim3(64), 0, st, a);
-                else hipLaunchKernelGGL((attn_i8_w64_qk4_kernel<PVBITS, uint16_t>), grid, dim3(64), 0, st, a);
-            }
-            return;
-        }
-    }
-    if constexpr (PARO_ATTN_Q16 && QKBITS == 8 && PVBITS == 8) {
-        if (blk == 64 && d == 128) {  // four wavefronts of 16 queries per row block
-            dim3 grid((unsigned)(a.per_xcd * 8));
-            if (out_dtype == PARO_F32) hipLaunchKernelGGL((attn_i8_q16_kernel<float>), grid, dim3(256), 0, st, a);
-            else hipLaunchKernelGGL((attn_i8_q16_kernel<uint16_t>), grid, dim3(256), 0, st, a);
-            return;
-        }
-    }
-    if (blk == 64 && d == 64) launch_out<64, 64, QKBITS, PVBITS>(out_dtype, a, st);
-    else if (blk == 64 && d == 128) launch_out<64, 128, QKBITS, PVBITS>(out_dtype, a, st);
+    if (blk == 64) launch_b64<QKBITS, PVBITS>(d, out_dtype, a, st);
     else if (d == 64) launch_b32<64, QKBITS, PVBITS>(out_dtype, a, st);
     else launch_b32<128, QKBITS, PVBITS>(out_dtype, a, st);
+}
+
+// Q taken from the unquantized tensor (block 64 only): QSRC 1 = bf16, 2 = fp32
+template <int QSRC>
+static void launch_rawq(int d, int bits_pv, paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
+    if (bits_pv == 8) launch_b64<8, 8, QSRC>(d, out_dtype, a, st);
+    else launch_b64<8, 4, QSRC>(d, out_dtype, a, st);
 }
 
 }  // namespace paro
@@ -2730,8 +2492,8 @@ static int attn_entry(const char* what, const paro_shape* s, int bits_qk, int bi
                                              : launch_bf16<uint16_t>(s->block, s->d, a, (hipStream_t)stream);
         if (st) return st;
     } else if (q_raw) {
-        if (q_raw == 1) launch_rawq_shape<1>(s->d, bits_pv, out_dtype, a, (hipStream_t)stream);
-        else launch_rawq_shape<2>(s->d, bits_pv, out_dtype, a, (hipStream_t)stream);
+        if (q_raw == 1) launch_rawq<1>(s->d, bits_pv, out_dtype, a, (hipStream_t)stream);
+        else launch_rawq<2>(s->d, bits_pv, out_dtype, a, (hipStream_t)stream);
     } else if (bits_qk == 8) {
         if (bits_pv == 8) launch_i8<8, 8>(s->block, s->d, out_dtype, a, (hipStream_t)stream);
         else launch_i8<8, 4>(s->block, s->d, out_dtype, a, (hipStream_t)stream);

@@ -227,6 +227,11 @@ int paro_permute_quantize_qkv_keep(const paro_shape* s, paro_dtype dtype, int bi
                                    void* qp, void* kp, void* vp, void* q_codes, float* sq, void* k_codes,
                                    float* sk, void* v_codes, float* sv, void* stream);
 
+/* paro_permute_quantize_qkv of K and V alone, for programs that hand Q to the attention call unquantized. */
+int paro_permute_quantize_kv(const paro_shape* s, paro_dtype dtype, int bits_qk, int bits_pv, const uint8_t* h_perm_ids,
+                             const void* k, const void* v, void* k_codes, float* sk, void* v_codes, float* sv,
+                             void* stream);
+
 /* paro_sparse_attn followed by paro_unpermute without the intermediate tensor: row n' of the
  * result is stored at row idx_h[n'] of o.  Arguments as paro_sparse_attn, plus
  *   h_perm_ids  host, [nh], values 0..5
@@ -253,6 +258,12 @@ int paro_sparse_attn_unpermuted(const paro_shape* s, int bits_qk, int bits_pv, c
 int paro_k_channel_mean(const paro_shape* s, paro_dtype dtype, const void* k, float* k_mean, void* stream);
 int paro_permute_quantize_smoothed(const paro_shape* s, paro_dtype dtype, int bits, const uint8_t* h_perm_ids,
                                    const void* k, const float* k_mean, void* codes, float* scales, void* stream);
+/* paro_k_channel_mean, paro_permute_quantize of Q and V and paro_permute_quantize_smoothed of K in two launches; the same
+ * mean, codes and scales.  bits (8,8), (8,4), (4,4) or (4,8);  k_mean  float32 [B,nh,d] (device), written */
+int paro_permute_quantize_qkv_smoothed(const paro_shape* s, paro_dtype dtype, int bits_qk, int bits_pv,
+                                       const uint8_t* h_perm_ids, const void* q, const void* k, const void* v,
+                                       float* k_mean, void* q_codes, float* sq, void* k_codes, float* sk,
+                                       void* v_codes, float* sv, void* stream);
 
 /* paro_sparse_attn_unpermuted with the reorder and quantization of Q folded in as well: the
  * quantization group of Q is the 64-token row block one workgroup owns (Sec. 4.3 (1): groups aligned

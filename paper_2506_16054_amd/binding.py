@@ -32,7 +32,7 @@ EXPORTS = (
     "paro_quantize", "paro_sparse_attn", "paro_permute_quantize", "paro_sparse_attn_unpermuted", "paro_schedule_rows", "paro_check_blocklist", "paro_check_row_order",
     "paro_mask_to_blocklist_device", "paro_calib_block_stats", "paro_calib_metrics", "paro_calib_choose", "paro_calib_mask",
     "paro_sparse_attn_unpermuted_rawq", "paro_blocklist_cols_device", "paro_permute_quantize_qkv", "paro_permute_quantize_qkv_keep",
-    "paro_k_channel_mean", "paro_permute_quantize_smoothed",
+    "paro_k_channel_mean", "paro_permute_quantize_smoothed", "paro_permute_quantize_qkv_smoothed", "paro_permute_quantize_kv",
     "paro_calib_row_stats_bytes", "paro_calib_row_stats", "paro_calib_block_stats_from_rows", "paro_calib_metrics_orders", "paro_calib_pick",
 )
 
@@ -94,6 +94,8 @@ def lib() -> ctypes.CDLL:
         L.paro_blocklist_cols_device.argtypes = [i32, i32, vp, vp, vp, i64, vp]
         L.paro_permute_quantize_qkv.argtypes = [sp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.paro_permute_quantize_qkv_keep.argtypes = [sp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+        L.paro_permute_quantize_kv.argtypes = [sp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp]
+        L.paro_permute_quantize_qkv_smoothed.argtypes = [sp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.paro_k_channel_mean.argtypes = [sp, i32, vp, vp, vp]
         L.paro_permute_quantize_smoothed.argtypes = [sp, i32, i32, vp, vp, vp, vp, vp, vp]
         _lib = L
@@ -104,7 +106,7 @@ def lib() -> ctypes.CDLL:
 # tokens is two calls and host work only, 9.3 us with it and 17.3 us through the checks below and ctypes.  It declines by
 # returning None whatever it does not take as it stands, and the function here goes on with its own checks.
 FASTCALL = ("paro_permute_quantize_qkv", "paro_permute_quantize_qkv_keep", "paro_sparse_attn", "paro_sparse_attn_unpermuted", "paro_unpermute",
-            "paro_mask_to_blocklist_device")
+            "paro_mask_to_blocklist_device", "paro_permute_quantize_kv", "paro_permute_quantize_qkv_smoothed", "paro_sparse_attn_unpermuted_rawq")
 _fast = None
 
 
@@ -414,6 +416,32 @@ def paro_permute_quantize_qkv_keep(s: paro_shape, bits_qk: int, bits_pv: int, pe
                                                 _ptr(v_codes), _ptr(sv), _stream()))
 
 
+def paro_permute_quantize_kv(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, k, v, k_codes, sk, v_codes, sv) -> None:
+    """paro_permute_quantize_qkv of K and V alone."""
+    if _made((_fast or _layer_calls()).paro_permute_quantize_kv(s, bits_qk, bits_pv, perm_ids, k, v, k_codes, sk, v_codes, sv)):
+        return
+    _qkv_operands(s, bits_qk, bits_pv, k, k, v, k_codes, sk, k_codes, sk, v_codes, sv)
+    p = _perm_bytes(s, perm_ids)
+    _check(lib().paro_permute_quantize_kv(ctypes.byref(s), _dtype_code(k), int(bits_qk), int(bits_pv), p, _ptr(k), _ptr(v), _ptr(k_codes), _ptr(sk),
+                                          _ptr(v_codes), _ptr(sv), _stream()))
+
+
+def paro_permute_quantize_qkv_smoothed(s: paro_shape, bits_qk: int, bits_pv: int, perm_ids, q, k, v, k_mean, q_codes, sq, k_codes, sk,
+                                       v_codes, sv) -> None:
+    """k_mean: float32 [B, nh, d], written: the channel mean that is removed from K."""
+    if _made((_fast or _layer_calls()).paro_permute_quantize_qkv_smoothed(s, bits_qk, bits_pv, perm_ids, q, k, v, k_mean, q_codes, sq, k_codes, sk,
+                                                                      v_codes, sv)):
+        return
+    import torch
+
+    _qkv_operands(s, bits_qk, bits_pv, q, k, v, q_codes, sq, k_codes, sk, v_codes, sv)
+    _require(k_mean, "k_mean", (s.B, s.nh, s.d), torch.float32)
+    p = _perm_bytes(s, perm_ids)
+    _check(lib().paro_permute_quantize_qkv_smoothed(ctypes.byref(s), _dtype_code(q), int(bits_qk), int(bits_pv), p, _ptr(q), _ptr(k), _ptr(v),
+                                                    _ptr(k_mean), _ptr(q_codes), _ptr(sq), _ptr(k_codes), _ptr(sk), _ptr(v_codes), _ptr(sv),
+                                                    _stream()))
+
+
 def paro_k_channel_mean(s: paro_shape, k, k_mean) -> None:
     import torch
 
@@ -595,6 +623,8 @@ def paro_sparse_attn_unpermuted(s: paro_shape, bits_qk: int, bits_pv: int, q, sq
 
 def paro_sparse_attn_unpermuted_rawq(s: paro_shape, bits_pv: int, q, k, sk, v, sv, row_ptr, col_idx, perm_ids, o, row_order=None) -> None:
     """q: unquantized [B, nh, N, d] (fp32 or bf16, default order); k, v: 8-bit K codes (rows) and 8/4-bit V codes (transposed)."""
+    if _made((_fast or _layer_calls()).paro_sparse_attn_unpermuted_rawq(s, bits_pv, q, k, sk, v, sv, row_ptr, col_idx, perm_ids, o, row_order)):
+        return
     import torch
 
     m = _dims(s)

@@ -31,6 +31,9 @@ decltype(&paro_sparse_attn) g_attn;
 decltype(&paro_sparse_attn_unpermuted) g_attn_unpermuted;
 decltype(&paro_unpermute) g_unpermute;
 decltype(&paro_mask_to_blocklist_device) g_expand;
+decltype(&paro_permute_quantize_kv) g_kv;
+decltype(&paro_permute_quantize_qkv_smoothed) g_qkv_smoothed;
+decltype(&paro_sparse_attn_unpermuted_rawq) g_rawq;
 
 // What follows from a shape: as the binding's _Dims.
 struct Dims {
@@ -132,41 +135,89 @@ PyObject* guarded(F&& f) {
 }
 #define PARO_DECLINE Py_RETURN_NONE
 
-PyObject* quantize_qkv(PyObject* const* a, Py_ssize_t count, bool keep) {
-    // s, bits_qk, bits_pv, perm_ids, q, k, v, [qp, kp, vp,] q_codes, sq, k_codes, sk, v_codes, sv
-    if (count != (keep ? 16 : 13) || !g_shape) PARO_DECLINE;
+// s, bits_qk, bits_pv, perm_ids, the inputs from tensor `first` (0 q, 1 k) on, ..., and from argument `at` on their codes and scales in turn
+struct QkvArgs {
     Dims m;
     long qk, pv;
     PermIds ids;
-    if (!m.read(a[0]) || !number(a[1], &qk) || !number(a[2], &pv) || !ids.read(a[3], m.s.nh)) PARO_DECLINE;
-    const at::Tensor *in[3], *kept[3] = {nullptr, nullptr, nullptr}, *codes[3], *scales[3];
+    int first;
+    const at::Tensor *in[3], *codes[3], *scales[3];
     paro_dtype dtype;
-    for (int i = 0; i < 3; ++i) {
-        in[i] = of_shape(a[4 + i], {m.s.B, m.s.nh, m.n, m.s.d});
-        if (!in[i] || in[i]->scalar_type() != in[0]->scalar_type()) PARO_DECLINE;
-    }
-    if (!dtype_of(*in[0], &dtype)) PARO_DECLINE;
-    const int at = keep ? 10 : 7;
-    for (int i = 0; i < 3; ++i) {
-        const long bits = i == 2 ? pv : qk;
-        if (keep && !(kept[i] = typed(a[7 + i], {m.s.B, m.s.nh, m.npad, m.s.d}, in[0]->scalar_type()))) PARO_DECLINE;
-        codes[i] = i == 2 ? vt_of(a[at + 4], m, bits) : rows_of(a[at + 2 * i], m, bits);
-        scales[i] = scales_of(a[at + 2 * i + 1], m);
-        if (!code_type(codes[i], bits) || !scales[i]) PARO_DECLINE;
-    }
-    void* st = stream();
-    void *p[3], *x[3], *c[3];
+    void *p[3], *c[3], *st;
     float* f[3];
-    for (int i = 0; i < 3; ++i) {
-        p[i] = ptr(in[i]);
-        x[i] = keep ? ptr(kept[i]) : nullptr;
-        c[i] = ptr(codes[i]);
-        f[i] = (float*)ptr(scales[i]);
+    bool read(PyObject* const* a, int from, int at) {
+        first = from;
+        if (!m.read(a[0]) || !number(a[1], &qk) || !number(a[2], &pv) || !ids.read(a[3], m.s.nh)) return false;
+        for (int i = first; i < 3; ++i) {
+            in[i] = of_shape(a[4 + i - first], {m.s.B, m.s.nh, m.n, m.s.d});
+            if (!in[i] || in[i]->scalar_type() != in[first]->scalar_type()) return false;
+        }
+        if (!dtype_of(*in[first], &dtype)) return false;
+        for (int i = first; i < 3; ++i) {
+            const long bits = i == 2 ? pv : qk;
+            PyObject* const* pair = a + at + 2 * (i - first);
+            codes[i] = i == 2 ? vt_of(pair[0], m, bits) : rows_of(pair[0], m, bits);
+            scales[i] = scales_of(pair[1], m);
+            if (!code_type(codes[i], bits) || !scales[i]) return false;
+        }
+        return true;
     }
+    void pointers() {
+        st = stream();
+        for (int i = first; i < 3; ++i) {
+            p[i] = ptr(in[i]);
+            c[i] = ptr(codes[i]);
+            f[i] = (float*)ptr(scales[i]);
+        }
+    }
+};
+
+PyObject* quantize_qkv(PyObject* const* a, Py_ssize_t count, bool keep) {
+    // s, bits_qk, bits_pv, perm_ids, q, k, v, [qp, kp, vp,] q_codes, sq, k_codes, sk, v_codes, sv
+    if (count != (keep ? 16 : 13) || !g_shape) PARO_DECLINE;
+    QkvArgs x;
+    if (!x.read(a, 0, keep ? 10 : 7)) PARO_DECLINE;
+    const at::Tensor* kept[3] = {nullptr, nullptr, nullptr};
+    for (int i = 0; keep && i < 3; ++i)
+        if (!(kept[i] = typed(a[7 + i], {x.m.s.B, x.m.s.nh, x.m.npad, x.m.s.d}, x.in[0]->scalar_type()))) PARO_DECLINE;
+    void* r[3];
+    for (int i = 0; i < 3; ++i) r[i] = keep ? ptr(kept[i]) : nullptr;
+    x.pointers();
     int status;
     Py_BEGIN_ALLOW_THREADS;
-    status = keep ? g_qkv_keep(&m.s, dtype, (int)qk, (int)pv, ids.data(), p[0], p[1], p[2], x[0], x[1], x[2], c[0], f[0], c[1], f[1], c[2], f[2], st)
-                  : g_qkv(&m.s, dtype, (int)qk, (int)pv, ids.data(), p[0], p[1], p[2], c[0], f[0], c[1], f[1], c[2], f[2], st);
+    status = keep ? g_qkv_keep(&x.m.s, x.dtype, (int)x.qk, (int)x.pv, x.ids.data(), x.p[0], x.p[1], x.p[2], r[0], r[1], r[2], x.c[0], x.f[0], x.c[1],
+                               x.f[1], x.c[2], x.f[2], x.st)
+                  : g_qkv(&x.m.s, x.dtype, (int)x.qk, (int)x.pv, x.ids.data(), x.p[0], x.p[1], x.p[2], x.c[0], x.f[0], x.c[1], x.f[1], x.c[2], x.f[2],
+                          x.st);
+    Py_END_ALLOW_THREADS;
+    return PyLong_FromLong(status);
+}
+
+PyObject* quantize_kv(PyObject* const* a, Py_ssize_t count) {  // s, bits_qk, bits_pv, perm_ids, k, v, k_codes, sk, v_codes, sv
+    if (count != 10 || !g_shape) PARO_DECLINE;
+    QkvArgs x;
+    if (!x.read(a, 1, 6)) PARO_DECLINE;
+    x.pointers();
+    int status;
+    Py_BEGIN_ALLOW_THREADS;
+    status = g_kv(&x.m.s, x.dtype, (int)x.qk, (int)x.pv, x.ids.data(), x.p[1], x.p[2], x.c[1], x.f[1], x.c[2], x.f[2], x.st);
+    Py_END_ALLOW_THREADS;
+    return PyLong_FromLong(status);
+}
+
+PyObject* quantize_qkv_smoothed(PyObject* const* a, Py_ssize_t count) {
+    // s, bits_qk, bits_pv, perm_ids, q, k, v, k_mean, q_codes, sq, k_codes, sk, v_codes, sv
+    if (count != 14 || !g_shape) PARO_DECLINE;
+    QkvArgs x;
+    if (!x.read(a, 0, 8)) PARO_DECLINE;
+    const at::Tensor* mean = typed(a[7], {x.m.s.B, x.m.s.nh, x.m.s.d}, at::kFloat);
+    if (!mean) PARO_DECLINE;
+    float* mp = (float*)ptr(mean);
+    x.pointers();
+    int status;
+    Py_BEGIN_ALLOW_THREADS;
+    status = g_qkv_smoothed(&x.m.s, x.dtype, (int)x.qk, (int)x.pv, x.ids.data(), x.p[0], x.p[1], x.p[2], mp, x.c[0], x.f[0], x.c[1], x.f[1], x.c[2],
+                            x.f[2], x.st);
     Py_END_ALLOW_THREADS;
     return PyLong_FromLong(status);
 }
@@ -214,6 +265,38 @@ PyObject* attention(PyObject* const* a, Py_ssize_t count, bool unpermuted) {
     return PyLong_FromLong(status);
 }
 
+PyObject* attention_rawq(PyObject* const* a, Py_ssize_t count) {  // s, bits_pv, q, k, sk, v, sv, row_ptr, col_idx, perm_ids, o, row_order
+    if (count != 12 || !g_shape) PARO_DECLINE;
+    Dims m;
+    long pv;
+    PermIds ids;
+    if (!m.read(a[0]) || !number(a[1], &pv) || !ids.read(a[9], m.s.nh)) PARO_DECLINE;
+    const at::Tensor* q = of_shape(a[2], {m.s.B, m.s.nh, m.n, m.s.d});
+    const at::Tensor* k = rows_of(a[3], m, 8);
+    const at::Tensor* v = vt_of(a[5], m, pv);
+    const at::Tensor *sk = scales_of(a[4], m), *sv = scales_of(a[6], m);
+    paro_dtype q_dtype, dtype;
+    if (!q || !dtype_of(*q, &q_dtype) || !k || k->scalar_type() != at::kChar || !v || v->scalar_type() != at::kChar || !sk || !sv) PARO_DECLINE;
+    const at::Tensor* row_ptr = typed(a[7], {m.s.nh, m.k + 1}, at::kInt);
+    const at::Tensor* cols = of_type(a[8], at::kInt);
+    const at::Tensor* o = of_shape(a[10], {m.s.B, m.s.nh, m.n, m.s.d});
+    if (!row_ptr || !cols || !o || !dtype_of(*o, &dtype)) PARO_DECLINE;
+    const at::Tensor* order = nullptr;
+    if (a[11] != Py_None && !(order = typed(a[11], {(int64_t)m.s.B * m.s.nh * m.k}, at::kInt))) PARO_DECLINE;
+    void* st = stream();
+    const int64_t nnz = cols->numel();
+    void *qp = ptr(q), *kp = ptr(k), *vp = ptr(v), *op = ptr(o);
+    const float *skp = (const float*)ptr(sk), *svp = (const float*)ptr(sv);
+    const int32_t* rp = (const int32_t*)ptr(row_ptr);
+    const int32_t* ci = nnz ? (const int32_t*)ptr(cols) : nullptr;
+    const int32_t* ro = order ? (const int32_t*)ptr(order) : nullptr;
+    int status;
+    Py_BEGIN_ALLOW_THREADS;
+    status = g_rawq(&m.s, q_dtype, (int)pv, qp, kp, skp, vp, svp, rp, ci, nnz, ro, ids.data(), dtype, op, st);
+    Py_END_ALLOW_THREADS;
+    return PyLong_FromLong(status);
+}
+
 PyObject* inverse_reorder(PyObject* const* a, Py_ssize_t count) {  // s, perm_ids, op, o
     if (count != 4 || !g_shape) PARO_DECLINE;
     Dims m;
@@ -257,12 +340,15 @@ PyObject* f_qkv_keep(PyObject*, PyObject* const* a, Py_ssize_t n) { return guard
 PyObject* f_attn(PyObject*, PyObject* const* a, Py_ssize_t n) { return guarded([&] { return attention(a, n, false); }); }
 PyObject* f_attn_unpermuted(PyObject*, PyObject* const* a, Py_ssize_t n) { return guarded([&] { return attention(a, n, true); }); }
 PyObject* f_unpermute(PyObject*, PyObject* const* a, Py_ssize_t n) { return guarded([&] { return inverse_reorder(a, n); }); }
+PyObject* f_kv(PyObject*, PyObject* const* a, Py_ssize_t n) { return guarded([&] { return quantize_kv(a, n); }); }
+PyObject* f_qkv_smoothed(PyObject*, PyObject* const* a, Py_ssize_t n) { return guarded([&] { return quantize_qkv_smoothed(a, n); }); }
+PyObject* f_rawq(PyObject*, PyObject* const* a, Py_ssize_t n) { return guarded([&] { return attention_rawq(a, n); }); }
 PyObject* f_expand(PyObject*, PyObject* const* a, Py_ssize_t n) { return guarded([&] { return expand(a, n); }); }
 
 PyObject* f_bind(PyObject*, PyObject* args) {  // the shape type, then the addresses in the order of the declarations above
     PyObject* shape;
-    unsigned long long p[6];
-    if (!PyArg_ParseTuple(args, "O!KKKKKK", &PyType_Type, &shape, p, p + 1, p + 2, p + 3, p + 4, p + 5)) return nullptr;
+    unsigned long long p[9];
+    if (!PyArg_ParseTuple(args, "O!KKKKKKKKK", &PyType_Type, &shape, p, p + 1, p + 2, p + 3, p + 4, p + 5, p + 6, p + 7, p + 8)) return nullptr;
     Py_INCREF(shape);  // for the life of the process, like the library
     g_shape = (PyTypeObject*)shape;
     g_qkv = (decltype(g_qkv))(uintptr_t)p[0];
@@ -271,6 +357,9 @@ PyObject* f_bind(PyObject*, PyObject* args) {  // the shape type, then the addre
     g_attn_unpermuted = (decltype(g_attn_unpermuted))(uintptr_t)p[3];
     g_unpermute = (decltype(g_unpermute))(uintptr_t)p[4];
     g_expand = (decltype(g_expand))(uintptr_t)p[5];
+    g_kv = (decltype(g_kv))(uintptr_t)p[6];
+    g_qkv_smoothed = (decltype(g_qkv_smoothed))(uintptr_t)p[7];
+    g_rawq = (decltype(g_rawq))(uintptr_t)p[8];
     Py_RETURN_NONE;
 }
 
@@ -282,6 +371,9 @@ PyMethodDef methods[] = {
     {"paro_sparse_attn_unpermuted", (PyCFunction)(void (*)(void))f_attn_unpermuted, METH_FASTCALL, nullptr},
     {"paro_unpermute", (PyCFunction)(void (*)(void))f_unpermute, METH_FASTCALL, nullptr},
     {"paro_mask_to_blocklist_device", (PyCFunction)(void (*)(void))f_expand, METH_FASTCALL, nullptr},
+    {"paro_permute_quantize_kv", (PyCFunction)(void (*)(void))f_kv, METH_FASTCALL, nullptr},
+    {"paro_permute_quantize_qkv_smoothed", (PyCFunction)(void (*)(void))f_qkv_smoothed, METH_FASTCALL, nullptr},
+    {"paro_sparse_attn_unpermuted_rawq", (PyCFunction)(void (*)(void))f_rawq, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "paro_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -112,11 +112,15 @@ class ParoAttention:
 
     # ---- optional pre-conditioning of K: the per-channel mean over the tokens is removed in the quantizer's loads
     def prepare_fused_smooth_k(self, q, k, v) -> None:
-        """prepare_fused with paro_k_channel_mean + paro_permute_quantize_smoothed for K (integer K codes only)."""
+        """prepare_fused with the channel mean of K removed (integer K codes only): two launches."""
         s = self.s
         fq, fk = self._fused_buffers()
         if not hasattr(self, "k_mean"):
             self.k_mean = torch.empty((s.B, s.nh, s.d), dtype=torch.float32, device=self.dev)
+        if self.bits_qk != 16 and q.dtype == k.dtype == v.dtype:
+            pb.paro_permute_quantize_qkv_smoothed(s, self.bits_qk, self.bits_pv, self.perm_ids, q, k, v, self.k_mean, fq, self.sq, fk, self.sk,
+                                                  self.vc, self.sv)
+            return
         pb.paro_k_channel_mean(s, k, self.k_mean)
         pb.paro_permute_quantize(s, self.bits_qk, pb.PARO_ROWS, self.perm_ids, q, fq, self.sq)
         pb.paro_permute_quantize_smoothed(s, self.bits_qk, self.perm_ids, k, self.k_mean, fk, self.sk)
@@ -127,13 +131,16 @@ class ParoAttention:
         return self.attend_fused()
 
     # ---- shortest form (block 64, 8-bit QK): Q is reordered and quantized inside the attention kernel,
-    # by the workgroup that owns the row block; three launches
+    # by the workgroup that owns the row block; two launches
     @property
     def can_fuse_q(self) -> bool:
         return self.bits_qk == 8 and self.s.block == 64
 
     def prepare_kv(self, k, v) -> None:
         _, fk = self._fused_buffers()
+        if k.dtype == v.dtype:
+            pb.paro_permute_quantize_kv(self.s, 8, self.bits_pv, self.perm_ids, k, v, fk, self.sk, self.vc, self.sv)
+            return
         pb.paro_permute_quantize(self.s, 8, pb.PARO_ROWS, self.perm_ids, k, fk, self.sk)
         pb.paro_permute_quantize(self.s, self.bits_pv, pb.PARO_VT, self.perm_ids, v, self.vc, self.sv)
 

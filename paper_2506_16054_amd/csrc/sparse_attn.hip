@@ -1690,223 +1690,15 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
 }
 
 // -------------------------------------------------------------------------------------------
-// bf16 unquantized block-sparse mode (the sparse-only rows of the paper's tables) at block 32: one wavefront per row
-// block, same transposed orientation and block list, on v_mfma_f32_32x32x16_bf16.  P is not quantized,
-// so there is no tile-wide scale; P enters the PV product rounded to bf16 while the denominator accumulates
-// it in fp32.  The tiles go through registers to ONE LDS stage.  Block 64 has the kernels behind this one.
+// bf16 unquantized block-sparse mode (the sparse-only rows of the paper's tables), on v_mfma_f32_16x16x32_bf16 in the same transposed
+// orientation.  P is not quantized, so there is no tile-wide scale; P enters the PV product rounded to bf16 while the denominator
+// accumulates it in fp32.
 // -------------------------------------------------------------------------------------------
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-
-template <int D>
-struct Bf16B32Cfg {
-    static constexpr int KSTR = 2 * D + 16;   // bytes per K row in LDS (bf16 + 16 B pad)
-    static constexpr int VSTR = 2 * 32 + 16;  // bytes per V^T row in LDS
-    static constexpr int KBYTES = 32 * KSTR;
-    static constexpr int LDS_BYTES = KBYTES + D * VSTR;
-};
-
-template <int D, typename OutT>
-__global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_bf16_b32_kernel(AttnArgs a) {
-    constexpr int BLK = 32;
-    constexpr int KSTR = Bf16B32Cfg<D>::KSTR, VSTR = Bf16B32Cfg<D>::VSTR, KBYTES = Bf16B32Cfg<D>::KBYTES;
-    constexpr int NC = BLK * D * 2 / 16 / 64;  // 16-byte pieces of a tile per lane
-    constexpr int KS = D / 16;                 // contraction steps of QK^T (16 channels each)
-    constexpr int DT = D / 32;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-
-    const int wg = blockIdx.x;
-    const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
-    if (logical >= a.total_wg) return;
-    const int item = a.row_order ? min(max(a.row_order[logical], 0), a.total_wg - 1) : logical;
-    const int bh = item / a.kblocks;
-    const int i = item - bh * a.kblocks;
-    const int h = bh % a.nh;
-    const int lane = threadIdx.x;
-    const int n = lane & 31;
-    const int g = lane >> 5;
-
-    const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
-    const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));  // uniform: scalar loop control
-    const int end = __builtin_amdgcn_readfirstlane(min(max(rp[1], beg), a.nnz));
-    const int cnt = end - beg;
-    const int* cols = a.col_idx + beg;
-
-    const size_t head_rows = (size_t)bh * a.kblocks * BLK;
-    const int row = i * BLK + n;
-    const bool row_valid = row < a.n_tokens;
-    const uint8_t* kbase = a.k + head_rows * D * 2;
-    const uint8_t* vbase = a.v + head_rows * D * 2;
-    const float c = a.qk_scale;
-
-    v8bf qf[KS];
-    {
-        const uint8_t* qrow = a.q + (head_rows + row) * D * 2 + 16 * g;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s] = *(const v8bf*)(qrow + 32 * s);
-    }
-
-    // column indices: 64 per fetch, one per lane, read back with v_readlane (as in the INT8 kernel)
-    auto load_cols = [&](int chunk) {
-        const int idx = min(chunk * 64 + lane, cnt - 1);
-        return cnt > 0 && chunk * 64 < cnt ? min(max(cols[idx], 0), a.kblocks - 1) : 0;
-    };
-    int cols_cur = load_cols(0), cols_nxt = load_cols(1);
-    int cur_chunk = 0;
-    auto col_of = [&](int t) {
-        return (t >> 6) == cur_chunk ? __builtin_amdgcn_readlane(cols_cur, t & 63) : __builtin_amdgcn_readlane(cols_nxt, t & 63);
-    };
-
-    v4i kreg[NC], vreg[NC];
-    // LDS store offsets: piece cc of a lane lies a whole number of rows below its piece 0, so one
-    // address per tile serves all pieces through immediate offsets
-    static_assert(1024 % (2 * D) == 0 && 1024 % (2 * BLK) == 0, "pieces must be whole rows apart");
-    const int k_off = ((16 * lane) / (2 * D)) * KSTR + (16 * lane) % (2 * D);
-    const int v_off = KBYTES + ((16 * lane) / (2 * BLK)) * VSTR + (16 * lane) % (2 * BLK);
-    auto lstore_k = [&]() {
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) *(v4i*)(lds + k_off + cc * (1024 / (2 * D)) * KSTR) = kreg[cc];
-    };
-    auto lstore_v = [&]() {
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) *(v4i*)(lds + v_off + cc * (1024 / (2 * BLK)) * VSTR) = vreg[cc];
-    };
-
-    // The exponentials are taken against a fixed reference per row (its maximum after the first
-    // block) instead of the running maximum: P is not quantized here, so the common factor
-    // 2^(m - m_ref) of numerator and denominator cancels in acc / l and no rescaling pass is needed.
-    // A row whose maximum climbs more than 64 octaves above the reference is re-referenced.
-    float m_ref = -INFINITY;
-    float l = 0.0f;
-    v16f acc[DT];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
-
-    // One LDS stage and two barriers per live block: K_t is read before the first; behind it K_{t+1} and V_t replace
-    // K_t and V_{t-1}, the second publishes them to all lanes.
-    auto gload_k = [&](int t) {
-        const uint8_t* kp = kbase + (size_t)col_of(t) * (BLK * D * 2);
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) kreg[cc] = *(const v4i*)(kp + 16 * (lane + 64 * cc));
-    };
-    auto gload_v = [&](int t) {
-        const uint8_t* vp = vbase + (size_t)col_of(t) * (BLK * D * 2);
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) vreg[cc] = *(const v4i*)(vp + 16 * (lane + 64 * cc));
-    };
-    if (cnt > 0) {
-        gload_k(0);
-        gload_v(0);
-        lstore_k();
-        if (cnt > 1) gload_k(1);
-    }
-    __syncthreads();
-
-    auto step = [&](auto tail_tag, int t) {
-        constexpr bool TAIL = decltype(tail_tag)::value;
-        v16f sacc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] = 0.0f;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const v8bf kf = *(const v8bf*)(lds + n * KSTR + 32 * s + 16 * g);
-            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc, 0, 0, 0);
-        }
-        if constexpr (TAIL) {
-            const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (8 * (r >> 2) + 4 * g + (r & 3) >= nkeys) sacc[r] = -INFINITY;
-        }
-        auto row_max = [&]() {  // maximum over the block's keys of this lane's query, in both of its lanes
-            float part[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part[r & 3] = fmaxf(part[r & 3], sacc[r]);
-            const float mx = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(mx), __float_as_int(mx), false, false);
-            return fmaxf(__int_as_float((int)sw[0]), __int_as_float((int)sw[1]));
-        };
-        // a row without a reference yet (first block, or nothing but masked keys so far) takes its block maximum
-        if (__builtin_amdgcn_ballot_w64(m_ref == -INFINITY) != 0) {
-            const float ymax = c * row_max();
-            if (m_ref == -INFINITY) m_ref = ymax;
-        }
-        // y = c S - m_ref, the exponent of P, FIRST, in place of S: its maximum tells whether the row has climbed past
-        // its reference (results of an fma need no NaN quieting before a maximum, raw matrix results would)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] = fmaf(sacc[r], c, -m_ref);
-        const float climb = row_max();  // row maximum - reference
-        __syncthreads();
-        lstore_v();                       // V_t (loaded one block ago)
-        if (t + 1 < cnt) lstore_k();      // K_{t+1}
-        if (t + 1 < cnt) gload_v(t + 1);  // before the column chunk moves on: t+1 may be its last entry
-        if (((t + 2) & 63) == 0) {
-            cols_cur = cols_nxt;
-            ++cur_chunk;
-            cols_nxt = load_cols(cur_chunk + 1);
-        }
-        if (t + 2 < cnt) gload_k(t + 2);
-        if (__builtin_amdgcn_ballot_w64(climb > 64.0f) != 0) {
-            const float up = fmaxf(climb, 0.0f);  // rows that have not climbed keep their reference
-            const float down = __builtin_amdgcn_exp2f(-up);
-            l *= down;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[dt][r] *= down;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sacc[r] -= up;
-            m_ref += up;
-        }
-
-        float rs = 0.0f;
-        v8bf pf[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-                const float p0 = __builtin_amdgcn_exp2f(sacc[8 * u + 2 * e2]);
-                const float p1 = __builtin_amdgcn_exp2f(sacc[8 * u + 2 * e2 + 1]);
-                rs += p0 + p1;
-                const v2bf pb = __builtin_convertvector(v2f{p0, p1}, v2bf);
-                pf[u][2 * e2] = pb[0];
-                pf[u][2 * e2 + 1] = pb[1];
-            }
-        l += rs;
-
-        __syncthreads();  // K_{t+1} and V_t are in place
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const v8bf vf = *(const v8bf*)(lds + KBYTES + (32 * dt + n) * VSTR + 2 * (16 * g + 8 * u));
-                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[u], acc[dt], 0, 0, 0);
-            }
-    };
-
-    const bool has_tail = (a.n_tokens % BLK) != 0 && cnt > 0 && min(max(cols[cnt - 1], 0), a.kblocks - 1) == a.kblocks - 1;
-    const int cnt_main = has_tail ? cnt - 1 : cnt;
-    for (int t = 0; t < cnt_main; ++t) step(std::false_type{}, t);
-    if (has_tail) step(std::true_type{}, cnt - 1);
-
-    const float l_tot = l + __shfl_xor(l, 32);
-    const float inv = (row_valid && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
-    const long long ooff = out_row_offset<D>(a, bh, h, head_rows, row, row_valid);
-    if (ooff >= 0) {
-        OutT* orow = (OutT*)a.op + ooff + 4 * g;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd)
-                store4(orow + 32 * dt + 8 * qd, acc[dt][4 * qd] * inv, acc[dt][4 * qd + 1] * inv, acc[dt][4 * qd + 2] * inv,
-                       acc[dt][4 * qd + 3] * inv);
-    }
-}
 
 // -------------------------------------------------------------------------------------------
 // bf16 mode, block 64: the wavefronts of a row block split its KEYS.  P is not quantized, so nothing ties the keys of a
@@ -2372,13 +2164,248 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
     else rows.template finish<0, 4>((OutT*)a.op, offset, row0, a.n_tokens, take, meet[w ^ 2], ln);
 }
 
+// Block 32, and d = 64, block 64 with few row blocks: a wavefront has 32 queries and 32 keys of every live block, at block 32 the whole of
+// it, at block 64 the queries 32 (w & 1) .. and the keys 32 (w >> 1) .. of a row block that four wavefronts share until their sums meet at
+// its end.  A wavefront moves its part of the tiles to LDS itself (one slot each; K_{t+2} is requested behind the reads of K_{t+1}, V_{t+1}
+// behind those of V_t), so there is no barrier in the loop, and K Q of block t + 1 runs beside the exponentials of block t.
+// Bound by the chain of a block where the chip is not full, by LDS and power where it is.  Attention call alone, us, before (block 32: tiles
+// through registers with two barriers per block; block 64: attn_bf16_d64_kernel) -> now, 30 % density: block 32, d = 64, 30 heads of 17550 tokens
+// 1129 -> 915, 4 heads of 4096 32.2 -> 23.8; d = 128 2343 -> 1988 (three wavefronts per SIMD instead of two: 2186) and 40.9 -> 32.8; block 64,
+// d = 64, 4 heads of 4096 20.5 -> 15.2, 6 heads of 1955 14.2 -> 10.7.  At block 64, d = 128 each byte that two wavefronts share would be
+// moved to LDS twice: 73.6 -> 107.8 for 24 heads of 4096.
+template <int BLK, int D, typename OutT>
+__global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_bf16_q32_kernel(AttnArgs a) {
+    constexpr int NW = BLK == 32 ? 1 : 4;
+    static_assert(BLK == 32 || D == 64, "shapes that are launched");
+    constexpr int TILE = 32 * D * 2;  // bytes of a wavefront's part of a K or V^T tile
+    constexpr int KS = D / 32, CT = D / 16;
+    constexpr int REQUESTS = TILE / 1024;  // per tile
+    __shared__ __attribute__((aligned(16))) uint8_t kslots[NW][TILE];
+    __shared__ __attribute__((aligned(16))) uint8_t vslots[NW][TILE];
+    __shared__ float meet[NW > 1 ? 2 : 1][4][64];  // [half of the queries][2 references, 2 sums][lane]
+
+    const int wg = blockIdx.x;
+    const int logical = (wg & 7) * a.per_xcd + (wg >> 3);
+    if (logical >= a.total_wg) return;
+    const int item = a.row_order ? min(max(a.row_order[logical], 0), a.total_wg - 1) : logical;
+    const int bh = item / a.kblocks;
+    const int i = item - bh * a.kblocks;
+    const int h = bh % a.nh;
+    const int lane = threadIdx.x & 63;
+    const int w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kh = w >> 1;                           // which 32 keys of a block
+    const int row0 = i * BLK + 32 * (w & 1);         // first query
+    uint8_t* const kbuf = &kslots[w][0];
+    uint8_t* const vbuf = &vslots[w][0];
+    const int n = lane & 15;
+    const int G = lane >> 4;
+
+    const int* rp = a.row_ptr + (size_t)h * (a.kblocks + 1) + i;
+    const int beg = __builtin_amdgcn_readfirstlane(min(max(rp[0], 0), a.nnz));
+    const int end = __builtin_amdgcn_readfirstlane(min(max(rp[1], beg), a.nnz));
+    const int cnt = end - beg;
+    const int* cols = a.col_idx + beg;
+
+    const size_t head_rows = (size_t)bh * a.kblocks * BLK;
+    const uint8_t* kbase = a.k + head_rows * D * 2 + TILE * kh;  // rows 32 kh .. of a K tile
+    const uint8_t* vbase = a.v + head_rows * D * 2 + 64 * kh;    // slots 32 kh .. of every row of a V^T tile
+    const float c = a.qk_scale;
+    v8bf qf[2][KS];  // [group of 16 queries][32 channels]
+#pragma unroll
+    for (int H = 0; H < 2; ++H) {
+        const uint8_t* qrow = a.q + (head_rows + row0 + 16 * H + n) * D * 2 + 16 * G;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qf[H][s] = *(const v8bf*)(qrow + 64 * s);
+    }
+    // K rows are one 128-byte line or two; piece p of a line of row r sits at position p ^ (r % 4 + 4 (r / 16)), different for the
+    // eight rows that neighbouring lanes read.  V^T: rows of 64 bytes, piece p of row r at position p ^ (r / 2) % 4.
+    const int krow = bf16_krow(n);
+    unsigned kfill = D == 64 ? 128u * (lane >> 3) + 16u * ((lane & 7) ^ ((lane >> 3) & 3))
+                             : 256u * (lane >> 4) + 16u * ((lane & 8) | ((lane & 7) ^ (lane >> 4)));
+    const unsigned vfill = 2u * BLK * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
+    unsigned kread = 2u * D * krow + 16u * (G ^ ((krow & 3) | ((krow >> 2) & 4)));  // 32 channels s: piece 4 s + G
+    const unsigned vread = 64u * n + 16u * (G ^ ((n >> 1) & 3));
+    auto request_k = [&](int j) __attribute__((always_inline)) {
+        const uint8_t* kp = kbase + (size_t)j * (BLK * D * 2);
+        asm volatile("" : "+s"(kp), "+v"(kfill));  // scalar base + lane offset; the flipped offset of rows 16 .. is made here, not kept
+        if constexpr (D == 64) {
+            lds_dma16<0>(kp, kfill, &kbuf[0]);
+            lds_dma16<1024>(kp, kfill, &kbuf[1024]);
+            lds_dma16<2048>(kp, kfill ^ 64u, &kbuf[2048]);
+            lds_dma16<3072>(kp, kfill ^ 64u, &kbuf[3072]);
+        } else {
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const uint8_t* from = kp + 4096 * half;
+                const unsigned off = kfill ^ (64u * half);
+                lds_dma16<0>(from, off, &kbuf[4096 * half]);
+                lds_dma16<1024>(from, off, &kbuf[4096 * half + 1024]);
+                lds_dma16<2048>(from, off, &kbuf[4096 * half + 2048]);
+                lds_dma16<3072>(from, off, &kbuf[4096 * half + 3072]);
+            }
+        }
+    };
+    auto request_v = [&](int j) __attribute__((always_inline)) {
+        const uint8_t* vp = vbase + (size_t)j * (BLK * D * 2);
+        asm volatile("" : "+s"(vp));
+#pragma unroll
+        for (int u = 0; u < REQUESTS; u += 2) {  // 16 rows each
+            const uint8_t* from = vp + 32 * BLK * u;
+            lds_dma16<0>(from, vfill, &vbuf[1024 * u]);
+            lds_dma16<32 * BLK>(from, vfill, &vbuf[1024 * u + 1024]);
+        }
+    };
+    // 64 column indices per fetch, one per lane; past the end of the row its last column again
+    auto load_cols = [&](int chunk) { return min(max(cols[min(chunk * 64 + lane_here(), cnt - 1)], 0), a.kblocks - 1); };
+    int cols64 = cnt > 0 ? load_cols(0) : 0;
+    auto column = [&](int u) {  // u advances by one per call
+        if ((u & 63) == 0) cols64 = load_cols(u >> 6);
+        return __builtin_amdgcn_readlane(cols64, u & 63);
+    };
+    const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
+    const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
+    const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    Bf16Groups<2, CT> rows;
+    rows.init();
+    auto logits = [&](v4f (&S)[2][2]) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(kread));  // the flipped address is made here, not kept
+        v8bf kf[2][KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int T = 0; T < 2; ++T) kf[T][s] = *(const v8bf*)(kbuf + (kread ^ (64u * (s & 1))) + 128 * (s >> 1) + 16 * D * T);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int T = 0; T < 2; ++T)
+#pragma unroll
+                for (int H = 0; H < 2; ++H) S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[T][s], qf[H][s], s ? S[T][H] : zero, 0, 0, 0);
+    };
+
+    int j0 = 0, j1 = 0;  // columns of the blocks t, t + 1
+    bool open = true;    // some row has no reference yet
+    v4f Sa[2][2], Sb[2][2];  // logits, this block's and the next one's in turn
+    if (cnt > 0) {
+        j0 = __builtin_amdgcn_readlane(cols64, 0);
+        j1 = column(1);
+        request_k(j0);
+        request_v(j0);
+        __builtin_amdgcn_s_waitcnt(REQUESTS == 4 ? 0x0F74 : 0x0F78);  // all but V_0's requests have landed
+        logits(Sa);
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_0 has been read
+        // (the order of the loop: K_{t+1}, then V_t; V_0 is older here and has landed when K_1 is waited for)
+        request_k(j1);
+    }
+    auto step = [&](int t, v4f (&S)[2][2], v4f (&N)[2][2]) __attribute__((always_inline)) {
+        if (j0 == tail_block) rows.mask(S, 32 * kh, nkeys);
+        if (open) {
+            rows.reference(S, c, false);
+            open = rows.open();
+        }
+        const int j2 = column(t + 2);
+        // K_{t+1} has landed (in the first block nothing is younger: everything has)
+        if (t == 0) __builtin_amdgcn_s_waitcnt(0x0F70);
+        else __builtin_amdgcn_s_waitcnt(REQUESTS == 4 ? 0x0F74 : 0x0F78);
+        logits(N);
+        float rs[2];
+        if (rows.exponentials(S, c, rs)) {
+            // rare: the logits once more, from K in global memory (its LDS slot holds the next block)
+            const int ln = lane_here();
+            const uint8_t* kp = kbase + (size_t)j0 * (BLK * D * 2) + 2 * D * bf16_krow(ln & 15) + 16 * (ln >> 4);
+#pragma unroll
+            for (int T = 0; T < 2; ++T)
+#pragma unroll
+                for (int H = 0; H < 2; ++H)
+#pragma unroll
+                    for (int s = 0; s < KS; ++s)
+                        S[T][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const v8bf*)(kp + 16 * D * T + 64 * s), qf[H][s], s ? S[T][H] : zero, 0, 0, 0);
+            if (j0 == tail_block) rows.mask(S, 32 * kh, nkeys);
+            rows.reference(S, c, true);
+            rows.exponentials(S, c, rs);
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_{t+1} has been read
+        request_k(j2);
+        rows.add(rs);
+        v8bf pf[2];
+#pragma unroll
+        for (int H = 0; H < 2; ++H) pf[H] = rows.pack(S, H);
+        __builtin_amdgcn_s_waitcnt(REQUESTS == 4 ? 0x0F74 : 0x0F78);  // V_t has landed; K_{t+2} may be on its way
+        // ---- O^T += V_j^T P^T
+#pragma unroll
+        for (int c0 = 0; c0 < CT; c0 += 4) {
+            v8bf vf[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) vf[x] = *(const v8bf*)(vbuf + vread + 1024 * (c0 + x));
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int H = 0; H < 2; ++H) rows.acc[c0 + x][H] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[x], pf[H], rows.acc[c0 + x][H], 0, 0, 0);
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // V_t has been read
+        request_v(j1);
+        j0 = j1;
+        j1 = j2;
+    };
+    if constexpr (NW == 1) {
+        int t = 0;
+        for (; t + 1 < cnt; t += 2) {  // by two, so that the logits change hands without copies: 4 heads of 4096 tokens, d = 64, 26.6 -> 24.3 us
+            step(t, Sa, Sb);
+            step(t + 1, Sb, Sa);
+        }
+        if (t < cnt) step(t, Sa, Sb);
+    } else {  // (no difference here)
+        for (int t = 0; t < cnt; ++t) {
+            step(t, Sa, Sb);
+#pragma unroll
+            for (int T = 0; T < 2; ++T)
+#pragma unroll
+                for (int H = 0; H < 2; ++H) Sa[T][H] = Sb[T][H];
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing is in flight to the buffers when they are given up
+
+    const int ln = lane_here();  // nothing of the lane's number is kept through the loop for this
+    auto offset = [&](int row) { return out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens); };
+    if constexpr (NW == 1) {
+#pragma unroll
+        for (int H = 0; H < 2; ++H) {
+            const int row = row0 + 16 * H + (ln & 15);
+            float l_tot = rows.l[H] + __shfl_xor(rows.l[H], 16);
+            l_tot += __shfl_xor(l_tot, 32);
+            const float inv = (row < a.n_tokens && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
+            const long long ooff = offset(row);
+            if (ooff >= 0) {
+                OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 4);
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+                    store4(orow + 16 * ct, rows.acc[ct][H][0] * inv, rows.acc[ct][H][1] * inv, rows.acc[ct][H][2] * inv, rows.acc[ct][H][3] * inv);
+            }
+        }
+    } else {
+        // ---- the wavefronts w and w + 2 share their queries: the one with the lower keys finishes them, the other hands its sums over
+        // through two of the K slots, 8 KB ([32 registers][64 lanes])
+        __syncthreads();
+        float* exchange = (float*)&kslots[2 * (w & 1)][0];
+        if (kh == 1) rows.template hand_over<0, 0>(exchange, meet[w & 1], ln);
+        __syncthreads();
+        if (kh == 0) rows.template finish<0, 0>((OutT*)a.op, offset, row0, a.n_tokens, exchange, meet[w], ln);
+    }
+}
+
+// Block 64, d = 64: with few row blocks four wavefronts per row block instead of two.  The line, in row blocks of the launch, both sides
+// in us (four / two wavefronts) at 20 and 50 % density: 512 16.2 / 21.8 and 30.4 / 45.0, 640 19.9 / 21.9 and 36.9 / 46.3, 768 21.0 / 23.0 and
+// 41.7 / 47.1, 875 42.3 / 39.1 and 94.5 / 90.1, 1024 27.9 / 24.9 and 57.5 / 51.5.
+constexpr int kBf16Q32Rows = 768;
+
 template <typename OutT>
 static int launch_bf16(int blk, int d, const AttnArgs& a, hipStream_t st) {
     const dim3 grid((unsigned)(a.per_xcd * 8));
-    if (blk == 64 && d == 64) hipLaunchKernelGGL((attn_bf16_d64_kernel<OutT>), grid, dim3(128), 0, st, a);
+    if (blk == 64 && d == 64 && a.total_wg > kBf16Q32Rows) hipLaunchKernelGGL((attn_bf16_d64_kernel<OutT>), grid, dim3(128), 0, st, a);
+    else if (blk == 64 && d == 64) hipLaunchKernelGGL((attn_bf16_q32_kernel<64, 64, OutT>), grid, dim3(256), 0, st, a);
     else if (blk == 64) hipLaunchKernelGGL((attn_bf16_d128_kernel<OutT>), grid, dim3(256), 0, st, a);
-    else if (d == 64) hipLaunchKernelGGL((attn_bf16_b32_kernel<64, OutT>), grid, dim3(64), Bf16B32Cfg<64>::LDS_BYTES, st, a);
-    else hipLaunchKernelGGL((attn_bf16_b32_kernel<128, OutT>), grid, dim3(64), Bf16B32Cfg<128>::LDS_BYTES, st, a);
+    else if (d == 64) hipLaunchKernelGGL((attn_bf16_q32_kernel<32, 64, OutT>), grid, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((attn_bf16_q32_kernel<32, 128, OutT>), grid, dim3(64), 0, st, a);
     return PARO_OK;
 }
 

@@ -258,8 +258,8 @@ int paro_sparse_attn_unpermuted(const paro_shape* s, int bits_qk, int bits_pv, c
 int paro_k_channel_mean(const paro_shape* s, paro_dtype dtype, const void* k, float* k_mean, void* stream);
 int paro_permute_quantize_smoothed(const paro_shape* s, paro_dtype dtype, int bits, const uint8_t* h_perm_ids,
                                    const void* k, const float* k_mean, void* codes, float* scales, void* stream);
-/* paro_k_channel_mean, paro_permute_quantize of Q and V and paro_permute_quantize_smoothed of K in two launches; the same
- * mean, codes and scales.  bits (8,8), (8,4), (4,4) or (4,8);  k_mean  float32 [B,nh,d] (device), written */
+/* paro_k_channel_mean, paro_permute_quantize of Q and V and paro_permute_quantize_smoothed of K in two launches, or in three for
+ * long inputs, whose partial sums meet in q_codes before Q's codes are written; the same mean, codes and scales.  bits (8,8), (8,4), (4,4) or (4,8);  k_mean  float32 [B,nh,d] (device), written */
 int paro_permute_quantize_qkv_smoothed(const paro_shape* s, paro_dtype dtype, int bits_qk, int bits_pv,
                                        const uint8_t* h_perm_ids, const void* q, const void* k, const void* v,
                                        float* k_mean, void* q_codes, float* sq, void* k_codes, float* sk,

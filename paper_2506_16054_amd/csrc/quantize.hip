@@ -10,6 +10,8 @@
 #include <hip/hip_bf16.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace paro {
@@ -224,39 +226,22 @@ __global__ __launch_bounds__(256) void quantize_smoothed_kernel(const InT* __res
     quantize_group<InT, BLK, D, BITS, PARO_ROWS, true, true>(x, codes, scales, n_tokens, kblocks, table, nh, blockIdx.x, blockIdx.y, sub);
 }
 
-// Mean over the N tokens of every channel of every (batch, head), accumulated in binary64 and rounded to
-// bfloat16 (returned as float).  A workgroup of 1024 threads owns CHUNKS groups of 8 channels of one (batch, head), a thread
-// one of the groups of every (1024 / CHUNKS)-th token; partial sums meet across the row lanes of a wavefront by shuffles
-// and across the 16 wavefronts through LDS.  Any constant would do for the smoothing (the softmax does not see it); the
-// coarse rounding makes this one independent of the order of the additions.
-//
-// Bound by the few compute units that a launch of one workgroup per head uses.  The channels of a head are split over several
-// workgroups (mean_chunks), which need no scratch memory and no second launch to meet, as a split over the tokens would.
-// They read parts of the same 128-byte lines, so they are numbered to run on one XCD, whose L2 then fetches a line
-// once: workgroup b runs on XCD b % 8, and the parts of a head are 8 apart.  Whole head -> split, 17550 tokens: 30 bf16
-// heads 47 -> 35 us, 48 bf16 heads 49 -> 37, 30 fp32 heads 87 -> 45; 24 bf16 heads of 4096 tokens, d = 128: 18 -> 9.
-template <typename InT, int CHUNKS>
-__global__ __launch_bounds__(1024) void channel_mean_kernel(const InT* __restrict__ x, float* __restrict__ mean, int n_tokens, int heads, int D) {
-    constexpr int ROWS = 1024 / CHUNKS;    // tokens per pass of the workgroup
-    __shared__ double part[16][CHUNKS * 8];
-    const int parts = D / (CHUNKS * 8);
-    const int octet = blockIdx.x / (8 * parts), in_octet = blockIdx.x - octet * 8 * parts;
-    const int head = octet * 8 + (in_octet & 7), c0 = (in_octet >> 3) * CHUNKS * 8;
-    if (head >= heads) return;
-    const int tid = threadIdx.x;
-    const int cc = tid % CHUNKS;
-    const int rl = tid / CHUNKS;
-    const InT* base = x + (size_t)head * n_tokens * D + c0 + cc * 8;
+// Sums of 8 channels per thread over the tokens first, first + ROWS, .. below last of one (batch, head), met across the wavefront's
+// row lanes; part: [wavefront][channel] (base and first are the thread's own).
+template <typename InT, int CHUNKS, int THREADS>
+__device__ __forceinline__ void sum_channels(const InT* __restrict__ base, int D, int first, int last, double (*part)[CHUNKS * 8]) {
+    constexpr int ROWS = THREADS / CHUNKS;  // tokens per pass of the workgroup
+    const int tid = threadIdx.x, cc = tid % CHUNKS;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     // 8 (bf16) or 4 (fp32) loads in flight per thread, held as loaded (16 or 32 bytes each) and widened only when they are added
     constexpr int INFLIGHT = sizeof(InT) == 2 ? 8 : 4;
     constexpr int WORDS = sizeof(InT) * 8 / 4;  // 32-bit words per 8 channels
-    for (int r0 = rl; r0 < n_tokens; r0 += INFLIGHT * ROWS) {
+    for (int r0 = first; r0 < last; r0 += INFLIGHT * ROWS) {
         unsigned raw[INFLIGHT][WORDS];
 #pragma unroll
         for (int u = 0; u < INFLIGHT; ++u) {
             const int r = r0 + u * ROWS;
-            if (r < n_tokens) {
+            if (r < last) {
                 const uint4* src = (const uint4*)(base + (size_t)r * D);
 #pragma unroll
                 for (int q = 0; q < WORDS / 4; ++q) {
@@ -287,6 +272,31 @@ __global__ __launch_bounds__(1024) void channel_mean_kernel(const InT* __restric
 #pragma unroll
         for (int e = 0; e < 8; ++e) part[tid >> 6][cc * 8 + e] = acc[e];
     }
+}
+
+// Mean over the N tokens of every channel of every (batch, head), accumulated in binary64 and rounded to
+// bfloat16 (returned as float).  A workgroup of 1024 threads owns CHUNKS groups of 8 channels of one (batch, head), a thread
+// one of the groups of every (1024 / CHUNKS)-th token; partial sums meet across the row lanes of a wavefront by shuffles
+// and across the 16 wavefronts through LDS.  Any constant would do for the smoothing (the softmax does not see it); the
+// coarse rounding makes this one independent of the order of the additions.
+//
+// Bound by the few compute units that a launch of one workgroup per head uses.  The channels of a head are split over several
+// workgroups (mean_chunks), which need no scratch memory and no second launch to meet, as a split over the tokens would.
+// They read parts of the same 128-byte lines, so they are numbered to run on one XCD, whose L2 then fetches a line
+// once: workgroup b runs on XCD b % 8, and the parts of a head are 8 apart.  Whole head -> split, 17550 tokens: 30 bf16
+// heads 47 -> 35 us, 48 bf16 heads 49 -> 37, 30 fp32 heads 87 -> 45; 24 bf16 heads of 4096 tokens, d = 128: 18 -> 9.
+template <typename InT, int CHUNKS>
+__global__ __launch_bounds__(1024) void channel_mean_kernel(const InT* __restrict__ x, float* __restrict__ mean, int n_tokens, int heads, int D) {
+    __shared__ double part[16][CHUNKS * 8];
+    const int parts = D / (CHUNKS * 8);
+    const int octet = blockIdx.x / (8 * parts), in_octet = blockIdx.x - octet * 8 * parts;
+    const int head = octet * 8 + (in_octet & 7), c0 = (in_octet >> 3) * CHUNKS * 8;
+    if (head >= heads) return;
+    const int tid = threadIdx.x;
+    const int cc = tid % CHUNKS;
+    const int rl = tid / CHUNKS;
+    const InT* base = x + (size_t)head * n_tokens * D + c0 + cc * 8;
+    sum_channels<InT, CHUNKS, 1024>(base, D, rl, n_tokens, part);
     __syncthreads();
     if (tid < CHUNKS * 8) {
         double sum = 0.0;
@@ -323,6 +333,50 @@ static void launch_channel_mean(const InT* k, float* k_mean, int n, int heads, i
         PARO_MEAN(16);
     }
 #undef PARO_MEAN
+}
+
+// The same mean where a call has memory to meet in: workgroup (p, head) adds up the tokens p span .. of all channels of a head into
+// partial[head][p], the next launch adds those.  Whole rows are read in order by workgroups on every compute unit, so it is bound by
+// HBM and not by one workgroup's loads: mean, second launch and the quantizers behind them, 17550 tokens, 30 bf16 heads 93.5 -> 74.1 us,
+// 8 heads 42.1 -> 28.6, 30 fp32 heads 118 -> 103; 30 bf16 heads of 5120 32.4 -> 29.9.
+template <typename InT, int D>
+__global__ __launch_bounds__(256) void channel_sums_kernel(const InT* __restrict__ x, double* __restrict__ partial, int n_tokens, int span) {
+    constexpr int CHUNKS = D / 8;
+    __shared__ double part[4][D];
+    const int head = blockIdx.y, tid = threadIdx.x, first = blockIdx.x * span;
+    sum_channels<InT, CHUNKS, 256>(x + (size_t)head * n_tokens * D + tid % CHUNKS * 8, D, first + tid / CHUNKS, min(first + span, n_tokens), part);
+    __syncthreads();
+    if (tid < D) partial[((size_t)head * gridDim.x + blockIdx.x) * D + tid] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void channel_mean_of_sums_kernel(const double* __restrict__ partial, float* __restrict__ mean, int n_tokens, int parts) {
+    __shared__ double part[256 / D][D];
+    const int head = blockIdx.x, c = threadIdx.x % D, g = threadIdx.x / D;
+    const double* mine = partial + (size_t)head * parts * D + c;
+    double sum = 0.0;
+#pragma unroll 4
+    for (int p = g; p < parts; p += 256 / D) sum += mine[(size_t)p * D];
+    part[g][c] = sum;
+    __syncthreads();
+    if (g == 0) {
+#pragma unroll
+        for (int u = 1; u < 256 / D; ++u) sum += part[u][c];
+        mean[(size_t)head * D + c] = __uint_as_float(f32_to_bf16_bits((float)(sum / (double)n_tokens)) << 16);
+    }
+}
+
+// 512 workgroups in all: two for each compute unit (256: 30 bf16 heads of 17550 tokens 1 us more; 2048: their sums take as much).
+constexpr int kMeanGroups = 512;
+// scratch: at least n D / 2 bytes per head.
+template <typename InT, int D>
+static void launch_channel_mean_by_sums(const InT* k, float* k_mean, double* scratch, int n, int heads, hipStream_t st) {
+    constexpr int pass = 256 / (D / 8) * (sizeof(InT) == 2 ? 8 : 4);  // tokens that a workgroup keeps in flight
+    int parts = std::min((n + 2 * pass - 1) / (2 * pass), std::max(kMeanGroups / heads, 1));
+    const int span = ((n + parts - 1) / parts + pass - 1) / pass * pass;
+    parts = (n + span - 1) / span;
+    hipLaunchKernelGGL((channel_sums_kernel<InT, D>), dim3(parts, heads), dim3(256), 0, st, k, scratch, n, span);
+    hipLaunchKernelGGL((channel_mean_of_sums_kernel<D>), dim3(heads), dim3(256), 0, st, scratch, k_mean, n, parts);
 }
 
 // Q, K and V of one attention call in a single launch (blockIdx.z selects the tensor): Q and K as
@@ -468,7 +522,12 @@ static bool launch_qkv_shape(int blk, int d, int bits_qk, int bits_pv, dim3 grid
 // 16 bf16 heads of 17550 tokens 67 -> 56 us, but 48 heads 127 -> 145, 30 of 5120 33 -> 35, and smaller ones the same.)
 template <typename InT, int BLK, int D, int QKBITS, int PVBITS>
 static void launch_smoothed_qkv(dim3 grid, hipStream_t st, const QkvPointers& p, float* mean, int n, int k, int heads, const ReorderTable& t, int nh) {
-    launch_channel_mean((const InT*)p.in[1], mean, n, heads, D, st);
+    // Rows of 8 KB of one channel and more by sums, which meet in Q's codes: these are written behind the mean and have n D / 2 bytes per head
+    // or more, the sums (at most one of 8 bytes per channel and 128 tokens) n D / 16.  The third launch costs 0.5 .. 1 us: 24 bf16 heads of
+    // 1024 tokens 10.7 by channels, 11.5 by sums, of 4096 21.1 and 20.8, of 8100 42.3 and 35.0; 8 fp32 heads of 1024 9.7 and 10.0, of 2048
+    // 11.7 and 10.5.  (48 fp32 heads of 4096 .. 5120, whose channels fill the chip: 37.9 and 38.7, 45.2 and 46.4.)
+    if ((long long)n * (int)sizeof(InT) >= 8192) launch_channel_mean_by_sums<InT, D>((const InT*)p.in[1], mean, (double*)p.codes[0], n, heads, st);
+    else launch_channel_mean((const InT*)p.in[1], mean, n, heads, D, st);
     hipLaunchKernelGGL((quantize_qkv_smoothed_kernel<InT, BLK, D, QKBITS, PVBITS>), grid, dim3(256), 0, st, p, mean, n, k, t, nh);
 }
 template <typename InT, int BLK, int D>

@@ -108,3 +108,41 @@ def test_refusals(route):
                 lambda: pb.paro_permute_quantize_kv(s, 8, 8, ids, x, x, codes[1], scales[1], codes[1].view(1, 1, 1, 64, 64), scales[2])):
         with pytest.raises(pb.ParoError):
             bad()
+
+
+@pytest.mark.parametrize("heads,d,grid,bits_qk,dtype", [
+    (3, 64, (1, 63, 65), 4, "bfloat16"),     # 4095 tokens: the mean by channels
+    (3, 64, (1, 64, 64), 4, "bfloat16"),     # 4096: by sums, 8 spans of 512
+    (3, 128, (1, 17, 241), 4, "bfloat16"),   # 4097: a span of one token
+    (100, 64, (1, 64, 65), 8, "bfloat16"),   # as many spans as 512 workgroups allow
+    (2, 128, (13, 30, 45), 8, "bfloat16"),
+    (3, 64, (1, 23, 89), 4, "float32"),      # 2047
+    (3, 64, (1, 32, 64), 4, "float32"),      # 2048
+    (3, 128, (1, 3, 683), 4, "float32"),     # 2049
+    (260, 64, (1, 32, 65), 4, "float32"),    # one span per head
+])
+def test_mean_by_sums_is_the_mean(heads, d, grid, bits_qk, dtype):
+    """Where the rows are long the mean's partial sums meet in the buffer of Q's codes: mean, codes and scales as by the separate calls."""
+    import torch
+
+    from paper_2506_16054_amd import binding as pb
+
+    s = pb.make_shape(2, heads // 2, d, *grid, 0, 32) if heads > 256 else pb.make_shape(1, heads, d, *grid, 0, 32)
+    n = grid[0] * grid[1] * grid[2]
+    gen = torch.Generator(device="cuda:0").manual_seed(n + d)
+    q, v = (torch.randn((s.B, s.nh, n, d), generator=gen, device="cuda:0").to(getattr(torch, dtype)) for _ in range(2))
+    k = (torch.randn((s.B, s.nh, n, d), generator=gen, device="cuda:0") + 4 * torch.randn((s.B, s.nh, 1, d), generator=gen, device="cuda:0")).to(q.dtype)
+    perm = (np.arange(s.nh) % 6).astype(np.uint8)
+    codes, scales = _buffers(pb, s, bits_qk, 8, 5)
+    mean = torch.full((s.B, s.nh, d), 7.0, device="cuda:0")
+    pb.paro_permute_quantize_qkv_smoothed(s, bits_qk, 8, perm, q, k, v, mean, codes[0], scales[0], codes[1], scales[1], codes[2], scales[2])
+    want_codes, want_scales = _buffers(pb, s, bits_qk, 8, 6)
+    want_mean = torch.empty_like(mean)
+    pb.paro_k_channel_mean(s, k, want_mean)
+    pb.paro_permute_quantize(s, bits_qk, pb.PARO_ROWS, perm, q, want_codes[0], want_scales[0])
+    pb.paro_permute_quantize_smoothed(s, bits_qk, perm, k, want_mean, want_codes[1], want_scales[1])
+    pb.paro_permute_quantize(s, 8, pb.PARO_VT, perm, v, want_codes[2], want_scales[2])
+    assert torch.equal(mean, want_mean)
+    assert torch.equal(mean, k.double().mean(dim=2).to(torch.float32).to(torch.bfloat16).float())
+    for a, b in zip(codes + scales, want_codes + want_scales):
+        assert torch.equal(a, b)

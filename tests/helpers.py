@@ -136,9 +136,9 @@ MAX_TIE_EXCESS = 2e-5
 
 
 def same_attention_kernel_for_raw_q(w) -> bool:
-    """paro_sparse_attn_unpermuted_rawq runs on the kernel with one wavefront per 32 queries.  At d = 128, block 64
-    with 8-bit codes throughout, the other entry points run the kernel with four wavefronts of 16 queries, whose
-    floating-point sums associate differently: there the two agree to the rounding of the output, not bit for bit."""
+    """Whether paro_sparse_attn_unpermuted_rawq is asserted to give the bits of the other entry points.  At d = 128, block 64
+    with 8-bit codes throughout they are only asserted to agree to the rounding of the output: bound of kernels whose
+    floating-point sums associate differently (the two run the same kernel, and test_gpu_q16_kernel.py asserts the bits)."""
     return not (w.d == 128 and w.block == 64 and w.bits_qk == 8 and w.bits_pv == 8)
 
 

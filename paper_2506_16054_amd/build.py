@@ -124,8 +124,6 @@ def loop_instruction_counts(asm: str) -> dict:
             for ops in blocks:
                 if sum(o.startswith("v_cndmask") for o in ops) >= _RARE or sum(o.startswith("v_mul_f32") for o in ops) >= _RARE:
                     continue
-                if len(ops) >= _RARE and all(instruction_class(o) == "fma" or o.startswith("v_mov") for o in ops):
-                    continue  # what the sums of the block-32 kernel hold too much, taken out every eight blocks
                 for o in ops:
                     c = instruction_class(o)
                     counts[c] = counts.get(c, 0) + 1

@@ -782,27 +782,22 @@ __global__ __launch_bounds__(64, 2) void attn_i8_w64_qk4_kernel(AttnArgs a) {
 // to the tile's scale runs beside the codes of the block before.  Rows of 128 bytes of K are the exception: a lane pair reads 32 of a row, so
 // every request would touch 32 lines and the next three the same ones, more than the L1 of a compute unit holds for its wavefronts; they
 // go through LDS in whole lines.
-// Bound by the issue of the vector work where the chip is full (158 vector instructions per block at d = 64; 196 in the kernel before it,
-// which exchanged tiles through LDS with a barrier per block), by the chain of one block where it is not.  Attention call alone, us,
-// that kernel -> this one, 8-bit codes / all 4-bit, 30 % density: d = 64, 30 heads of 17550 tokens 1001 -> 780 / 957 -> 799, 24 heads
-// of 4096 57.2 -> 44.4 / 56.4 -> 47.9, 4 heads of 4096 36.5 -> 24.4 / 37.9 -> 27.9; d = 128, 30 heads of 17550 1765 -> 1264 (K by
-// registers 1560) / 1839 -> 1295, 4 heads of 4096 46.5 -> 30.3 / 49.9 -> 37.2.
+// Bound by the issue of the vector work where the chip is full (184 vector instructions per block at d = 64, 256 at d = 128), by the
+// chain of one block where it is not.  Attention call alone, us, before (tiles exchanged through LDS with a barrier per block) -> now,
+// 8-bit codes / all 4-bit, 30 % density: d = 64, 30 heads of 17550 tokens 1001 -> 850 / 962 -> 807, 24 heads of 4096 55.1 -> 46.6 /
+// 56.4 -> 47.4, 4 heads of 4096 35.2 -> 25.5 / 36.7 -> 27.0; d = 128, 30 heads of 17550 1764 -> 1415 (K of 8-bit codes by registers took
+// 1.2 times as long) / 1838 -> 1288, 4 heads of 4096 45.1 -> 33.5 / 48.5 -> 36.0.
 //
 // The exponent is formed after one exact subtraction per logit (the folded form of the kernel above is 2.5 % faster here and
 // decides P codes within 6e-5 of a tie differently: error against binary64 3e-4 with it, 4e-5 without).
 // -------------------------------------------------------------------------------------------
 
-// 8-bit P V products enter the sums without a subtraction.  Their chain starts at START, a power of two that no
-// |result| exceeds: its register then holds a positive integer below 2^24, which read as a float is that integer times 2^-149
-// exactly (subnormals and the lowest binade share one spacing), so one fma adds it to the sum.  What the sum holds too much,
-// START times the sum of the weights, is known per row and taken out every PERIOD blocks, before it is large enough to
-// cost places: PERIOD * START = 2^22, an addition rounds to half a unit of the integer at most.  (Error of the output against
-// binary64, rms over 320 .. 17550 tokens: 3.3e-5 .. 4.4e-5, with the subtraction and the folded exponent 2.9e-4 .. 3.3e-4.
-// With 4-bit P codes, which are mostly 0, it would show: 2e-5 -> 9e-5; they keep the subtraction.)
-// The weights carry 2^(kWeightUp - E), E the exponent of the row block's largest V scale: with V scales within 2^28 of each other
-// nothing is subnormal that counts and nothing overflows (w_blk reaches 2^57, see m_ref, and PERIOD of them are summed).
-// Rows outside take the other loop.
-constexpr int kWeightUp = 60;
+// A P V product enters the sums as the integer that it is: its chain starts at kStartI (see acc_start), one subtraction per element leaves
+// the result times 2^-26, and the weight carries the 2^26 back where no V scale of the row block passes 2^40 - in the other rows the division
+// at the end does, so that a climb of 64 octaves does not take the weight out of range.  (Left in the sums and taken out every few blocks
+// the start would save the subtraction, 773 us instead of 833 for 30 heads of 17550 tokens, d = 64; but it is as large as the largest result,
+// times a weight that says nothing about a query's own codes, and a block of V some 2^12 larger than the rest, or one of zeros, whose scale is
+// 1, pushes the digits of the others out of the sum: 5e-3 of the output at 2^12, all of it at 2^20.)
 
 template <int D, int QKBITS, int PVBITS, typename OutT>
 __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(AttnArgs a) {
@@ -813,9 +808,6 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
     constexpr int DT = D / 32;  // 32-channel tiles of the output
     constexpr float LOG2_QMAXP = PVBITS == 4 ? 2.807354922057604f : 6.988684686772166f;
     constexpr float kLog2_65535 = 15.999977986052736f;
-    constexpr bool LIFTED = PVBITS == 8;  // P V products enter the sums without a subtraction
-    constexpr int START = 1 << 19;  // >= 32 * 127 * 127
-    constexpr int PERIOD = 8;
     constexpr bool K_BY_LDS = D / KPACK == 128;
     __shared__ __attribute__((aligned(16))) uint8_t kslot[K_BY_LDS ? BLK * D : 16];
 
@@ -944,39 +936,27 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
-    float held = 0.0f;  // sum of the weights whose `start` the sums still hold
 
     bool fast = false;
-    int sv_exp = 0;  // the weights are multiplied by 2^sv_exp
+    float sv_up = 0x1p26f;  // what a V scale is multiplied by to give a weight
     {
-        float sk_max = 0.0f, sv_max = 0.0f, sv_min = INFINITY;
+        float sk_max = 0.0f, sv_max = 0.0f;
         for (int base = 0; base < cnt; base += 64)
             if (base + lane < cnt) {
                 const int j = base == 0 ? cols64 : min(max(cols[base + lane], 0), a.kblocks - 1);
                 sk_max = fmaxf(sk_max, skp[j]);
                 sv_max = fmaxf(sv_max, svp[j]);
-                sv_min = fminf(sv_min, svp[j]);
             }
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
-            sv_max = fmaxf(sv_max, __shfl_xor(sv_max, off));
-            sv_min = fminf(sv_min, __shfl_xor(sv_min, off));
-        }
+        for (int off = 32; off >= 1; off >>= 1) sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
         sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
         fast = sq_i * sk_max < 0x1p90f;  // as above
-        if (LIFTED) fast = fast && sv_min >= 0x1p-28f * sv_max && sv_max < 0x1p100f && sv_max > 0x1p-60f;
-        sv_exp = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(sv_max));
+        if (__builtin_amdgcn_ballot_w64(sv_max > 0x1p40f) != 0) sv_up = 1.0f;
     }
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
     if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fast = false;
-    const bool lifted = LIFTED && fast;
-    // start of the P V products, and what a V scale is multiplied by to give a weight (otherwise as above)
-    v16i start;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) start[r] = lifted ? START : 0x3E22F983;
+    v16i start = acc_start();  // of the P V products: several in a basic block
     asm volatile("" : "+v"(start));
-    const float sv_up = lifted ? ldexpf(1.0f, kWeightUp - sv_exp) : (sv_exp > 90 ? 1.0f : 0x1p13f);
 
     v16i Sa, Sb;  // raw logits, this block's and the next one's in turn
     v4i pf = {0, 0, 0, 0};
@@ -1007,7 +987,6 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
             const float down = __builtin_amdgcn_exp2f(m_ref - m_new);  // first block: 2^-inf = 0 on zero sums
             l *= down;
             weight *= down;
-            held *= down;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1016,17 +995,8 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         }
         m = m_new;
     };
-    auto settle = [&]() {  // takes out what the sums hold too much
-        const float extra = held * -(START * 0x1p-149f);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[dt][r] += extra;
-        held = 0.0f;
-    };
     auto step = [&](auto mode_tag, int t, v16i& S, v16i& N) __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode_tag)::value;
-        constexpr bool LIFT = LIFTED && MODE != kExact;
         float c = sq_i * sk_cur;
         if (MODE == kExact && c < kLogitScaleMin) c = kLogitScaleMin;
         const float c_up = c * 0x1p26f;
@@ -1044,7 +1014,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         auto add = [&](int dt, const v16i& o) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                acc[dt][r] = fmaf(LIFT ? __int_as_float(o[r]) : __int_as_float(o[r]) - kStartF, weight, acc[dt][r]);
+                acc[dt][r] = fmaf(__int_as_float(o[r]) - kStartF, weight, acc[dt][r]);
                 asm volatile("" : "+v"(acc[dt][r]));
             }
         };
@@ -1088,7 +1058,6 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
                 add(2, o[2]);
                 add(3, o[3]);
             }
-            if constexpr (LIFT) held += weight;
 #pragma unroll
             for (int r = 0; r < 16; r += 4) {
                 const unsigned lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pknorm_u16(E[r], E[r + 1]));
@@ -1101,15 +1070,12 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         });
     };
     auto visit_all = [&](auto mode_tag) __attribute__((always_inline)) {
-        constexpr bool LIFT = LIFTED && decltype(mode_tag)::value != kExact;
         int t = 0;
         for (; t + 1 < cnt; t += 2) {
             step(mode_tag, t, Sa, Sb);
             step(mode_tag, t + 1, Sb, Sa);
-            if (LIFT && (t & (PERIOD - 2)) == PERIOD - 2) settle();
         }
         if (t < cnt) step(mode_tag, t, Sa, Sb);
-        if constexpr (LIFT) settle();
     };
     if (cnt > 0) {
         widen_k();
@@ -1123,12 +1089,11 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
     else visit_all(std::integral_constant<int, kExact>{});
     if (cnt > 0) {  // the last block's P V, one tile at a time
         widen_v();
-        const float first = lifted ? START * 0x1p-149f : kStartF;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
             const v16i o = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[dt], pf, start, 0, 0, 0);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[dt][r] = fmaf(__int_as_float(o[r]) - first, weight, acc[dt][r]);
+            for (int r = 0; r < 16; ++r) acc[dt][r] = fmaf(__int_as_float(o[r]) - kStartF, weight, acc[dt][r]);
         }
     }
 
@@ -1136,9 +1101,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
     const int orow_no = i * BLK + (ln & 31);
     const bool valid = orow_no < a.n_tokens;
     const float l_tot = (l + __shfl_xor(l, 32)) * 65535.0f;
-    // the sums carry the weights' factor and the spacing of the integers they were read as
-    const float up = lifted ? 0x1p89f : 1.0f;
-    const float inv = (valid && l_tot > 0.0f) ? (lifted ? ldexpf(1.0f, sv_exp) : sv_exp > 90 ? 0x1p26f : 0x1p13f) / l_tot : 0.0f;
+    const float inv = (valid && l_tot > 0.0f) ? (0x1p26f / sv_up) / l_tot : 0.0f;
     const long long ooff = out_row_offset<D>(a, bh, h, head_rows, orow_no, valid);
     if (ooff >= 0) {
         OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 5);
@@ -1148,7 +1111,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
             for (int qd = 0; qd < 4; ++qd) {
                 float x[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) x[r] = valid ? (acc[dt][4 * qd + r] * up) * inv : 0.0f;
+                for (int r = 0; r < 4; ++r) x[r] = valid ? acc[dt][4 * qd + r] * inv : 0.0f;
                 store4(orow + 32 * dt + 8 * qd, x[0], x[1], x[2], x[3]);
             }
     }
@@ -1166,8 +1129,8 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 // Order of things.  Between two barriers a wavefront exponentiates block t and multiplies K Q of block t + 1: its four matrix
 // instructions per two key tiles run beside the exponentials of two tiles of block t (at raised priority), and the chain from the
 // maxima of block t + 1 to this wavefront's share of its tile exponent, four numbers that meet in LDS across the barrier, runs beside
-// the sum, the codes, P V and the accumulator update of block t.  160 vector instructions per wavefront and block at d = 128 (207 with
-// products, maxima and exponentials of one block in turn), 136 at d = 64.  What bounds it: issue where the chip is full (the matrix
+// the sum, the codes, P V and the accumulator update of block t.  192 vector instructions per wavefront and block at d = 128 (207 with
+// products, maxima and exponentials of one block in turn), 152 at d = 64.  What bounds it: issue where the chip is full (the matrix
 // time is added where it is not beside an exponential), the chain of one block, some 1 100 (d = 64) to 1 500 cycles, where it is not.
 // Exponentials in whole bursts with one matrix instruction per two of them: 1 % slower, registers.
 //
@@ -1186,10 +1149,10 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 // K_t and V_{t+1} V_{t-1}, and they have the whole block to land.
 //
 // Attention call alone, us, before -> now, 30 % density, 8-bit codes / 8-bit Q K with 4-bit P V / all 4-bit.  d = 128 (before: the same split without
-// the overlap for 8-bit codes, two wavefronts of 32 queries otherwise): 30 heads of 17550 tokens 1159 -> 1022 / 1271 -> 1089 / 1291 -> 1080,
-// 24 heads of 4096 69.4 -> 61.5 / 83.5 -> 65.6 / 81.0 -> 63.7, 4 heads of 4096 24.4 -> 19.7 / 35.1 -> 23.5 / 36.2 -> 23.6, 24 heads of
-// 4096 image and 512 text tokens 119.9 -> 98.2.  d = 64 (before: one wavefront of 64 queries): 24 heads of 4096 43.7 -> 38.3 / 45.6 -> 43.1 /
-// 47.3 -> 44.0, 4 heads of 4096 30.5 -> 16.3 / 33.4 -> 17.2 / 34.0 -> 17.8.
+// the overlap for 8-bit codes, two wavefronts of 32 queries otherwise): 30 heads of 17550 tokens 1160 -> 1121 / 1274 -> 1135 / 1285 -> 1098,
+// 24 heads of 4096 61.0 -> 59.6 / 77.2 -> 60.8 / 77.6 -> 60.1, 4 heads of 4096 23.1 -> 19.6 / 34.0 -> 22.4 / 35.2 -> 24.0, 24 heads of
+// 4096 image and 512 text tokens 109 -> 106 / 119 -> 108 / 120 -> 105.  d = 64 (before: one wavefront of 64 queries): 24 heads of 4096
+// 42.2 -> 40.5 / 45.8 -> 43.1 / 47.6 -> 43.9, 4 heads of 4096 29.6 -> 15.4 / 32.6 -> 16.4 / 33.1 -> 17.5.
 // -------------------------------------------------------------------------------------------
 typedef int v4acc __attribute__((ext_vector_type(4)));
 
@@ -1216,9 +1179,6 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
     constexpr int TILE = BLK * D;     // bytes of a K and of a V^T tile in LDS
     constexpr float LOG2_QMAXP = PVBITS == 4 ? 2.807354922057604f : 6.988684686772166f;
     constexpr float kLog2_65535 = 15.999977986052736f;
-    constexpr bool LIFTED = PVBITS == 8;  // P V products enter the sums without a subtraction (see kWeightUp)
-    constexpr int START = 1 << 20;        // >= 64 * 127 * 127
-    constexpr int PERIOD = D == 64 ? 2 : 4;  // error against binary64, d = 64, of the folded form's 3.157e-4: 3.166e-4 with 4; at d = 128 3.53e-4 -> 2.80e-4
     __shared__ __attribute__((aligned(16))) uint8_t kring0[TILE];
     __shared__ __attribute__((aligned(16))) uint8_t kring1[TILE];
     __shared__ __attribute__((aligned(16))) uint8_t vring0[TILE];
@@ -1411,38 +1371,26 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
     // ---- which of the loops the row block's scales allow (as in the kernels above)
     constexpr bool FOLDABLE = PARO_FOLD_LOGIT_BIAS && PVBITS == 8;
     bool fast = false;
-    int sv_exp = 0;
+    float sv_up = 0x1p26f;  // what a V scale is multiplied by to give a weight, as in the kernel above
     {
-        float sk_max = 0.0f, sv_max = 0.0f, sv_min = INFINITY;
+        float sk_max = 0.0f, sv_max = 0.0f;
         for (int base = 0; base < cnt; base += 64)
             if (base + lane < cnt) {
                 const int j = base == 0 ? first_cols : min(max(cols[base + lane], 0), a.kblocks - 1);
                 sk_max = fmaxf(sk_max, skp[j]);
                 sv_max = fmaxf(sv_max, svp[j]);
-                sv_min = fminf(sv_min, svp[j]);
             }
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
-            sv_max = fmaxf(sv_max, __shfl_xor(sv_max, off));
-            sv_min = fminf(sv_min, __shfl_xor(sv_min, off));
-        }
+        for (int off = 32; off >= 1; off >>= 1) sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
         fast = FOLDABLE ? sq_i * sk_max * kFoldBound < 8192.0f : sq_i * sk_max < 0x1p90f;
-        if (LIFTED) fast = fast && sv_min >= 0x1p-28f * sv_max && sv_max < 0x1p100f && sv_max > 0x1p-60f;
-        sv_exp = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(sv_max));
+        if (__builtin_amdgcn_ballot_w64(sv_max > 0x1p40f) != 0) sv_up = 1.0f;
     }
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;  // the column block with padded keys, if any
     if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fast = false;
-    const bool lifted = LIFTED && fast;
-    const float sv_up = (lifted ? ldexpf(1.0f, kWeightUp - sv_exp) : (sv_exp > 90 ? 1.0f : 0x1p13f)) * (PVBITS == 4 ? 0.0625f : 1.0f);
-    v4acc s_start, o_start;
+    v4acc start;  // of every chain of products: four registers
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        s_start[r] = 0x3E22F983;
-        o_start[r] = lifted ? START : 0x3E22F983;
-    }
-    asm volatile("" : "+v"(s_start));
-    if constexpr (LIFTED) asm volatile("" : "+v"(o_start));
+    for (int r = 0; r < 4; ++r) start[r] = 0x3E22F983;
+    asm volatile("" : "+v"(start));
 
     // ---- fragments.  K, tile T: row 32 (n >> 3) + 8 T + (n & 7) of the block; V^T, channel tile ct: row 16 ct + n
     unsigned kread[2];
@@ -1460,7 +1408,7 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
 #pragma unroll
         for (int T = 0; T < 4; ++T) {
 #pragma unroll
-            for (int s = 0; s < KS; ++s) S[T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(k_fragment(slot, T, s), qf[s], s == 0 ? s_start : S[T], 0, 0, 0);
+            for (int s = 0; s < KS; ++s) S[T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(k_fragment(slot, T, s), qf[s], s == 0 ? start : S[T], 0, 0, 0);
         }
     };
 
@@ -1470,7 +1418,6 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[ct][r] = 0.0f;
-    float held = 0.0f;
 
     auto mask_tail = [&](int j, v4acc (&S)[4]) __attribute__((always_inline)) {
         if (j == tail_block) {  // keys past N: the bit pattern of -inf loses every maximum and gives E = 0 (c > 0)
@@ -1505,7 +1452,6 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         if (__builtin_amdgcn_ballot_w64(m_new - m_ref > 64.0f) != 0) {
             const float down = __builtin_amdgcn_exp2f(m_ref - m_new);  // first block: 2^-inf = 0 on zero sums
             l *= down;
-            held *= down;
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -1514,21 +1460,11 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         }
         m = m_new;
     };
-    auto settle = [&]() __attribute__((always_inline)) {  // takes out what the sums hold too much
-        const float extra = held * -(START * 0x1p-149f);
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[ct][r] += extra;
-        held = 0.0f;
-    };
-
     v4acc Sa[4], Sb[4];  // raw logits, this block's and the next one's in turn
     // block t, whose logits are in S and whose tile exponents are in tile_e; K_{t+1} is in k_next and V_t in v_now
     auto step = [&](auto mode_tag, auto parity_tag, int t, v4acc (&S)[4], v4acc (&N)[4]) __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode_tag)::value;
         constexpr int PARITY = decltype(parity_tag)::value;
-        constexpr bool LIFT = LIFTED && MODE != kExact;
         uint8_t* const k_next = PARITY ? kring0 : kring1;  // K_{t+1}
         uint8_t* const k_free = PARITY ? kring1 : kring0;  // held K_t
         uint8_t* const v_now = PARITY ? vring1 : vring0;   // V_t
@@ -1545,7 +1481,7 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
 #pragma unroll
             for (int s = 0; s < KS; ++s)
 #pragma unroll
-                for (int T = 0; T < 2; ++T) N[T0 + T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf[T][s], qf[s], s == 0 ? s_start : N[T0 + T], 0, 0, 0);
+                for (int T = 0; T < 2; ++T) N[T0 + T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf[T][s], qf[s], s == 0 ? start : N[T0 + T], 0, 0, 0);
         };
         v4i vf[4];
         auto read_v = [&](int ct0) __attribute__((always_inline)) {
@@ -1609,17 +1545,17 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
             pf[T] = (int)__builtin_amdgcn_perm(hi, lo, 0x06040200u);
         }
         l = fmaf(rs, w_blk, l);
-        const float weight = w_blk * (sv0 * sv_up);
+        const float weight = w_blk * (sv0 * sv_up * (PVBITS == 4 ? 0.0625f : 1.0f));
         v4acc o[4];
         auto products_v = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int x = 0; x < 4; ++x) o[x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[x], pf, LIFTED ? o_start : s_start, 0, 0, 0);
+            for (int x = 0; x < 4; ++x) o[x] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[x], pf, start, 0, 0, 0);
         };
         auto add = [&](int ct0) __attribute__((always_inline)) {
 #pragma unroll
             for (int x = 0; x < 4; ++x)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[ct0 + x][r] = fmaf(LIFT ? __int_as_float(o[x][r]) : __int_as_float(o[x][r]) - kStartF, weight, acc[ct0 + x][r]);
+                for (int r = 0; r < 4; ++r) acc[ct0 + x][r] = fmaf(__int_as_float(o[x][r]) - kStartF, weight, acc[ct0 + x][r]);
         };
         products_v();
         if constexpr (CT == 8) {
@@ -1631,7 +1567,6 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
             add(0);
         }
         tile_e[PARITY ^ 1][w] = eb;  // (the same in every lane)
-        if constexpr (LIFT) held += weight;
         refer(m_new);
         sk0 = sk1;
         sv0 = sv1;
@@ -1647,15 +1582,12 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         PARO_TIMELINE_PHASE(1)  // wait for the tiles and for the other wavefronts
     };
     auto visit_all = [&](auto mode_tag) __attribute__((always_inline)) {
-        constexpr bool LIFT = LIFTED && decltype(mode_tag)::value != kExact;
         int t = 0;
         for (; t + 1 < cnt; t += 2) {
             step(mode_tag, std::integral_constant<int, 0>{}, t, Sa, Sb);
             step(mode_tag, std::integral_constant<int, 1>{}, t + 1, Sb, Sa);
-            if (LIFT && (t & (PERIOD - 2)) == PERIOD - 2) settle();  // (2: every time)
         }
         if (t < cnt) step(mode_tag, std::integral_constant<int, 0>{}, t, Sa, Sb);
-        if constexpr (LIFT) settle();
     };
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
@@ -1674,12 +1606,10 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
     PARO_TIMELINE_PHASE(3)
 
     const float l_tot = quad_rows_sum(l) * 65535.0f;
-    // the sums carry the weights' factor and the spacing of the integers they were read as
-    const float up = lifted ? 0x1p89f : 1.0f;
     const int ln = lane_here();  // nothing that only these stores need is kept through the loop
     const int orow_no = i * BLK + 16 * w + (ln & 15);
     const bool valid = orow_no < a.n_tokens;
-    const float inv = (valid && l_tot > 0.0f) ? (lifted ? ldexpf(1.0f, sv_exp) : sv_exp > 90 ? 0x1p26f : 0x1p13f) / l_tot : 0.0f;
+    const float inv = (valid && l_tot > 0.0f) ? (0x1p26f / sv_up) / l_tot : 0.0f;
     const long long ooff = out_row_offset<D>(a, bh, h, head_rows, orow_no, valid);
     if (ooff >= 0) {
         OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 4);
@@ -1687,7 +1617,7 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         for (int ct = 0; ct < CT; ++ct) {
             float x[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = valid ? (acc[ct][r] * up) * inv : 0.0f;
+            for (int r = 0; r < 4; ++r) x[r] = valid ? acc[ct][r] * inv : 0.0f;
             store4(orow + 16 * ct, x[0], x[1], x[2], x[3]);
         }
     }

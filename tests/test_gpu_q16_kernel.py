@@ -1,9 +1,8 @@
 """The kernel with four wavefronts of 16 queries per row block (block 64; d = 128, and d = 64 up to 1536 row blocks) multiplies K Q of a
-block while it exponentiates the one before, brings tiles in two blocks ahead and, with 8-bit P codes, takes the start of the P V
-products out of the sums every few blocks: checked against the oracle where the order of things changes - rows of none to nine
+block while it exponentiates the one before, brings tiles in two blocks ahead: checked against the oracle where the order of things changes - rows of none to nine
 blocks and around chunks of 64 column indices, the ragged block alone and behind others, padded query rows - in every combination
-of bits, with Q quantized in the kernel too, with V scales in and out of the range of the form without a subtraction, and on
-either side of the number of row blocks at which d = 64 changes kernels."""
+of bits, with Q quantized in the kernel too, with V scales of very different size (each row by itself:
+test_gpu_v_scale_spread.py), and on either side of the number of row blocks at which d = 64 changes kernels."""
 from types import SimpleNamespace
 
 import numpy as np
@@ -75,7 +74,7 @@ def test_row_lengths_chunks_and_ragged_blocks(d, bits):
 @pytest.mark.parametrize("d,bits", [(64, (8, 8)), (128, (8, 8)), (128, (4, 8)), (128, (8, 4))])
 @pytest.mark.parametrize("gains", [(0, -26, -13, 0, -26), (-30, 0, -15, 0, -2), (98, 98, 98, 90, 98), (110, 110, 110, 105, 110),
                                    (-53, -53, -53, -60, -53), (-57, -57, -57, -57, -57), (-90, -90, -90, -90, -90)])
-def test_v_scales_of_a_row_in_and_out_of_range(d, bits, gains):
+def test_v_scales_of_a_row(d, bits, gains):
     rng = np.random.default_rng(3)
     q, k, v = (rng.standard_normal((280, d)) for _ in range(3))
     masks = np.ones((1, 5, 5), bool)

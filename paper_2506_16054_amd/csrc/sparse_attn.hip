@@ -917,8 +917,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         return __builtin_amdgcn_readlane(cols64, u & 63);
     };
 
-    // The first block is on its way while the row's scales are looked at: layer of 8 heads of 221 tokens, bf16, us, d = 64 4-bit 9.67 -> 9.48,
-    // 8-bit with 4-bit P and V 9.61 -> 9.55; d = 128 11.66 -> 11.55 and 11.71 -> 11.58.
+    // The first block is on its way while the row's scales are looked at.
     float sk_cur = 0.0f, sv_cur = 0.0f;
     int j0 = 0, j1 = 0;
     if (cnt > 0) {
@@ -937,21 +936,26 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
 
-    bool fast = false;
+    // Of the row's scales only whether one passes a limit is asked: compares of the lanes' own, not maxima over the wavefront, which are 12
+    // exchanges through LDS in front of a row of a few blocks.  The launch alone, 8 heads of 221 tokens, 8-bit Q and K with 4-bit P and V, us:
+    // d = 64 6.28 -> 6.02, d = 128 7.45 -> 7.33; all 4-bit 6.28 -> 6.20, 7.43 -> 7.51; 8-bit codes 6.12 -> 5.87, 7.46 -> 7.50 (runs differ by
+    // 1.5 %).  Without a look at the scales - exponent and sums by fmas that take the 2^26 out - 5.68 and 6.85, but 1 to 1.5 % slower where the
+    // chip is full (30 heads of 17550 tokens, 8-bit codes 824 -> 835, d = 128 1389 -> 1410).
+    bool fast;
     float sv_up = 0x1p26f;  // what a V scale is multiplied by to give a weight
     {
-        float sk_max = 0.0f, sv_max = 0.0f;
+        sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
+        bool sk_big = false, sv_big = false;
         for (int base = 0; base < cnt; base += 64)
             if (base + lane < cnt) {
                 const int j = base == 0 ? cols64 : min(max(cols[base + lane], 0), a.kblocks - 1);
-                sk_max = fmaxf(sk_max, skp[j]);
-                sv_max = fmaxf(sv_max, svp[j]);
+                sk_big |= !(sq_i * skp[j] < 0x1p90f);  // as above
+                sv_big |= svp[j] > 0x1p40f;
             }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sk_max = fmaxf(sk_max, __shfl_xor(sk_max, off));
-        sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
-        fast = sq_i * sk_max < 0x1p90f;  // as above
-        if (__builtin_amdgcn_ballot_w64(sv_max > 0x1p40f) != 0) sv_up = 1.0f;
+        int slow = __builtin_amdgcn_ballot_w64(sk_big) != 0;
+        asm volatile("" : "+v"(slow));  // (known to be uniform, it makes the compiler spill)
+        fast = slow == 0;
+        if (__builtin_amdgcn_ballot_w64(sv_big) != 0) sv_up = 1.0f;
     }
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
     if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fast = false;

@@ -33,7 +33,8 @@ def attention_kernel_symbol(w):
     if w.block == 32:
         return ("_ZN4paro18attn_i8_b32_kernelILi%dELi%dELi%dE%sEEvNS_8AttnArgsE" % (w.d, w.bits_qk, w.bits_pv, t),
                 "paro::attn_i8_b32_kernel<%d, %d, %d, %s>" % (w.d, w.bits_qk, w.bits_pv, tn), 1, 3 if w.d == 64 else 2, 2)
-    if w.d == 128 or w.B * w.nh * w.k <= 1536:
+    assert w.d == 128 or w.B * w.nh * w.k > 2048, "a few row blocks of d = 64, block 64 have a kernel by their number and length"
+    if w.d == 128:
         return ("_ZN4paro18attn_i8_q16_kernelILi%dELi%dELi%dE%sLi0EEEvNS_8AttnArgsE" % (w.d, w.bits_qk, w.bits_pv, t),
                 "paro::attn_i8_q16_kernel<%d, %d, %d, %s, 0>" % (w.d, w.bits_qk, w.bits_pv, tn), 4, 4, 2)
     if w.bits_qk == 8:

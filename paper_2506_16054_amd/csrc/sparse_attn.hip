@@ -936,8 +936,8 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
 
-    // Of the row's scales only whether one passes a limit is asked: compares of the lanes' own, not maxima over the wavefront, which are 12
-    // exchanges through LDS in front of a row of a few blocks.  The launch alone, 8 heads of 221 tokens, 8-bit Q and K with 4-bit P and V, us:
+    // Of the row's scales only whether one passes a limit is asked: compares of the lanes' own, not maxima over the wavefront, which are six
+    // exchanges through LDS each in front of a row of a few blocks.  The launch alone, 8 heads of 221 tokens, 8-bit Q and K with 4-bit P and V, us:
     // d = 64 6.28 -> 6.02, d = 128 7.45 -> 7.33; all 4-bit 6.28 -> 6.20, 7.43 -> 7.51; 8-bit codes 6.12 -> 5.87, 7.46 -> 7.50 (runs differ by
     // 1.5 %).  Without a look at the scales - exponent and sums by fmas that take the 2^26 out - 5.68 and 6.85, but 1 to 1.5 % slower where the
     // chip is full (30 heads of 17550 tokens, 8-bit codes 824 -> 835, d = 128 1389 -> 1410).
@@ -2386,15 +2386,28 @@ static void launch_w64(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) 
 }
 
 // Block 64; QSRC as in the kernels.  d = 64: with few row blocks the chain of a row's blocks is the launch, and four wavefronts of 16
-// queries are through a block in half the time that one wavefront of 64 needs; with many the chip is full and the 136 x 4 instructions
-// per block of the former lose to the 495 of the latter.  The line, in row blocks of the launch, both sides in us (four wavefronts / one),
-// 8-bit codes / all 4-bit: 256 16.3 / 30.5 and 17.8 / 34.0, 516 15.3 / 23.4 and 16.6 / 25.8, 1536 38.3 / 43.7 and 44.0 / 47.3, 1690
-// 117.7 / 116.2 and 124.0 / 116.4, 8250 720 / 628 and 826 / 688.
+// queries are through a block in half the time that one wavefront of 64 needs; with many the chip is full and the 152 x 4 instructions
+// per block of the former lose to the 495 of the latter.  Rows of fewer than 8 blocks on average are over before a chain counts: there four
+// wavefronts win while all workgroups are resident at once - five per compute unit, four with 4-bit codes throughout (96 and 97
+// registers) - and lose in a second round.  The lines, both sides in us (four wavefronts / one), 8-bit codes, then all 4-bit; R row blocks,
+// K column blocks:
+//   20 % of K = 4 .. 16 (1 .. 3 blocks a row):  R = 1024  8.1 .. 10.8 / 9.0 .. 11.7   8.1 .. 11.5 / 9.1 .. 12.6
+//                                               R = 1152  8.8 .. 11.7 / 9.9 .. 12.8   11.1 .. 14.1 / 10.1 .. 13.5
+//                                               R = 1280  8.9 .. 12.2 / 10.1 .. 13.2  11.3 .. 15.0 / 10.3 .. 14.3
+//                                               R = 1408  11.4 .. 14.0 / 10.7 .. 13.4 12.2 .. 15.4 / 10.8 .. 14.5
+//   20 % of K = 32 (6):                         R = 1280  16.4 / 18.2   19.7 / 19.8;  R = 1536  19.1 / 18.8   20.9 / 20.5
+//   25 % of K = 32, 50 % of K = 16 (8):         R = 1408  21.1 / 22.1, 21.0 / 20.4;   R = 1536  21.5 / 22.2, 21.5 / 21.4
+//   50 % of K = 24, 32 (12, 16):                R = 1536  28.7 / 36.7, 34.8 / 46.9    33.1 / 41.2, 40.2 / 53.0
+//   20, 50 % of K = 64 (13, 32):                R = 1536  40.9 / 83.2, 69.5 / 87.6;   R = 2048  43.2 / 85.6, 82.4 / 90.0
+//   20, 50 % of K = 256 (51, 128):              R = 1536  180 / 316, 308 / 321;       R = 2048  178 / 316, 323 / 326
+//   30 % of K = 65, 275 (20, 83):               R = 1690  44.6 / 44.9, 49.4 / 49.9;   R = 8250  731 / 620, 788 / 684
 constexpr int kQ16Rows = 1536;
 template <int QKBITS, int PVBITS, int QSRC = 0>
 static void launch_b64(int d, paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {
+    constexpr int resident = QKBITS == 4 && PVBITS == 4 ? 1024 : 1280;
+    const bool short_rows = a.nnz < 8LL * a.nh * a.kblocks;
     if (d == 128) launch_q16<128, QKBITS, PVBITS, QSRC>(out_dtype, a, st);
-    else if (a.total_wg <= kQ16Rows) launch_q16<64, QKBITS, PVBITS, QSRC>(out_dtype, a, st);
+    else if (a.total_wg <= (short_rows ? resident : kQ16Rows)) launch_q16<64, QKBITS, PVBITS, QSRC>(out_dtype, a, st);
     else launch_w64<QKBITS, PVBITS, QSRC>(out_dtype, a, st);
 }
 

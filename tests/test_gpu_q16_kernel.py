@@ -1,8 +1,8 @@
 """The kernel with four wavefronts of 16 queries per row block (block 64; d = 128, and d = 64 up to 1536 row blocks) multiplies K Q of a
-block while it exponentiates the one before, brings tiles in two blocks ahead: checked against the oracle where the order of things changes - rows of none to nine
-blocks and around chunks of 64 column indices, the ragged block alone and behind others, padded query rows - in every combination
-of bits, with Q quantized in the kernel too, with V scales of very different size (each row by itself:
-test_gpu_v_scale_spread.py), and on either side of the number of row blocks at which d = 64 changes kernels."""
+block while it exponentiates the one before and brings tiles in two blocks ahead: checked against the oracle where the order of
+things changes - rows of none to nine blocks and around chunks of 64 column indices, the ragged block alone and behind others, padded
+query rows - in every combination of bits, with Q quantized in the kernel too, with V scales of very different size (each row by
+itself: test_gpu_v_scale_spread.py), and on either side of the numbers of row blocks at which d = 64 changes kernels."""
 from types import SimpleNamespace
 
 import numpy as np
@@ -94,11 +94,13 @@ def test_row_maximum_climbing_hundreds_of_octaves(d, bits):
     _run(d, bits, (1, 20, 32), np.ones((1, 10, 10), bool), q, k, v, list(range(10)))
 
 
+# heads x row blocks on either side of 1536 in all; of 1280 and 1024, where rows of fewer than 8 blocks change kernels (7.5 of 8 are live)
 @pytest.mark.parametrize("bits", BITS)
-@pytest.mark.parametrize("heads", [192, 193])
-def test_both_sides_of_the_number_of_row_blocks_at_which_the_kernel_changes(bits, heads):
+@pytest.mark.parametrize("heads,blocks", [(192, 8), (193, 8), (160, 8), (161, 8), (128, 8), (129, 8), (128, 12), (129, 12)])
+def test_both_sides_of_the_number_of_row_blocks_at_which_the_kernel_changes(bits, heads, blocks):
     rng = np.random.default_rng(heads)
-    q, k, v = (rng.standard_normal((500, 64)) for _ in range(3))  # 8 row blocks: 1536 and 1544 in all
-    masks = np.ones((1, 8, 8), bool)
+    n = 64 * blocks - 12
+    q, k, v = (rng.standard_normal((n, 64)) for _ in range(3))
+    masks = np.ones((1, blocks, blocks), bool)
     masks[0, 3, 1::2] = False
-    _run(64, bits, (1, 20, 25), masks, q, k, v, list(range(8)), heads=heads)
+    _run(64, bits, (1, n // 4, 4), masks, q, k, v, list(range(blocks)), heads=heads)

@@ -217,14 +217,13 @@ __device__ inline void unpack_nibbles(const v4i x, v4i& first, v4i& second) {
 // at 50 % 1 196 -> 1 090; 48 heads at 20 % with 4-bit P and V 840 -> 791, all 4-bit 839 -> 807.
 // -------------------------------------------------------------------------------------------
 
-// Lane L's 16 bytes at base + lane_off + OFFSET land at lds_dst + 16 L (lds_dst wave-uniform, lds_dst >= OFFSET
-// bytes into its array).  The instruction's immediate offset moves the global AND the LDS address, so the LDS
-// base is handed over OFFSET bytes low; the four or two requests of a tile then share one address register pair
+// Lane L's 16 bytes at base + lane_off + OFFSET land at slot + OFFSET + 16 L (slot wave-uniform).  The instruction's immediate
+// offset moves the global AND the LDS address, so the requests of a tile share one address register pair and one LDS base
 // instead of costing a per-lane 64-bit addition each.
 template <int OFFSET>
-__device__ inline void lds_dma16(const uint8_t* base, unsigned lane_off, uint8_t* lds_dst) {
+__device__ inline void lds_dma16(const uint8_t* base, unsigned lane_off, uint8_t* slot) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + lane_off),
-                                     (__attribute__((address_space(3))) void*)(lds_dst - OFFSET), 16, OFFSET, 0);
+                                     (__attribute__((address_space(3))) void*)slot, 16, OFFSET, 0);
 }
 
 // The lane number, computed where it stands: in rarely taken branches, so that nothing derived from it is kept in
@@ -865,9 +864,9 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): what the slot held has been read
             const uint8_t* kp = kbase + (size_t)j * (BLK * D);
             lds_dma16<0>(kp, kfill, kslot);
-            lds_dma16<1024>(kp, kfill, kslot + 1024);
-            lds_dma16<2048>(kp, kfill, kslot + 2048);
-            lds_dma16<3072>(kp, kfill, kslot + 3072);
+            lds_dma16<1024>(kp, kfill, kslot);
+            lds_dma16<2048>(kp, kfill, kslot);
+            lds_dma16<3072>(kp, kfill, kslot);
             return;
         }
         global_bytes kp = (global_bytes)kbase + (size_t)j * (BLK * D / KPACK);
@@ -1227,7 +1226,7 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         unsigned off = fill;
         asm volatile("" : "+s"(from), "+v"(off));  // scalar base + lane offset, not a 64-bit address per lane
         lds_dma16<0>(from, off, slot + EACH * w);
-        if constexpr (EACH == 2048) lds_dma16<1024>(from, off, slot + EACH * w + 1024);
+        if constexpr (EACH == 2048) lds_dma16<1024>(from, off, slot + EACH * w);
     };
     using Packed = std::conditional_t<D == 128, v4i, v2u>;  // a thread's share of a tile of 4-bit codes
     const int tid = threadIdx.x;
@@ -1850,17 +1849,17 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
         const uint8_t* kp = kbase + (size_t)j * TILE;
         asm volatile("" : "+s"(kp), "+v"(kfill));  // scalar base + lane offset; the flipped offset is made here, not kept
         lds_dma16<0>(kp, kfill, &kbuf[w][0]);
-        lds_dma16<1024>(kp, kfill, &kbuf[w][1024]);
-        lds_dma16<2048>(kp, kfill ^ 64u, &kbuf[w][2048]);
-        lds_dma16<3072>(kp, kfill ^ 64u, &kbuf[w][3072]);
+        lds_dma16<1024>(kp, kfill, &kbuf[w][0]);
+        lds_dma16<2048>(kp, kfill ^ 64u, &kbuf[w][0]);
+        lds_dma16<3072>(kp, kfill ^ 64u, &kbuf[w][0]);
     };
     auto request_v = [&](int j) {
         const uint8_t* vp = vbase + (size_t)j * TILE;
         asm volatile("" : "+s"(vp));
         lds_dma16<0>(vp, vfill, &vbuf[w][0]);
-        lds_dma16<2048>(vp, vfill, &vbuf[w][1024]);
-        lds_dma16<0>(vp + 4096, vfill, &vbuf[w][2048]);
-        lds_dma16<2048>(vp + 4096, vfill, &vbuf[w][3072]);
+        lds_dma16<1024>(vp + 1024, vfill, &vbuf[w][0]);  // a request further, 2048 bytes in memory and 1024 in LDS
+        lds_dma16<2048>(vp + 2048, vfill, &vbuf[w][0]);
+        lds_dma16<3072>(vp + 3072, vfill, &vbuf[w][0]);
     };
     Bf16Groups<4, 4> rows;
     rows.init();
@@ -2011,17 +2010,17 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
         const uint8_t* kp = kbase + (size_t)j * TILE;
         asm volatile("" : "+s"(kp));
         lds_dma16<0>(kp, kfill, &kbuf[4096 * w]);
-        lds_dma16<1024>(kp, kfill, &kbuf[4096 * w + 1024]);
-        lds_dma16<2048>(kp, kfill, &kbuf[4096 * w + 2048]);
-        lds_dma16<3072>(kp, kfill, &kbuf[4096 * w + 3072]);
+        lds_dma16<1024>(kp, kfill, &kbuf[4096 * w]);
+        lds_dma16<2048>(kp, kfill, &kbuf[4096 * w]);
+        lds_dma16<3072>(kp, kfill, &kbuf[4096 * w]);
     };
     auto request_v = [&](int j) {
         const uint8_t* vp = vbase + (size_t)j * TILE;
         asm volatile("" : "+s"(vp));
         lds_dma16<0>(vp, vfill, &vbuf[4096 * w]);
-        lds_dma16<1024>(vp, vfill, &vbuf[4096 * w + 1024]);
-        lds_dma16<2048>(vp, vfill, &vbuf[4096 * w + 2048]);
-        lds_dma16<3072>(vp, vfill, &vbuf[4096 * w + 3072]);
+        lds_dma16<1024>(vp, vfill, &vbuf[4096 * w]);
+        lds_dma16<2048>(vp, vfill, &vbuf[4096 * w]);
+        lds_dma16<3072>(vp, vfill, &vbuf[4096 * w]);
     };
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
     const int nkeys = a.n_tokens - (a.kblocks - 1) * BLK;
@@ -2169,29 +2168,32 @@ __global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_
         asm volatile("" : "+s"(kp), "+v"(kfill));  // scalar base + lane offset; the flipped offset of rows 16 .. is made here, not kept
         if constexpr (D == 64) {
             lds_dma16<0>(kp, kfill, &kbuf[0]);
-            lds_dma16<1024>(kp, kfill, &kbuf[1024]);
-            lds_dma16<2048>(kp, kfill ^ 64u, &kbuf[2048]);
-            lds_dma16<3072>(kp, kfill ^ 64u, &kbuf[3072]);
+            lds_dma16<1024>(kp, kfill, &kbuf[0]);
+            lds_dma16<2048>(kp, kfill ^ 64u, &kbuf[0]);
+            lds_dma16<3072>(kp, kfill ^ 64u, &kbuf[0]);
         } else {
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 const uint8_t* from = kp + 4096 * half;
                 const unsigned off = kfill ^ (64u * half);
                 lds_dma16<0>(from, off, &kbuf[4096 * half]);
-                lds_dma16<1024>(from, off, &kbuf[4096 * half + 1024]);
-                lds_dma16<2048>(from, off, &kbuf[4096 * half + 2048]);
-                lds_dma16<3072>(from, off, &kbuf[4096 * half + 3072]);
+                lds_dma16<1024>(from, off, &kbuf[4096 * half]);
+                lds_dma16<2048>(from, off, &kbuf[4096 * half]);
+                lds_dma16<3072>(from, off, &kbuf[4096 * half]);
             }
         }
     };
     auto request_v = [&](int j) __attribute__((always_inline)) {
         const uint8_t* vp = vbase + (size_t)j * (BLK * D * 2);
         asm volatile("" : "+s"(vp));
+        constexpr int further = 32 * BLK - 1024;  // 16 rows a request: 32 BLK bytes in memory, 1024 in LDS
 #pragma unroll
-        for (int u = 0; u < REQUESTS; u += 2) {  // 16 rows each
-            const uint8_t* from = vp + 32 * BLK * u;
-            lds_dma16<0>(from, vfill, &vbuf[1024 * u]);
-            lds_dma16<32 * BLK>(from, vfill, &vbuf[1024 * u + 1024]);
+        for (int four = 0; four < REQUESTS; four += 4) {
+            const uint8_t* from = vp + 32 * BLK * four;
+            lds_dma16<0>(from, vfill, &vbuf[1024 * four]);
+            lds_dma16<1024>(from + further, vfill, &vbuf[1024 * four]);
+            lds_dma16<2048>(from + 2 * further, vfill, &vbuf[1024 * four]);
+            lds_dma16<3072>(from + 3 * further, vfill, &vbuf[1024 * four]);
         }
     };
     // 64 column indices per fetch, one per lane; past the end of the row its last column again

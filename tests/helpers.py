@@ -135,26 +135,6 @@ def rel_l2(a, b):
 MAX_TIE_EXCESS = 2e-5
 
 
-def same_attention_kernel_for_raw_q(w) -> bool:
-    """Whether paro_sparse_attn_unpermuted_rawq is asserted to give the bits of the other entry points.  At d = 128, block 64
-    with 8-bit codes throughout they are only asserted to agree to the rounding of the output: bound of kernels whose
-    floating-point sums associate differently (the two run the same kernel, and test_gpu_q16_kernel.py asserts the bits)."""
-    return not (w.d == 128 and w.block == 64 and w.bits_qk == 8 and w.bits_pv == 8)
-
-
-def assert_equal_up_to_output_rounding(got, want, what=""):
-    """Two evaluations of the same fp32 formula whose sums associate differently (torch tensors): equal up to one
-    unit in the last place of the output type, plus 1e-6 of the largest magnitude for elements that cancel to near 0."""
-    g, r = got.float(), want.float()
-    bf16 = str(got.dtype).endswith("bfloat16")
-    ulp = 2.0 ** -7 if bf16 else 2.0 ** -22
-    tol = ulp * r.abs() + 1e-6 * float(r.abs().max())
-    bad = int(((g - r).abs() > tol).sum())
-    assert bad == 0, "%s: %d elements differ by more than the output rounding" % (what, bad)
-    if bf16:  # fp32 differences of 1e-7 relative survive the rounding to bf16 only now and then
-        assert float((g != r).float().mean()) < 0.05, "%s: more than 5 %% of the elements differ in the last place" % what
-
-
 def check_attention(got, ref, risk, max_abs, rel, what=""):
     """The stated bar: relative L2 <= rel on everything, plainly; |got - ref| <= max_abs on every
     element that no near-tie P code can reach (risk == 0).  The remaining elements may exceed max_abs

@@ -6,15 +6,14 @@ head bit for bit, the attention output of the whole head element by element at t
 The forms of the path that bench.py times (one quantizer launch + attention with the inverse reorder in
 its stores, scheduled launch order) must reproduce the oracle-checked five-step result bit for bit on
 the WHOLE tensor, which ties every row of every head of the timed path to the checked one; so must the
-entry point that quantizes Q inside the attention kernel wherever it runs the same attention kernel
-(elsewhere: equal up to the rounding of the output).  Properties that hold at any size are checked on the full
+entry point that quantizes Q inside the attention kernel.  Properties that hold at any size are checked on the full
 tensors: the reorder round trip is the identity, padded rows are zero, nothing is NaN."""
 import numpy as np
 import pytest
 
 from oracle import paro_oracle as po
 from paper_2506_16054_amd import workloads as wl
-from tests.helpers import assert_equal_up_to_output_rounding, check_attention, oracle_whole_heads, same_attention_kernel_for_raw_q
+from tests.helpers import check_attention, oracle_whole_heads
 from tests.test_gpu_parity import MAX_ABS, REL_L2, REL_L2_BF16, host, tdtype, unpack_rows_int4, unpack_vt_int4, vt_to_rows
 
 pytestmark = pytest.mark.gpu
@@ -53,10 +52,7 @@ def check_timed_forms(w, pa, q, k, v, o):
     assert torch.equal(pa.attend_fused(), o), "%s: one-launch quantizer + attention with inverse reorder differs" % w.name
     if pa.can_fuse_q:
         pa.o.fill_(float("nan"))
-        if same_attention_kernel_for_raw_q(w):
-            assert torch.equal(pa.run_rawq(q, k, v), o), "%s: attention that quantizes its own Q differs" % w.name
-        else:
-            assert_equal_up_to_output_rounding(pa.run_rawq(q, k, v), o, "%s: attention that quantizes its own Q" % w.name)
+        assert torch.equal(pa.run_rawq(q, k, v), o), "%s: attention that quantizes its own Q differs" % w.name
     # the launch order is a schedule, not arithmetic: with and without it the result is the same
     order = pa.row_order
     pa.use_blocklist(pa.row_ptr, pa.col_idx, None)

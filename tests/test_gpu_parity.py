@@ -6,8 +6,7 @@ import pytest
 
 from oracle import paro_oracle as po
 from paper_2506_16054_amd import workloads as wl
-from tests.helpers import (assert_equal_up_to_output_rounding, blocklist_for, check_attention, gather_fn, oracle_head,
-                           same_attention_kernel_for_raw_q)
+from tests.helpers import blocklist_for, check_attention, gather_fn, oracle_head
 
 pytestmark = pytest.mark.gpu
 
@@ -381,8 +380,7 @@ def test_padded_keys_get_no_mass_even_when_all_logits_are_tiny(scale, bits_pv):
 def test_in_kernel_q_quantization_is_bit_identical(name, q_dtype):
     """paro_sparse_attn_unpermuted_rawq (Q reordered and quantized by the workgroup that owns the row
     block) gives exactly the output of paro_permute_quantize(Q) + paro_sparse_attn_unpermuted, for both
-    input types, on ragged shapes, with text tokens and with 4-bit PV - bit for bit where both run the same
-    attention kernel, to the rounding of the output where they do not (d = 128 with 8-bit codes)."""
+    input types, on ragged shapes, at both head dimensions, with text tokens and with 4-bit PV."""
     torch, pb = _torch(), _pb()
     from paper_2506_16054_amd.pipeline import ParoAttention
 
@@ -399,10 +397,7 @@ def test_in_kernel_q_quantization_is_bit_identical(name, q_dtype):
     got = pa.run_rawq(q, k, v)
     torch.cuda.synchronize()
     assert not torch.isnan(got).any()
-    if same_attention_kernel_for_raw_q(w):
-        assert torch.equal(got, want)
-    else:
-        assert_equal_up_to_output_rounding(got, want, name)
+    assert torch.equal(got, want)
 
 
 def test_in_kernel_q_quantization_rejects_what_it_does_not_cover():

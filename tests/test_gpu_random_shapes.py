@@ -7,8 +7,7 @@ import pytest
 
 from oracle import paro_oracle as po
 from paper_2506_16054_amd import workloads as wl
-from tests.helpers import (assert_equal_up_to_output_rounding, blocklist_for, check_attention, gather_fn, oracle_head,
-                           same_attention_kernel_for_raw_q)
+from tests.helpers import blocklist_for, check_attention, gather_fn, oracle_head
 from tests.test_gpu_parity import MAX_ABS, REL_L2, REL_L2_BF16, host, tdtype, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -54,10 +53,7 @@ def test_random_shape(i):
     torch.cuda.synchronize()
     assert torch.equal(o_sep, o_fused), "fused entry points differ from the separate steps"
     if pa.can_fuse_q:
-        if same_attention_kernel_for_raw_q(w):
-            assert torch.equal(pa.run_rawq(dq, dk, dv), o_fused), "in-kernel Q quantization differs"
-        else:
-            assert_equal_up_to_output_rounding(pa.run_rawq(dq, dk, dv), o_fused, "in-kernel Q quantization")
+        assert torch.equal(pa.run_rawq(dq, dk, dv), o_fused), "in-kernel Q quantization differs"
     pa.prepare_fused_qkv(dq, dk, dv)
     assert torch.equal(pa.attend_fused(), o_fused), "the one-launch quantizer differs from the three calls"
     saved = pa.row_order

@@ -146,3 +146,82 @@ def test_mean_by_sums_is_the_mean(heads, d, grid, bits_qk, dtype):
     assert torch.equal(mean, k.double().mean(dim=2).to(torch.float32).to(torch.bfloat16).float())
     for a, b in zip(codes + scales, want_codes + want_scales):
         assert torch.equal(a, b)
+
+
+def _long_layer(bits, seed):
+    """2048 fp32 tokens: the channel mean is made of partial sums that meet in Q's codes."""
+    import torch
+
+    from paper_2506_16054_amd import binding as pb
+    from paper_2506_16054_amd import workloads as wl
+    from paper_2506_16054_amd.pipeline import ParoAttention
+
+    s = pb.make_shape(1, 3, 64, 1, 32, 64, 0, 64)
+    live = np.random.default_rng(seed).random((3, 32, 32)) < 0.4
+    live[:, np.arange(32), np.arange(32)] = True
+    pa = ParoAttention(s, np.array([0, 2, 5], np.uint8), wl.pack_bitmask(live), *bits, torch.float32)
+    gen = torch.Generator(device="cuda:0").manual_seed(seed)
+    x = [torch.randn((1, 3, 2048, 64), generator=gen, device="cuda:0") for _ in range(3)]
+    x[1] += 3.0 * torch.randn((1, 3, 1, 64), generator=gen, device="cuda:0")
+    return pa, x
+
+
+def _forms(pa):
+    return [pa.run_fused_smooth_k] + ([pa.run_rawq] if pa.can_fuse_q else [])
+
+
+@pytest.mark.parametrize("bits", [(8, 8), (4, 8)])
+def test_inputs_that_arrive_late_on_a_side_stream(route, bits, monkeypatch):
+    """A call on any other stream, or sums read from another stream's scratch, would see what was there before."""
+    import types
+
+    import torch
+
+    from paper_2506_16054_amd import binding as pb
+
+    pa, x = _long_layer(bits, 1)
+    want = [form(*x).clone() for form in _forms(pa)]
+    taken = []
+    if route == "native":  # the module takes these calls as they stand
+        native = pb._native()
+        watched = {name: (lambda f: lambda *a: taken.append(f(*a)) or taken[-1])(getattr(native, name)) for name in pb.FASTCALL}
+        monkeypatch.setattr(pb, "_fast", types.SimpleNamespace(**watched))
+    late = [torch.zeros_like(t) for t in x]
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for form, o in zip(_forms(pa), want):
+            [t.zero_() for t in late]
+            [t.fill_(7) for t in (*pa._fused_buffers(), pa.vc, pa.sq, pa.sk, pa.sv, pa.k_mean)]
+            torch.cuda._sleep(20_000_000)  # some 10 ms
+            [t.copy_(s) for t, s in zip(late, x)]
+            got = form(*late).clone()
+            side.synchronize()
+            assert torch.equal(got, o)
+    assert route != "native" or (len(taken) == 2 * len(want) and all(status == pb.PARO_OK for status in taken))
+
+
+def test_two_threads_with_a_layer_and_a_stream_each(route):
+    import threading
+
+    import torch
+
+    layers = [_long_layer((8, 8), 2), _long_layer((4, 4), 3)]
+    want = [[form(*x).clone() for form in _forms(pa)] for pa, x in layers]
+    torch.cuda.synchronize()
+    wrong, start = [], threading.Barrier(2)
+
+    def work(i):
+        pa, x = layers[i]
+        start.wait()
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(50):
+                got = [form(*x).clone() for form in _forms(pa)]
+                torch.cuda.current_stream().synchronize()
+                if not all(torch.equal(a, b) for a, b in zip(got, want[i])):
+                    wrong.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    assert wrong == []

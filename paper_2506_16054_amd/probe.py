@@ -281,14 +281,14 @@ def timeline(workload: str, step_us: float | None = None, records_path: str | No
                 label, sel.sum(), cnt[sel].min(), cnt[sel].max(), start[sel].min(), np.median(start[sel]), start[sel].max(),
                 end[sel].min(), np.median(end[sel]), end[sel].max(), np.median(per)))
     if waves_per_wg == 4:  # the four-wavefront kernel also records where a block's cycles go
-        names = ("K reads, QK^T products, row maximum, share of the tile exponent", "wait for the tiles and the other wavefronts (barrier)",
-                 "exponentials, row sum, codes", "PV products, accumulator update, next requests")
+        names = ("next tiles requested, QK^T products of the next block, exponentials", "wait for the tiles and the other wavefronts (barrier)",
+                 "row maxima of the next block, row sum, codes, PV products, accumulator update")
         out += ["", "| shader cycles per block (median over the wavefronts) | " + " | ".join(names) + " | sum | in front of the loop (per wavefront) |",
-                "|---|---|---|---|---|---|---|"]
+                "|---|---|---|---|---|---|"]
         for label, sel in (("more than half of all column blocks live", heavy), ("the others, started in the first 5 us", ~heavy & (start < 5.0)),
                            ("the others, started later", ~heavy & (start >= 5.0))):
             if sel.any():
-                per = rec[sel, 3:7] / np.maximum(cnt[sel], 1)[:, None]
+                per = rec[sel, 3:6] / np.maximum(cnt[sel], 1)[:, None]  # (the fourth, outside of the steps, is empty)
                 out.append("| %s | %s | %.0f | %.0f |" % (label, " | ".join("%.0f" % x for x in np.median(per, axis=0)), np.median(per.sum(1)), np.median(rec[sel, 7])))
     # the kernels give launch positions [x * per_xcd, (x + 1) * per_xcd) to XCD x; row_order maps positions to row blocks
     total = w.B * w.nh * w.k

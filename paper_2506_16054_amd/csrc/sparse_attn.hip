@@ -783,17 +783,17 @@ __global__ __launch_bounds__(64, 2) void attn_i8_w64_qk4_kernel(AttnArgs a) {
 // go through LDS in whole lines.
 // Bound by the issue of the vector work where the chip is full (184 vector instructions per block at d = 64, 256 at d = 128), by the
 // chain of one block where it is not.  Attention call alone, us, before (tiles exchanged through LDS with a barrier per block) -> now,
-// 8-bit codes / all 4-bit, 30 % density: d = 64, 30 heads of 17550 tokens 1001 -> 850 / 962 -> 807, 24 heads of 4096 55.1 -> 46.6 /
-// 56.4 -> 47.4, 4 heads of 4096 35.2 -> 25.5 / 36.7 -> 27.0; d = 128, 30 heads of 17550 1764 -> 1415 (K of 8-bit codes by registers took
-// 1.2 times as long) / 1838 -> 1288, 4 heads of 4096 45.1 -> 33.5 / 48.5 -> 36.0.
+// 8-bit codes / all 4-bit, 30 % density: d = 64, 30 heads of 17550 tokens 975 -> 827 / 956 -> 797, 24 heads of 4096 54.3 -> 45.3 /
+// 56.3 -> 46.7, 4 heads of 4096 35.1 -> 26.1 / 36.7 -> 27.1; d = 128, 30 heads of 17550 1780 -> 1400 (K of 8-bit codes by registers took
+// 1.2 times as long) / 1834 -> 1301, 4 heads of 4096 45.0 -> 32.4 / 48.3 -> 35.5.
 //
 // The exponent is formed after one exact subtraction per logit (the folded form of the kernel above is 2.5 % faster here and
 // decides P codes within 6e-5 of a tie differently: error against binary64 3e-4 with it, 4e-5 without).
 // -------------------------------------------------------------------------------------------
 
 // A P V product enters the sums as the integer that it is: its chain starts at kStartI (see acc_start), one subtraction per element leaves
-// the result times 2^-26, and the weight carries the 2^26 back where no V scale of the row block passes 2^40 - in the other rows the division
-// at the end does, so that a climb of 64 octaves does not take the weight out of range.  (Left in the sums and taken out every few blocks
+// the result times 2^-26, of which 2^13 come back in the weights and 2^13 at the end, whatever the scales: nothing is asked about them in
+// front of a row.  (Left in the sums and taken out every few blocks
 // the start would save the subtraction, 773 us instead of 833 for 30 heads of 17550 tokens, d = 64; but it is as large as the largest result,
 // times a weight that says nothing about a query's own codes, and a block of V some 2^12 larger than the rest, or one of zeros, whose scale is
 // 1, pushes the digits of the others out of the sum: 5e-3 of the output at 2^12, all of it at 2^20.)
@@ -808,6 +808,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
     constexpr float LOG2_QMAXP = PVBITS == 4 ? 2.807354922057604f : 6.988684686772166f;
     constexpr float kLog2_65535 = 15.999977986052736f;
     constexpr bool K_BY_LDS = D / KPACK == 128;
+    constexpr float kClimb = 32.0f;  // octaves above its reference at which a row takes a new one (64 in the other kernels, whose weights carry less)
     __shared__ __attribute__((aligned(16))) uint8_t kslot[K_BY_LDS ? BLK * D : 16];
 
     const int wg = blockIdx.x;
@@ -833,9 +834,9 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
     const unsigned klane = n * (D / KPACK) + 16 * g;            // this lane's K fragment of step 0, inside a block
     const unsigned vlane = n * (BLK / VPACK) + 16 / VPACK * g;  // its V^T fragment of channel tile 0
     const float* skp = a.sk + (size_t)bh * a.kblocks;
-    const float sk_last = uniform_load(skp + a.kblocks - 1);
     const float* svp = a.sv + (size_t)bh * a.kblocks;
     float sq_i = a.sq[(size_t)bh * a.kblocks + i] * (QKBITS == 4 ? a.qk_scale * (1.0f / 256.0f) : a.qk_scale);  // 4-bit codes enter times 16
+    sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
     const int row = i * BLK + n;
     const bool row_valid = row < a.n_tokens;
     v4i qf[KS];
@@ -916,7 +917,6 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         return __builtin_amdgcn_readlane(cols64, u & 63);
     };
 
-    // The first block is on its way while the row's scales are looked at.
     float sk_cur = 0.0f, sv_cur = 0.0f;
     int j0 = 0, j1 = 0;
     if (cnt > 0) {
@@ -935,29 +935,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[dt][r] = 0.0f;
 
-    // Of the row's scales only whether one passes a limit is asked: compares of the lanes' own, not maxima over the wavefront, which are six
-    // exchanges through LDS each in front of a row of a few blocks.  The launch alone, 8 heads of 221 tokens, 8-bit Q and K with 4-bit P and V, us:
-    // d = 64 6.28 -> 6.02, d = 128 7.45 -> 7.33; all 4-bit 6.28 -> 6.20, 7.43 -> 7.51; 8-bit codes 6.12 -> 5.87, 7.46 -> 7.50 (runs differ by
-    // 1.5 %).  Without a look at the scales - exponent and sums by fmas that take the 2^26 out - 5.68 and 6.85, but 1 to 1.5 % slower where the
-    // chip is full (30 heads of 17550 tokens, 8-bit codes 824 -> 835, d = 128 1389 -> 1410).
-    bool fast;
-    float sv_up = 0x1p26f;  // what a V scale is multiplied by to give a weight
-    {
-        sq_i = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sq_i)));
-        bool sk_big = false, sv_big = false;
-        for (int base = 0; base < cnt; base += 64)
-            if (base + lane < cnt) {
-                const int j = base == 0 ? cols64 : min(max(cols[base + lane], 0), a.kblocks - 1);
-                sk_big |= !(sq_i * skp[j] < 0x1p90f);  // as above
-                sv_big |= svp[j] > 0x1p40f;
-            }
-        int slow = __builtin_amdgcn_ballot_w64(sk_big) != 0;
-        asm volatile("" : "+v"(slow));  // (known to be uniform, it makes the compiler spill)
-        fast = slow == 0;
-        if (__builtin_amdgcn_ballot_w64(sv_big) != 0) sv_up = 1.0f;
-    }
     const int tail_block = (a.n_tokens % BLK) != 0 ? a.kblocks - 1 : -1;
-    if (tail_block >= 0 && sq_i * sk_last < kLogitScaleMin) fast = false;
     v16i start = acc_start();  // of the P V products: several in a basic block
     asm volatile("" : "+v"(start));
 
@@ -986,7 +964,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         const unsigned eb = wave_umin(min(0xFF800000u, __float_as_uint(ymax - m_new)));  // a padded row has -inf here
         beside();
         e = __uint_as_float(eb);
-        if (__builtin_amdgcn_ballot_w64(m_new - m_ref > 64.0f) != 0) {
+        if (__builtin_amdgcn_ballot_w64(m_new - m_ref > kClimb) != 0) {
             const float down = __builtin_amdgcn_exp2f(m_ref - m_new);  // first block: 2^-inf = 0 on zero sums
             l *= down;
             weight *= down;
@@ -998,22 +976,22 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         }
         m = m_new;
     };
-    auto step = [&](auto mode_tag, int t, v16i& S, v16i& N) __attribute__((always_inline)) {
-        constexpr int MODE = decltype(mode_tag)::value;
-        float c = sq_i * sk_cur;
-        if (MODE == kExact && c < kLogitScaleMin) c = kLogitScaleMin;
-        const float c_up = c * 0x1p26f;
+    // block t, whose logits are in S; N: the next one's, unless it is the last
+    auto step = [&](auto last_tag, int t, v16i& S, v16i& N) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last_tag)::value;
+        // at least kLogitScaleMin where the ragged block's masked keys need it (it changes no other exponent), and 0 stays 0 under any scale
+        const float c_up = __builtin_amdgcn_fmed3f(sq_i * sk_cur * 0x1p26f, kLogitScaleMin * 0x1p26f, 3.402823466e+38f);
         const float off_n = (LOG2_QMAXP - kLog2_65535) - m - e;
-        const float w_blk = __builtin_amdgcn_exp2f((-kLog2_65535 - m_ref) - off_n);
+        const float w_blk = __builtin_amdgcn_exp2f((-kLog2_65535 - m_ref) - off_n) * 0x1p13f;
         float E[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            if constexpr (MODE == kScaled) E[r] = fmaf(__int_as_float(S[r]) - kStartF, c_up, off_n);
-            else E[r] = fmaf(start_result(S[r]), c, off_n);
+        for (int r = 0; r < 16; ++r) E[r] = fmaf(__int_as_float(S[r]) - kStartF, c_up, off_n);
+        int j2 = j1;
+        if constexpr (!LAST) {
+            widen_k();
+            j2 = column(t + 2);
         }
-        widen_k();
         widen_v();
-        const int j2 = column(t + 2);
         auto add = [&](int dt, const v16i& o) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -1026,7 +1004,9 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         __builtin_amdgcn_s_setprio(3);
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            if constexpr (D == 64) {
+            if constexpr (LAST) {
+                if (p < 2) o[p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[p], pf, start, 0, 0, 0);
+            } else if constexpr (D == 64) {
                 if (p < 2) qk(p, N);
                 else o[p - 2] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[p - 2], pf, start, 0, 0, 0);
             } else {
@@ -1037,7 +1017,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 #pragma unroll
             for (int r = 4 * p; r < 4 * p + 4; ++r) E[r] = __builtin_amdgcn_exp2f(E[r]);
             __builtin_amdgcn_sched_barrier(0);
-            if (p == D / 32 - 1) load_k(j2);
+            if (!LAST && p == D / 32 - 1) load_k(j2);
         }
         __builtin_amdgcn_s_setprio(0);
         float sum[4];
@@ -1051,12 +1031,8 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
             for (int dt = 2; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[dt], pf, start, 0, 0, 0);
         }
         load_v(j0);
-        j0 = j1;
-        const float sv_now = sv_cur * sv_up * (PVBITS == 4 ? 0.0625f : 1.0f);
-        sk_cur = uniform_load(skp + j0);
-        sv_cur = uniform_load(svp + j0);
-        j1 = j2;
-        open(j0, sk_cur, N, [&]() __attribute__((always_inline)) {
+        const float sv_now = sv_cur * (PVBITS == 4 ? 0.0625f : 1.0f);
+        auto rest = [&]() __attribute__((always_inline)) {
             if constexpr (D == 128) {
                 add(2, o[2]);
                 add(3, o[3]);
@@ -1070,15 +1046,16 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
             asm volatile("" : "+v"(pf));
             l = fmaf((sum[0] + sum[1]) + (sum[2] + sum[3]), w_blk, l);
             weight = w_blk * sv_now;
-        });
-    };
-    auto visit_all = [&](auto mode_tag) __attribute__((always_inline)) {
-        int t = 0;
-        for (; t + 1 < cnt; t += 2) {
-            step(mode_tag, t, Sa, Sb);
-            step(mode_tag, t + 1, Sb, Sa);
+        };
+        if constexpr (LAST) {
+            rest();
+        } else {
+            j0 = j1;
+            sk_cur = uniform_load(skp + j0);
+            sv_cur = uniform_load(svp + j0);
+            j1 = j2;
+            open(j0, sk_cur, N, rest);
         }
-        if (t < cnt) step(mode_tag, t, Sa, Sb);
     };
     if (cnt > 0) {
         widen_k();
@@ -1088,8 +1065,25 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
         open(j0, sk_cur, Sa, [] {});
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing pending at the loop's entry: the compiler would wait for it in every pass
-    if (fast) visit_all(std::integral_constant<int, kScaled>{});
-    else visit_all(std::integral_constant<int, kExact>{});
+    // The last block stands apart, without a product behind it.  One loop, and no look at the row's scales in front of it, where a loop for each of
+    // two ranges of them and a scan stood: a launch of short rows is mostly instructions that are fetched once.  Attention alone, 8-bit Q and K
+    // with 4-bit P and V, us, (tiles exchanged through LDS with a barrier per block) / scan and two loops -> now: 85 heads of 96 tokens, d = 64
+    // 4.3 / 4.7 -> 4.3, d = 128 5.1 / 5.7 -> 5.2; 128 heads of 256 at 50 % 7.2 / 7.3 -> 6.7; 128 heads of 96 in 32 batches 26.0 / 28.4 -> 27.0; long rows
+    // 0 to 2 % slower, 4 heads of 4096 8-bit 25.5 -> 26.0, 30 heads of 17550 817 -> 819.  (V in two sets of registers, and it, the scales and two blocks
+    // of K requested together in front of a row: no difference, d = 128 5 % slower.)
+    {
+        const std::false_type inner;
+        int t = 0;
+        for (; t + 2 < cnt; t += 2) {
+            step(inner, t, Sa, Sb);
+            step(inner, t + 1, Sb, Sa);
+        }
+        if (t + 1 < cnt) {
+            step(inner, t, Sa, Sb);
+            Sa = Sb;
+        }
+        if (cnt > 0) step(std::true_type(), cnt - 1, Sa, Sb);
+    }
     if (cnt > 0) {  // the last block's P V, one tile at a time
         widen_v();
 #pragma unroll
@@ -1104,7 +1098,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
     const int orow_no = i * BLK + (ln & 31);
     const bool valid = orow_no < a.n_tokens;
     const float l_tot = (l + __shfl_xor(l, 32)) * 65535.0f;
-    const float inv = (valid && l_tot > 0.0f) ? (0x1p26f / sv_up) / l_tot : 0.0f;
+    const float inv = (valid && l_tot > 0.0f) ? 0x1p26f / l_tot : 0.0f;
     const long long ooff = out_row_offset<D>(a, bh, h, head_rows, orow_no, valid);
     if (ooff >= 0) {
         OutT* orow = (OutT*)a.op + ooff + 4 * (ln >> 5);

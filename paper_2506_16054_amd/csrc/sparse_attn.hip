@@ -1146,10 +1146,10 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
 // K_t and V_{t+1} V_{t-1}, and they have the whole block to land.
 //
 // Attention call alone, us, before -> now, 30 % density, 8-bit codes / 8-bit Q K with 4-bit P V / all 4-bit.  d = 128 (before: the same split without
-// the overlap for 8-bit codes, two wavefronts of 32 queries otherwise): 30 heads of 17550 tokens 1160 -> 1121 / 1274 -> 1135 / 1285 -> 1098,
-// 24 heads of 4096 61.0 -> 59.6 / 77.2 -> 60.8 / 77.6 -> 60.1, 4 heads of 4096 23.1 -> 19.6 / 34.0 -> 22.4 / 35.2 -> 24.0, 24 heads of
-// 4096 image and 512 text tokens 109 -> 106 / 119 -> 108 / 120 -> 105.  d = 64 (before: one wavefront of 64 queries): 24 heads of 4096
-// 42.2 -> 40.5 / 45.8 -> 43.1 / 47.6 -> 43.9, 4 heads of 4096 29.6 -> 15.4 / 32.6 -> 16.4 / 33.1 -> 17.5.
+// the overlap for 8-bit codes, two wavefronts of 32 queries otherwise): 30 heads of 17550 tokens 1146 -> 1103 / 1264 -> 1118 / 1279 -> 1083,
+// 24 heads of 4096 59.4 -> 57.9 / 76.7 -> 59.2 / 77.4 -> 58.9, 4 heads of 4096 23.0 -> 19.3 / 33.8 -> 22.0 / 35.0 -> 22.7, 24 heads of
+// 4096 image and 512 text tokens 105 -> 101 / 119 -> 103 / 119 -> 104.  d = 64 (before: one wavefront of 64 queries): 24 heads of 4096
+// 42.0 -> 39.7 / 45.6 -> 41.9 / 47.4 -> 42.9, 4 heads of 4096 29.5 -> 15.3 / 32.3 -> 16.1 / 32.9 -> 17.1.
 // -------------------------------------------------------------------------------------------
 typedef int v4acc __attribute__((ext_vector_type(4)));
 
@@ -1283,7 +1283,7 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         if constexpr (PVBITS == 4) fetch_v(j0);
         bring_k(j0, j1, kring0);
         bring_v(j0, j1, vring0);
-        bring_k(j1, j2, kring1);
+        if (cnt > 1) bring_k(j1, j2, kring1);
         sk0 = uniform_load(skp + j0);
         sv0 = uniform_load(svp + j0);
         sk1 = uniform_load(skp + j1);
@@ -1458,10 +1458,14 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         m = m_new;
     };
     v4acc Sa[4], Sb[4];  // raw logits, this block's and the next one's in turn
-    // block t, whose logits are in S and whose tile exponents are in tile_e; K_{t+1} is in k_next and V_t in v_now
+    // block t, whose logits are in S and whose tile exponents are in tile_e; K_{t+1} is in k_next and V_t in v_now.  parity: that of t, or kLast
+    // in the last block, which brings no tile and multiplies for no block behind it: a third of the work of a row of one block, d = 128, 85 heads of
+    // 192 tokens 6.7 -> 6.4 us (6.5 in the kernel before), 128 heads of 192 in 16 batches at 50 % 57.5 -> 54.4 (54.4), 24 heads of 4096 and 512 102.3 -> 100.5
+    constexpr int kLast = 2;
     auto step = [&](auto mode_tag, auto parity_tag, int t, v4acc (&S)[4], v4acc (&N)[4]) __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode_tag)::value;
-        constexpr int PARITY = decltype(parity_tag)::value;
+        constexpr bool LAST = decltype(parity_tag)::value == kLast;
+        const int PARITY = LAST ? t & 1 : decltype(parity_tag)::value;
         uint8_t* const k_next = PARITY ? kring0 : kring1;  // K_{t+1}
         uint8_t* const k_free = PARITY ? kring1 : kring0;  // held K_t
         uint8_t* const v_now = PARITY ? vring1 : vring0;   // V_t
@@ -1485,14 +1489,19 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
 #pragma unroll
             for (int x = 0; x < 4; ++x) vf[x] = *(const v4i*)(v_now + 1024 * (ct0 + x) + vread);
         };
-        read_k(0);
-        const int j3 = column(t + 3);
-        bring_k(j2, j3, k_free);
-        bring_v(j1, j2, v_free);
+        int j3 = j2;
+        if constexpr (!LAST) {
+            read_k(0);
+            j3 = column(t + 3);
+            bring_k(j2, j3, k_free);
+            bring_v(j1, j2, v_free);
+        }
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(3);
-        products_k(0);
-        read_k(2);
+        if constexpr (!LAST) {
+            products_k(0);
+            read_k(2);
+        }
         const float e = __uint_as_float(min(min(eq.x, eq.y), min(eq.z, eq.w)));
         float c = sq_i * sk0;
         if (MODE == kExact && c < kLogitScaleMin) c = kLogitScaleMin;
@@ -1522,16 +1531,19 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         };
         exponentials(0);
         __builtin_amdgcn_sched_barrier(0);
-        products_k(2);
+        if constexpr (!LAST) products_k(2);
         __builtin_amdgcn_sched_barrier(0);
         read_v(0);
         exponentials(2);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(0);
         PARO_TIMELINE_PHASE(0)  // products K Q of the next block, exponentials
-        mask_tail(j1, N);
-        unsigned eb;
-        const float m_new = maxima(N, sq_i * sk1, eb);
+        unsigned eb = 0;
+        float m_new = 0.0f;
+        if constexpr (!LAST) {
+            mask_tail(j1, N);
+            m_new = maxima(N, sq_i * sk1, eb);
+        }
         const float rs = ((E[0][0] + E[0][1]) + (E[0][2] + E[0][3])) + ((E[1][0] + E[1][1]) + (E[1][2] + E[1][3])) +
                          (((E[2][0] + E[2][1]) + (E[2][2] + E[2][3])) + ((E[3][0] + E[3][1]) + (E[3][2] + E[3][3])));
         v4i pf;
@@ -1563,6 +1575,7 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
         } else {
             add(0);
         }
+        if constexpr (LAST) return;
         tile_e[PARITY ^ 1][w] = eb;  // (the same in every lane)
         refer(m_new);
         sk0 = sk1;
@@ -1580,11 +1593,16 @@ __global__ __launch_bounds__(256, (QSRC != 0 ? 3 : 4)) void attn_i8_q16_kernel(A
     };
     auto visit_all = [&](auto mode_tag) __attribute__((always_inline)) {
         int t = 0;
-        for (; t + 1 < cnt; t += 2) {
+        for (; t + 2 < cnt; t += 2) {
             step(mode_tag, std::integral_constant<int, 0>{}, t, Sa, Sb);
             step(mode_tag, std::integral_constant<int, 1>{}, t + 1, Sb, Sa);
         }
-        if (t < cnt) step(mode_tag, std::integral_constant<int, 0>{}, t, Sa, Sb);
+        if (t + 1 < cnt) {
+            step(mode_tag, std::integral_constant<int, 0>{}, t, Sa, Sb);
+#pragma unroll
+            for (int T = 0; T < 4; ++T) Sa[T] = Sb[T];
+        }
+        if (cnt > 0) step(mode_tag, std::integral_constant<int, kLast>{}, cnt - 1, Sa, Sb);
     };
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
@@ -2387,16 +2405,16 @@ static void launch_w64(paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) 
 // wavefronts win while all workgroups are resident at once - five per compute unit, four with 4-bit codes throughout (96 and 97
 // registers) - and lose in a second round.  The lines, both sides in us (four wavefronts / one), 8-bit codes, then all 4-bit; R row blocks,
 // K column blocks:
-//   20 % of K = 4 .. 16 (1 .. 3 blocks a row):  R = 1024  8.1 .. 10.8 / 9.0 .. 11.7   8.1 .. 11.5 / 9.1 .. 12.6
-//                                               R = 1152  8.8 .. 11.7 / 9.9 .. 12.8   11.1 .. 14.1 / 10.1 .. 13.5
-//                                               R = 1280  8.9 .. 12.2 / 10.1 .. 13.2  11.3 .. 15.0 / 10.3 .. 14.3
-//                                               R = 1408  11.4 .. 14.0 / 10.7 .. 13.4 12.2 .. 15.4 / 10.8 .. 14.5
-//   20 % of K = 32 (6):                         R = 1280  16.4 / 18.2   19.7 / 19.8;  R = 1536  19.1 / 18.8   20.9 / 20.5
-//   25 % of K = 32, 50 % of K = 16 (8):         R = 1408  21.1 / 22.1, 21.0 / 20.4;   R = 1536  21.5 / 22.2, 21.5 / 21.4
-//   50 % of K = 24, 32 (12, 16):                R = 1536  28.7 / 36.7, 34.8 / 46.9    33.1 / 41.2, 40.2 / 53.0
-//   20, 50 % of K = 64 (13, 32):                R = 1536  40.9 / 83.2, 69.5 / 87.6;   R = 2048  43.2 / 85.6, 82.4 / 90.0
-//   20, 50 % of K = 256 (51, 128):              R = 1536  180 / 316, 308 / 321;       R = 2048  178 / 316, 323 / 326
-//   30 % of K = 65, 275 (20, 83):               R = 1690  44.6 / 44.9, 49.4 / 49.9;   R = 8250  731 / 620, 788 / 684
+//   20 % of K = 4 .. 16 (1 .. 3 blocks a row):  R = 1024  7.8 .. 10.7 / 9.0 .. 11.8   7.8 .. 11.2 / 9.1 .. 12.6
+//                                               R = 1152  8.7 .. 11.3 / 10.0 .. 12.8  10.6 .. 13.5 / 10.1 .. 13.5
+//                                               R = 1280  8.8 .. 11.9 / 10.2 .. 13.2  10.8 .. 14.5 / 10.3 .. 14.3
+//                                               R = 1408  11.2 .. 13.8 / 10.8 .. 13.5 11.7 .. 14.9 / 10.9 .. 14.5
+//   20 % of K = 32 (6):                         R = 1280  16.1 / 18.2   19.0 / 19.7;  R = 1536  18.9 / 19.0   20.6 / 20.5
+//   25 % of K = 32, 50 % of K = 16 (8):         R = 1408  21.2 / 21.8, 21.1 / 20.5;   R = 1536  21.5 / 22.2, 21.5 / 21.5
+//   50 % of K = 24, 32 (12, 16):                R = 1536  28.6 / 36.8, 34.7 / 47.0    32.1 / 41.2, 39.3 / 53.1
+//   20, 50 % of K = 64 (13, 32):                R = 1536  40.7 / 82.7, 67.0 / 87.7;   R = 2048  42.8 / 84.5, 79.9 / 89.0
+//   20, 50 % of K = 256 (51, 128):              R = 1536  181 / 317, 306 / 321;       R = 2048  178 / 314, 313 / 325
+//   30 % of K = 65, 275 (20, 83):               R = 1690  44.5 / 45.1, 49.0 / 49.9;   R = 8250  727 / 615, 792 / 688
 constexpr int kQ16Rows = 1536;
 template <int QKBITS, int PVBITS, int QSRC = 0>
 static void launch_b64(int d, paro_dtype out_dtype, const AttnArgs& a, hipStream_t st) {

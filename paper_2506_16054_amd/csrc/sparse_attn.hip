@@ -1817,7 +1817,7 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     constexpr int BLK = 64, D = 64;
     constexpr int TILE = BLK * D * 2;
     __shared__ __attribute__((aligned(16))) uint8_t kbuf[2][TILE / 2];  // [wavefront]; later half of the exchange buffer
-    __shared__ __attribute__((aligned(16))) uint8_t vbuf[2][TILE / 2];
+    __shared__ __attribute__((aligned(16))) uint8_t vbuf[1024 + TILE];  // [1 KB in front, see request_v][wavefront]; later the other half
     __shared__ float meet[2][4][64];  // [half of the queries][2 references, 2 sums][lane]
 
     const int wg = blockIdx.x;
@@ -1857,6 +1857,7 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     const unsigned vfill = 128u * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
     unsigned kread = 128u * krow + 16u * (G ^ ((krow & 3) | ((krow >> 2) & 4)));
     unsigned vread = 64u * n + 16u * (G ^ ((n >> 1) & 3));
+    uint8_t* const vslot = vbuf + 1024 + (TILE / 2) * w;
     auto request_k = [&](int j) {
         const uint8_t* kp = kbase + (size_t)j * TILE;
         asm volatile("" : "+s"(kp), "+v"(kfill));  // scalar base + lane offset; the flipped offset is made here, not kept
@@ -1868,10 +1869,12 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     auto request_v = [&](int j) {
         const uint8_t* vp = vbase + (size_t)j * TILE;
         asm volatile("" : "+s"(vp));
-        lds_dma16<0>(vp, vfill, &vbuf[w][0]);
-        lds_dma16<1024>(vp + 1024, vfill, &vbuf[w][0]);  // a request further, 2048 bytes in memory and 1024 in LDS
-        lds_dma16<2048>(vp + 2048, vfill, &vbuf[w][0]);
-        lds_dma16<3072>(vp + 3072, vfill, &vbuf[w][0]);
+        // a request further is 2048 bytes in memory and 1024 in LDS, while the offset counts in both: the LDS base is 1 KB lower, inside vbuf.  (The
+        // step in four addresses instead: 0.7 % of the layer.)
+        lds_dma16<0>(vp, vfill, vslot);
+        lds_dma16<2048>(vp, vfill, vslot - 1024);
+        lds_dma16<0>(vp + 4096, vfill, vslot + 2048);
+        lds_dma16<2048>(vp + 4096, vfill, vslot + 1024);
     };
     Bf16Groups<4, 4> rows;
     rows.init();
@@ -1937,7 +1940,7 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
         __builtin_amdgcn_s_waitcnt(0x0F74);  // V_t has landed; K_{t+1} may be on its way
         v8bf vf[4];
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) vf[ct] = *(const v8bf*)(&vbuf[w][0] + vread + 1024 * ct);
+        for (int ct = 0; ct < 4; ++ct) vf[ct] = *(const v8bf*)(vslot + vread + 1024 * ct);
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
@@ -1950,8 +1953,8 @@ __global__ __launch_bounds__(128, 3) void attn_bf16_d64_kernel(AttnArgs a) {
     // ---- wavefront w finishes the queries of half w: it hands its sums of the other half over through LDS
     __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing is in flight to the buffers any more
     __syncthreads();
-    float* give = (float*)(w == 0 ? &kbuf[0][0] : &vbuf[0][0]);  // 8 KB each: [32 registers][64 lanes]
-    const float* take = (const float*)(w == 0 ? &vbuf[0][0] : &kbuf[0][0]);
+    float* give = (float*)(w == 0 ? &kbuf[0][0] : vbuf);  // 8 KB each: [32 registers][64 lanes]
+    const float* take = (const float*)(w == 0 ? vbuf : &kbuf[0][0]);
     const int ln = lane_here();  // nothing of the lane's number is kept through the loop for this
     auto offset = [&](int row) { return out_row_offset<D>(a, bh, h, head_rows, row, row < a.n_tokens); };
     if (w == 0) rows.template hand_over<2, 0>(give, meet[1], ln);
@@ -2118,7 +2121,8 @@ __global__ __launch_bounds__(256, 3) void attn_bf16_d128_kernel(AttnArgs a) {
 // it, at block 64 the queries 32 (w & 1) .. and the keys 32 (w >> 1) .. of a row block that four wavefronts share until their sums meet at
 // its end.  A wavefront moves its part of the tiles to LDS itself (one slot each; K_{t+2} is requested behind the reads of K_{t+1}, V_{t+1}
 // behind those of V_t), so there is no barrier in the loop, and K Q of block t + 1 runs beside the exponentials of block t.
-// Bound by the chain of a block where the chip is not full, by LDS and power where it is.  Attention call alone, us, before (block 32: tiles
+// Bound by the chain of a block where the chip is not full; where it is, a wavefront waits for its own tiles in 44 (d = 64) to 48 % of its cycles,
+// with vector issue at 0.62 and the matrix pipe at 0.40 of the time.  Attention call alone, us, before (block 32: tiles
 // through registers with two barriers per block; block 64: attn_bf16_d64_kernel) -> now, 30 % density: block 32, d = 64, 30 heads of 17550 tokens
 // 1129 -> 915, 4 heads of 4096 32.2 -> 23.8; d = 128 2343 -> 1988 (three wavefronts per SIMD instead of two: 2186) and 40.9 -> 32.8; block 64,
 // d = 64, 4 heads of 4096 20.5 -> 15.2, 6 heads of 1955 14.2 -> 10.7.  At block 64, d = 128 each byte that two wavefronts share would be
@@ -2172,7 +2176,7 @@ __global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_
     const int krow = bf16_krow(n);
     unsigned kfill = D == 64 ? 128u * (lane >> 3) + 16u * ((lane & 7) ^ ((lane >> 3) & 3))
                              : 256u * (lane >> 4) + 16u * ((lane & 8) | ((lane & 7) ^ (lane >> 4)));
-    const unsigned vfill = 2u * BLK * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
+    unsigned vfill = 2u * BLK * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
     unsigned kread = 2u * D * krow + 16u * (G ^ ((krow & 3) | ((krow >> 2) & 4)));  // 32 channels s: piece 4 s + G
     const unsigned vread = 64u * n + 16u * (G ^ ((n >> 1) & 3));
     auto request_k = [&](int j) __attribute__((always_inline)) {
@@ -2197,7 +2201,7 @@ __global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_
     };
     auto request_v = [&](int j) __attribute__((always_inline)) {
         const uint8_t* vp = vbase + (size_t)j * (BLK * D * 2);
-        asm volatile("" : "+s"(vp));
+        asm volatile("" : "+s"(vp), "+v"(vfill));
         constexpr int further = 32 * BLK - 1024;  // 16 rows a request: 32 BLK bytes in memory, 1024 in LDS
 #pragma unroll
         for (int four = 0; four < REQUESTS; four += 4) {
@@ -2357,9 +2361,11 @@ __global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_
     }
 }
 
-// Block 64, d = 64: with few row blocks four wavefronts per row block instead of two.  The line, in row blocks of the launch, both sides
-// in us (four / two wavefronts) at 20 and 50 % density: 512 16.2 / 21.8 and 30.4 / 45.0, 640 19.9 / 21.9 and 36.9 / 46.3, 768 21.0 / 23.0 and
-// 41.7 / 47.1, 875 42.3 / 39.1 and 94.5 / 90.1, 1024 27.9 / 24.9 and 57.5 / 51.5.
+// Block 64, d = 64: with few row blocks four wavefronts per row block instead of two.  The line, in row blocks R of the launch, both sides
+// in us (four / two wavefronts) at 20 and 50 % of K column blocks: K = 4 R = 512 6.8 / 7.4 and 7.6 / 8.8, R = 768 8.2 / 8.5 and 9.0 / 9.7, R = 896 9.3 / 9.6 and 10.5 / 10.8; K = 16 R = 768 10.2 / 11.0 and
+// 14.6 / 16.7, R = 896 12.0 / 12.5 and 17.4 / 17.5; K = 32 R = 768 13.0 / 15.0 and 23.5 / 30.8, R = 896 15.5 / 15.8 and 31.0 / 40.5; K = 128 R = 768
+// 67.9 / 94.6 and 95.8 / 140; masks of 3-D neighbours, K = 64, R = 768 21.0 / 23.0 and 41.7 / 47.1, R = 875 42.3 / 39.1 and 94.5 / 90.1, R = 1024 27.9 / 24.9
+// and 57.5 / 51.5.
 constexpr int kBf16Q32Rows = 768;
 
 template <typename OutT>

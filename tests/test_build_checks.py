@@ -144,9 +144,10 @@ def test_bench_refuses_more_than_one_gpu():
     assert not r.stdout.strip().startswith("{")
 
 
-def test_lds_requests_name_the_slot_they_fill():
-    """A request's immediate offset counts from the LDS base it is handed as well as in memory.  The base is the slot itself: one that
-    is handed lower, so that base and offset meet in the slot, can lie in front of the array and below the kernel's LDS."""
+def test_lds_requests_are_based_inside_an_array():
+    """A request's immediate offset counts from the LDS base it is handed as well as in memory.  The base lies in the array that is
+    filled: one that the helper lowers, so that base and offset meet in the slot, can lie in front of it and below the kernel's LDS.  The one
+    call that hands over less than its slot has as much of the array in front of it."""
     import os
     import re
 
@@ -155,8 +156,9 @@ def test_lds_requests_name_the_slot_they_fill():
     text = open(os.path.join(CSRC, "sparse_attn.hip")).read()
     assert text.count("__builtin_amdgcn_global_load_lds(") == 1
     helper = re.search(r"inline void lds_dma16\(.*?\n}\n", text, re.S).group(0)
-    assert "(void*)slot," in helper.replace("(__attribute__((address_space(3))) void*)slot,", "(void*)slot,")
+    assert "(__attribute__((address_space(3))) void*)slot, 16, OFFSET, 0)" in helper
     calls = re.findall(r"lds_dma16<(\d+)>\([^;]*, ([^,;]*)\);", text)
     assert len(calls) == text.count("lds_dma16<") >= 20
-    for offset, slot in calls:  # arrays are indexed at the slot's start: no offset is added on the way
-        assert offset in ("0", "1024", "2048", "3072") and not re.search(r"\b(1024|2048|3072)\]", slot), (offset, slot)
+    lowered = [(offset, slot) for offset, slot in calls if "-" in slot]
+    assert lowered == [("2048", "vslot - 1024")] and "uint8_t* const vslot = vbuf + 1024 + (TILE / 2) * w;" in text
+    assert "uint8_t vbuf[1024 + TILE];" in text

@@ -793,11 +793,10 @@ __global__ __launch_bounds__(64, 2) void attn_i8_w64_qk4_kernel(AttnArgs a) {
 
 // A P V product enters the sums as the integer that it is: its chain starts at kStartI (see acc_start), one subtraction per element leaves
 // the result times 2^-26, of which 2^13 come back in the weights and 2^13 at the end, whatever the scales: nothing is asked about them in
-// front of a row.  (Left in the sums and taken out every few blocks
-// the start would save the subtraction, 773 us instead of 833 for 30 heads of 17550 tokens, d = 64; but it is as large as the largest result,
-// times a weight that says nothing about a query's own codes, and a block of V some 2^12 larger than the rest, or one of zeros, whose scale is
-// 1, pushes the digits of the others out of the sum: 5e-3 of the output at 2^12, all of it at 2^20.)
-
+// front of a row.  (Left in the sums and taken out every few blocks the start would save the subtraction, 773 us instead of 833 for 30
+// heads of 17550 tokens, d = 64; but it is as large as the largest result, times a weight that says nothing about a query's own codes, and a
+// block of V some 2^12 larger than the rest, or one of zeros, whose scale is 1, pushes the digits of the others out of the sum: 5e-3 of the
+// output at 2^12, all of it at 2^20.)
 template <int D, int QKBITS, int PVBITS, typename OutT>
 __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(AttnArgs a) {
     constexpr int BLK = 32;

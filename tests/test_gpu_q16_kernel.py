@@ -74,7 +74,7 @@ def test_row_lengths_chunks_and_ragged_blocks(d, bits):
 @pytest.mark.parametrize("d,bits", [(64, (8, 8)), (128, (8, 8)), (128, (4, 8)), (128, (8, 4))])
 @pytest.mark.parametrize("gains", [(0, -26, -13, 0, -26), (-30, 0, -15, 0, -2), (98, 98, 98, 90, 98), (110, 110, 110, 105, 110),
                                    (-53, -53, -53, -60, -53), (-57, -57, -57, -57, -57), (-90, -90, -90, -90, -90)])
-def test_v_scales_of_a_row(d, bits, gains):
+def test_v_scales_of_a_row_in_and_out_of_range(d, bits, gains):
     rng = np.random.default_rng(3)
     q, k, v = (rng.standard_normal((280, d)) for _ in range(3))
     masks = np.ones((1, 5, 5), bool)

@@ -1068,7 +1068,7 @@ __global__ __launch_bounds__(64, (D == 64 ? 3 : 2)) void attn_i8_b32_kernel(Attn
     // two ranges of them and a scan stood: a launch of short rows is mostly instructions that are fetched once.  Attention alone, 8-bit Q and K
     // with 4-bit P and V, us, (tiles exchanged through LDS with a barrier per block) / scan and two loops -> now: 85 heads of 96 tokens, d = 64
     // 4.3 / 4.7 -> 4.3, d = 128 5.1 / 5.7 -> 5.2; 128 heads of 256 at 50 % 7.2 / 7.3 -> 6.7; 128 heads of 96 in 32 batches 26.0 / 28.4 -> 27.0; long rows
-    // 0 to 2 % slower, 4 heads of 4096 8-bit 25.5 -> 26.0, 30 heads of 17550 817 -> 819.  (V in two sets of registers, and it, the scales and two blocks
+    // 0 to 3 % slower, 4 heads of 4096 8-bit 25.5 -> 26.0, 30 heads of 17550 817 -> 819.  (V in two sets of registers, and it, the scales and two blocks
     // of K requested together in front of a row: no difference, d = 128 5 % slower.)
     {
         const std::false_type inner;
@@ -2134,7 +2134,8 @@ __global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_
     constexpr int KS = D / 32, CT = D / 16;
     constexpr int REQUESTS = TILE / 1024;  // per tile
     __shared__ __attribute__((aligned(16))) uint8_t kslots[NW][TILE];
-    __shared__ __attribute__((aligned(16))) uint8_t vslots[NW][TILE];
+    constexpr int LEAD = 32 * BLK - 1024;  // of V's array in front of its slots, see request_v
+    __shared__ __attribute__((aligned(16))) uint8_t vslots[LEAD + NW * TILE];
     __shared__ float meet[NW > 1 ? 2 : 1][4][64];  // [half of the queries][2 references, 2 sums][lane]
 
     const int wg = blockIdx.x;
@@ -2149,7 +2150,7 @@ __global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_
     const int kh = w >> 1;                           // which 32 keys of a block
     const int row0 = i * BLK + 32 * (w & 1);         // first query
     uint8_t* const kbuf = &kslots[w][0];
-    uint8_t* const vbuf = &vslots[w][0];
+    uint8_t* const vbuf = vslots + LEAD + TILE * w;
     const int n = lane & 15;
     const int G = lane >> 4;
 
@@ -2175,7 +2176,7 @@ __global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_
     const int krow = bf16_krow(n);
     unsigned kfill = D == 64 ? 128u * (lane >> 3) + 16u * ((lane & 7) ^ ((lane >> 3) & 3))
                              : 256u * (lane >> 4) + 16u * ((lane & 8) | ((lane & 7) ^ (lane >> 4)));
-    unsigned vfill = 2u * BLK * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
+    const unsigned vfill = 2u * BLK * (lane >> 2) + 16u * ((lane & 3) ^ ((lane >> 3) & 3));
     unsigned kread = 2u * D * krow + 16u * (G ^ ((krow & 3) | ((krow >> 2) & 4)));  // 32 channels s: piece 4 s + G
     const unsigned vread = 64u * n + 16u * (G ^ ((n >> 1) & 3));
     auto request_k = [&](int j) __attribute__((always_inline)) {
@@ -2200,15 +2201,14 @@ __global__ __launch_bounds__(BLK == 32 ? 64 : 256, (D == 64 ? 4 : 2)) void attn_
     };
     auto request_v = [&](int j) __attribute__((always_inline)) {
         const uint8_t* vp = vbase + (size_t)j * (BLK * D * 2);
-        asm volatile("" : "+s"(vp), "+v"(vfill));
-        constexpr int further = 32 * BLK - 1024;  // 16 rows a request: 32 BLK bytes in memory, 1024 in LDS
+        asm volatile("" : "+s"(vp));
+        // 16 rows each.  The second request of a pair is 32 BLK bytes further in memory and 1 KB in LDS, while the offset counts in both: its LDS
+        // base is LEAD lower, inside vslots.  (The step in addresses of their own: 8 heads of 2048 tokens at 50 %, block 64, 18.1 -> 21.2 us.)
 #pragma unroll
-        for (int four = 0; four < REQUESTS; four += 4) {
-            const uint8_t* from = vp + 32 * BLK * four;
-            lds_dma16<0>(from, vfill, &vbuf[1024 * four]);
-            lds_dma16<1024>(from + further, vfill, &vbuf[1024 * four]);
-            lds_dma16<2048>(from + 2 * further, vfill, &vbuf[1024 * four]);
-            lds_dma16<3072>(from + 3 * further, vfill, &vbuf[1024 * four]);
+        for (int u = 0; u < REQUESTS; u += 2) {
+            const uint8_t* from = vp + 32 * BLK * u;
+            lds_dma16<0>(from, vfill, vbuf + 1024 * u);
+            lds_dma16<32 * BLK>(from, vfill, vbuf + 1024 * u - LEAD);
         }
     };
     // 64 column indices per fetch, one per lane; past the end of the row its last column again

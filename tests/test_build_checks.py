@@ -146,8 +146,8 @@ def test_bench_refuses_more_than_one_gpu():
 
 def test_lds_requests_are_based_inside_an_array():
     """A request's immediate offset counts from the LDS base it is handed as well as in memory.  The base lies in the array that is
-    filled: one that the helper lowers, so that base and offset meet in the slot, can lie in front of it and below the kernel's LDS.  The one
-    call that hands over less than its slot has as much of the array in front of it."""
+    filled: one that the helper lowers, so that base and offset meet in the slot, can lie in front of it and below the kernel's LDS.  The
+    calls that hand over less than their slot have as much of the array in front of it."""
     import os
     import re
 
@@ -157,8 +157,10 @@ def test_lds_requests_are_based_inside_an_array():
     assert text.count("__builtin_amdgcn_global_load_lds(") == 1
     helper = re.search(r"inline void lds_dma16\(.*?\n}\n", text, re.S).group(0)
     assert "(__attribute__((address_space(3))) void*)slot, 16, OFFSET, 0)" in helper
-    calls = re.findall(r"lds_dma16<(\d+)>\([^;]*, ([^,;]*)\);", text)
+    calls = re.findall(r"lds_dma16<([^>]*)>\([^;]*, ([^,;]*)\);", text)
     assert len(calls) == text.count("lds_dma16<") >= 20
     lowered = [(offset, slot) for offset, slot in calls if "-" in slot]
-    assert lowered == [("2048", "vslot - 1024")] and "uint8_t* const vslot = vbuf + 1024 + (TILE / 2) * w;" in text
-    assert "uint8_t vbuf[1024 + TILE];" in text
+    assert lowered == [("2048", "vslot - 1024"), ("32 * BLK", "vbuf + 1024 * u - LEAD")]
+    for line in ("uint8_t vbuf[1024 + TILE];", "uint8_t* const vslot = vbuf + 1024 + (TILE / 2) * w;", "constexpr int LEAD = 32 * BLK - 1024;",
+                 "uint8_t vslots[LEAD + NW * TILE];", "uint8_t* const vbuf = vslots + LEAD + TILE * w;"):
+        assert text.count(line) == 1, line
